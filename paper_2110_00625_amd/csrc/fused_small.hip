@@ -37,6 +37,7 @@
 // stream as index_stream_kernel; workgroup 0 of a learner also stores them for kavg_indices), unless
 // the caller supplied its own.
 #include "kavg_internal.h"
+#include "fused_common.h"
 
 #include <type_traits>
 
@@ -73,40 +74,6 @@ struct Smem {
     int gave_up;                // a wait ran out of polls
 };
 
-// a partial and its tag as one 64-bit word
-__device__ __forceinline__ void st_tagged(uint64_t* p, float v, uint32_t tag) {
-    __hip_atomic_store(p, ((uint64_t)tag << 32) | __builtin_bit_cast(uint32_t, v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ uint64_t ld_tagged(const uint64_t* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ uint64_t splitmix64_mix(uint64_t z) {
-    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-    return z ^ (z >> 31);
-}
-
-// value of lane (l ^ pattern) within rows of 16 lanes, by data-parallel primitives (no LDS round trip)
-template <int CTRL>
-__device__ __forceinline__ float dpp_move(float x) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
-}
-// sum / maximum over each row of 16 lanes, left in all 16 (same operand pairs in every lane: bit-identical)
-__device__ __forceinline__ float row16_sum(float x) {
-    x += dpp_move<0xB1>(x);        // quad_perm [1,0,3,2]
-    x += dpp_move<0x4E>(x);        // quad_perm [2,3,0,1]
-    x += dpp_move<0x141>(x);       // row_half_mirror
-    x += dpp_move<0x140>(x);       // row_mirror
-    return x;
-}
-__device__ __forceinline__ float row16_max(float x) {
-    x = fmaxf(x, dpp_move<0xB1>(x));
-    x = fmaxf(x, dpp_move<0x4E>(x));
-    x = fmaxf(x, dpp_move<0x141>(x));
-    x = fmaxf(x, dpp_move<0x140>(x));
-    return x;
-}
-
 __global__ void __launch_bounds__(NT)
 fused_small_kernel(FusedSmallCall a, int S, int CW, int UH) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -126,8 +93,7 @@ fused_small_kernel(FusedSmallCall a, int S, int CW, int UH) {
     for (int e = tid; e < a.K * a.B; e += NT) {
         int32_t v;
         if (a.generate_idx) {
-            const uint64_t c = ((uint64_t)j << 40) | ((uint64_t)(a.t0 + (uint32_t)(e / a.B)) << 16) | (uint32_t)(e % a.B);
-            v = (int32_t)(splitmix64_mix(a.seed + (c + 1) * 0x9E3779B97F4A7C15ull) % (uint64_t)a.N);
+            v = index_draw(a.seed, (uint32_t)j, a.t0 + (uint32_t)(e / a.B), (uint32_t)(e % a.B), a.N);
             if (first) a.idx[(size_t)j * a.K * a.B + e] = v;
         } else {
             v = a.idx[(size_t)j * a.K * a.B + e];

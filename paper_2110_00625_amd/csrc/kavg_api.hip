@@ -39,8 +39,8 @@ struct Layout {
     size_t off_draw = 0, off_pool = 0, off_dpool = 0, off_partial = 0, off_pbias = 0;
     bool conv_implicit = false;            // convolutions 2.. form their patch matrices inside the MFMA kernel's loaders
     size_t off_wrot = 0;                   // ... and their data gradient reads the weights as [(tap, o)][c_in]
-    // all K steps of a small fp32 model in one launch (fused_small.hip): scratch and wait counters; 0 = shape not eligible
-    size_t off_fused = 0;
+    // all K steps of a small fp32 model in one launch (fused_small.hip, fused_units.hip): scratch; 0 bytes = shape not eligible
+    size_t off_fused = 0, fused_bytes = 0;
     size_t total = 0;
 };
 
@@ -113,8 +113,15 @@ Layout make_layout(int P, int K, int B, int L, const int* dims, int dtype, const
         }
         lo.off_scratch = need ? take(need) : 0;
         // (sized for a device of up to 256 compute units; the context decides with the real count)
-        if (L == 2 && M == 0 && fused_small_shape_ok(P, K, B, dims[0], dims[1], dims[2], 256))
-            lo.off_fused = take(fused_small_scratch_bytes(P, dims[0]));
+        if (L == 2 && M == 0) {
+            if (fused_small_shape_ok(P, K, B, dims[0], dims[1], dims[2], 256)) lo.fused_bytes = fused_small_scratch_bytes(P, dims[0]);
+            const int UN = fused_units_plan(P, K, B, dims[0], dims[1], dims[2], 256);
+            if (UN > 0) {
+                const size_t need_units = fused_units_scratch_bytes(P, B, dims[1], UN);
+                if (need_units > lo.fused_bytes) lo.fused_bytes = need_units;
+            }
+            if (lo.fused_bytes) lo.off_fused = take(lo.fused_bytes);
+        }
     }
     if (M > 0) {
         const size_t rows = (size_t)B * cv.H * cv.W;
@@ -216,6 +223,7 @@ struct kavg_ctx {
     hipGraphExec_t gexec = nullptr;
     ConvSpec cv;                        // convolution stack in front of the MLP (empty: plain MLP)
     bool fused_ok = false;              // the shape and the device allow all K steps in one launch (fused_small.hip)
+    bool units_ok = false;              // ... or in the one-launch kernel for wide hidden layers on short inputs (fused_units.hip)
     bool fused_on = true;               // ... and the caller has not switched it off (kavg_set_fused)
     unsigned spin_limit = 1u << 20;     // polls a workgroup of that launch spends on one wait before it gives up
     int compute_units = 0;
@@ -433,13 +441,14 @@ int init_common(kavg_ctx** out, int P, int K, float lr, float mu, int n_layers, 
     c->prof_every = 1;
     for (int k = 0; k < KAVG_NCLASS; ++k) { c->prof_used[k] = 0; c->prof_ms[k] = 0.0; c->prof_launches[k] = 0; c->prof_seen[k] = 0; }
     hipError_t e = hipMemsetAsync(c->flag(), 0, ALIGN, c->stream);
-    if (e == hipSuccess && lo.off_fused) {
+    if (e == hipSuccess && lo.fused_bytes) {
         int dev = 0, cus = 0;
         e = hipGetDevice(&dev);
         if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-        c->compute_units = cus;
-        c->fused_ok = e == hipSuccess && fused_small_shape_ok(P, K, B, dims[0], dims[1], dims[2], cus);
-        if (e == hipSuccess) e = hipMemsetAsync(c->ws + lo.off_fused, 0, fused_small_scratch_bytes(P, dims[0]), c->stream);
+        c->compute_units = cus < 256 ? cus : 256;          // (what the scratch was sized for)
+        c->fused_ok = e == hipSuccess && fused_small_shape_ok(P, K, B, dims[0], dims[1], dims[2], c->compute_units);
+        c->units_ok = e == hipSuccess && fused_units_plan(P, K, B, dims[0], dims[1], dims[2], c->compute_units) > 0;
+        if (e == hipSuccess) e = hipMemsetAsync(c->ws + lo.off_fused, 0, lo.fused_bytes, c->stream);
     }
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) {
@@ -598,14 +607,16 @@ namespace {
 int issue_steps_deferred(kavg_ctx* c);
 int issue_steps_conv(kavg_ctx* c);
 
-bool fused_now(const kavg_ctx* c) { return c->fused_ok && c->fused_on && !c->vel; }
+bool fused_now(const kavg_ctx* c) { return (c->fused_ok || c->units_ok) && c->fused_on && !c->vel; }
 
-// Small fp32 model: indices, all K steps and the per-step losses in one launch (fused_small.hip).  The launch
-// carries the step counter (index stream, tags), so it is issued directly, never replayed from a graph.
+// Small fp32 model: indices, all K steps and the per-step losses in one launch (fused_small.hip, fused_units.hip).  The
+// launch carries the step counter (index stream, tags), so it is issued directly, never replayed from a graph.
+// Where both kernels cover a shape the one that splits by hidden units runs: it exchanges C instead of 64 values per row
+// and workgroup.
 int issue_steps_fused(kavg_ctx* c) {
     hipStream_t st = c->stream;
     if (c->fused_tag + (uint32_t)c->K + 1u < c->fused_tag) {    // the tags would wrap: start over on a clean scratch
-        KAVG_HIP(c, hipMemsetAsync(c->ws + c->lo.off_fused, 0, fused_small_scratch_bytes(c->P, c->dims[0]), st));
+        KAVG_HIP(c, hipMemsetAsync(c->ws + c->lo.off_fused, 0, c->lo.fused_bytes, st));
         c->fused_tag = 0;
     }
     FusedSmallCall q{};
@@ -615,14 +626,14 @@ int issue_steps_fused(kavg_ctx* c) {
     q.X = (const float*)c->X; q.y = c->y; q.idx = c->idx();
     q.generate_idx = c->user_idx ? 0 : 1; q.seed = c->seed; q.t0 = c->t0; q.N = (uint32_t)c->N;
     q.partial = (uint64_t*)(c->ws + c->lo.off_fused);
-    q.hints = (uint32_t*)(q.partial + fused_small_partial_words(c->P, c->dims[0]));
+    q.hints = c->units_ok ? nullptr : (uint32_t*)(q.partial + fused_small_partial_words(c->P, c->dims[0]));
     q.tag0 = c->fused_tag;
     q.err = c->flag() + 1;
     q.losses = c->losses();
     q.lr = c->lr; q.spin_limit = c->spin_limit;
     q.compute_units = c->compute_units;
     Bracket br(c, KAVG_CLASS_FORWARD);
-    KAVG_HIP(c, launch_fused_small(q, st));
+    KAVG_HIP(c, c->units_ok ? launch_fused_units(q, st) : launch_fused_small(q, st));
     c->fused_tag += (uint32_t)c->K;
     return KAVG_OK;
 }
