@@ -1,12 +1,8 @@
 // fp32 path of the learner step (KAVG_FP32): forward, backward-data and the
 // fused weight-gradient + SGD update, batched over learners.
 //
-// One generic LDS-tiled kernel computes   O[r][c] = sum_k R(r,k) * Cm(c,k)
-// for operands given by (row stride, contraction stride, optional row gather),
-// with three epilogues.  The contraction runs on the matrix cores in full fp32
-// (v_mfma_f32_32x32x2_f32: exact fp32 products, fp32 accumulation; no reduced
-// precision), each of the four wavefronts owning one 32x32 quarter of the 64x64
-// tile, k ascending, so results are deterministic and independent of timing.
+// All three are products O[r][c] = sum_k R(r,k) * Cm(c,k) on the matrix cores in full fp32
+// (v_mfma_f32_32x32x2_f32: exact fp32 products, fp32 accumulation; no reduced precision):
 //
 //   forward        r = sample, c = output unit, k = input unit
 //                  O = act(A_{l-1} W_l^T + b_l)
@@ -16,186 +12,436 @@
 //                  W_l <- W_l - lr * dZ_l^T A_{l-1};  b_l <- b_l - lr * colsum(dZ_l)
 //                  (the learner update of Algorithm 1; 1/B already sits in dZ_L)
 //
-// The fp32 workloads are small (a few output tiles per learner, long
-// contractions), so the forward pass may split the contraction over several
-// workgroups: each writes its partial tile to a scratch buffer and a second
-// small kernel adds the partials in ascending split order, then applies bias
-// and ReLU.  The number of splits depends only on the shapes.
+// Operands move in 16-byte pieces, global -> registers (two slices ahead) -> LDS (two buffers, one barrier per slice).
+// A piece needs 4-byte alignment only, so rows of any length take the same path; only the last slice of a contraction
+// and tiles at the edge of an operand are read word by word, and nothing outside an operand is read at all.  An
+// operand with k contiguous in memory ("K": activations, dZ, W of the forward pass) lies in LDS as [x][k] and a lane
+// reads four k at once; one with x contiguous ("X": W of backward-data, both operands of the update) as [k][x].
+// Step i of a group of eight k takes k = 4*(lane/32) + i from either layout.  k order and tiles depend on the shapes
+// only, so results are deterministic.
+//
+// What bounds these kernels: 3072-512 with 64 rows and 8 learners is 1.6 GFLOP per product, 10 us of the matrix
+// cores' fp32 rate; the update also moves 100 MB of weights, 15 us out of the memory-side cache.  Measured on
+// 3072-512-256-10 (8 learners, 64 rows): split forward product 24 -> 13 us per launch (mean of the two layers),
+// backward-data 24 -> 10 us, all updates of a step 75 -> 31 us; a round of four steps 657 -> 336 us.  (Before: 64x64
+// tiles everywhere, operands moved word by word, one slice ahead, the weights read after the contraction.)
+//
+// The forward pass may split the contraction over several workgroups where a layer has few output tiles: each writes
+// its partial tile to a scratch buffer and a second small kernel adds the partials in ascending split order, then
+// applies bias and ReLU.  The updates of all layers of a step are one launch: they depend on nothing but the backward
+// pass, and on small models each launch is a few microseconds of latency.
 #include "kavg_internal.h"
 
 namespace kavg {
 
 namespace {
 
-constexpr int TILE = 64;   // output tile is TILE x TILE
-constexpr int BK = 32;     // contraction slice
-constexpr int PADW = TILE + 4;
-constexpr int NPER = TILE * BK / 256;   // elements of a slice each thread moves per operand
+constexpr int BK = 32;         // contraction slice
+constexpr int TC = 64;         // columns of a forward / backward tile
+constexpr int UR = 64, UC = 128;   // tile of the update: units x inputs
+constexpr int KPITCH = BK + 4; // [x][k] rows: 16-byte reads of 16 lanes fall on 16 different groups of four banks
+__host__ __device__ constexpr int xpitch(int X) { return X + 8; }   // [k][x] rows: rows k and k+4 lie 32 banks apart
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
 
-enum { EPI_FWD = 0, EPI_BWD = 1, EPI_UPD = 2, EPI_PARTIAL = 3 };
+enum { EPI_FWD = 0, EPI_BWD = 1, EPI_PARTIAL = 2 };
 
-struct Operand {
-    const float* base;      // learner 0
-    size_t learner_stride;  // elements between learners
-    long ld_x;              // stride of the row (r or c) index
-    long ld_k;              // stride of the contraction index
-    const int32_t* gather;  // optional: replaces the strided index by a looked-up row
-    long gather_stride;     // per learner
-    int gather_on_k;        // 0: gather applies to x, 1: to k
+// Workgroup -> piece of work: workgroup g runs on XCD g mod 8, so each XCD gets one contiguous range and the operands
+// of a learner stay in one L2.
+__device__ __forceinline__ int xcd_range(int g, int n_padded) { return (g & 7) * (n_padded >> 3) + (g >> 3); }
+
+// The loaders issue no load behind a branch: a wait for one slice is then a counted wait and not a wait for everything
+// in flight.  A piece that would leave its operand is read from the last place where it fits and shifted on its way to
+// LDS; what lies outside the contraction becomes zero there.  WORDS: an extent is below 4, no piece fits, words are
+// read one by one (from clamped places).
+
+// elements sh .. of a piece, for sh in 0..3 (what is shifted in is not used)
+__device__ __forceinline__ f32x4 shifted(const f32x4& v, int sh) {
+    f32x4 o;
+    o[0] = sh == 0 ? v[0] : sh == 1 ? v[1] : sh == 2 ? v[2] : v[3];
+    o[1] = sh == 0 ? v[1] : sh == 1 ? v[2] : v[3];
+    o[2] = sh == 0 ? v[2] : v[3];
+    o[3] = v[3];
+    return o;
+}
+
+// k-contiguous operand, X rows: thread t moves pieces (row t/8 + 32 i, k 4*(t%8))
+template <int X, bool WORDS>
+struct KLoader {
+    static constexpr int N = X / 32;
+    const float* p[N];
+    int k4, at, nK, k_end;
+    __device__ __forceinline__ void init(const float* base, long ld, const int32_t* gather, int x0, int nX, int nK_, int k_end_, int tid) {
+        k4 = (tid & 7) * 4;
+        at = (tid >> 3) * KPITCH + k4;
+        nK = nK_; k_end = k_end_;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int x = min(x0 + (tid >> 3) + 32 * i, nX - 1);      // rows beyond the operand only reach outputs that are not stored
+            p[i] = base + (gather ? (long)gather[x] : (long)x) * ld;
+        }
+    }
+    __device__ __forceinline__ void load(f32x4 (&v)[N], int k0) const {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            if constexpr (WORDS) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[i][e] = p[i][min(k0 + k4 + e, nK - 1)];
+            } else {
+                v[i] = *(const f32x4u*)(p[i] + min(k0 + k4, nK - 4));
+            }
+        }
+    }
+    __device__ __forceinline__ void store(f32x4 (&v)[N], float* lds, int k0) const {
+        if (k0 + BK > k_end) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) {
+                if constexpr (!WORDS) v[i] = shifted(v[i], max(k0 + k4 - (nK - 4), 0));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[i][e] = k0 + k4 + e < k_end ? v[i][e] : 0.f;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < N; ++i) *(f32x4*)(lds + at + 32 * i * KPITCH) = v[i];
+    }
 };
 
-struct Args {
-    Operand R, C;
+// x-contiguous operand, X columns: thread t moves pieces (row t/(X/4) + (1024/X) i, columns 4*(t%(X/4)))
+template <int X, bool WORDS, bool EDGE>
+struct XLoader {
+    static constexpr int PPR = X / 4, ROWS = 256 / PPR, N = BK / ROWS;
+    const float* p;          // base, at the piece's (clamped) columns
+    long ld;
+    int kr, at, nK, sh;      // sh: how far the piece was moved to fit
+    int xw[4];               // WORDS: the (clamped) columns
+    bool edge;
+    // nX: readable columns of a row
+    __device__ __forceinline__ void init(const float* base, long ld_, int x0, int nX, int nK_, int tid) {
+        const int x = x0 + (tid % PPR) * 4;
+        kr = tid / PPR;
+        at = kr * xpitch(X) + (tid % PPR) * 4;
+        nK = nK_;
+        ld = ld_;
+        edge = x0 + X > nX;
+        sh = max(x - (nX - 4), 0);
+        p = WORDS ? base : base + min(x, nX - 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) xw[e] = min(x + e, nX - 1);
+    }
+    // row[i]: memory row of the piece in the slice, inside the operand
+    __device__ __forceinline__ void load(f32x4 (&v)[N], const int (&row)[N]) const {
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const float* r = p + row[i] * ld;
+            if constexpr (WORDS) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[i][e] = r[xw[e]];
+            } else {
+                v[i] = *(const f32x4u*)r;
+            }
+        }
+    }
+    __device__ __forceinline__ void rows(int (&row)[N], int k0) const {
+#pragma unroll
+        for (int i = 0; i < N; ++i) row[i] = min(k0 + kr + ROWS * i, nK - 1);
+    }
+    // take: -1 where the rows are looked up in the table, 0 where the table is ignored
+    __device__ __forceinline__ void rows(int (&row)[N], int k0, const int32_t* table, int take) const {
+        rows(row, k0);
+#pragma unroll
+        for (int i = 0; i < N; ++i) row[i] = (table[row[i]] & take) | (row[i] & ~take);
+    }
+    __device__ __forceinline__ void store(f32x4 (&v)[N], float* lds, int k0) const {
+        if (!WORDS && EDGE && edge) {
+#pragma unroll
+            for (int i = 0; i < N; ++i) v[i] = shifted(v[i], sh);
+        }
+        if (k0 + BK > nK) {
+#pragma unroll
+            for (int i = 0; i < N; ++i)
+                if (k0 + kr + ROWS * i >= nK) v[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int i = 0; i < N; ++i) *(f32x4*)(lds + at + ROWS * i * xpitch(X)) = v[i];
+    }
+};
+
+// The slices of a contraction, two ahead in registers: step(set, slice, request the slice after next).  Straight-line code around every request, see the loaders.
+template <class Load, class Step>
+__device__ __forceinline__ void pipeline(int n, Load load, Step step) {
+    load(0, 0);
+    if (n == 1) {
+        step(0, 0, false);
+        return;
+    }
+    load(1, 1);
+    int s = 0;
+    for (; s + 3 < n; s += 2) { step(0, s, true); step(1, s + 1, true); }
+    if (s + 2 < n) { step(0, s, true); step(1, s + 1, false); step(0, s + 2, false); }
+    else { step(0, s, false); step(1, s + 1, false); }
+}
+
+struct RowArgs {
+    const float* R; size_t r_lstride; int ldR; const int32_t* gather; long gather_lstride;   // [r][k], k contiguous
+    const float* C; size_t c_lstride; long ldC;                     // forward: [c][k]; backward: [k][c]
     int nR, nC, nK;
-    int k_chunk;            // contraction range of one split (multiple of BK); nK when not split
-    // epilogue
-    float* out;  size_t out_stride;  int ld_out;       // FWD/BWD output, UPD: master weights, PARTIAL: scratch
-    size_t split_stride;                               // PARTIAL: elements between splits
-    const float* bias; size_t bias_stride;             // FWD: bias
-    float* bias_rw;                                    // UPD: bias to update (stride = bias_stride)
-    const float* mask; size_t mask_stride; int ld_mask;// BWD: previous activations
-    const float* dz; size_t dz_stride; int ld_dz;      // UPD: dZ for the bias gradient [B][ld_dz]
-    int relu;
-    float lr;
-    float* u; float* ub; float beta;                   // UPD: velocities of weights / bias (null: plain SGD)
+    int k_chunk, splits;                                            // contraction range of one split (nK: not split)
+    int tiles_r, tiles_c, total, padded;
+    float* out; size_t out_lstride; int ld_out; size_t split_stride;
+    const float* bias; size_t bias_lstride; int relu;               // forward
+    const float* mask; size_t mask_lstride; int ld_mask;            // backward: previous activations
 };
 
-// Where thread `tid` finds its NPER elements of a slice: element i is (x, k) with the memory-
-// contiguous index running fastest over the threads.
-struct Mover {
-    const float* p[NPER];   // address for k = 0 of the (clamped) row x
-    int x[NPER], k[NPER];
-    bool ok[NPER];          // x lies inside the operand
-};
+// TR = 64: four wavefronts own the quarters of a 64x64 tile.  TR = 32: two wavefronts side by side, two more with the
+// other half of every slice; their sums meet in LDS.  (32 rows serve batches whose last 64-row tile would be at most
+// half full, and layers with too few 64-row tiles for the chip.)
+template <int EPI, int TR, bool WORDS>
+__global__ void __launch_bounds__(256, WORDS ? 3 : 4) rows_kernel(RowArgs a) {
+    constexpr bool CK = EPI != EPI_BWD;
+    constexpr int CSZ = CK ? TC * KPITCH : BK * xpitch(TC);
+    __shared__ __align__(16) float lds[2][TR * KPITCH + CSZ];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, m = lane & 31, half = lane >> 5;
+    int at = xcd_range(blockIdx.x, a.padded);
+    if (at >= a.total) return;
+    const int ct = at % a.tiles_c; at /= a.tiles_c;
+    const int rt = at % a.tiles_r; at /= a.tiles_r;
+    const int split = at % a.splits, learner = at / a.splits;
+    const int r0 = rt * TR, c0 = ct * TC;
+    const int rq = TR == 64 ? (wave >> 1) * 32 : 0, cq = (wave & 1) * 32;
+    const int k_begin = split * a.k_chunk, k_end = min(k_begin + a.k_chunk, a.nK);
 
-__device__ __forceinline__ void mover_init(Mover& m, const Operand& o, int learner, int x0, int nX, int tid) {
-    const float* base = o.base + (size_t)learner * o.learner_stride;
-    const int32_t* g = o.gather ? o.gather + (long)learner * o.gather_stride : nullptr;
-    const bool kfast = (o.ld_k == 1 && !(g && o.gather_on_k));
-#pragma unroll
-    for (int i = 0; i < NPER; ++i) {
-        const int e = tid + 256 * i;
-        if (kfast) { m.x[i] = e / BK; m.k[i] = e % BK; } else { m.x[i] = e % TILE; m.k[i] = e / TILE; }
-        const int x = x0 + m.x[i];
-        m.ok[i] = x < nX;
-        const int xc = m.ok[i] ? x : nX - 1;
-        const long row = (g && !o.gather_on_k) ? (long)g[xc] : (long)xc;
-        m.p[i] = base + row * o.ld_x;
-    }
-}
-
-// The thread's NPER elements of the slice starting at k0.  No load is predicated: positions outside
-// the operand or beyond k_end are read from clamped addresses and replaced by zeros, so that all
-// loads of the slice are in flight together; with a gather on the contraction index, all row
-// indices are requested first, then all elements (one wait, not one per element).
-__device__ __forceinline__ void mover_load_all(const Mover& m, const Operand& o, int learner, int k0, int k_end,
-                                               float (&out)[NPER]) {
-    long off[NPER];
-    if (o.gather && o.gather_on_k) {
-        const int32_t* g = o.gather + (long)learner * o.gather_stride;
-        int32_t row[NPER];
-#pragma unroll
-        for (int i = 0; i < NPER; ++i) row[i] = g[min(k0 + m.k[i], k_end - 1)];
-#pragma unroll
-        for (int i = 0; i < NPER; ++i) off[i] = (long)row[i] * o.ld_k;
-    } else {
-#pragma unroll
-        for (int i = 0; i < NPER; ++i) off[i] = (long)min(k0 + m.k[i], k_end - 1) * o.ld_k;
-    }
-    float v[NPER];
-#pragma unroll
-    for (int i = 0; i < NPER; ++i) v[i] = m.p[i][off[i]];
-#pragma unroll
-    for (int i = 0; i < NPER; ++i) out[i] = (m.ok[i] && k0 + m.k[i] < k_end) ? v[i] : 0.f;
-}
-
-template <int EPI>
-__global__ void __launch_bounds__(256) gemm_f32_kernel(Args a) {
-    __shared__ float Rs[BK][PADW];
-    __shared__ float Cs[BK][PADW];
-    const int tid = threadIdx.x;
-    const int split = blockIdx.z % ((a.nK + a.k_chunk - 1) / a.k_chunk);
-    const int learner = blockIdx.z / ((a.nK + a.k_chunk - 1) / a.k_chunk);
-    const int r0 = blockIdx.y * TILE, c0 = blockIdx.x * TILE;
-    const int lane = tid & 63, wave = tid >> 6;
-    const int rq = (wave >> 1) * 32, cq = (wave & 1) * 32;    // this wavefront's quarter of the tile
-    const int k_begin = split * a.k_chunk;
-    const int k_end = k_begin + a.k_chunk < a.nK ? k_begin + a.k_chunk : a.nK;
-
-    Mover mr, mc;
-    mover_init(mr, a.R, learner, r0, a.nR, tid);
-    mover_init(mc, a.C, learner, c0, a.nC, tid);
+    typedef KLoader<TR, WORDS> RLoader;
+    typedef KLoader<TC, WORDS> CKLoader;
+    typedef XLoader<TC, WORDS, true> CXLoader;
+    RLoader lr;
+    CKLoader lck;
+    CXLoader lcx;
+    lr.init(a.R + (size_t)learner * a.r_lstride, a.ldR, a.gather ? a.gather + learner * a.gather_lstride : nullptr, r0, a.nR, a.nK, k_end, tid);
+    if constexpr (CK) lck.init(a.C + (size_t)learner * a.c_lstride, a.ldC, nullptr, c0, a.nC, a.nK, k_end, tid);
+    else lcx.init(a.C + (size_t)learner * a.c_lstride, a.ldC, c0, a.nC, a.nK, tid);
 
     f32x16 acc = {};
-    float rv_next[NPER], cv_next[NPER];
-    mover_load_all(mr, a.R, learner, k_begin, k_end, rv_next);
-    mover_load_all(mc, a.C, learner, k_begin, k_end, cv_next);
-    for (int k0 = k_begin; k0 < k_end; k0 += BK) {
-#pragma unroll
-        for (int i = 0; i < NPER; ++i) {
-            Rs[mr.k[i]][mr.x[i]] = rv_next[i];
-            Cs[mc.k[i]][mc.x[i]] = cv_next[i];
+    f32x4 rv[2][RLoader::N], cv[2][2];
+    auto load = [&](int set, int s) __attribute__((always_inline)) {
+        const int k0 = k_begin + s * BK;
+        lr.load(rv[set], k0);
+        if constexpr (CK) lck.load(cv[set], k0);
+        else {
+            int row[CXLoader::N];
+            lcx.rows(row, k0);
+            lcx.load(cv[set], row);
         }
+    };
+    auto step = [&](int set, int s, bool more) __attribute__((always_inline)) {
+        const int k0 = k_begin + s * BK;
+        float* R = lds[set];
+        float* C = lds[set] + TR * KPITCH;
+        lr.store(rv[set], R, k0);
+        if constexpr (CK) lck.store(cv[set], C, k0); else lcx.store(cv[set], C, k0);
+        if (more) load(set, s + 2);
         __syncthreads();
-        if (k0 + BK < k_end) {
-            mover_load_all(mr, a.R, learner, k0 + BK, k_end, rv_next);      // next slice in flight during the FMAs
-            mover_load_all(mc, a.C, learner, k0 + BK, k_end, cv_next);
-        }
-        // A step of the matrix instruction takes two k: lane l supplies R(row l%32, k l/32) and Cm(col l%32, k l/32);
-        // consecutive lanes read consecutive LDS words.
+        constexpr int G = TR == 64 ? BK / 8 : BK / 16;                // groups of eight k this wavefront contracts
+        const int g0 = TR == 64 ? 0 : (wave >> 1) * G;
 #pragma unroll
-        for (int k = 0; k < BK; k += 2)
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(Rs[k + (lane >> 5)][rq + (lane & 31)], Cs[k + (lane >> 5)][cq + (lane & 31)],
-                                                       acc, 0, 0, 0);
-        __syncthreads();
-    }
+        for (int g = 0; g < G; ++g) {
+            const int k = (g0 + g) * 8 + 4 * half;
+            const f32x4 r4 = *(const f32x4*)(R + (rq + m) * KPITCH + k);
+            f32x4 c4;
+            if constexpr (CK) c4 = *(const f32x4*)(C + (cq + m) * KPITCH + k);
+            else {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) c4[i] = C[(k + i) * xpitch(TC) + cq + m];
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(r4[i], c4[i], acc, 0, 0, 0);
+        }
+    };
+    pipeline((k_end - k_begin + BK - 1) / BK, load, step);
 
-    // accumulator v of lane l is the output (row 8*(v/4) + 4*(l/32) + v%4, column l%32) of the quarter
-    const int c = c0 + cq + (lane & 31);
+    // accumulator v of lane l is the output (row 8*(v/4) + 4*(l/32) + v%4, column l%32) of the wavefront's block
+    int v0 = 0, v1 = 16;
+    if constexpr (TR == 32) {
+        // the two halves of the contraction: each wavefront hands over half of its sums and finishes the other half
+        const int kh = wave >> 1;
+        __syncthreads();
+        float* xch = lds[0];
+#pragma unroll
+        for (int v = 0; v < 8; ++v) xch[(wave * 8 + v) * 64 + lane] = kh ? acc[v] : acc[v + 8];
+        __syncthreads();
+#pragma unroll
+        for (int v = 0; v < 8; ++v) {
+            const float other = xch[((wave ^ 2) * 8 + v) * 64 + lane];
+            if (kh) acc[v + 8] = other + acc[v + 8]; else acc[v] = acc[v] + other;
+        }
+        v0 = kh * 8; v1 = v0 + 8;
+    }
+    const int c = c0 + cq + m;
+    if (c >= a.nC) return;
+    float* out = a.out + (size_t)learner * a.out_lstride + c;
+    if (EPI == EPI_PARTIAL) out += (size_t)split * a.split_stride;
+    const float b = EPI == EPI_FWD ? a.bias[(size_t)learner * a.bias_lstride + c] : 0.f;
+    const float* mask = EPI == EPI_BWD ? a.mask + (size_t)learner * a.mask_lstride + c : nullptr;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-        const int r = r0 + rq + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-        if (r >= a.nR || c >= a.nC) continue;
-        if (EPI == EPI_FWD) {
-            float z = acc[v] + a.bias[(size_t)learner * a.bias_stride + c];
-            if (a.relu) z = fmaxf(z, 0.f);
-            a.out[(size_t)learner * a.out_stride + (size_t)r * a.ld_out + c] = z;
-        } else if (EPI == EPI_PARTIAL) {
-            a.out[(size_t)split * a.split_stride + (size_t)learner * a.out_stride + (size_t)r * a.ld_out + c] = acc[v];
-        } else if (EPI == EPI_BWD) {
-            const float m = a.mask[(size_t)learner * a.mask_stride + (size_t)r * a.ld_mask + c];
-            a.out[(size_t)learner * a.out_stride + (size_t)r * a.ld_out + c] = m > 0.f ? acc[v] : 0.f;
-        } else {
-            const size_t at = (size_t)learner * a.out_stride + (size_t)r * a.ld_out + c;
-            float g = acc[v];
-            if (a.u) { g = a.beta * a.u[at] + g; a.u[at] = g; }
-            a.out[at] = a.out[at] - a.lr * g;
-        }
+        const int r = r0 + rq + 8 * (v >> 2) + 4 * half + (v & 3);
+        if (v < v0 || v >= v1 || r >= a.nR) continue;
+        float z = acc[v];
+        if (EPI == EPI_FWD) { z += b; if (a.relu) z = fmaxf(z, 0.f); }
+        if (EPI == EPI_BWD) z = mask[(size_t)r * a.ld_mask] > 0.f ? z : 0.f;
+        out[(size_t)r * a.ld_out] = z;
     }
+}
 
-    if (EPI == EPI_UPD && blockIdx.x == 0 && tid < TILE) {
-        // bias gradient of this tile's output units: column sums of dZ_l over the batch
-        const int r = r0 + tid;
-        if (r < a.nR) {
-            const float* dz = a.dz + (size_t)learner * a.dz_stride;
-            // eight rows requested together, added in ascending order
-            float s = 0.f;
-            int m = 0;
-            for (; m + 8 <= a.nK; m += 8) {
-                float t[8];
+struct UpdLayer {
+    const float* dz; size_t dz_lstride; int ld_dz;                  // [k][r]
+    const float* in; size_t in_lstride; int ld_in; const int32_t* gather; long gather_lstride;   // [k][c]
+    float* w; float* b; float* u; float* ub;                        // u, ub: velocities, null: plain SGD
+    int d_out, d_in, tiles_r, tiles_c, total, padded;
+};
+constexpr int GROUP = 8;       // layers per launch
+struct UpdArgs {
+    UpdLayer layer[GROUP];
+    int n_layers, B;
+    size_t lstride;            // between learners, in weights and velocities
+    float lr, beta;
+};
+
+// 64 x 128 tile of a layer's weights (53 KB of LDS, 168 registers: three workgroups per compute unit).  A wavefront owns
+// 32 x 64: two column blocks interleaved (column 2m + i), so that a lane holds pairs of neighbouring columns and moves
+// them in 8-byte pieces, 256 bytes per row and half wavefront.  The weights are requested right after the first operand
+// slice and arrive under the contraction.  One slice ahead in registers: two ahead cost the third workgroup (31 -> 37 us).
+// INSIDE: the whole tile lies inside the layer.
+template <bool WORDS, bool INSIDE>
+__device__ __forceinline__ void update_tile(const UpdArgs& a, const UpdLayer& q, int learner, int rt, int ct, float* lds) {
+    constexpr int RSZ = BK * xpitch(UR), CSZ = BK * xpitch(UC);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, m = lane & 31, half = lane >> 5;
+    const int r0 = rt * UR, c0 = ct * UC, nK = a.B;
+    const int rq = (wave >> 1) * 32, cq = (wave & 1) * 64;
+
+    typedef XLoader<UR, WORDS, !INSIDE> RLoader;
+    typedef XLoader<UC, WORDS, !INSIDE> CLoader;
+    RLoader lr;
+    CLoader lc;
+    // (without a gather the look-ups read, and ignore, words of dZ: no branch around a load)
+    const int32_t* table = q.gather ? q.gather + learner * q.gather_lstride : (const int32_t*)q.dz;
+    lr.init(q.dz + (size_t)learner * q.dz_lstride, q.ld_dz, r0, q.ld_dz, nK, tid);
+    lc.init(q.in + (size_t)learner * q.in_lstride, q.ld_in, c0, q.d_in, nK, tid);
+
+    f32x4 rv[RLoader::N], cv[CLoader::N];
+    int row[2][CLoader::N];      // memory rows of a slice, looked up before the slice that precedes it is requested
+    const int take = q.gather ? -1 : 0;
+    lc.rows(row[0], 0, table, take);
+    auto load = [&](int s) __attribute__((always_inline)) {
+        int rr[RLoader::N];
+        lc.rows(row[1], (s + 1) * BK, table, take);
+        lr.rows(rr, s * BK);
+        lr.load(rv, rr);
+        lc.load(cv, row[0]);
 #pragma unroll
-                for (int u = 0; u < 8; ++u) t[u] = dz[(size_t)(m + u) * a.ld_dz + r];
+        for (int i = 0; i < CLoader::N; ++i) row[0][i] = row[1][i];
+    };
+
+    // the tile's weights: rows rb + 8*(v/4) + v%4, columns c and c+1; places outside are read clamped, never stored
+    const int c = c0 + cq + 2 * m, rb = r0 + rq + 4 * half;
+    const size_t wat = (size_t)learner * a.lstride, tat = wat + (size_t)r0 * q.d_in + c0;
+    const unsigned lane_at = (unsigned)(rq + 4 * half) * (unsigned)q.d_in + cq + 2 * m;      // inside the tile
+    float w0[16], w1[16];
+    const int cl = WORDS ? min(c, q.d_in - 1) : min(c, q.d_in - 2), ch = min(c + 1, q.d_in - 1);
+    auto fetch = [&](const float* src, float (&x0)[16], float (&x1)[16]) __attribute__((always_inline)) {
 #pragma unroll
-                for (int u = 0; u < 8; ++u) s += t[u];
+        for (int v = 0; v < 16; ++v) {
+            if constexpr (INSIDE) {
+                const f32x2u t = *(const f32x2u*)(src + tat + (size_t)(8 * (v >> 2) + (v & 3)) * q.d_in + lane_at);
+                x0[v] = t.x; x1[v] = t.y;
+            } else {
+                const float* s = src + wat + (size_t)min(rb + 8 * (v >> 2) + (v & 3), q.d_out - 1) * q.d_in;
+                if constexpr (WORDS) { x0[v] = s[cl]; x1[v] = s[ch]; }
+                else { const f32x2u t = *(const f32x2u*)(s + cl); x0[v] = t.x; x1[v] = t.y; }
             }
-            for (; m < a.nK; ++m) s += dz[(size_t)m * a.ld_dz + r];
-            const size_t at = (size_t)learner * a.bias_stride + r;
-            if (a.ub) { s = a.beta * a.ub[at] + s; a.ub[at] = s; }
-            a.bias_rw[at] = a.bias_rw[at] - a.lr * s;
         }
+    };
+    const bool last_odd = !INSIDE && !WORDS && c == q.d_in - 1;     // this pair was read one column to the left
+    auto put = [&](float* dst, const float (&x0)[16], const float (&x1)[16]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            if constexpr (INSIDE) {
+                const f32x2u t = {x0[v], x1[v]};
+                *(f32x2u*)(dst + tat + (size_t)(8 * (v >> 2) + (v & 3)) * q.d_in + lane_at) = t;
+            } else {
+                const int r = rb + 8 * (v >> 2) + (v & 3);
+                float* d = dst + wat + (size_t)r * q.d_in + c;
+                if (r < q.d_out && c < q.d_in) d[0] = x0[v];
+                if (r < q.d_out && c + 1 < q.d_in) d[1] = x1[v];
+            }
+        }
+    };
+
+    f32x16 acc0 = {}, acc1 = {};
+    float bsum = 0.f;                                               // column sum of dZ: unit r0 + tid, samples ascending
+    const bool bias = ct == 0 && tid < UR;
+    auto step = [&](int s, bool more) __attribute__((always_inline)) {
+        float* R = lds + (s & 1) * (RSZ + CSZ);
+        float* C = R + RSZ;
+        lr.store(rv, R, s * BK);
+        lc.store(cv, C, s * BK);
+        if (more) load(s + 1);
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < BK / 2; ++t) {
+            const int k = (t >> 2) * 8 + (t & 3) + 4 * half;
+            const float r1 = R[k * xpitch(UR) + rq + m];
+            const float2 c2 = *(const float2*)(C + k * xpitch(UC) + cq + 2 * m);
+            acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(r1, c2.x, acc0, 0, 0, 0);
+            acc1 = __builtin_amdgcn_mfma_f32_32x32x2f32(r1, c2.y, acc1, 0, 0, 0);
+        }
+        if (bias) {
+#pragma unroll 8
+            for (int k = 0; k < BK; ++k) bsum += R[k * xpitch(UR) + tid];
+        }
+    };
+    load(0);
+    fetch(q.w, w0, w1);
+    const int n = (nK + BK - 1) / BK;
+    step(0, true);               // outside the loop: its waits leave the weights in flight (and no branch: the request is
+                                 // for the last row over and over where there is one slice only)
+    for (int s = 1; s + 1 < n; ++s) step(s, true);
+    if (n > 1) step(n - 1, false);
+
+    float g0[16], g1[16];
+#pragma unroll
+    for (int v = 0; v < 16; ++v) { g0[v] = acc0[v]; g1[v] = acc1[v]; }
+    if (q.u) {                                                      // heavy ball inside the learner
+        float u0[16], u1[16];
+        fetch(q.u, u0, u1);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) { g0[v] = a.beta * (last_odd ? u1[v] : u0[v]) + g0[v]; g1[v] = a.beta * u1[v] + g1[v]; }
+        put(q.u, g0, g1);
     }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) { w0[v] = (last_odd ? w1[v] : w0[v]) - a.lr * g0[v]; w1[v] -= a.lr * g1[v]; }
+    put(q.w, w0, w1);
+    if (bias && r0 + tid < q.d_out) {
+        const size_t bat = wat + r0 + tid;
+        if (q.ub) { bsum = a.beta * q.ub[bat] + bsum; q.ub[bat] = bsum; }
+        q.b[bat] = q.b[bat] - a.lr * bsum;
+    }
+}
+
+template <bool WORDS>
+__global__ void __launch_bounds__(256, WORDS ? 2 : 3) update_kernel(UpdArgs a) {
+    __shared__ __align__(16) float lds[2 * BK * (xpitch(UR) + xpitch(UC))];
+    int g = blockIdx.x, li = 0;
+    while (li + 1 < a.n_layers && g >= a.layer[li].padded) g -= a.layer[li++].padded;
+    const UpdLayer& q = a.layer[li];
+    int at = xcd_range(g, q.padded);
+    if (at >= q.total) return;
+    const int rt = at % q.tiles_r; at /= q.tiles_r;
+    const int ct = at % q.tiles_c, learner = at / q.tiles_c;
+    if (!WORDS && (rt + 1) * UR <= q.d_out && (ct + 1) * UC <= q.d_in) update_tile<WORDS, !WORDS>(a, q, learner, rt, ct, lds);
+    else update_tile<WORDS, false>(a, q, learner, rt, ct, lds);
 }
 
 // out[j][r][c] = act(sum_s partial[s][j][r][c] + bias[j][c]), splits added in ascending order
@@ -225,10 +471,27 @@ finish_forward_kernel(const float* __restrict__ partial, size_t split_stride, in
     out[e] = z;
 }
 
+int div_up(int a, int b) { return (a + b - 1) / b; }
+
+// Rows per tile of a forward / backward product: 32 where that leaves no more padding than half of a 64-row tile would
+// waste, or where 64-row tiles are too few for the 256 compute units.
+int tile_rows(int P, int B, int cols, int splits) {
+    if (div_up(B, 32) & 1) return 32;
+    return (long)div_up(B, 64) * div_up(cols, TC) * P * splits < 256 ? 32 : 64;
+}
+
 template <int EPI>
-hipError_t run(const Args& a, int P, int splits, hipStream_t st) {
-    dim3 grid((a.nC + TILE - 1) / TILE, (a.nR + TILE - 1) / TILE, P * splits);
-    hipLaunchKernelGGL(gemm_f32_kernel<EPI>, grid, dim3(256), 0, st, a);
+hipError_t run_rows(RowArgs& a, int P, hipStream_t st) {
+    const int TR = tile_rows(P, a.nR, a.nC, a.splits);
+    a.tiles_r = div_up(a.nR, TR);
+    a.tiles_c = div_up(a.nC, TC);
+    a.total = a.tiles_r * a.tiles_c * a.splits * P;
+    a.padded = div_up(a.total, 8) * 8;
+    const bool words = a.nK < 4 || (EPI == EPI_BWD && a.nC < 4);
+    if (words && TR == 64) hipLaunchKernelGGL((rows_kernel<EPI, 64, true>), dim3(a.padded), dim3(256), 0, st, a);
+    else if (words) hipLaunchKernelGGL((rows_kernel<EPI, 32, true>), dim3(a.padded), dim3(256), 0, st, a);
+    else if (TR == 64) hipLaunchKernelGGL((rows_kernel<EPI, 64, false>), dim3(a.padded), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((rows_kernel<EPI, 32, false>), dim3(a.padded), dim3(256), 0, st, a);
     return hipGetLastError();
 }
 
@@ -237,7 +500,7 @@ hipError_t run(const Args& a, int P, int splits, hipStream_t st) {
 // How the forward pass of a layer splits its contraction: returns the number of splits and the
 // contraction range of each (a multiple of the slice length).  Depends on the shapes only.
 int f32_forward_plan(int P, int B, int d_in, int d_out, int* chunk_out) {
-    const long tiles = (long)((B + TILE - 1) / TILE) * ((d_out + TILE - 1) / TILE) * P;
+    const long tiles = (long)div_up(B, 64) * div_up(d_out, TC) * P;
     long s = 1;
     if (tiles < 256 && d_in > 4 * BK) {
         s = (512 + tiles - 1) / tiles;               // aim at ~512 workgroups
@@ -253,53 +516,67 @@ int f32_forward_plan(int P, int B, int d_in, int d_out, int* chunk_out) {
 }
 
 hipError_t f32_forward(const LayerCall& c, hipStream_t st) {
-    Args a = {};
-    a.R = {(const float*)c.in, c.in_stride, c.ld_in, 1, c.gather, c.gather_stride, 0};
-    if (c.gather) a.R.learner_stride = 0;               // all learners read the one data set
-    a.C = {c.w, c.w_stride, c.d_in, 1, nullptr, 0, 0};
+    RowArgs a = {};
+    a.R = (const float*)c.in; a.r_lstride = c.gather ? 0 : c.in_stride; a.ldR = c.ld_in;    // gathered: one data set for all
+    a.gather = c.gather; a.gather_lstride = c.gather_stride;
+    a.C = c.w; a.c_lstride = c.w_stride; a.ldC = c.d_in;
     a.nR = c.B; a.nC = c.d_out; a.nK = c.d_in;
-    a.out = (float*)c.out; a.out_stride = c.out_stride; a.ld_out = c.ld_out;
-    a.bias = c.b; a.bias_stride = c.w_stride;
+    a.out = (float*)c.out; a.out_lstride = c.out_stride; a.ld_out = c.ld_out;
+    a.bias = c.b; a.bias_lstride = c.w_stride;
     a.relu = c.relu;
-    int chunk = 0;
-    const int splits = f32_forward_plan(c.P, c.B, c.d_in, c.d_out, &chunk);
-    if (splits == 1 || !c.scratch) {
-        a.k_chunk = a.nK;
-        return run<EPI_FWD>(a, c.P, 1, st);
+    a.splits = f32_forward_plan(c.P, c.B, c.d_in, c.d_out, &a.k_chunk);
+    if (a.splits == 1 || !c.scratch) {
+        a.k_chunk = a.nK; a.splits = 1;
+        return run_rows<EPI_FWD>(a, c.P, st);
     }
-    a.k_chunk = chunk;
     a.out = (float*)c.scratch;
     a.split_stride = (size_t)c.P * c.out_stride;
-    hipError_t e = run<EPI_PARTIAL>(a, c.P, splits, st);
+    hipError_t e = run_rows<EPI_PARTIAL>(a, c.P, st);
     if (e != hipSuccess) return e;
     const size_t total = (size_t)c.P * c.out_stride;
     hipLaunchKernelGGL(finish_forward_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
-                       (const float*)c.scratch, a.split_stride, splits, c.b, c.w_stride, (float*)c.out, c.P, c.B,
+                       (const float*)c.scratch, a.split_stride, a.splits, c.b, c.w_stride, (float*)c.out, c.P, c.B,
                        c.ld_out, c.d_out, c.relu);
     return hipGetLastError();
 }
 
 hipError_t f32_backward_data(const LayerCall& c, hipStream_t st) {
-    Args a = {};
-    a.R = {(const float*)c.dz, c.dz_stride, c.ld_dz, 1, nullptr, 0, 0};
-    a.C = {c.w, c.w_stride, 1, c.d_in, nullptr, 0, 0};  // Cm(c = input unit, k = output unit) = W[k][c]
-    a.nR = c.B; a.nC = c.d_in; a.nK = c.d_out; a.k_chunk = a.nK;
-    a.out = (float*)c.dz_prev; a.out_stride = c.dz_prev_stride; a.ld_out = c.ld_in;
-    a.mask = (const float*)c.in; a.mask_stride = c.in_stride; a.ld_mask = c.ld_in;
-    return run<EPI_BWD>(a, c.P, 1, st);
+    RowArgs a = {};
+    a.R = (const float*)c.dz; a.r_lstride = c.dz_stride; a.ldR = c.ld_dz;
+    a.C = c.w; a.c_lstride = c.w_stride; a.ldC = c.d_in;             // Cm(c = input unit, k = output unit) = W[k][c]
+    a.nR = c.B; a.nC = c.d_in; a.nK = c.d_out; a.k_chunk = a.nK; a.splits = 1;
+    a.out = (float*)c.dz_prev; a.out_lstride = c.dz_prev_stride; a.ld_out = c.ld_in;
+    a.mask = (const float*)c.in; a.mask_lstride = c.in_stride; a.ld_mask = c.ld_in;
+    return run_rows<EPI_BWD>(a, c.P, st);
 }
 
-hipError_t f32_update(const LayerCall& c, hipStream_t st) {
-    Args a = {};
-    a.R = {(const float*)c.dz, c.dz_stride, 1, c.ld_dz, nullptr, 0, 0};        // R(r = unit, k = sample) = dZ[k][r]
-    a.C = {(const float*)c.in, c.in_stride, 1, c.ld_in, c.gather, c.gather_stride, 1};  // Cm(c, k = sample) = A[k][c]
-    if (c.gather) a.C.learner_stride = 0;
-    a.nR = c.d_out; a.nC = c.d_in; a.nK = c.B; a.k_chunk = a.nK;
-    a.out = c.w; a.out_stride = c.w_stride; a.ld_out = c.d_in;
-    a.bias_rw = c.b; a.bias_stride = c.w_stride;
-    a.dz = (const float*)c.dz; a.dz_stride = c.dz_stride; a.ld_dz = c.ld_dz;
-    a.lr = c.lr; a.u = c.u; a.ub = c.ub; a.beta = c.beta;
-    return run<EPI_UPD>(a, c.P, 1, st);
+hipError_t f32_update(const LayerCall* calls, int n, hipStream_t st) {
+    for (int at = 0; at < n; at += GROUP) {
+        UpdArgs a = {};
+        a.n_layers = n - at < GROUP ? n - at : GROUP;
+        a.B = calls[at].B; a.lstride = calls[at].w_stride; a.lr = calls[at].lr; a.beta = calls[at].beta;
+        int wgs = 0;
+        bool words = false;
+        for (int i = 0; i < a.n_layers; ++i) {
+            const LayerCall& c = calls[at + i];
+            UpdLayer& q = a.layer[i];
+            q.dz = (const float*)c.dz; q.dz_lstride = c.dz_stride; q.ld_dz = c.ld_dz;
+            q.in = (const float*)c.in; q.in_lstride = c.gather ? 0 : c.in_stride; q.ld_in = c.ld_in;
+            q.gather = c.gather; q.gather_lstride = c.gather_stride;
+            q.w = c.w; q.b = c.b; q.u = c.u; q.ub = c.ub;
+            q.d_out = c.d_out; q.d_in = c.d_in;
+            q.tiles_r = div_up(c.d_out, UR); q.tiles_c = div_up(c.d_in, UC);
+            q.total = q.tiles_r * q.tiles_c * c.P;
+            q.padded = div_up(q.total, 8) * 8;
+            wgs += q.padded;
+            words = words || c.d_in < 4 || c.ld_dz < 4 || c.d_in >= 1 << 24;     // (2^24: reach of lane_at)
+        }
+        if (words) hipLaunchKernelGGL(update_kernel<true>, dim3(wgs), dim3(256), 0, st, a);
+        else hipLaunchKernelGGL(update_kernel<false>, dim3(wgs), dim3(256), 0, st, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace kavg

@@ -666,19 +666,37 @@ int issue_steps(kavg_ctx* c) {
             KAVG_HIP(c, launch_softmax_ce(c->logits(), c->lo.ldz, c->dims[L], c->y, idx_k, idx_ls, c->B, c->P,
                                           c->ws + c->lo.off_dz[L - 1], (long)c->B * c->lo.ldz, bf ? 1 : 0, rowloss_k, st));
         }
+        if (!bf) {
+            // the data gradients of all layers, then the updates of all layers in one launch
+            for (int l = head ? L - 1 : L; l > 1; --l) {
+                Bracket br(c, KAVG_CLASS_BACKWARD);
+                KAVG_HIP(c, f32_backward_data(layer_call(c, l, k), st));
+            }
+            std::vector<LayerCall> updates;
+            for (int l = 1; l <= L; ++l) updates.push_back(layer_call(c, l, k));
+            if (c->prof_mask & ((1u << KAVG_CLASS_UPDATE) | (1u << KAVG_CLASS_HEAD))) {     // one bracket per layer
+                for (int l = L; l >= 1; --l) {
+                    Bracket br(c, head && l == L ? KAVG_CLASS_HEAD : KAVG_CLASS_UPDATE);
+                    KAVG_HIP(c, f32_update(&updates[l - 1], 1, st));
+                }
+            } else {
+                KAVG_HIP(c, f32_update(updates.data(), L, st));
+            }
+            continue;
+        }
         for (int l = L; l >= 1; --l) {                       // backward; W_l is read before it is updated
             LayerCall q = layer_call(c, l, k);
             if (head && l == L) {
                 Bracket br(c, KAVG_CLASS_HEAD);
-                KAVG_HIP(c, head_update(q, idx_k, idx_ls, bf ? 1 : 0, st));
+                KAVG_HIP(c, head_update(q, idx_k, idx_ls, st));
                 continue;
             }
             if (l > 1) {
                 Bracket br(c, KAVG_CLASS_BACKWARD);
-                KAVG_HIP(c, bf ? bf16_backward_data(q, st) : f32_backward_data(q, st));
+                KAVG_HIP(c, bf16_backward_data(q, st));
             }
             Bracket br(c, KAVG_CLASS_UPDATE);
-            KAVG_HIP(c, bf ? bf16_update(q, st) : f32_update(q, st));
+            KAVG_HIP(c, bf16_update(q, st));
         }
     }
     {
@@ -815,7 +833,7 @@ int issue_steps_conv(kavg_ctx* c) {
             LayerCall q = layer_call(c, l, k);
             if (head && l == L) {
                 Bracket br(c, KAVG_CLASS_HEAD);
-                KAVG_HIP(c, head_update(q, idx_k, idx_ls, 1, st));
+                KAVG_HIP(c, head_update(q, idx_k, idx_ls, st));
                 continue;
             }
             {
@@ -983,7 +1001,7 @@ int issue_steps_deferred(kavg_ctx* c) {
             LayerCall q = call(l, k, slot);
             if (head && l == L) {
                 Bracket br(c, KAVG_CLASS_HEAD);
-                KAVG_HIP(c, head_update(q, idx_k, idx_ls, 1, st));       // the thin last layer is stepped at once
+                KAVG_HIP(c, head_update(q, idx_k, idx_ls, st));       // the thin last layer is stepped at once
                 continue;
             }
             if (l > 1) {

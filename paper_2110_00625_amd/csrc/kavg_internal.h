@@ -121,7 +121,7 @@ hipError_t launch_bias_step(uint16_t* bhi, uint16_t* blo, size_t b_stride, const
 int f32_forward_plan(int P, int B, int d_in, int d_out, int* chunk_out);
 hipError_t f32_forward(const LayerCall& c, hipStream_t st);
 hipError_t f32_backward_data(const LayerCall& c, hipStream_t st);
-hipError_t f32_update(const LayerCall& c, hipStream_t st);
+hipError_t f32_update(const LayerCall* layers, int n, hipStream_t st);   // all n layers in one launch
 // bf16 MFMA path
 hipError_t bf16_forward(const LayerCall& c, hipStream_t st);
 hipError_t bf16_backward_data(const LayerCall& c, hipStream_t st);
@@ -132,7 +132,7 @@ bool head_supported(int C);
 // idx: this step's indices of learner 0, idx_lstride elements between learners
 hipError_t head_forward_backward(const LayerCall& c, const int32_t* y, const int32_t* idx, long idx_lstride,
                                  float* rowloss, int bf16, hipStream_t st);
-hipError_t head_update(const LayerCall& c, const int32_t* idx, long idx_lstride, int bf16, hipStream_t st);
+hipError_t head_update(const LayerCall& c, const int32_t* idx, long idx_lstride, hipStream_t st);   // bf16 (fp32: f32_update)
 
 // ---- convolutional layers (conv.hip): 3x3, stride 1, zero padding 1, channels-last bf16 images ----
 // patches[j][(n,h,w)][(kh,kw,c)] from images in[j][n][h][w][c] (or, with gather, from rows gather[j*gstride+n] of a shared set)
