@@ -13,9 +13,8 @@
 // (rotate_weights_kernel rebuilds that view from the current weights before every use), so it comes
 // out of the MFMA kernel already masked by the ReLU of the layer below and rounded to bf16.
 //
-// The first convolution gathers its images out of the data set and has only 9*c_0 = 72 columns: its
-// patch matrix is written out (im2col_kernel) and feeds the generic dense kernels.  The same explicit
-// path, with the fp32 product dZ * W per (position, tap, channel) folded back onto the image by
+// The first convolution gathers its images out of the data set: its patch matrix is written out
+// (im2col_kernel) and feeds the generic dense kernels.  The same explicit path, with the fp32 product dZ * W per (position, tap, channel) folded back onto the image by
 // col2im_mask_kernel, serves every convolution when an image has 2^14 positions or more (beyond the
 // range of the loaders' multiply-shift divisions).
 //
@@ -25,9 +24,10 @@
 // ascending order and takes the SGD step of Algorithm 1 on the master's two planes (split.h).
 // Between the last convolution and the MLP sits the mean over the H*W positions.
 //
-// Images 32 pixels wide do not take these paths where the tile kernels cover the layer (conv_first.hip,
-// conv_direct.hip, conv_wgrad.hip: the image rows a workgroup needs are held in LDS and every tap reads them
-// at a shifted pixel); what is here serves every other shape, and the pooling and the master step for all.
+// Most layers do not take these paths: images 32 pixels wide run on conv_first.hip, conv_direct.hip and conv_wgrad.hip
+// where these cover the layer, others with up to 128 channels out on conv_flat.hip and conv_flat_wgrad.hip (the pixels a
+// workgroup needs are held in LDS and every tap reads them at a shifted place).  What is here serves every other shape,
+// and the pooling and the master step serve all.
 #include "kavg_internal.h"
 #include "split.h"
 #include "conv_pool.h"
@@ -158,8 +158,17 @@ conv_step_kernel(uint16_t* whi, uint16_t* wlo, uint16_t* bhi, uint16_t* blo, siz
     const int i = is_w ? e : e - n_w;
     const float* p = is_w ? partial + (size_t)j * S * n_w + i : pbias + (size_t)j * S * n_b + i;
     const size_t step = is_w ? (size_t)n_w : (size_t)n_b;
+    // eight partial sums requested together, added in ascending order (one at a time: 14 us per launch with 16 ranges)
     float s = 0.f;
-    for (int q = 0; q < S; ++q) s += p[(size_t)q * step];
+    int q = 0;
+    for (; q + 8 <= S; q += 8) {
+        float t[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) t[u] = p[(size_t)(q + u) * step];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += t[u];
+    }
+    for (; q < S; ++q) s += p[(size_t)q * step];
     uint16_t* hi = (is_w ? whi : bhi) + (size_t)j * lstride + i;
     uint16_t* lo = (is_w ? wlo : blo) + (size_t)j * lstride + i;
     const float v = __builtin_bit_cast(float, split_join(*hi, *lo)) - lr * s;

@@ -1,0 +1,48 @@
+// 3x3 convolution, forward and data gradient, for images of any width (conv_flat.hip).
+#pragma once
+#include "kavg_internal.h"
+
+namespace kavg {
+
+// Positions with margins (conv_flat.hip): table[i] = pixel (n H + h) W + w of position i - (W+1) - 1, or -1 on a margin.
+int conv_flat_table_len(int B, int H, int W);
+hipError_t launch_flat_table(int32_t* table, int B, int H, int W, hipStream_t st);
+
+// Weights in the order in which a wavefront of the kernels takes them as matrix operands, see conv_flat.hip.
+struct FlatPlan {
+    int CK, NB, PWAVES;          // channels per group; output blocks per wavefront; wavefronts side by side in positions
+    int slabs, blocks;           // 16-channel slabs of the contraction; 32-channel blocks of the output (padded)
+    size_t frag_elems() const { return (size_t)9 * slabs * blocks * 512; }
+};
+// the plan of one direction of a layer: c_k channels contracted, c_n channels out; false: not covered
+bool conv_flat_plan(int B, int H, int W, int c_k, int c_n, FlatPlan* plan);
+
+// one layer of launch_pack_weights: W [c_out][9][c_in] (hi plane) into operand order, for the forward pass and,
+// where bwd is not null, for the data gradient; lstride: elements between learners
+struct PackLayer {
+    const uint16_t* w;
+    uint16_t* fwd; size_t fwd_lstride; FlatPlan fwd_plan;
+    uint16_t* bwd; size_t bwd_lstride; FlatPlan bwd_plan;
+    int c_in, c_out;
+};
+hipError_t launch_pack_weights(const PackLayer* layers, int n, size_t w_lstride, int P, hipStream_t st);
+
+// c.out = relu(conv(c.in, W) + b); gather != null: the images are rows gather[learner * gstride + n] of the data set X
+hipError_t conv_flat_forward(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag, const int32_t* table, const void* X, const int32_t* gather,
+                             long gstride, hipStream_t st);
+// c.dz_in = [c.in > 0] * (transposed convolution of c.dz with W).  dpool != null (the last convolution, below the
+// mean over the positions): c.dz is not read; the gradient images are formed while loading from the layer's own
+// activations c.out and dpool [P][B][c_out], as pool_backward_kernel would.
+hipError_t conv_flat_backward_data(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag, const int32_t* table, const void* dpool,
+                                   hipStream_t st);
+
+// Weight gradient (conv_flat_wgrad.hip): ranges of positions per learner, or 0 when the kernel does not cover the layer.
+// first: the first convolution (gathered images of 8 channels).
+int conv_flat_wgrad_splits(int P, int B, int H, int W, int c_in, int c_out, bool first);
+// partial[learner * splits + range][c_out][9 c_in] (fp32) and the column sums of dZ in partial_bias; c.splits as above.
+// gather (8 input channels) and dpool as in the functions above it.
+hipError_t conv_flat_wgrad(const ConvCall& c, const int32_t* table, const void* X, const int32_t* gather, long gstride,
+                           const void* dpool, hipStream_t st);
+
+
+}  // namespace kavg

@@ -14,6 +14,7 @@
 #include "kavg_internal.h"
 #include "conv_wgrad.h"
 #include "conv_direct.h"
+#include "conv_flat.h"
 #include "conv_first.h"
 #include "split.h"
 
@@ -38,6 +39,12 @@ struct Layout {
     std::vector<int> splits_halo;          // the same for the all-taps weight-gradient kernel; 0: shape not covered
     size_t off_draw = 0, off_pool = 0, off_dpool = 0, off_partial = 0, off_pbias = 0;
     bool conv_implicit = false;            // convolutions 2.. form their patch matrices inside the MFMA kernel's loaders
+    // images of any width (conv_flat.hip, conv_flat_wgrad.hip), per convolution: plans (slabs = 0: shape not covered), weights
+    // in operand order, ranges of the weight gradient (0: not covered); one table of positions for all
+    std::vector<FlatPlan> flat_f, flat_b;
+    std::vector<size_t> off_frag_f, off_frag_b;
+    std::vector<int> splits_flat;
+    size_t off_flat_table = 0;
     size_t off_wrot = 0;                   // ... and their data gradient reads the weights as [(tap, o)][c_in]
     // all K steps of a small fp32 model in one launch (fused_small.hip, fused_units.hip): scratch; 0 bytes = shape not eligible
     size_t off_fused = 0, fused_bytes = 0;
@@ -131,7 +138,19 @@ Layout make_layout(int P, int K, int B, int L, const int* dims, int dtype, const
             const int S1 = (t == 1 && lo.conv_implicit) ? conv_first_splits(P, B, cv.H, cv.W, cv.ch[0], cv.ch[1]) : 0;
             // explicit patches: every convolution of very large images, and a first convolution (it gathers its images)
             // that the kernels of conv_first.hip do not cover
-            const bool expl = (t == 1 && S1 == 0) || !lo.conv_implicit;
+            FlatPlan pf = {}, pb = {};
+            int Sf = 0;
+            if (lo.conv_implicit) {
+                Sf = conv_flat_wgrad_splits(P, B, cv.H, cv.W, cv.ch[t - 1], cv.ch[t], t == 1);
+                if (t > 1 || Sf) (void)conv_flat_plan(B, cv.H, cv.W, cv.ch[t - 1], cv.ch[t], &pf);
+                if (t > 1) (void)conv_flat_plan(B, cv.H, cv.W, cv.ch[t], cv.ch[t - 1], &pb);
+                if (t == 1 && !pf.slabs) Sf = 0;
+            }
+            lo.splits_flat.push_back(Sf);
+            lo.flat_f.push_back(pf); lo.flat_b.push_back(pb);
+            lo.off_frag_f.push_back(pf.slabs ? take((size_t)P * pf.frag_elems() * 2) : 0);
+            lo.off_frag_b.push_back(pb.slabs ? take((size_t)P * pb.frag_elems() * 2) : 0);
+            const bool expl = (t == 1 && S1 == 0 && Sf == 0) || !lo.conv_implicit;
             lo.off_patch.push_back(expl ? take((size_t)P * rows * 9 * cv.ch[t - 1] * 2) : 0);
             lo.off_cact.push_back(take((size_t)P * rows * cv.ch[t] * 2));
             lo.off_cdz.push_back(take((size_t)P * rows * cv.ch[t] * 2));
@@ -146,12 +165,16 @@ Layout make_layout(int P, int K, int B, int L, const int* dims, int dtype, const
             const int Sh = t == 1 ? S1 : lo.conv_implicit ? conv_wgrad_halo_splits(P, B, cv.H, cv.W, cv.ch[t - 1], cv.ch[t]) : 0;
             lo.splits_halo.push_back(Sh);
             if (Sh > S) S = Sh;                                          // (sizes the partial buffers below)
+            if (Sf > S) S = Sf;
             const size_t nw = (size_t)cv.ch[t] * 9 * cv.ch[t - 1];
             if ((size_t)P * S * nw * 4 > partial) partial = (size_t)P * S * nw * 4;
             if ((size_t)P * S * cv.ch[t] * 4 > pbias) pbias = (size_t)P * S * cv.ch[t] * 4;
         }
         lo.off_draw = draw ? take(draw) : 0;
         lo.off_wrot = wrot ? take(wrot) : 0;
+        bool flat = false;
+        for (int t = 1; t <= M; ++t) flat = flat || lo.flat_f[t - 1].slabs || lo.flat_b[t - 1].slabs || lo.splits_flat[t - 1];
+        lo.off_flat_table = flat ? take((size_t)conv_flat_table_len(B, cv.H, cv.W) * 4) : 0;
         lo.off_pool = take((size_t)P * B * cv.ch[M] * 2);
         lo.off_dpool = take((size_t)P * B * cv.ch[M] * 2);
         lo.off_partial = take(partial);
@@ -450,6 +473,7 @@ int init_common(kavg_ctx** out, int P, int K, float lr, float mu, int n_layers, 
         c->units_ok = e == hipSuccess && fused_units_plan(P, K, B, dims[0], dims[1], dims[2], c->compute_units) > 0;
         if (e == hipSuccess) e = hipMemsetAsync(c->ws + lo.off_fused, 0, lo.fused_bytes, c->stream);
     }
+    if (e == hipSuccess && lo.off_flat_table) e = launch_flat_table((int32_t*)(c->ws + lo.off_flat_table), B, cv.H, cv.W, c->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
     if (e != hipSuccess) {
         fail(nullptr, KAVG_EDEVICE, "clearing the workspace flag failed: %s", hipGetErrorString(e));
@@ -742,8 +766,8 @@ extern "C++" HistoryLayout history_layout(const kavg_ctx* c, int m) {
 // of Section 4).  Per step a convolution is three products on B*H*W rows (forward, data gradient, weight
 // gradient), and the mean over the positions joins the convolutions and the MLP.  Which kernels run them is
 // decided per layer from its shape: the tile kernels for images 32 pixels wide (conv_first.hip,
-// conv_direct.hip, conv_wgrad.hip), else the generic MFMA kernel on the implicit patch matrix, else (first
-// layer, or images of 2^14 positions and more) the same kernel on a patch matrix that is written out.
+// conv_direct.hip, conv_wgrad.hip), those for any width (conv_flat.hip, conv_flat_wgrad.hip), else the generic MFMA
+// kernel on the implicit patch matrix, else (first layer, or images of 2^14 positions and more) the same kernel on a patch matrix that is written out.
 int issue_steps_conv(kavg_ctx* c) {
     hipStream_t st = c->stream;
     const Layout& lo = c->lo;
@@ -791,12 +815,38 @@ int issue_steps_conv(kavg_ctx* c) {
         v.splits = lo.splits_halo[0];
         return v;
     };
+    // Which kernels run convolution t: those for images 32 pixels wide where they cover the layer, those for any width
+    // elsewhere.  (The workload's layers on the latter, us per launch against the former: forward 33 / 69 / 174 against
+    // 26 / 71 / 183, data gradient 85 / 226 against 75 / 199, weight gradient 32 / 89 / 260 against 33 / 54 / 168.)
+    auto flat_forward = [&](int t) {
+        return lo.flat_f[t - 1].slabs && !(t == 1 ? first_direct : conv_direct_ok(H, W, cv.ch[t - 1], cv.ch[t], false));
+    };
+    auto flat_backward = [&](int t) { return lo.flat_b[t - 1].slabs && !conv_direct_ok(H, W, cv.ch[t - 1], cv.ch[t], true); };
+    auto flat_update = [&](int t) { return lo.splits_flat[t - 1] > 0 && lo.splits_halo[t - 1] == 0; };
+    const int32_t* table = (const int32_t*)(c->ws + lo.off_flat_table);
+    std::vector<PackLayer> pack;                                    // weights in the operand order of conv_flat.hip
+    for (int t = 1; t <= M; ++t) {
+        PackLayer q{};
+        q.w = c->hi_planes() + lo.cw_off[t - 1];
+        q.c_in = cv.ch[t - 1]; q.c_out = cv.ch[t];
+        q.fwd_plan = lo.flat_f[t - 1]; q.fwd_lstride = q.fwd_plan.frag_elems();
+        q.bwd_plan = lo.flat_b[t - 1]; q.bwd_lstride = q.bwd_plan.frag_elems();
+        q.fwd = flat_forward(t) ? (uint16_t*)(c->ws + lo.off_frag_f[t - 1]) : nullptr;
+        q.bwd = flat_backward(t) ? (uint16_t*)(c->ws + lo.off_frag_b[t - 1]) : nullptr;
+        pack.push_back(q);
+    }
     for (int k = 0; k < c->K; ++k) {
         const int32_t* idx_k = c->idx() + (size_t)k * B;
         const long idx_ls = (long)c->K * B;
         float* rowloss_k = c->rowloss() + (size_t)k * P * B;
+        KAVG_HIP(c, launch_pack_weights(pack.data(), M, lo.stride, P, st));
         for (int t = 1; t <= M; ++t) {                              // convolutions, forward
             Bracket br(c, KAVG_CLASS_FORWARD);
+            if (pack[t - 1].fwd) {
+                KAVG_HIP(c, conv_flat_forward(t == 1 ? first_call() : implicit_call(t), lo.flat_f[t - 1], pack[t - 1].fwd, table, c->X,
+                                              t == 1 ? idx_k : nullptr, idx_ls, st));
+                continue;
+            }
             if (t == 1 && first_direct) {
                 KAVG_HIP(c, conv_first_forward(first_call(), c->X, idx_k, idx_ls, st));
                 continue;
@@ -845,9 +895,9 @@ int issue_steps_conv(kavg_ctx* c) {
         }
         // The gradient of the mean over the positions: written out for the generic kernels; the tile kernels of
         // the last convolution form it while loading (both of them must be in use, or the buffer is needed).
-        const bool pool_fused = M > 1 && lo.conv_implicit && lo.splits_halo[M - 1] > 0 &&
-                                B / lo.splits_halo[M - 1] <= conv_wgrad_halo_pool_images() &&
-                                conv_direct_ok(H, W, cv.ch[M - 1], cv.ch[M], true);
+        const bool pool_fused = M > 1 && lo.conv_implicit && (flat_backward(M) || conv_direct_ok(H, W, cv.ch[M - 1], cv.ch[M], true)) &&
+                                (flat_update(M) || (lo.splits_halo[M - 1] > 0 &&
+                                                    B / lo.splits_halo[M - 1] <= conv_wgrad_halo_pool_images()));
         const void* dpool_M = c->ws + lo.off_dpool;
         if (!pool_fused) {
             Bracket br(c, KAVG_CLASS_BACKWARD);
@@ -859,7 +909,10 @@ int issue_steps_conv(kavg_ctx* c) {
                 ConvCall v = implicit_call(t);
                 {
                     Bracket br(c, KAVG_CLASS_BACKWARD);
-                    if (conv_direct_ok(H, W, v.c_in, v.c_out, true)) {
+                    if (pack[t - 1].bwd) {
+                        KAVG_HIP(c, conv_flat_backward_data(v, lo.flat_b[t - 1], pack[t - 1].bwd, table,
+                                                            (pool_fused && t == M) ? dpool_M : nullptr, st));
+                    } else if (conv_direct_ok(H, W, v.c_in, v.c_out, true)) {
                         KAVG_HIP(c, conv_direct_backward_data(v, (pool_fused && t == M) ? dpool_M : nullptr, st));
                     } else {
                         KAVG_HIP(c, launch_rotate_weights(v.ws, lo.stride, (uint16_t*)(c->ws + lo.off_wrot), v.wrot_stride, P,
@@ -868,7 +921,10 @@ int issue_steps_conv(kavg_ctx* c) {
                     }
                 }
                 Bracket br(c, KAVG_CLASS_UPDATE);
-                if (lo.splits_halo[t - 1] > 0) {
+                if (flat_update(t)) {
+                    v.splits = lo.splits_flat[t - 1];
+                    KAVG_HIP(c, conv_flat_wgrad(v, table, nullptr, nullptr, 0, (pool_fused && t == M) ? dpool_M : nullptr, st));
+                } else if (lo.splits_halo[t - 1] > 0) {
                     v.splits = lo.splits_halo[t - 1];
                     KAVG_HIP(c, conv_wgrad_halo(v, (pool_fused && t == M) ? dpool_M : nullptr, st));
                 } else {
@@ -878,10 +934,15 @@ int issue_steps_conv(kavg_ctx* c) {
                                              P, v.splits, v.c_out * 9 * v.c_in, v.c_out, c->lr, st));
                 continue;
             }
-            if (t == 1 && first_direct) {
+            if (t == 1 && (flat_update(1) || first_direct)) {
                 Bracket br(c, KAVG_CLASS_UPDATE);
                 ConvCall v = first_call();
-                KAVG_HIP(c, conv_first_wgrad(v, c->X, idx_k, idx_ls, st));
+                if (flat_update(1)) {
+                    v.splits = lo.splits_flat[0];
+                    KAVG_HIP(c, conv_flat_wgrad(v, table, c->X, idx_k, idx_ls, nullptr, st));
+                } else {
+                    KAVG_HIP(c, conv_first_wgrad(v, c->X, idx_k, idx_ls, st));
+                }
                 KAVG_HIP(c, launch_conv_step(v.ws, v.wlo, (uint16_t*)v.bhi, (uint16_t*)v.blo, lo.stride, v.partial, v.partial_bias,
                                              P, v.splits, v.c_out * 9 * v.c_in, v.c_out, c->lr, st));
                 continue;

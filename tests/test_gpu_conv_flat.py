@@ -1,0 +1,39 @@
+"""Convolutions on images of any size (conv_flat.hip, conv_flat_wgrad.hip) where their tiles, rings and channel groups end,
+against the oracle, on the scale of one local step: replica - start = -lr * gradient."""
+import numpy as np
+import pytest
+
+from tests.test_gpu_conv import _setup, conv_slices
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # P, B, H, W, channels, dims
+    (2, 3, 5, 6, (8, 16), (16, 10)),                 # one convolution on small images: every tile holds several of them
+    (40, 1, 4, 4, (8, 8, 16), (16, 10)),             # many learners, a range shorter than a slice
+    (2, 4, 9, 28, (8, 32, 64), (64, 10)),
+    (1, 2, 7, 33, (8, 24, 40, 72), (72, 12)),        # channels between the tile sizes: two, three and six slabs
+    (1, 2, 6, 62, (8, 64, 64), (64, 10)),            # the widest image that a ring of 256 rows holds
+    (1, 2, 5, 64, (8, 96, 128), (128, 10)),          # a ring of 512 rows; 96 and 128 channels out, two groups in
+    (2, 2, 6, 20, (8, 128, 96, 16), (16, 10)),       # 128 and 96 contraction channels
+    (1, 2, 5, 32, (8, 32, 64), (64, 10)),            # 32 pixels wide, a height that the tile kernels for that width refuse
+    (1, 2, 6, 10, (8, 136, 24), (24, 10)),           # 136 channels: one side of each layer on the generic kernels
+    (1, 1, 3, 150, (8, 16, 48), (48, 10)),           # wide and low
+    (1, 40, 1, 1, (8, 32, 32), (32, 10)),            # images of one pixel: margins everywhere
+]
+
+
+@pytest.mark.parametrize("P,B,H,W,channels,dims", CASES, ids=["%dx%d-%s" % (c[2], c[3], "-".join(map(str, c[4]))) for c in CASES])
+def test_one_step(P, B, H, W, channels, dims):
+    """Both sides start from the same state and round at the same points, so they differ by fp32 sums (1e-6 of the step)
+    and, rarely, by a value whose rounding to bf16 falls the other way: 2^-8 of one term of a gradient element."""
+    g, o, spec = _setup(P, 1, B, H, W, channels, dims, 75, lr=0.5)
+    start = g.params().astype(np.float64)
+    g.local_steps()
+    o.local_steps()
+    for j in sorted({0, P - 1}):
+        got, want = g.replica(j) - start, np.asarray(o.replica(j)) - start
+        for name, sl in conv_slices(spec):
+            e = np.max(np.abs(got[sl] - want[sl])) / max(np.max(np.abs(want[sl])), 1e-30)
+            print("  learner %d %-8s %.3g" % (j, name, e))
+            assert e < 2.0 ** -8, "%s of learner %d: %.3g" % (name, j, e)
