@@ -715,6 +715,11 @@ int issue_steps(kavg_ctx* c) {
                 KAVG_HIP(c, head_update(q, idx_k, idx_ls, st));
                 continue;
             }
+            if (bf16_strip_ok(q)) {                   // data gradient and update in one pass over the weights
+                Bracket br(c, KAVG_CLASS_UPDATE);
+                KAVG_HIP(c, bf16_strip(q, st));
+                continue;
+            }
             if (l > 1) {
                 Bracket br(c, KAVG_CLASS_BACKWARD);
                 KAVG_HIP(c, bf16_backward_data(q, st));

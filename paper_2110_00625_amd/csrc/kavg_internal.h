@@ -126,6 +126,9 @@ hipError_t f32_update(const LayerCall* layers, int n, hipStream_t st);   // all 
 hipError_t bf16_forward(const LayerCall& c, hipStream_t st);
 hipError_t bf16_backward_data(const LayerCall& c, hipStream_t st);
 hipError_t bf16_update(const LayerCall& c, hipStream_t st);
+// data gradient and update of a layer in one pass over its weights (strip_bf16.hip); which calls it takes
+bool bf16_strip_ok(const LayerCall& c);
+hipError_t bf16_strip(const LayerCall& c, hipStream_t st);
 
 // ---- classifier head for small class counts (last layer: forward + loss + data gradient, then update) ----
 bool head_supported(int C);
