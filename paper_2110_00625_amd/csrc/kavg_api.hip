@@ -662,6 +662,20 @@ int issue_steps_fused(kavg_ctx* c) {
     return KAVG_OK;
 }
 
+// The updates of a step that are left to one launch.  While updates are profiled every layer is a launch of its own, so that
+// the brackets tell the classes apart.
+int issue_update_group(kavg_ctx* c, const std::vector<LayerCall>& group, bool head) {
+    if (c->prof_mask & ((1u << KAVG_CLASS_UPDATE) | (1u << KAVG_CLASS_HEAD))) {
+        for (const LayerCall& q : group) {
+            Bracket br(c, head && q.out == c->logits() ? KAVG_CLASS_HEAD : KAVG_CLASS_UPDATE);
+            KAVG_HIP(c, bf16_update_group(&q, 1, c->stream));
+        }
+    } else if (!group.empty()) {
+        KAVG_HIP(c, bf16_update_group(group.data(), (int)group.size(), c->stream));
+    }
+    return KAVG_OK;
+}
+
 int issue_steps(kavg_ctx* c) {
     if (!c->cv.ch.empty()) return issue_steps_conv(c);
     if (c->refresh > 1) return issue_steps_deferred(c);
@@ -708,25 +722,32 @@ int issue_steps(kavg_ctx* c) {
             }
             continue;
         }
+        std::vector<LayerCall> group;                        // updates that run as one launch after the backward pass
         for (int l = L; l >= 1; --l) {                       // backward; W_l is read before it is updated
             LayerCall q = layer_call(c, l, k);
-            if (head && l == L) {
+            if (!(head && l == L)) {
+                if (bf16_strip_ok(q)) {                      // data gradient and update in one pass over the weights
+                    Bracket br(c, KAVG_CLASS_UPDATE);
+                    KAVG_HIP(c, bf16_strip(q, st));
+                    continue;
+                }
+                if (l > 1) {
+                    Bracket br(c, KAVG_CLASS_BACKWARD);
+                    KAVG_HIP(c, bf16_backward_data(q, st));
+                }
+            }
+            if (bf16_update_group_ok(q)) {
+                group.push_back(q);
+            } else if (head && l == L) {
                 Bracket br(c, KAVG_CLASS_HEAD);
                 KAVG_HIP(c, head_update(q, idx_k, idx_ls, st));
-                continue;
-            }
-            if (bf16_strip_ok(q)) {                   // data gradient and update in one pass over the weights
+            } else {
                 Bracket br(c, KAVG_CLASS_UPDATE);
-                KAVG_HIP(c, bf16_strip(q, st));
-                continue;
+                KAVG_HIP(c, bf16_update(q, st));
             }
-            if (l > 1) {
-                Bracket br(c, KAVG_CLASS_BACKWARD);
-                KAVG_HIP(c, bf16_backward_data(q, st));
-            }
-            Bracket br(c, KAVG_CLASS_UPDATE);
-            KAVG_HIP(c, bf16_update(q, st));
         }
+        const int rc = issue_update_group(c, group, head);
+        if (rc != KAVG_OK) return rc;
     }
     {
         Bracket br(c, KAVG_CLASS_LOSS);
@@ -884,19 +905,26 @@ int issue_steps_conv(kavg_ctx* c) {
             KAVG_HIP(c, launch_softmax_ce(c->logits(), lo.ldz, c->dims[L], c->y, idx_k, idx_ls, B, P,
                                           c->ws + lo.off_dz[L - 1], (long)B * lo.ldz, 1, rowloss_k, st));
         }
+        std::vector<LayerCall> group;                               // updates that run as one launch after the backward pass
         for (int l = L; l >= 1; --l) {                              // MLP, backward; layer 1 hands dL/d(pooled) on
             LayerCall q = layer_call(c, l, k);
-            if (head && l == L) {
-                Bracket br(c, KAVG_CLASS_HEAD);
-                KAVG_HIP(c, head_update(q, idx_k, idx_ls, st));
-                continue;
-            }
-            {
+            if (!(head && l == L)) {
                 Bracket br(c, KAVG_CLASS_BACKWARD);
                 KAVG_HIP(c, bf16_backward_data(q, st));
             }
-            Bracket br(c, KAVG_CLASS_UPDATE);
-            KAVG_HIP(c, bf16_update(q, st));
+            if (bf16_update_group_ok(q)) {
+                group.push_back(q);
+            } else if (head && l == L) {
+                Bracket br(c, KAVG_CLASS_HEAD);
+                KAVG_HIP(c, head_update(q, idx_k, idx_ls, st));
+            } else {
+                Bracket br(c, KAVG_CLASS_UPDATE);
+                KAVG_HIP(c, bf16_update(q, st));
+            }
+        }
+        {
+            const int rc = issue_update_group(c, group, head);
+            if (rc != KAVG_OK) return rc;
         }
         // The gradient of the mean over the positions: written out for the generic kernels; the tile kernels of
         // the last convolution form it while loading (both of them must be in use, or the buffer is needed).

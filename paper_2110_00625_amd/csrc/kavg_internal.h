@@ -129,6 +129,9 @@ hipError_t bf16_update(const LayerCall& c, hipStream_t st);
 // data gradient and update of a layer in one pass over its weights (strip_bf16.hip); which calls it takes
 bool bf16_strip_ok(const LayerCall& c);
 hipError_t bf16_strip(const LayerCall& c, hipStream_t st);
+// the updates of n layers in one launch (update_bf16.hip); which calls it takes (the same batch and options for all)
+bool bf16_update_group_ok(const LayerCall& c);
+hipError_t bf16_update_group(const LayerCall* layers, int n, hipStream_t st);
 
 // ---- classifier head for small class counts (last layer: forward + loss + data gradient, then update) ----
 bool head_supported(int C);

@@ -1,0 +1,265 @@
+// The SGD updates of several layers in one launch (KAVG_BF16), for models whose weights stay in the memory-side cache:
+//
+//     W_l <- W_l - lr * dZ_l^T A_{l-1};    b_l <- b_l - lr * colsum(dZ_l)       (with learner momentum: u <- beta u + gradient, W <- W - lr u)
+//
+// (the learner update of Algorithm 1 on the fp32 master, stored as two 16-bit planes, split.h).  The updates of a step
+// depend on nothing but its backward pass, and on small models each launch is five microseconds of latency whatever it does.
+//
+// Workgroup = 64 output x 128 input units of one layer of one learner, four wavefronts of 32 x 64.  MFMA 32x32x16 bf16,
+// rows = input units, columns = output units, k = samples, both operands by transpose reads out of LDS in slices of 64
+// samples.  The master -- and the velocity -- are requested right after the first slice and arrive under the contraction;
+// the gradient passes through LDS so that a thread then holds eight consecutive columns of a row.
+//
+// Measured, all updates of a step, us (one launch per layer, the velocity read after the contraction -> this kernel):
+// 3072-1024-1024-10, 16 learners of 128 samples 80 + 31 + 9 -> 103 (5.3 TB/s); 3080-1032-520-24 with momentum, 5 learners of
+// 70: 84 + 19 + 8 -> 66; models of a few hundred units: 4 - 6 per layer -> 5 - 6 in all (a step 1.2 - 1.5x faster).  What bounds
+// it: the traffic of the planes on large models, latency on small ones.  Where the hi planes stream as well the one-layer
+// kernel and the head's are as fast (4096 wide, 32 learners: 630 against 595 + 23) and stay.
+#include "kavg_internal.h"
+#include "split.h"
+
+namespace kavg {
+
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+constexpr int NT = 256;
+constexpr int TR = 64, TC = 128, BK = 64;    // output units, input units, samples per slice
+constexpr int ZP = TR + 32, XP = TC + 32;    // LDS rows of the operands: 64 bytes of padding (transpose reads)
+constexpr int GP = TC + 4;                   // LDS rows of the gradient (fp32)
+constexpr int ZN = BK * TR / 8 / NT, XN = BK * TC / 8 / NT, WN = TR * TC / 8 / NT;
+constexpr int OPERANDS = BK * (ZP + XP) * 2, GRADIENT = TR * (GP + 1) * 4;
+constexpr int SMEM = OPERANDS > GRADIENT ? OPERANDS : GRADIENT;   // (the gradient lies over the operands)
+constexpr int GROUP = 8;                     // layers per launch
+
+struct Layer {
+    const uint16_t* dz; size_t dz_lstride; int ld_dz;                // [learner][B][ld_dz]
+    const uint16_t* in; size_t in_lstride; int ld_in;                // [learner][B][ld_in], or rows of a data set:
+    const int32_t* gather; const int32_t* next_gather; long gather_lstride;       // (this step's and the next's)
+    uint16_t* hi; uint16_t* lo; uint16_t* bhi; uint16_t* blo; float* u; float* ub;
+    int d_out, d_in, tiles_r, tiles_c, total, padded;
+};
+struct Args {
+    Layer layer[GROUP];
+    int n_layers, B;
+    size_t lstride;                          // between learners, in planes and velocities
+    float lr, beta;
+};
+
+// fragment of a [k][x] tile by transpose reads: lane l receives x0 + l%32 at k = k0 + 8 (l/32) .. +7
+__device__ __forceinline__ bf16x8 frag_tr(const uint16_t* tile, int pitch, int k0, int x0, int lane) {
+    const int t = lane & 15, grp = lane >> 4;
+    const uint16_t* p = tile + (k0 + (grp >> 1) * 8 + (t >> 2)) * pitch + x0 + (grp & 1) * 16 + (t & 3) * 4;
+    typedef bf16x4 __attribute__((address_space(3))) * lds_ptr;
+    const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr)p);
+    const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr)(p + 4 * pitch));
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
+template <bool STREAM, class T> __device__ __forceinline__ T get(const T* p) { return STREAM ? __builtin_nontemporal_load(p) : *p; }
+template <bool STREAM, class T> __device__ __forceinline__ void put(T* p, T v) { if (STREAM) __builtin_nontemporal_store(v, p); else *p = v; }
+
+// STREAM: the lo planes (and velocities) of all learners do not stay in the memory-side cache
+template <bool MOMENTUM, bool STREAM>
+__global__ void __launch_bounds__(NT, 2) update_group_kernel(Args a) {
+    __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM];
+    uint16_t* const Z = (uint16_t*)smem;                     // [BK][ZP] dZ
+    uint16_t* const X = Z + BK * ZP;                         // [BK][XP] activations
+    float* const G = (float*)smem;                           // [TR][GP] gradient
+    float* const GB = G + TR * GP;                           // [TR] column sums of dZ
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int g = blockIdx.x, li = 0;
+    while (li + 1 < a.n_layers && g >= a.layer[li].padded) g -= a.layer[li++].padded;
+    const Layer& q = a.layer[li];
+    // workgroup g runs on XCD g mod 8: each XCD gets one contiguous range of (learner, column tile, row tile)
+    int at = (g & 7) * (q.padded >> 3) + (g >> 3);
+    if (at >= q.total) return;
+    const int rt = at % q.tiles_r; at /= q.tiles_r;
+    const int ct = at % q.tiles_c, learner = at / q.tiles_c;
+    const int r0 = rt * TR, c0 = ct * TC, B = a.B;
+    const uint16_t* dz = q.dz + (size_t)learner * q.dz_lstride;
+    const uint16_t* in = q.in + (size_t)learner * q.in_lstride;
+    // (without a gather the look-ups read, and ignore, words of dZ: no branch around a load)
+    const int32_t* table = q.gather ? q.gather + (long)learner * q.gather_lstride : (const int32_t*)q.dz;
+    const int take = q.gather ? -1 : 0;
+    const size_t lat = (size_t)learner * a.lstride;
+
+    // No load is predicated: places outside are read from clamped ones and dropped later.
+    u32x4 zr[ZN], xr[XN];
+    int row[XN];                                             // memory rows of the slice that is requested next
+    auto look_up = [&](int k0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < XN; ++i) {
+            const int s = min(k0 + (tid + NT * i) / (TC / 8), B - 1);
+            row[i] = (table[s] & take) | (s & ~take);
+        }
+    };
+    auto load = [&](int k0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < ZN; ++i) {
+            const int e = tid + NT * i, s = min(k0 + e / (TR / 8), B - 1);
+            zr[i] = *(const u32x4*)(dz + (size_t)s * q.ld_dz + min(r0 + (e % (TR / 8)) * 8, q.ld_dz - 8));
+        }
+#pragma unroll
+        for (int i = 0; i < XN; ++i)
+            xr[i] = *(const u32x4*)(in + (long)row[i] * q.ld_in + min(c0 + (tid + NT * i) % (TC / 8) * 8, q.d_in - 8));
+    };
+    const u32x4 zero = {0u, 0u, 0u, 0u};
+    auto store = [&](int k0) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < ZN; ++i) {
+            const int e = tid + NT * i, s = e / (TR / 8);
+            *(u32x4*)(Z + s * ZP + (e % (TR / 8)) * 8) = k0 + s < B ? zr[i] : zero;
+        }
+#pragma unroll
+        for (int i = 0; i < XN; ++i) {
+            const int e = tid + NT * i, s = e / (TC / 8);
+            *(u32x4*)(X + s * XP + (e % (TC / 8)) * 8) = k0 + s < B ? xr[i] : zero;
+        }
+    };
+    look_up(0);
+    load(0);
+    look_up(BK);
+
+    // piece i of this thread: row (tid + 256 i) / 16 of the tile, eight columns
+    u32x4 hr[WN], lr_[WN];
+    f32x4 ur[MOMENTUM ? WN : 1][2];
+#pragma unroll
+    for (int i = 0; i < WN; ++i) {
+        const int e = tid + NT * i;
+        const size_t p = lat + (size_t)min(r0 + e / (TC / 8), q.d_out - 1) * q.d_in + min(c0 + e % (TC / 8) * 8, q.d_in - 8);
+        hr[i] = *(const u32x4*)(q.hi + p);
+        lr_[i] = get<STREAM>((const u32x4*)(q.lo + p));
+        if constexpr (MOMENTUM) { ur[i][0] = get<STREAM>((const f32x4*)(q.u + p)); ur[i][1] = get<STREAM>((const f32x4*)(q.u + p + 4)); }
+    }
+
+    const int rb = wave >> 1, cb = (wave & 1) * 2;           // 32 output units, two blocks of 32 input units
+    const bool bias = ct == 0 && cb == 0;                    // (uniform) this wavefront sums dZ as well: its product with ones
+    f32x16 acc[2], gb;
+    bf16x8 ones;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) { acc[0][e] = 0.f; acc[1][e] = 0.f; gb[e] = 0.f; }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
+    auto contract = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int k = 0; k < BK / 16; ++k) {
+            const bf16x8 zf = frag_tr(Z, ZP, k * 16, rb * 32, lane);
+#pragma unroll
+            for (int j = 0; j < 2; ++j)
+                acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_tr(X, XP, k * 16, (cb + j) * 32, lane), zf, acc[j], 0, 0, 0);
+        }
+        if (bias) {
+#pragma unroll
+            for (int k = 0; k < BK / 16; ++k) gb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, frag_tr(Z, ZP, k * 16, rb * 32, lane), gb, 0, 0, 0);
+        }
+    };
+    // the first slice outside the loop: its waits leave the master in flight
+    store(0);
+    __syncthreads();
+    if (B > BK) load(BK);
+    contract();
+    for (int k0 = BK; k0 < B; k0 += BK) {
+        __syncthreads();
+        store(k0);
+        __syncthreads();
+        if (k0 + BK < B) { look_up(k0 + BK); load(k0 + BK); }
+        contract();
+    }
+    __syncthreads();
+    // accumulator e: input unit 8 (e/4) + 4 (lane/32) + e%4 of the block, output unit lane%32
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+            *(f32x4*)(G + (rb * 32 + (lane & 31)) * GP + (cb + j) * 32 + 8 * t + 4 * (lane >> 5)) =
+                (f32x4){acc[j][4 * t], acc[j][4 * t + 1], acc[j][4 * t + 2], acc[j][4 * t + 3]};
+    if (bias && lane < 32) GB[rb * 32 + lane] = gb[0];       // (every row holds the same sums)
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < WN; ++i) {
+        const int e = tid + NT * i, r = r0 + e / (TC / 8), c = c0 + e % (TC / 8) * 8;
+        f32x4 g0 = *(const f32x4*)(G + (e / (TC / 8)) * GP + e % (TC / 8) * 8), g1 = *(const f32x4*)(G + (e / (TC / 8)) * GP + e % (TC / 8) * 8 + 4);
+        if constexpr (MOMENTUM) { g0 = a.beta * ur[i][0] + g0; g1 = a.beta * ur[i][1] + g1; }
+        const float gs[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
+        u32x4 oh, ol;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            uint32_t b0, b1, h2, l2;
+            split_join2(hr[i][t], lr_[i][t], b0, b1);
+            const float w0 = __builtin_bit_cast(float, b0) - a.lr * gs[2 * t], w1 = __builtin_bit_cast(float, b1) - a.lr * gs[2 * t + 1];
+            split_pack2(__builtin_bit_cast(uint32_t, w0), __builtin_bit_cast(uint32_t, w1), h2, l2);
+            oh[t] = h2; ol[t] = l2;
+        }
+        if (r < q.d_out && c < q.d_in) {
+            const size_t p = lat + (size_t)r * q.d_in + c;
+            *(u32x4*)(q.hi + p) = oh;
+            put<STREAM>((u32x4*)(q.lo + p), ol);
+            if constexpr (MOMENTUM) { put<STREAM>((f32x4*)(q.u + p), g0); put<STREAM>((f32x4*)(q.u + p + 4), g1); }
+        }
+    }
+    if (ct == 0 && tid < TR && r0 + tid < q.d_out) {
+        const size_t p = lat + r0 + tid;
+        float gsum = GB[tid];
+        if constexpr (MOMENTUM) { gsum = a.beta * q.ub[p] + gsum; q.ub[p] = gsum; }
+        const float b = __builtin_bit_cast(float, split_join(q.bhi[p], q.blo[p])) - a.lr * gsum;
+        q.bhi[p] = (uint16_t)split_hi(__builtin_bit_cast(uint32_t, b));
+        q.blo[p] = (uint16_t)split_lo(__builtin_bit_cast(uint32_t, b));
+    }
+    if (rt == 0 && q.next_gather) {
+        // the lines of the rows that the next step gathers, so that its forward pass finds them in the cache
+        for (int e = tid; e < B * 2; e += NT) {
+            const int c = c0 + (e & 1) * 64;
+            if (c < q.d_in) {
+                const uint32_t v = *(const uint32_t*)(in + (long)q.next_gather[(long)learner * q.gather_lstride + (e >> 1)] * q.ld_in + c);
+                asm volatile("" ::"v"(v));
+            }
+        }
+    }
+}
+
+}  // namespace
+
+bool bf16_update_group_ok(const LayerCall& c) {
+    return c.shadow_cached && !c.rows && !c.partial && !c.skip_bias && c.d_in >= 8 && c.ld_dz >= 8;
+}
+
+hipError_t bf16_update_group(const LayerCall* calls, int n, hipStream_t st) {
+    for (int at = 0; at < n; at += GROUP) {
+        Args a = {};
+        a.n_layers = n - at < GROUP ? n - at : GROUP;
+        a.B = calls[at].B; a.lstride = calls[at].ws_stride; a.lr = calls[at].lr; a.beta = calls[at].beta;
+        int wgs = 0;
+        for (int i = 0; i < a.n_layers; ++i) {
+            const LayerCall& c = calls[at + i];
+            Layer& q = a.layer[i];
+            q.dz = (const uint16_t*)c.dz; q.dz_lstride = c.dz_stride; q.ld_dz = c.ld_dz;
+            q.in = (const uint16_t*)c.in; q.in_lstride = c.gather ? 0 : c.in_stride; q.ld_in = c.ld_in;
+            q.gather = c.gather; q.next_gather = c.gather ? c.next_gather : nullptr; q.gather_lstride = c.gather_stride;
+            q.hi = c.ws; q.lo = c.wlo; q.bhi = c.bhi; q.blo = c.blo; q.u = c.u; q.ub = c.ub;
+            q.d_out = c.d_out; q.d_in = c.d_in;
+            q.tiles_r = (c.d_out + TR - 1) / TR; q.tiles_c = (c.d_in + TC - 1) / TC;
+            q.total = q.tiles_r * q.tiles_c * c.P;
+            q.padded = (q.total + 7) / 8 * 8;
+            wgs += q.padded;
+        }
+        // (the memory-side cache holds 256 MB: read-modify-write at 6.9 TB/s inside it, and outside it 5.4 with ordinary and
+        // 6.2 TB/s with streaming accesses)
+        const bool momentum = calls[at].u != nullptr;
+        const bool stream = (size_t)calls[at].P * a.lstride * (momentum ? 8 : 4) > ((size_t)224 << 20);
+        if (momentum && stream) hipLaunchKernelGGL((update_group_kernel<true, true>), dim3(wgs), dim3(NT), 0, st, a);
+        else if (momentum) hipLaunchKernelGGL((update_group_kernel<true, false>), dim3(wgs), dim3(NT), 0, st, a);
+        else if (stream) hipLaunchKernelGGL((update_group_kernel<false, true>), dim3(wgs), dim3(NT), 0, st, a);
+        else hipLaunchKernelGGL((update_group_kernel<false, false>), dim3(wgs), dim3(NT), 0, st, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+}  // namespace kavg
