@@ -17,30 +17,31 @@
 // and tiles at the edge of an operand are read word by word, and nothing outside an operand is read at all.  An
 // operand with k contiguous in memory ("K": activations, dZ, W of the forward pass) lies in LDS as [x][k] and a lane
 // reads four k at once; one with x contiguous ("X": W of backward-data, both operands of the update) as [k][x].
-// Step i of a group of eight k takes k = 4*(lane/32) + i from either layout.  k order and tiles depend on the shapes
-// only, so results are deterministic.
+// Every output is one chain of matrix instructions over ascending pairs of k (per split, see below), whatever the tile, so
+// results depend on neither tiles nor timing.  (In fp32 a pre-activation whose sum is taken in another order can fall on
+// the other side of zero, once in some ten million, and moves a row of a gradient by a sample's share.)
 //
 // What bounds these kernels: 3072-512 with 64 rows and 8 learners is 1.6 GFLOP per product, 10 us of the matrix
 // cores' fp32 rate; the update also moves 100 MB of weights, 15 us out of the memory-side cache.  Measured on
-// 3072-512-256-10 (8 learners, 64 rows): split forward product 24 -> 13 us per launch (mean of the two layers),
-// backward-data 24 -> 10 us, all updates of a step 75 -> 31 us; a round of four steps 657 -> 336 us.  (Before: 64x64
+// 3072-512-256-10 (8 learners, 64 rows): split forward product 24 -> 14 us per launch (mean of the two layers),
+// backward-data 24 -> 11 us, the updates of a step 75 -> 29 + 5 us; a round of four steps 657 -> 358 us.  (Before: 64x64
 // tiles everywhere, operands moved word by word, one slice ahead, the weights read after the contraction.)
 //
 // The forward pass may split the contraction over several workgroups where a layer has few output tiles: each writes
 // its partial tile to a scratch buffer and a second small kernel adds the partials in ascending split order, then
-// applies bias and ReLU.  The updates of all layers of a step are one launch: they depend on nothing but the backward
-// pass, and on small models each launch is a few microseconds of latency.
+// applies bias and ReLU.  The updates of all layers of a step (but a thin last one, head.hip) are one launch: they depend
+// on nothing but the backward pass, and on small models each launch is a few microseconds of latency.
 #include "kavg_internal.h"
+#include "loss_mean.h"
 
 namespace kavg {
 
 namespace {
 
 constexpr int BK = 32;         // contraction slice
-constexpr int TC = 64;         // columns of a forward / backward tile
 constexpr int UR = 64, UC = 128;   // tile of the update: units x inputs
 constexpr int KPITCH = BK + 4; // [x][k] rows: 16-byte reads of 16 lanes fall on 16 different groups of four banks
-__host__ __device__ constexpr int xpitch(int X) { return X + 8; }   // [k][x] rows: rows k and k+4 lie 32 banks apart
+__host__ __device__ constexpr int xpitch(int X) { return X + 8; }   // [k][x] rows
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
@@ -76,7 +77,8 @@ struct KLoader {
     int k4, at, nK, k_end;
     __device__ __forceinline__ void init(const float* base, long ld, const int32_t* gather, int x0, int nX, int nK_, int k_end_, int tid) {
         k4 = (tid & 7) * 4;
-        at = (tid >> 3) * KPITCH + k4;
+        // in LDS the even k of a group of eight come first, then the odd ones: a half wavefront reads every second k
+        at = (tid >> 3) * KPITCH + (k4 & ~7) + (k4 & 7) / 2;
         nK = nK_; k_end = k_end_;
 #pragma unroll
         for (int i = 0; i < N; ++i) {
@@ -105,7 +107,10 @@ struct KLoader {
             }
         }
 #pragma unroll
-        for (int i = 0; i < N; ++i) *(f32x4*)(lds + at + 32 * i * KPITCH) = v[i];
+        for (int i = 0; i < N; ++i) {
+            *(float2*)(lds + at + 32 * i * KPITCH) = make_float2(v[i][0], v[i][2]);
+            *(float2*)(lds + at + 32 * i * KPITCH + 4) = make_float2(v[i][1], v[i][3]);
+        }
     }
 };
 
@@ -195,12 +200,12 @@ struct RowArgs {
     const float* mask; size_t mask_lstride; int ld_mask;            // backward: previous activations
 };
 
-// TR = 64: four wavefronts own the quarters of a 64x64 tile.  TR = 32: two wavefronts side by side, two more with the
-// other half of every slice; their sums meet in LDS.  (32 rows serve batches whose last 64-row tile would be at most
-// half full, and layers with too few 64-row tiles for the chip.)
+// 64 x 64 tile in quarters, or 32 x 128 with the four wavefronts side by side (for batches whose last 64-row tile would be
+// at most half full).
 template <int EPI, int TR, bool WORDS>
-__global__ void __launch_bounds__(256, WORDS ? 3 : 4) rows_kernel(RowArgs a) {
+__global__ void __launch_bounds__(256, WORDS || TR == 32 ? 3 : 4) rows_kernel(RowArgs a) {
     constexpr bool CK = EPI != EPI_BWD;
+    constexpr int TC = TR == 64 ? 64 : 128;
     constexpr int CSZ = CK ? TC * KPITCH : BK * xpitch(TC);
     __shared__ __align__(16) float lds[2][TR * KPITCH + CSZ];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, m = lane & 31, half = lane >> 5;
@@ -210,7 +215,7 @@ __global__ void __launch_bounds__(256, WORDS ? 3 : 4) rows_kernel(RowArgs a) {
     const int rt = at % a.tiles_r; at /= a.tiles_r;
     const int split = at % a.splits, learner = at / a.splits;
     const int r0 = rt * TR, c0 = ct * TC;
-    const int rq = TR == 64 ? (wave >> 1) * 32 : 0, cq = (wave & 1) * 32;
+    const int rq = TR == 64 ? (wave >> 1) * 32 : 0, cq = TR == 64 ? (wave & 1) * 32 : wave * 32;
     const int k_begin = split * a.k_chunk, k_end = min(k_begin + a.k_chunk, a.nK);
 
     typedef KLoader<TR, WORDS> RLoader;
@@ -224,7 +229,7 @@ __global__ void __launch_bounds__(256, WORDS ? 3 : 4) rows_kernel(RowArgs a) {
     else lcx.init(a.C + (size_t)learner * a.c_lstride, a.ldC, c0, a.nC, a.nK, tid);
 
     f32x16 acc = {};
-    f32x4 rv[2][RLoader::N], cv[2][2];
+    f32x4 rv[2][RLoader::N], cv[2][TC / 32];
     auto load = [&](int set, int s) __attribute__((always_inline)) {
         const int k0 = k_begin + s * BK;
         lr.load(rv[set], k0);
@@ -243,17 +248,14 @@ __global__ void __launch_bounds__(256, WORDS ? 3 : 4) rows_kernel(RowArgs a) {
         if constexpr (CK) lck.store(cv[set], C, k0); else lcx.store(cv[set], C, k0);
         if (more) load(set, s + 2);
         __syncthreads();
-        constexpr int G = TR == 64 ? BK / 8 : BK / 16;                // groups of eight k this wavefront contracts
-        const int g0 = TR == 64 ? 0 : (wave >> 1) * G;
 #pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const int k = (g0 + g) * 8 + 4 * half;
-            const f32x4 r4 = *(const f32x4*)(R + (rq + m) * KPITCH + k);
+        for (int g = 0; g < BK / 8; ++g) {                            // half a wavefront: k = 8 g + half, + 2, + 4, + 6
+            const f32x4 r4 = *(const f32x4*)(R + (rq + m) * KPITCH + 8 * g + 4 * half);
             f32x4 c4;
-            if constexpr (CK) c4 = *(const f32x4*)(C + (cq + m) * KPITCH + k);
+            if constexpr (CK) c4 = *(const f32x4*)(C + (cq + m) * KPITCH + 8 * g + 4 * half);
             else {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) c4[i] = C[(k + i) * xpitch(TC) + cq + m];
+                for (int i = 0; i < 4; ++i) c4[i] = C[(8 * g + 2 * i + half) * xpitch(TC) + cq + m];
             }
 #pragma unroll
             for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(r4[i], c4[i], acc, 0, 0, 0);
@@ -262,22 +264,6 @@ __global__ void __launch_bounds__(256, WORDS ? 3 : 4) rows_kernel(RowArgs a) {
     pipeline((k_end - k_begin + BK - 1) / BK, load, step);
 
     // accumulator v of lane l is the output (row 8*(v/4) + 4*(l/32) + v%4, column l%32) of the wavefront's block
-    int v0 = 0, v1 = 16;
-    if constexpr (TR == 32) {
-        // the two halves of the contraction: each wavefront hands over half of its sums and finishes the other half
-        const int kh = wave >> 1;
-        __syncthreads();
-        float* xch = lds[0];
-#pragma unroll
-        for (int v = 0; v < 8; ++v) xch[(wave * 8 + v) * 64 + lane] = kh ? acc[v] : acc[v + 8];
-        __syncthreads();
-#pragma unroll
-        for (int v = 0; v < 8; ++v) {
-            const float other = xch[((wave ^ 2) * 8 + v) * 64 + lane];
-            if (kh) acc[v + 8] = other + acc[v + 8]; else acc[v] = acc[v] + other;
-        }
-        v0 = kh * 8; v1 = v0 + 8;
-    }
     const int c = c0 + cq + m;
     if (c >= a.nC) return;
     float* out = a.out + (size_t)learner * a.out_lstride + c;
@@ -287,7 +273,7 @@ __global__ void __launch_bounds__(256, WORDS ? 3 : 4) rows_kernel(RowArgs a) {
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
         const int r = r0 + rq + 8 * (v >> 2) + 4 * half + (v & 3);
-        if (v < v0 || v >= v1 || r >= a.nR) continue;
+        if (r >= a.nR) continue;
         float z = acc[v];
         if (EPI == EPI_FWD) { z += b; if (a.relu) z = fmaxf(z, 0.f); }
         if (EPI == EPI_BWD) z = mask[(size_t)r * a.ld_mask] > 0.f ? z : 0.f;
@@ -307,6 +293,7 @@ struct UpdArgs {
     int n_layers, B;
     size_t lstride;            // between learners, in weights and velocities
     float lr, beta;
+    LossMeans losses;          // n > 0: computed by the workgroups behind those of the layers, four each
 };
 
 // 64 x 128 tile of a layer's weights (53 KB of LDS, 168 registers: three workgroups per compute unit).  A wavefront owns
@@ -391,7 +378,7 @@ __device__ __forceinline__ void update_tile(const UpdArgs& a, const UpdLayer& q,
         __syncthreads();
 #pragma unroll
         for (int t = 0; t < BK / 2; ++t) {
-            const int k = (t >> 2) * 8 + (t & 3) + 4 * half;
+            const int k = 2 * t + half;
             const float r1 = R[k * xpitch(UR) + rq + m];
             const float2 c2 = *(const float2*)(C + k * xpitch(UC) + cq + 2 * m);
             acc0 = __builtin_amdgcn_mfma_f32_32x32x2f32(r1, c2.x, acc0, 0, 0, 0);
@@ -436,6 +423,11 @@ __global__ void __launch_bounds__(256, WORDS ? 2 : 3) update_kernel(UpdArgs a) {
     int g = blockIdx.x, li = 0;
     while (li + 1 < a.n_layers && g >= a.layer[li].padded) g -= a.layer[li++].padded;
     const UpdLayer& q = a.layer[li];
+    if (g >= q.padded) {
+        const int r = (g - q.padded) * 4 + (threadIdx.x >> 6);
+        if (r < a.losses.n) loss_mean_wave(a.losses, r, threadIdx.x & 63);
+        return;
+    }
     int at = xcd_range(g, q.padded);
     if (at >= q.total) return;
     const int rt = at % q.tiles_r; at /= q.tiles_r;
@@ -473,18 +465,11 @@ finish_forward_kernel(const float* __restrict__ partial, size_t split_stride, in
 
 int div_up(int a, int b) { return (a + b - 1) / b; }
 
-// Rows per tile of a forward / backward product: 32 where that leaves no more padding than half of a 64-row tile would
-// waste, or where 64-row tiles are too few for the 256 compute units.
-int tile_rows(int P, int B, int cols, int splits) {
-    if (div_up(B, 32) & 1) return 32;
-    return (long)div_up(B, 64) * div_up(cols, TC) * P * splits < 256 ? 32 : 64;
-}
-
 template <int EPI>
 hipError_t run_rows(RowArgs& a, int P, hipStream_t st) {
-    const int TR = tile_rows(P, a.nR, a.nC, a.splits);
+    const int TR = div_up(a.nR, 32) & 1 ? 32 : 64;      // 32: a last tile of 64 rows would be at most half full
     a.tiles_r = div_up(a.nR, TR);
-    a.tiles_c = div_up(a.nC, TC);
+    a.tiles_c = div_up(a.nC, TR == 64 ? 64 : 128);
     a.total = a.tiles_r * a.tiles_c * a.splits * P;
     a.padded = div_up(a.total, 8) * 8;
     const bool words = a.nK < 4 || (EPI == EPI_BWD && a.nC < 4);
@@ -500,7 +485,7 @@ hipError_t run_rows(RowArgs& a, int P, hipStream_t st) {
 // How the forward pass of a layer splits its contraction: returns the number of splits and the
 // contraction range of each (a multiple of the slice length).  Depends on the shapes only.
 int f32_forward_plan(int P, int B, int d_in, int d_out, int* chunk_out) {
-    const long tiles = (long)div_up(B, 64) * div_up(d_out, TC) * P;
+    const long tiles = (long)div_up(B, 64) * div_up(d_out, 64) * P;
     long s = 1;
     if (tiles < 256 && d_in > 4 * BK) {
         s = (512 + tiles - 1) / tiles;               // aim at ~512 workgroups
@@ -550,7 +535,7 @@ hipError_t f32_backward_data(const LayerCall& c, hipStream_t st) {
     return run_rows<EPI_BWD>(a, c.P, st);
 }
 
-hipError_t f32_update(const LayerCall* calls, int n, hipStream_t st) {
+hipError_t f32_update(const LayerCall* calls, int n, const LossMeans* losses, hipStream_t st) {
     for (int at = 0; at < n; at += GROUP) {
         UpdArgs a = {};
         a.n_layers = n - at < GROUP ? n - at : GROUP;
@@ -570,6 +555,10 @@ hipError_t f32_update(const LayerCall* calls, int n, hipStream_t st) {
             q.padded = div_up(q.total, 8) * 8;
             wgs += q.padded;
             words = words || c.d_in < 4 || c.ld_dz < 4 || c.d_in >= 1 << 24;     // (2^24: reach of lane_at)
+        }
+        if (losses && at + a.n_layers == n) {
+            a.losses = *losses;
+            wgs += (losses->n + 3) / 4;
         }
         if (words) hipLaunchKernelGGL(update_kernel<true>, dim3(wgs), dim3(256), 0, st, a);
         else hipLaunchKernelGGL(update_kernel<false>, dim3(wgs), dim3(256), 0, st, a);

@@ -3,14 +3,13 @@
 // With ten classes the last layer is a sliver: its forward product, the
 // softmax cross-entropy, its data gradient and its weight update together
 // move a few hundred KB per learner, and as four generic launches they cost
-// four launch-plus-pipeline latencies.  Two kernels replace them (fp32: the
-// first one; the update of the last layer is part of the fp32 update launch):
+// four launch-plus-pipeline latencies.  Two kernels replace them:
 //
 //  head_forward_backward   one wavefront per sample row:
 //        z = A_{L-1}[s] W_L^T + b_L                     (lanes split the contraction, butterfly sum)
 //        loss_s = -log softmax(z)[y_s],  dZ_L[s] = (softmax(z) - onehot(y_s)) / B   (the 1/B_n of Algorithm 1)
 //        dZ_{L-1}[s] = (dZ_L[s] W_L) * [A_{L-1}[s] > 0]
-//  head_update (bf16)      W_L <- W_L - lr * dZ_L^T A_{L-1},  b_L <- b_L - lr * colsum(dZ_L)
+//  head_update             W_L <- W_L - lr * dZ_L^T A_{L-1},  b_L <- b_L - lr * colsum(dZ_L)
 //        (the learner update of Algorithm 1 for the last layer; runs after the kernel above
 //        because that one reads the weights of before the step)
 //
@@ -99,7 +98,7 @@ struct HeadArgs {
     const void* act; int ld_act; size_t act_lstride;      // A_{L-1} [P][B][ld_act], or the data set when gather != null
     const int32_t* gather; long gather_lstride;           // row s of learner j is data row gather[j*gather_lstride + s]
     const void* wmul; size_t wmul_lstride;                // weights as multiplied: bf16 (hi) plane or fp32, [C][d]
-    size_t w_lstride;                                     // between learners in fp32 parameters and velocities
+    float* wmaster; size_t w_lstride;                     // fp32 mode: the layer's weights
     float* bias;                                          // fp32 mode: its bias (stride w_lstride)
     uint16_t* whi; uint16_t* wlo; size_t ws_lstride;      // bf16 mode: hi / lo planes of the weights (split.h)
     uint16_t* bhi; uint16_t* blo;                         // bf16 mode: hi / lo planes of the bias (stride ws_lstride)
@@ -261,18 +260,29 @@ __global__ void __launch_bounds__(256) head_forward_backward_kernel(HeadArgs a) 
 }
 
 // One row of dZ_L (ldz <= 16 values) as floats; entries beyond ldz are zero.
+template <bool BF16>
 __device__ __forceinline__ void load_dz_row(const void* dz, size_t at, int ldz, float* out /*[16]*/) {
 #pragma unroll
     for (int i = 0; i < 16; ++i) out[i] = 0.f;
-    const u32x4 lo = *(const u32x4*)((const uint16_t*)dz + at);
-    u32x4 hi = {0u, 0u, 0u, 0u};
-    if (ldz > 8) hi = *(const u32x4*)((const uint16_t*)dz + at + 8);
+    if (BF16) {
+        const u32x4 lo = *(const u32x4*)((const uint16_t*)dz + at);
+        u32x4 hi = {0u, 0u, 0u, 0u};
+        if (ldz > 8) hi = *(const u32x4*)((const uint16_t*)dz + at + 8);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        out[2 * i] = __builtin_bit_cast(float, lo[i] << 16);
-        out[2 * i + 1] = __builtin_bit_cast(float, lo[i] & 0xFFFF0000u);
-        out[8 + 2 * i] = __builtin_bit_cast(float, hi[i] << 16);
-        out[8 + 2 * i + 1] = __builtin_bit_cast(float, hi[i] & 0xFFFF0000u);
+        for (int i = 0; i < 4; ++i) {
+            out[2 * i] = __builtin_bit_cast(float, lo[i] << 16);
+            out[2 * i + 1] = __builtin_bit_cast(float, lo[i] & 0xFFFF0000u);
+            out[8 + 2 * i] = __builtin_bit_cast(float, hi[i] << 16);
+            out[8 + 2 * i + 1] = __builtin_bit_cast(float, hi[i] & 0xFFFF0000u);
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (4 * i < ldz) {                                // ldz is a multiple of 8
+                const f32x4 v = *(const f32x4*)((const float*)dz + at + 4 * i);
+                out[4 * i] = v.x; out[4 * i + 1] = v.y; out[4 * i + 2] = v.z; out[4 * i + 3] = v.w;
+            }
+        }
     }
 }
 
@@ -282,9 +292,9 @@ __device__ __forceinline__ void load_dz_row(const void* dz, size_t at, int ldz, 
 // sixteen groups, after which lane group g applies the update of class c = g.
 constexpr int XCH_CS = 16 * 32 + 36;      // floats between classes in a wavefront's exchange patch (36: classes fall on different banks)
 
-template <int CT>
+template <bool BF16, int CT>
 __global__ void __launch_bounds__(256) head_update_kernel(HeadArgs a) {
-    constexpr int N = Piece<true>::N;
+    constexpr int N = Piece<BF16>::N;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int grp = lane >> 2, pl = lane & 3;
     const int q = blockIdx.x * 16 + wave * 4 + pl;
@@ -305,10 +315,10 @@ __global__ void __launch_bounds__(256) head_update_kernel(HeadArgs a) {
     for (int s = grp; s < a.B; s += 16) {
         const size_t arow = a.act_lstride ? (size_t)learner * a.act_lstride + (size_t)s * a.ld_act
                                           : (size_t)g[s] * a.ld_act;
-        Piece<true> x;
+        Piece<BF16> x;
         x.load(a.act, arow + (size_t)qq * N);
         float gz[16];
-        load_dz_row(a.dz, (size_t)learner * a.dz_lstride + (size_t)s * a.ldz, a.ldz, gz);
+        load_dz_row<BF16>(a.dz, (size_t)learner * a.dz_lstride + (size_t)s * a.ldz, a.ldz, gz);
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
             bsum[c] += gz[c];                                  // bias gradient: column sum of dZ_L
@@ -322,25 +332,43 @@ __global__ void __launch_bounds__(256) head_update_kernel(HeadArgs a) {
         bsum[c] = groups_sum(b);
     }
     float mine[N];
-    // Lane group g needs class g's gradient of the wavefront's four pieces, summed over the sixteen sample
-    // groups: each lane leaves its CT x 8 partial sums in the wavefront's LDS patch and lane group g adds
-    // the sixteen partials of class g in ascending group order (a butterfly would move every value four
-    // times, this moves it twice).  A wavefront's LDS accesses complete in order: no barrier.
-    extern __shared__ __align__(16) float head_xch[];
-    float* patch = head_xch + wave * (CT * XCH_CS);
+    if constexpr (BF16) {
+        // Lane group g needs class g's gradient of the wavefront's four pieces, summed over the sixteen sample
+        // groups: each lane leaves its CT x 8 partial sums in the wavefront's LDS patch and lane group g adds
+        // the sixteen partials of class g in ascending group order (a butterfly would move every value four
+        // times, this moves it twice).  A wavefront's LDS accesses complete in order: no barrier.
+        extern __shared__ __align__(16) float head_xch[];
+        float* patch = head_xch + wave * (CT * XCH_CS);
 #pragma unroll
-    for (int c = 0; c < CT; ++c) {
-        *(f32x4*)(patch + c * XCH_CS + lane * 8) = (f32x4){acc[c][0], acc[c][1], acc[c][2], acc[c][3]};
-        *(f32x4*)(patch + c * XCH_CS + lane * 8 + 4) = (f32x4){acc[c][4], acc[c][5], acc[c][6], acc[c][7]};
-    }
+        for (int c = 0; c < CT; ++c) {
+            *(f32x4*)(patch + c * XCH_CS + lane * 8) = (f32x4){acc[c][0], acc[c][1], acc[c][2], acc[c][3]};
+            *(f32x4*)(patch + c * XCH_CS + lane * 8 + 4) = (f32x4){acc[c][4], acc[c][5], acc[c][6], acc[c][7]};
+        }
 #pragma unroll
-    for (int e = 0; e < N; ++e) mine[e] = 0.f;
-    const float* src = patch + min(grp, CT - 1) * XCH_CS + pl * 8;
+        for (int e = 0; e < N; ++e) mine[e] = 0.f;
+        const float* src = patch + min(grp, CT - 1) * XCH_CS + pl * 8;
 #pragma unroll
-    for (int g2 = 0; g2 < 16; ++g2) {
-        const f32x4 lo4 = *(const f32x4*)(src + g2 * 32), hi4 = *(const f32x4*)(src + g2 * 32 + 4);
-        mine[0] += lo4.x; mine[1 % N] += lo4.y; mine[2 % N] += lo4.z; mine[3 % N] += lo4.w;
-        mine[4 % N] += hi4.x; mine[5 % N] += hi4.y; mine[6 % N] += hi4.z; mine[7 % N] += hi4.w;
+        for (int g2 = 0; g2 < 16; ++g2) {
+            const f32x4 lo4 = *(const f32x4*)(src + g2 * 32), hi4 = *(const f32x4*)(src + g2 * 32 + 4);
+            mine[0] += lo4.x; mine[1 % N] += lo4.y; mine[2 % N] += lo4.z; mine[3 % N] += lo4.w;
+            mine[4 % N] += hi4.x; mine[5 % N] += hi4.y; mine[6 % N] += hi4.z; mine[7 % N] += hi4.w;
+        }
+    } else {
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+#pragma unroll
+            for (int e = 0; e < N; ++e) {
+                float v = acc[c][e];
+                acc[c][e] = groups_sum(v);
+            }
+#pragma unroll
+        for (int e = 0; e < N; ++e) mine[e] = 0.f;
+#pragma unroll
+        for (int c = 0; c < CT; ++c)
+            if (c == grp) {
+#pragma unroll
+                for (int e = 0; e < N; ++e) mine[e] = acc[c][e];
+            }
     }
     if (live && grp < a.C) {
         const size_t uat = (size_t)learner * a.w_lstride + (size_t)grp * a.d + (size_t)q * N;   // velocity (fp32 layout)
@@ -348,22 +376,28 @@ __global__ void __launch_bounds__(256) head_update_kernel(HeadArgs a) {
 #pragma unroll
             for (int e = 0; e < N; ++e) { mine[e] = a.beta * a.u[uat + e] + mine[e]; a.u[uat + e] = mine[e]; }
         }
-        // the master lives in two 16-bit planes; the hi plane is what the next products read
-        const size_t at = (size_t)learner * a.ws_lstride + (size_t)grp * a.d + (size_t)q * N;
-        const u32x4 h = *(const u32x4*)(a.whi + at), l = *(const u32x4*)(a.wlo + at);
-        u32x4 oh, ol;
+        if (BF16) {
+            // the master lives in two 16-bit planes; the hi plane is what the next products read
+            const size_t at = (size_t)learner * a.ws_lstride + (size_t)grp * a.d + (size_t)q * N;
+            const u32x4 h = *(const u32x4*)(a.whi + at), l = *(const u32x4*)(a.wlo + at);
+            u32x4 oh, ol;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            uint32_t b0, b1;
-            split_join2(h[i], l[i], b0, b1);
-            const float w0 = __builtin_bit_cast(float, b0) - a.lr * mine[(2 * i) % N];
-            const float w1 = __builtin_bit_cast(float, b1) - a.lr * mine[(2 * i + 1) % N];
-            uint32_t h2, l2;
-            split_pack2(__builtin_bit_cast(uint32_t, w0), __builtin_bit_cast(uint32_t, w1), h2, l2);
-            oh[i] = h2; ol[i] = l2;
+            for (int i = 0; i < 4; ++i) {
+                uint32_t b0, b1;
+                split_join2(h[i], l[i], b0, b1);
+                const float w0 = __builtin_bit_cast(float, b0) - a.lr * mine[(2 * i) % N];
+                const float w1 = __builtin_bit_cast(float, b1) - a.lr * mine[(2 * i + 1) % N];
+                uint32_t h2, l2;
+                split_pack2(__builtin_bit_cast(uint32_t, w0), __builtin_bit_cast(uint32_t, w1), h2, l2);
+                oh[i] = h2; ol[i] = l2;
+            }
+            *(u32x4*)(a.whi + at) = oh;
+            *(u32x4*)(a.wlo + at) = ol;
+        } else {
+            float* wm = a.wmaster + uat;
+#pragma unroll
+            for (int e = 0; e < N; ++e) wm[e] = wm[e] - a.lr * mine[e];
         }
-        *(u32x4*)(a.whi + at) = oh;
-        *(u32x4*)(a.wlo + at) = ol;
     }
     if (blockIdx.x == 0 && wave == 0 && pl == 0 && grp < a.C) {   // every lane holds the full column sums
         float mine = 0.f;
@@ -371,10 +405,14 @@ __global__ void __launch_bounds__(256) head_update_kernel(HeadArgs a) {
         for (int c = 0; c < CT; ++c) if (c == grp) mine = bsum[c];
         const size_t at = (size_t)learner * a.w_lstride + grp;
         if (a.ub) { mine = a.beta * a.ub[at] + mine; a.ub[at] = mine; }
-        const size_t sat = (size_t)learner * a.ws_lstride + grp;
-        const float b = __builtin_bit_cast(float, split_join(a.bhi[sat], a.blo[sat])) - a.lr * mine;
-        a.bhi[sat] = (uint16_t)split_hi(__builtin_bit_cast(uint32_t, b));
-        a.blo[sat] = (uint16_t)split_lo(__builtin_bit_cast(uint32_t, b));
+        if (BF16) {
+            const size_t sat = (size_t)learner * a.ws_lstride + grp;
+            const float b = __builtin_bit_cast(float, split_join(a.bhi[sat], a.blo[sat])) - a.lr * mine;
+            a.bhi[sat] = (uint16_t)split_hi(__builtin_bit_cast(uint32_t, b));
+            a.blo[sat] = (uint16_t)split_lo(__builtin_bit_cast(uint32_t, b));
+        } else {
+            a.bias[at] = a.bias[at] - a.lr * mine;
+        }
     }
 }
 
@@ -384,7 +422,7 @@ HeadArgs make_args(const LayerCall& c, const int32_t* y, const int32_t* idx, lon
     a.gather = idx; a.gather_lstride = idx_lstride;
     a.wmul = bf16 ? (const void*)c.ws : (const void*)c.w;
     a.wmul_lstride = bf16 ? c.ws_stride : c.w_stride;
-    a.w_lstride = c.w_stride; a.bias = c.b;
+    a.wmaster = c.w; a.w_lstride = c.w_stride; a.bias = c.b;
     a.whi = c.ws; a.wlo = c.wlo; a.ws_lstride = c.ws_stride; a.bhi = c.bhi; a.blo = c.blo;
     a.y = y;
     a.dz = (void*)c.dz; a.ldz = c.ld_dz; a.dz_lstride = c.dz_stride;
@@ -412,22 +450,23 @@ void launch_fb(const HeadArgs& a, dim3 grid, hipStream_t st) {
     const int pieces = a.d / Piece<BF16>::N;
     if (pieces <= 128) launch_fb2<BF16, true>(a, grid, st); else launch_fb2<BF16, false>(a, grid, st);
 }
-template <int CT>
+template <bool BF16, int CT>
 hipError_t launch_upd_ct(const HeadArgs& a, dim3 grid, hipStream_t st) {
-    constexpr int SMEM = 4 * CT * XCH_CS * 4;                  // one exchange patch per wavefront
+    constexpr int SMEM = BF16 ? 4 * CT * XCH_CS * 4 : 0;       // one exchange patch per wavefront
     if (SMEM > 64 * 1024) {
-        static hipError_t raised = hipFuncSetAttribute((const void*)head_update_kernel<CT>,
+        static hipError_t raised = hipFuncSetAttribute((const void*)head_update_kernel<BF16, CT>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
         if (raised != hipSuccess) return raised;
     }
-    hipLaunchKernelGGL((head_update_kernel<CT>), grid, dim3(256), SMEM, st, a);
+    hipLaunchKernelGGL((head_update_kernel<BF16, CT>), grid, dim3(256), SMEM, st, a);
     return hipSuccess;
 }
+template <bool BF16>
 hipError_t launch_upd(const HeadArgs& a, dim3 grid, hipStream_t st) {
-    if (a.C <= 4) return launch_upd_ct<4>(a, grid, st);
-    if (a.C <= 8) return launch_upd_ct<8>(a, grid, st);
-    if (a.C <= 12) return launch_upd_ct<12>(a, grid, st);
-    return launch_upd_ct<16>(a, grid, st);
+    if (a.C <= 4) return launch_upd_ct<BF16, 4>(a, grid, st);
+    if (a.C <= 8) return launch_upd_ct<BF16, 8>(a, grid, st);
+    if (a.C <= 12) return launch_upd_ct<BF16, 12>(a, grid, st);
+    return launch_upd_ct<BF16, 16>(a, grid, st);
 }
 
 }  // namespace
@@ -440,11 +479,11 @@ hipError_t head_forward_backward(const LayerCall& c, const int32_t* y, const int
     return hipGetLastError();
 }
 
-hipError_t head_update(const LayerCall& c, const int32_t* idx, long idx_lstride, hipStream_t st) {
-    HeadArgs a = make_args(c, nullptr, idx, idx_lstride, nullptr, true);
-    const int pieces = c.d_in / 8;
+hipError_t head_update(const LayerCall& c, const int32_t* idx, long idx_lstride, int bf16, hipStream_t st) {
+    HeadArgs a = make_args(c, nullptr, idx, idx_lstride, nullptr, bf16 != 0);
+    const int pieces = c.d_in / (bf16 ? 8 : 1);
     dim3 grid((pieces + 15) / 16, c.P);
-    const hipError_t e = launch_upd(a, grid, st);
+    const hipError_t e = bf16 ? launch_upd<true>(a, grid, st) : launch_upd<false>(a, grid, st);
     return e != hipSuccess ? e : hipGetLastError();
 }
 

@@ -664,15 +664,26 @@ int issue_steps_fused(kavg_ctx* c) {
 
 // The updates of a step that are left to one launch.  While updates are profiled every layer is a launch of its own, so that
 // the brackets tell the classes apart.
-int issue_update_group(kavg_ctx* c, const std::vector<LayerCall>& group, bool head) {
-    if (c->prof_mask & ((1u << KAVG_CLASS_UPDATE) | (1u << KAVG_CLASS_HEAD))) {
+// last: the round's last step -- the mean losses of the round then run in the same launch, or in one of their own.
+int issue_update_group(kavg_ctx* c, const std::vector<LayerCall>& group, bool head, bool last) {
+    const bool bf = c->dtype == KAVG_BF16;
+    const LossMeans losses = {c->rowloss(), c->losses(), c->K * c->P, c->B};
+    auto update = [&](const LayerCall* q, int n, const LossMeans* l) {
+        return bf ? bf16_update_group(q, n, l, c->stream) : f32_update(q, n, l, c->stream);
+    };
+    const unsigned apart = (1u << KAVG_CLASS_UPDATE) | (1u << KAVG_CLASS_HEAD) | (1u << KAVG_CLASS_LOSS);
+    if (group.empty() || (c->prof_mask & apart)) {
         for (const LayerCall& q : group) {
             Bracket br(c, head && q.out == c->logits() ? KAVG_CLASS_HEAD : KAVG_CLASS_UPDATE);
-            KAVG_HIP(c, bf16_update_group(&q, 1, c->stream));
+            KAVG_HIP(c, update(&q, 1, nullptr));
         }
-    } else if (!group.empty()) {
-        KAVG_HIP(c, bf16_update_group(group.data(), (int)group.size(), c->stream));
+        if (last) {
+            Bracket br(c, KAVG_CLASS_LOSS);
+            KAVG_HIP(c, launch_loss_mean(losses, c->stream));
+        }
+        return KAVG_OK;
     }
+    KAVG_HIP(c, update(group.data(), (int)group.size(), last ? &losses : nullptr));
     return KAVG_OK;
 }
 
@@ -705,21 +716,19 @@ int issue_steps(kavg_ctx* c) {
                                           c->ws + c->lo.off_dz[L - 1], (long)c->B * c->lo.ldz, bf ? 1 : 0, rowloss_k, st));
         }
         if (!bf) {
-            // the data gradients of all layers, then the updates of all layers in one launch
+            // the data gradients of all layers, then the updates: of a thin last layer, and of all others in one launch
             for (int l = head ? L - 1 : L; l > 1; --l) {
                 Bracket br(c, KAVG_CLASS_BACKWARD);
                 KAVG_HIP(c, f32_backward_data(layer_call(c, l, k), st));
             }
-            std::vector<LayerCall> updates;
-            for (int l = 1; l <= L; ++l) updates.push_back(layer_call(c, l, k));
-            if (c->prof_mask & ((1u << KAVG_CLASS_UPDATE) | (1u << KAVG_CLASS_HEAD))) {     // one bracket per layer
-                for (int l = L; l >= 1; --l) {
-                    Bracket br(c, head && l == L ? KAVG_CLASS_HEAD : KAVG_CLASS_UPDATE);
-                    KAVG_HIP(c, f32_update(&updates[l - 1], 1, st));
-                }
-            } else {
-                KAVG_HIP(c, f32_update(updates.data(), L, st));
+            if (head) {
+                Bracket br(c, KAVG_CLASS_HEAD);
+                KAVG_HIP(c, head_update(layer_call(c, L, k), idx_k, idx_ls, 0, st));
             }
+            std::vector<LayerCall> updates;
+            for (int l = head ? L - 1 : L; l >= 1; --l) updates.push_back(layer_call(c, l, k));
+            const int rc = issue_update_group(c, updates, head, k == c->K - 1);
+            if (rc != KAVG_OK) return rc;
             continue;
         }
         std::vector<LayerCall> group;                        // updates that run as one launch after the backward pass
@@ -740,18 +749,14 @@ int issue_steps(kavg_ctx* c) {
                 group.push_back(q);
             } else if (head && l == L) {
                 Bracket br(c, KAVG_CLASS_HEAD);
-                KAVG_HIP(c, head_update(q, idx_k, idx_ls, st));
+                KAVG_HIP(c, head_update(q, idx_k, idx_ls, 1, st));
             } else {
                 Bracket br(c, KAVG_CLASS_UPDATE);
                 KAVG_HIP(c, bf16_update(q, st));
             }
         }
-        const int rc = issue_update_group(c, group, head);
+        const int rc = issue_update_group(c, group, head, k == c->K - 1);
         if (rc != KAVG_OK) return rc;
-    }
-    {
-        Bracket br(c, KAVG_CLASS_LOSS);
-        KAVG_HIP(c, launch_loss_mean(c->rowloss(), c->losses(), c->K * c->P, c->B, st));
     }
     return KAVG_OK;
 }
@@ -916,14 +921,14 @@ int issue_steps_conv(kavg_ctx* c) {
                 group.push_back(q);
             } else if (head && l == L) {
                 Bracket br(c, KAVG_CLASS_HEAD);
-                KAVG_HIP(c, head_update(q, idx_k, idx_ls, st));
+                KAVG_HIP(c, head_update(q, idx_k, idx_ls, 1, st));
             } else {
                 Bracket br(c, KAVG_CLASS_UPDATE);
                 KAVG_HIP(c, bf16_update(q, st));
             }
         }
         {
-            const int rc = issue_update_group(c, group, head);
+            const int rc = issue_update_group(c, group, head, k == c->K - 1);
             if (rc != KAVG_OK) return rc;
         }
         // The gradient of the mean over the positions: written out for the generic kernels; the tile kernels of
@@ -998,10 +1003,6 @@ int issue_steps_conv(kavg_ctx* c) {
             KAVG_HIP(c, launch_conv_step((uint16_t*)q.ws, (uint16_t*)q.wlo, (uint16_t*)q.bhi, (uint16_t*)q.blo, lo.stride,
                                          q.partial, q.partial_bias, P, q.splits, q.d_out * q.d_in, q.d_out, c->lr, st));
         }
-    }
-    {
-        Bracket br(c, KAVG_CLASS_LOSS);
-        KAVG_HIP(c, launch_loss_mean(c->rowloss(), c->losses(), c->K * P, B, st));
     }
     return KAVG_OK;
 }
@@ -1095,7 +1096,7 @@ int issue_steps_deferred(kavg_ctx* c) {
             LayerCall q = call(l, k, slot);
             if (head && l == L) {
                 Bracket br(c, KAVG_CLASS_HEAD);
-                KAVG_HIP(c, head_update(q, idx_k, idx_ls, st));       // the thin last layer is stepped at once
+                KAVG_HIP(c, head_update(q, idx_k, idx_ls, 1, st));       // the thin last layer is stepped at once
                 continue;
             }
             if (l > 1) {
@@ -1141,7 +1142,7 @@ int issue_steps_deferred(kavg_ctx* c) {
     }
     {
         Bracket br(c, KAVG_CLASS_LOSS);
-        KAVG_HIP(c, launch_loss_mean(c->rowloss(), c->losses(), K * P, B, st));
+        KAVG_HIP(c, launch_loss_mean({c->rowloss(), c->losses(), K * P, B}, st));
     }
     return KAVG_OK;
 }

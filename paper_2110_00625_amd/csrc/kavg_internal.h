@@ -40,8 +40,9 @@ hipError_t launch_broadcast(const float* w_tilde, float* reps, size_t stride,
 hipError_t launch_softmax_ce(const float* logits, int ldz, int C, const int32_t* y,
                              const int32_t* idx, long idx_learner_stride, int B, int P,
                              void* dz, long dz_learner_stride, int dz_bf16, float* rowloss, hipStream_t st);
-// losses[k][j] = mean_m rowloss[k][j][m]
-hipError_t launch_loss_mean(const float* rowloss, float* losses, int KP, int B, hipStream_t st);
+// losses[r] = mean_m rowloss[r][m], r = k*P + j, n of them (loss_mean.h)
+struct LossMeans { const float* rowloss; float* losses; int n, B; };
+hipError_t launch_loss_mean(const LossMeans& a, hipStream_t st);
 
 // ---- per-learner dense layers ----
 struct LayerCall {
@@ -121,7 +122,8 @@ hipError_t launch_bias_step(uint16_t* bhi, uint16_t* blo, size_t b_stride, const
 int f32_forward_plan(int P, int B, int d_in, int d_out, int* chunk_out);
 hipError_t f32_forward(const LayerCall& c, hipStream_t st);
 hipError_t f32_backward_data(const LayerCall& c, hipStream_t st);
-hipError_t f32_update(const LayerCall* layers, int n, hipStream_t st);   // all n layers in one launch
+// all n layers in one launch, and the mean losses of a round where `losses` is not null
+hipError_t f32_update(const LayerCall* layers, int n, const LossMeans* losses, hipStream_t st);
 // bf16 MFMA path
 hipError_t bf16_forward(const LayerCall& c, hipStream_t st);
 hipError_t bf16_backward_data(const LayerCall& c, hipStream_t st);
@@ -129,16 +131,17 @@ hipError_t bf16_update(const LayerCall& c, hipStream_t st);
 // data gradient and update of a layer in one pass over its weights (strip_bf16.hip); which calls it takes
 bool bf16_strip_ok(const LayerCall& c);
 hipError_t bf16_strip(const LayerCall& c, hipStream_t st);
-// the updates of n layers in one launch (update_bf16.hip); which calls it takes (the same batch and options for all)
+// the updates of n layers in one launch (update_bf16.hip), with the mean losses as f32_update; which calls it takes (the
+// same batch and options for all)
 bool bf16_update_group_ok(const LayerCall& c);
-hipError_t bf16_update_group(const LayerCall* layers, int n, hipStream_t st);
+hipError_t bf16_update_group(const LayerCall* layers, int n, const LossMeans* losses, hipStream_t st);
 
 // ---- classifier head for small class counts (last layer: forward + loss + data gradient, then update) ----
 bool head_supported(int C);
 // idx: this step's indices of learner 0, idx_lstride elements between learners
 hipError_t head_forward_backward(const LayerCall& c, const int32_t* y, const int32_t* idx, long idx_lstride,
                                  float* rowloss, int bf16, hipStream_t st);
-hipError_t head_update(const LayerCall& c, const int32_t* idx, long idx_lstride, hipStream_t st);   // bf16 (fp32: f32_update)
+hipError_t head_update(const LayerCall& c, const int32_t* idx, long idx_lstride, int bf16, hipStream_t st);
 
 // ---- convolutional layers (conv.hip): 3x3, stride 1, zero padding 1, channels-last bf16 images ----
 // patches[j][(n,h,w)][(kh,kw,c)] from images in[j][n][h][w][c] (or, with gather, from rows gather[j*gstride+n] of a shared set)

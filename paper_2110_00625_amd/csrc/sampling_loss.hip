@@ -1,6 +1,7 @@
 // Minibatch index stream, label / index validation, and the fused
 // softmax-cross-entropy + gradient kernel of the learner step.
 #include "kavg_internal.h"
+#include "loss_mean.h"
 
 namespace kavg {
 
@@ -170,19 +171,10 @@ hipError_t launch_softmax_ce(const float* logits, int ldz, int C, const int32_t*
     return hipGetLastError();
 }
 
-// losses[r] = (1/B) sum_m rowloss[r][m], r = k*P + j; one wavefront per r, fixed order.
-__global__ void __launch_bounds__(64)
-loss_mean_kernel(const float* __restrict__ rowloss, float* __restrict__ losses, int B) {
-    const int lane = threadIdx.x;
-    const float* p = rowloss + (long)blockIdx.x * B;
-    float s = 0.f;
-    for (int m = lane; m < B; m += 64) s += p[m];
-    s = wave_sum(s);
-    if (lane == 0) losses[blockIdx.x] = s / (float)B;
-}
+__global__ void __launch_bounds__(64) loss_mean_kernel(LossMeans a) { loss_mean_wave(a, blockIdx.x, threadIdx.x); }
 
-hipError_t launch_loss_mean(const float* rowloss, float* losses, int KP, int B, hipStream_t st) {
-    hipLaunchKernelGGL(loss_mean_kernel, dim3(KP), dim3(64), 0, st, rowloss, losses, B);
+hipError_t launch_loss_mean(const LossMeans& a, hipStream_t st) {
+    hipLaunchKernelGGL(loss_mean_kernel, dim3(a.n), dim3(64), 0, st, a);
     return hipGetLastError();
 }
 

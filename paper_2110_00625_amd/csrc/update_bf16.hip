@@ -16,6 +16,7 @@
 // it: the traffic of the planes on large models, latency on small ones.  Where the hi planes stream as well the one-layer
 // kernel and the head's are as fast (4096 wide, 32 learners: 630 against 595 + 23) and stay.
 #include "kavg_internal.h"
+#include "loss_mean.h"
 #include "split.h"
 
 namespace kavg {
@@ -49,6 +50,7 @@ struct Args {
     int n_layers, B;
     size_t lstride;                          // between learners, in planes and velocities
     float lr, beta;
+    LossMeans losses;                        // n > 0: computed by the workgroups behind those of the layers, four each
 };
 
 // fragment of a [k][x] tile by transpose reads: lane l receives x0 + l%32 at k = k0 + 8 (l/32) .. +7
@@ -76,6 +78,11 @@ __global__ void __launch_bounds__(NT, 2) update_group_kernel(Args a) {
     int g = blockIdx.x, li = 0;
     while (li + 1 < a.n_layers && g >= a.layer[li].padded) g -= a.layer[li++].padded;
     const Layer& q = a.layer[li];
+    if (g >= q.padded) {
+        const int r = (g - q.padded) * 4 + wave;
+        if (r < a.losses.n) loss_mean_wave(a.losses, r, lane);
+        return;
+    }
     // workgroup g runs on XCD g mod 8: each XCD gets one contiguous range of (learner, column tile, row tile)
     int at = (g & 7) * (q.padded >> 3) + (g >> 3);
     if (at >= q.total) return;
@@ -229,7 +236,7 @@ bool bf16_update_group_ok(const LayerCall& c) {
     return c.shadow_cached && !c.rows && !c.partial && !c.skip_bias && c.d_in >= 8 && c.ld_dz >= 8;
 }
 
-hipError_t bf16_update_group(const LayerCall* calls, int n, hipStream_t st) {
+hipError_t bf16_update_group(const LayerCall* calls, int n, const LossMeans* losses, hipStream_t st) {
     for (int at = 0; at < n; at += GROUP) {
         Args a = {};
         a.n_layers = n - at < GROUP ? n - at : GROUP;
@@ -247,6 +254,10 @@ hipError_t bf16_update_group(const LayerCall* calls, int n, hipStream_t st) {
             q.total = q.tiles_r * q.tiles_c * c.P;
             q.padded = (q.total + 7) / 8 * 8;
             wgs += q.padded;
+        }
+        if (losses && at + a.n_layers == n) {
+            a.losses = *losses;
+            wgs += (losses->n + 3) / 4;
         }
         // (the memory-side cache holds 256 MB: read-modify-write at 6.9 TB/s inside it, and outside it 5.4 with ordinary and
         // 6.2 TB/s with streaming accesses)
