@@ -147,31 +147,36 @@ pool_backward_kernel(const uint16_t* __restrict__ dpool, const uint16_t* __restr
     *(u32x4*)(dz + e * 8) = pool_grad_piece(m, g, inv);
 }
 
-// W[j][e] -= lr * sum_s partial[(j*S+s)][e]  and  b[j][r] -= lr * sum_s pbias[(j*S+s)][r]  on the master's planes
-__global__ void __launch_bounds__(256)
-conv_step_kernel(uint16_t* whi, uint16_t* wlo, uint16_t* bhi, uint16_t* blo, size_t lstride, const float* __restrict__ partial,
-                 const float* __restrict__ pbias, int S, int n_w, int n_b, float lr) {
-    const int e = blockIdx.x * 256 + threadIdx.x;
+// The SGD steps of several convolutions: adds up the S partial gradients of an element (eight requested together, added in
+// ascending order) and steps the master.  One launch for all layers of a step: one each, with one partial sum requested at a
+// time, took 14 us per layer on 28x28 images with channels 8-32-64, this takes STEP_US for both.
+constexpr int STEP_GROUP = 8;
+struct StepArgs { ConvStep layer[STEP_GROUP]; int n; size_t lstride; float lr; };
+
+__global__ void __launch_bounds__(256) conv_step_kernel(StepArgs a) {
+    int b = blockIdx.x, i0 = 0;
+    while (i0 + 1 < a.n && b >= (a.layer[i0].n_w + a.layer[i0].n_b + 255) / 256) { b -= (a.layer[i0].n_w + a.layer[i0].n_b + 255) / 256; ++i0; }
+    const ConvStep& q = a.layer[i0];
+    const int e = b * 256 + threadIdx.x;
     const int j = blockIdx.y;
-    if (e >= n_w + n_b) return;
-    const bool is_w = e < n_w;
-    const int i = is_w ? e : e - n_w;
-    const float* p = is_w ? partial + (size_t)j * S * n_w + i : pbias + (size_t)j * S * n_b + i;
-    const size_t step = is_w ? (size_t)n_w : (size_t)n_b;
-    // eight partial sums requested together, added in ascending order (one at a time: 14 us per launch with 16 ranges)
+    if (e >= q.n_w + q.n_b) return;
+    const bool is_w = e < q.n_w;
+    const int i = is_w ? e : e - q.n_w;
+    const float* p = is_w ? q.partial + (size_t)j * q.S * q.n_w + i : q.pbias + (size_t)j * q.S * q.n_b + i;
+    const size_t step = is_w ? (size_t)q.n_w : (size_t)q.n_b;
     float s = 0.f;
-    int q = 0;
-    for (; q + 8 <= S; q += 8) {
+    int r = 0;
+    for (; r + 8 <= q.S; r += 8) {
         float t[8];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) t[u] = p[(size_t)(q + u) * step];
+        for (int u = 0; u < 8; ++u) t[u] = p[(size_t)(r + u) * step];
 #pragma unroll
         for (int u = 0; u < 8; ++u) s += t[u];
     }
-    for (; q < S; ++q) s += p[(size_t)q * step];
-    uint16_t* hi = (is_w ? whi : bhi) + (size_t)j * lstride + i;
-    uint16_t* lo = (is_w ? wlo : blo) + (size_t)j * lstride + i;
-    const float v = __builtin_bit_cast(float, split_join(*hi, *lo)) - lr * s;
+    for (; r < q.S; ++r) s += p[(size_t)r * step];
+    uint16_t* hi = (is_w ? q.whi : q.bhi) + (size_t)j * a.lstride + i;
+    uint16_t* lo = (is_w ? q.wlo : q.blo) + (size_t)j * a.lstride + i;
+    const float v = __builtin_bit_cast(float, split_join(*hi, *lo)) - a.lr * s;
     *hi = (uint16_t)split_hi(__builtin_bit_cast(uint32_t, v));
     *lo = (uint16_t)split_lo(__builtin_bit_cast(uint32_t, v));
 }
@@ -234,11 +239,21 @@ hipError_t launch_rotate_weights(const uint16_t* whi, size_t w_lstride, uint16_t
     return hipGetLastError();
 }
 
-hipError_t launch_conv_step(uint16_t* whi, uint16_t* wlo, uint16_t* bhi, uint16_t* blo, size_t lstride, const float* partial,
-                            const float* pbias, int P, int S, int n_w, int n_b, float lr, hipStream_t st) {
-    hipLaunchKernelGGL(conv_step_kernel, dim3(blocks((size_t)n_w + n_b), P), dim3(256), 0, st, whi, wlo, bhi, blo, lstride,
-                       partial, pbias, S, n_w, n_b, lr);
-    return hipGetLastError();
+hipError_t launch_conv_steps(const ConvStep* layers, int n, size_t lstride, int P, float lr, hipStream_t st) {
+    for (int at = 0; at < n; at += STEP_GROUP) {
+        StepArgs a = {};
+        a.n = n - at < STEP_GROUP ? n - at : STEP_GROUP;
+        a.lstride = lstride; a.lr = lr;
+        unsigned wgs = 0;
+        for (int i = 0; i < a.n; ++i) {
+            a.layer[i] = layers[at + i];
+            wgs += blocks((size_t)a.layer[i].n_w + a.layer[i].n_b);
+        }
+        hipLaunchKernelGGL(conv_step_kernel, dim3(wgs, P), dim3(256), 0, st, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace kavg

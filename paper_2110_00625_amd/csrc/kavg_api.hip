@@ -37,7 +37,8 @@ struct Layout {
     std::vector<size_t> off_patch, off_cact, off_cdz;   // per convolution: patch matrix, output images, their dZ
     std::vector<int> splits;               // ranges of positions its weight gradient is split over
     std::vector<int> splits_halo;          // the same for the all-taps weight-gradient kernel; 0: shape not covered
-    size_t off_draw = 0, off_pool = 0, off_dpool = 0, off_partial = 0, off_pbias = 0;
+    size_t off_draw = 0, off_pool = 0, off_dpool = 0;
+    std::vector<size_t> off_partial, off_pbias;          // per convolution: partial weight gradients
     bool conv_implicit = false;            // convolutions 2.. form their patch matrices inside the MFMA kernel's loaders
     // images of any width (conv_flat.hip, conv_flat_wgrad.hip), per convolution: plans (slabs = 0: shape not covered), weights
     // in operand order, ranges of the weight gradient (0: not covered); one table of positions for all
@@ -132,7 +133,7 @@ Layout make_layout(int P, int K, int B, int L, const int* dims, int dtype, const
     }
     if (M > 0) {
         const size_t rows = (size_t)B * cv.H * cv.W;
-        size_t draw = 0, partial = 0, pbias = 0, wrot = 0;
+        size_t draw = 0, wrot = 0;
         lo.conv_implicit = (size_t)cv.H * cv.W < ((size_t)1 << 14);     // range of the loaders' multiply-shift divisions
         for (int t = 1; t <= M; ++t) {
             const int S1 = (t == 1 && lo.conv_implicit) ? conv_first_splits(P, B, cv.H, cv.W, cv.ch[0], cv.ch[1]) : 0;
@@ -167,8 +168,8 @@ Layout make_layout(int P, int K, int B, int L, const int* dims, int dtype, const
             if (Sh > S) S = Sh;                                          // (sizes the partial buffers below)
             if (Sf > S) S = Sf;
             const size_t nw = (size_t)cv.ch[t] * 9 * cv.ch[t - 1];
-            if ((size_t)P * S * nw * 4 > partial) partial = (size_t)P * S * nw * 4;
-            if ((size_t)P * S * cv.ch[t] * 4 > pbias) pbias = (size_t)P * S * cv.ch[t] * 4;
+            lo.off_partial.push_back(take((size_t)P * S * nw * 4));
+            lo.off_pbias.push_back(take((size_t)P * S * cv.ch[t] * 4));
         }
         lo.off_draw = draw ? take(draw) : 0;
         lo.off_wrot = wrot ? take(wrot) : 0;
@@ -177,8 +178,6 @@ Layout make_layout(int P, int K, int B, int L, const int* dims, int dtype, const
         lo.off_flat_table = flat ? take((size_t)conv_flat_table_len(B, cv.H, cv.W) * 4) : 0;
         lo.off_pool = take((size_t)P * B * cv.ch[M] * 2);
         lo.off_dpool = take((size_t)P * B * cv.ch[M] * 2);
-        lo.off_partial = take(partial);
-        lo.off_pbias = take(pbias);
     }
     lo.total = p;
     return lo;
@@ -831,7 +830,7 @@ int issue_steps_conv(kavg_ctx* c) {
         v.in = c->ws + lo.off_cact[t - 2]; v.out = c->ws + lo.off_cact[t - 1];
         v.dz = c->ws + lo.off_cdz[t - 1]; v.dz_in = c->ws + lo.off_cdz[t - 2];
         v.wrot = (const uint16_t*)(c->ws + lo.off_wrot); v.wrot_stride = (size_t)9 * v.c_out * v.c_in;
-        v.partial = (float*)(c->ws + lo.off_partial); v.partial_bias = (float*)(c->ws + lo.off_pbias);
+        v.partial = (float*)(c->ws + lo.off_partial[t - 1]); v.partial_bias = (float*)(c->ws + lo.off_pbias[t - 1]);
         v.splits = lo.splits[t - 1];
         return v;
     };
@@ -842,7 +841,7 @@ int issue_steps_conv(kavg_ctx* c) {
         v.ws = c->hi_planes() + lo.cw_off[0]; v.wlo = c->lo_planes() + lo.cw_off[0]; v.ws_stride = lo.stride;
         v.bhi = c->hi_planes() + lo.cb_off[0]; v.blo = c->lo_planes() + lo.cb_off[0];
         v.out = c->ws + lo.off_cact[0]; v.dz = c->ws + lo.off_cdz[0];
-        v.partial = (float*)(c->ws + lo.off_partial); v.partial_bias = (float*)(c->ws + lo.off_pbias);
+        v.partial = (float*)(c->ws + lo.off_partial[0]); v.partial_bias = (float*)(c->ws + lo.off_pbias[0]);
         v.splits = lo.splits_halo[0];
         return v;
     };
@@ -942,6 +941,7 @@ int issue_steps_conv(kavg_ctx* c) {
             KAVG_HIP(c, launch_pool_backward(c->ws + lo.off_dpool, c->ws + lo.off_cact[M - 1], c->ws + lo.off_cdz[M - 1],
                                              P, B, H * W, cv.ch[M], st));
         }
+        std::vector<ConvStep> steps;                                // SGD steps of all convolutions, after their data gradients
         for (int t = M; t >= 1; --t) {                              // convolutions, backward
             if (t > 1 && lo.conv_implicit) {
                 ConvCall v = implicit_call(t);
@@ -968,8 +968,7 @@ int issue_steps_conv(kavg_ctx* c) {
                 } else {
                     KAVG_HIP(c, bf16_conv_update_partial(v, st));
                 }
-                KAVG_HIP(c, launch_conv_step(v.ws, v.wlo, (uint16_t*)v.bhi, (uint16_t*)v.blo, lo.stride, v.partial, v.partial_bias,
-                                             P, v.splits, v.c_out * 9 * v.c_in, v.c_out, c->lr, st));
+                steps.push_back({v.ws, v.wlo, (uint16_t*)v.bhi, (uint16_t*)v.blo, v.partial, v.partial_bias, v.splits, v.c_out * 9 * v.c_in, v.c_out});
                 continue;
             }
             if (t == 1 && (flat_update(1) || first_direct)) {
@@ -981,8 +980,7 @@ int issue_steps_conv(kavg_ctx* c) {
                 } else {
                     KAVG_HIP(c, conv_first_wgrad(v, c->X, idx_k, idx_ls, st));
                 }
-                KAVG_HIP(c, launch_conv_step(v.ws, v.wlo, (uint16_t*)v.bhi, (uint16_t*)v.blo, lo.stride, v.partial, v.partial_bias,
-                                             P, v.splits, v.c_out * 9 * v.c_in, v.c_out, c->lr, st));
+                steps.push_back({v.ws, v.wlo, (uint16_t*)v.bhi, (uint16_t*)v.blo, v.partial, v.partial_bias, v.splits, v.c_out * 9 * v.c_in, v.c_out});
                 continue;
             }
             LayerCall q = conv_call(t);
@@ -996,13 +994,14 @@ int issue_steps_conv(kavg_ctx* c) {
                                                c->ws + lo.off_cdz[t - 2], P, B, H, W, cv.ch[t - 1], st));
             }
             Bracket br(c, KAVG_CLASS_UPDATE);
-            q.partial = (float*)(c->ws + lo.off_partial);
-            q.partial_bias = (float*)(c->ws + lo.off_pbias);
+            q.partial = (float*)(c->ws + lo.off_partial[t - 1]);
+            q.partial_bias = (float*)(c->ws + lo.off_pbias[t - 1]);
             q.splits = lo.splits[t - 1];
             KAVG_HIP(c, bf16_update(q, st));
-            KAVG_HIP(c, launch_conv_step((uint16_t*)q.ws, (uint16_t*)q.wlo, (uint16_t*)q.bhi, (uint16_t*)q.blo, lo.stride,
-                                         q.partial, q.partial_bias, P, q.splits, q.d_out * q.d_in, q.d_out, c->lr, st));
+            steps.push_back({q.ws, q.wlo, q.bhi, q.blo, q.partial, q.partial_bias, q.splits, q.d_out * q.d_in, q.d_out});
         }
+        Bracket br(c, KAVG_CLASS_UPDATE);
+        KAVG_HIP(c, launch_conv_steps(steps.data(), M, lo.stride, P, c->lr, st));
     }
     return KAVG_OK;
 }
