@@ -74,7 +74,8 @@ bool shapes_ok(int P, int K, int B, int L, const int* dims, int dtype) {
     return true;
 }
 
-Layout make_layout(int P, int K, int B, int L, const int* dims, int dtype, const ConvSpec& cv = ConvSpec()) {
+// units: with the scratch of fused_units.hip where it covers the shape
+Layout make_layout(int P, int K, int B, int L, const int* dims, int dtype, const ConvSpec& cv = ConvSpec(), bool units = true) {
     Layout lo;
     const size_t esz = dtype == KAVG_BF16 ? 2 : 4;     // activation / dZ element size
     size_t o = 0;
@@ -123,7 +124,7 @@ Layout make_layout(int P, int K, int B, int L, const int* dims, int dtype, const
         // (sized for a device of up to 256 compute units; the context decides with the real count)
         if (L == 2 && M == 0) {
             if (fused_small_shape_ok(P, K, B, dims[0], dims[1], dims[2], 256)) lo.fused_bytes = fused_small_scratch_bytes(P, dims[0]);
-            const int UN = fused_units_plan(P, K, B, dims[0], dims[1], dims[2], 256);
+            const int UN = units ? fused_units_plan(P, K, B, dims[0], dims[1], dims[2], 256) : 0;
             if (UN > 0) {
                 const size_t need_units = fused_units_scratch_bytes(P, B, dims[1], UN);
                 if (need_units > lo.fused_bytes) lo.fused_bytes = need_units;
@@ -428,7 +429,7 @@ bool conv_spec(ConvSpec* cv, int H, int W, int n_conv, const int* channels) {
 
 int init_common(kavg_ctx** out, int P, int K, float lr, float mu, int n_layers, const int* dims, int B,
                 int dtype, uint64_t index_seed, void* workspace_dev, size_t workspace_bytes,
-                void* hip_stream, const ConvSpec& cv) {
+                void* hip_stream, const ConvSpec& cv, bool units = true) {
     if (!out) return fail(nullptr, KAVG_EINVAL, "out is null");
     *out = nullptr;
     kavg_ctx* c = nullptr;
@@ -443,7 +444,7 @@ int init_common(kavg_ctx** out, int P, int K, float lr, float mu, int n_layers, 
     if (!(mu >= 0.f && mu < 1.f)) return fail(nullptr, KAVG_EINVAL, "mu must lie in [0,1)");
     if (!workspace_dev || ((uintptr_t)workspace_dev % ALIGN) != 0)
         return fail(nullptr, KAVG_EINVAL, "workspace must be a non-null, 256-byte aligned device pointer");
-    Layout lo = make_layout(P, K, B, n_layers, dims, dtype, cv);
+    Layout lo = make_layout(P, K, B, n_layers, dims, dtype, cv, units);
     if (workspace_bytes < lo.total)
         return fail(nullptr, KAVG_ENOMEM, "workspace has %zu bytes, %zu needed", workspace_bytes, lo.total);
     c = new (std::nothrow) kavg_ctx();
@@ -469,7 +470,7 @@ int init_common(kavg_ctx** out, int P, int K, float lr, float mu, int n_layers, 
         if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
         c->compute_units = cus < 256 ? cus : 256;          // (what the scratch was sized for)
         c->fused_ok = e == hipSuccess && fused_small_shape_ok(P, K, B, dims[0], dims[1], dims[2], c->compute_units);
-        c->units_ok = e == hipSuccess && fused_units_plan(P, K, B, dims[0], dims[1], dims[2], c->compute_units) > 0;
+        c->units_ok = e == hipSuccess && units && fused_units_plan(P, K, B, dims[0], dims[1], dims[2], c->compute_units) > 0;
         if (e == hipSuccess) e = hipMemsetAsync(c->ws + lo.off_fused, 0, lo.fused_bytes, c->stream);
     }
     if (e == hipSuccess && lo.off_flat_table) e = launch_flat_table((int32_t*)(c->ws + lo.off_flat_table), B, cv.H, cv.W, c->stream);
@@ -541,10 +542,16 @@ int kavg_init_static(kavg_ctx** out, int P, int K, float lr, float mu, int n_lay
                      int dtype, uint64_t index_seed, void* hip_stream) {
     if (!out) return fail(nullptr, KAVG_EINVAL, "out is null");
     *out = nullptr;
-    const size_t need = kavg_workspace_bytes(P, K, B, n_layers, dims, dtype);
+    size_t need = kavg_workspace_bytes(P, K, B, n_layers, dims, dtype);
     if (need == 0)
         return fail(nullptr, KAVG_EINVAL, "bad shape: need P,K,B >= 1 (P,K <= 2^24, B <= 65536), "
                     "dims >= 1 and, for bf16, d_0..d_{L-1} multiples of 8");
+    bool units = true;
+    if (need > STATIC_WS_BYTES) {            // the block also takes what fits without the scratch of fused_units.hip: one launch per layer then
+        size_t bare = need;
+        try { bare = make_layout(P, K, B, n_layers, dims, dtype, ConvSpec(), false).total; } catch (...) {}
+        if (bare <= STATIC_WS_BYTES) { units = false; need = bare; }
+    }
     if (need > STATIC_WS_BYTES)
         return fail(nullptr, KAVG_ENOMEM, "this configuration needs %zu bytes of workspace, the library's own block "
                     "holds %zu: use kavg_init with a caller workspace", need, STATIC_WS_BYTES);
@@ -561,8 +568,8 @@ int kavg_init_static(kavg_ctx** out, int P, int K, float lr, float mu, int n_lay
     }
     if (g_static_owner[dev])
         return fail(nullptr, KAVG_ESTATE, "the library's workspace on device %d is in use by another context", dev);
-    const int rc = kavg_init(out, P, K, lr, mu, n_layers, dims, B, dtype, index_seed, g_static_ptr[dev],
-                             STATIC_WS_BYTES, hip_stream);
+    const int rc = init_common(out, P, K, lr, mu, n_layers, dims, B, dtype, index_seed, g_static_ptr[dev], STATIC_WS_BYTES,
+                               hip_stream, ConvSpec(), units);
     if (rc != KAVG_OK) return rc;
     (*out)->static_dev = dev;
     g_static_owner[dev] = *out;

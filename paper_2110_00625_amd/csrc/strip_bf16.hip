@@ -169,7 +169,7 @@ __global__ void __launch_bounds__(NT) strip_kernel(StripArgs a) {
             if (BT * RC / 8 % NT == 0 || e < BT * RC / 8)
                 *(u32x4*)(Z + s * ZP + (e % (RC / 8)) * 8) = s < a.B && r < a.ld_dz ? zr[set][i] : zero;
         }
-        *(u32x4*)(W + wrow * XP + wcol) = hr[set];
+        *(u32x4*)(W + wrow * XP + wcol) = r0 + wrow < a.d_out ? hr[set] : zero;      // (an infinite weight times no gradient is not zero)
         __syncthreads();
         load((set + SETS - 1) % SETS, r0 + (SETS - 1) * RC);
         __builtin_amdgcn_sched_barrier(0);                   // (left alone, the compiler moves the requests to their use)

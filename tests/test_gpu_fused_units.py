@@ -76,3 +76,25 @@ def test_a_wait_that_gives_up_ends_the_launch_and_is_reported():
     g.set_wait_limit(1 << 20)
     g.set_state(w0, np.zeros_like(w0), 0)
     _run_and_compare(g, o, dims, 2, TOL_FP32, "after a wait limit of one poll")
+
+
+def test_the_librarys_own_block_takes_a_model_whose_scratch_does_not_fit():
+    """256-256-10 with 56 learners: 33.1 MiB with the scratch of the one-launch path, 29.6 without.  A context in the 32 MiB
+    block then runs one launch per layer, bit for bit what a caller workspace gives with that path chosen."""
+    torch = _torch()
+    P, K, B, dims = 56, 2, 64, (256, 256, 10)
+    h, _ = _pair(P, K, 0.05, 0.9, dims, B, False, 194)
+    h.set_fused(False)
+    assert h.workspace.numel() > 32 << 20
+    g = kavg.MAvg(P, K, 0.05, 0.9, dims, B, kavg.KAVG_FP32, index_seed=197, static_workspace=True)
+    rng = np.random.default_rng(6)
+    X = torch.from_numpy(rng.standard_normal((600, 256), dtype=np.float32)).cuda()
+    y = torch.from_numpy(rng.integers(0, 10, 600).astype(np.int32)).cuda()
+    w0 = h.params()
+    for c in (g, h):
+        c.set_data(X, y)
+        c.set_params(w0)
+        c.local_steps()
+    for j in (0, P - 1):
+        assert np.array_equal(g.replica(j), h.replica(j))
+    g.close()
