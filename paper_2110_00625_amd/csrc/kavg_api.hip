@@ -639,6 +639,12 @@ int issue_steps_conv(kavg_ctx* c);
 
 bool fused_now(const kavg_ctx* c) { return (c->fused_ok || c->units_ok) && c->fused_on && !c->vel; }
 
+// The caller is recording the context's stream into a graph of their own.  (The null stream cannot be recorded.)
+bool recording(hipStream_t st) {
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    return st != nullptr && (hipStreamIsCapturing(st, &s) != hipSuccess || s != hipStreamCaptureStatusNone);
+}
+
 // Small fp32 model: indices, all K steps and the per-step losses in one launch (fused_small.hip, fused_units.hip).  The
 // launch carries the step counter (index stream, tags), so it is issued directly, never replayed from a graph.
 // Where both kernels cover a shape the one that splits by hidden units runs: it exchanges C instead of 64 values per row
@@ -1173,7 +1179,9 @@ int kavg_local_steps(kavg_ctx* c) {
         return fail(c, KAVG_ESTATE, "local step counter would exceed 2^24");
     hipStream_t st = c->stream;
     KAVG_NOTHROW_BEGIN
-    const bool fused = fused_now(c);
+    // A recorded launch would be replayed with the tags it was recorded with: a workgroup would then take the partials of
+    // the replay before, whose tags are the same, for those of its partners.  Separate launches carry no tags.
+    const bool fused = fused_now(c) && !recording(st);
     {
         Bracket br(c, KAVG_CLASS_INDEX);
         if (c->user_idx)
