@@ -152,6 +152,10 @@ int kavg_set_data(kavg_ctx* ctx, const void* X_dev, const int32_t* y_dev, int64_
  * of fp32 sums.  kavg_fused: 1 when kavg_local_steps takes that path on this context.
  * kavg_set_fused(ctx, 0) switches it off (the steps then run as separate launches), 1 on again.  A call made while the
  * caller records the stream into a graph runs separate launches as well: they can be replayed.
+ * All workgroups of such a launch have to be on the chip together.  Those of the contexts of one process take turns on a
+ * device, whatever their streams and threads; other kernels only delay them.  What holds compute units for longer than the
+ * wait limit (a kernel of another process that waits in the same way, a collective whose peers do not come) makes a
+ * wait give up: set kavg_set_fused(ctx, 0) beside such work.
  * Wider hidden layers on inputs of at most 512 features (same other limits, any d_0 >= 4) also run their K steps in
  * one launch where a learner's hidden units divide over at most 16 workgroups and all workgroups find a compute unit;
  * kavg_fused does not report that second kernel, kavg_set_fused and kavg_set_wait_limit govern it alike. */

@@ -407,6 +407,10 @@ size_t fused_small_scratch_bytes(int P, int d0) {          // (hint words for a 
     return fused_small_partial_words(P, d0) * 8 + (size_t)2 * P * fused_small_chunks(d0) * 2 * (NT / 64) * 4;
 }
 
+int fused_small_workgroups(int P, int d0, int d1, int compute_units) {
+    return P * fused_small_chunks(d0) * fused_small_unit_split(P, d0, d1, compute_units);
+}
+
 hipError_t launch_fused_small(const FusedSmallCall& c, hipStream_t st) {
     const int S = fused_small_chunks(c.d0), CW = fused_small_chunk_width(c.d0);
     const int UH = fused_small_unit_split(c.P, c.d0, c.d1, c.compute_units);

@@ -400,21 +400,32 @@ int fused_units_plan(int P, int K, int B, int d0, int d1, int C, int compute_uni
 size_t fused_units_scratch_bytes(int P, int B, int d1, int UN) { return (size_t)2 * P * ((d1 + UN - 1) / UN) * B * CLS * 8; }
 
 namespace {
+// Workgroups of a launch.  One XCD per learner where its compute units hold all workgroups that then fall to it and there
+// are enough partners for it to matter (rounds of 256-256-10, us: 6 learners x 16 groups 79 on one XCD, 88 spread;
+// 6 x 8 groups 81 / 83; 48 x 4 groups 159 / 153).
+int units_grid(int P, int G, int compute_units, int* spread) {
+    const int per_xcd = (P + 7) / 8 * G;
+    *spread = per_xcd > compute_units / 8 || G < 8 ? 1 : 0;
+    return *spread ? P * G : 8 * per_xcd;
+}
+
 template <bool VEC, int UN>
 hipError_t launch_units(const FusedSmallCall& c, hipStream_t st) {
     const UnitsLayout q = units_layout(c.B, c.K, c.d0, c.d1, UN);
     static hipError_t raised = hipFuncSetAttribute((const void*)fused_units_kernel<VEC, UN>,
                                                    hipFuncAttributeMaxDynamicSharedMemorySize, LDS_WORDS * 4);
     if (raised != hipSuccess) return raised;
-    // One XCD per learner where its compute units hold all workgroups that then fall to it and there are enough partners
-    // for it to matter (rounds of 256-256-10, us: 6 learners x 16 groups 79 on one XCD, 88 spread; 6 x 8 groups 81 / 83;
-    // 48 x 4 groups 159 / 153).
-    const int per_xcd = (c.P + 7) / 8 * q.G;
-    const int spread = per_xcd > c.compute_units / 8 || q.G < 8 ? 1 : 0;
-    hipLaunchKernelGGL((fused_units_kernel<VEC, UN>), dim3(spread ? c.P * q.G : 8 * per_xcd), dim3(NT), q.words * 4, st, c, spread);
+    int spread;
+    const int grid = units_grid(c.P, q.G, c.compute_units, &spread);
+    hipLaunchKernelGGL((fused_units_kernel<VEC, UN>), dim3(grid), dim3(NT), q.words * 4, st, c, spread);
     return hipGetLastError();
 }
 }  // namespace
+
+int fused_units_workgroups(int P, int d1, int UN, int compute_units) {
+    int spread;
+    return units_grid(P, (d1 + UN - 1) / UN, compute_units, &spread);
+}
 
 hipError_t launch_fused_units(const FusedSmallCall& c, hipStream_t st) {
     const bool vec = c.d0 % 4 == 0;

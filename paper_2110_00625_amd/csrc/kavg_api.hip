@@ -2,11 +2,13 @@
 // launch sequences of the learner loop and the meta step (Algorithm 1).
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <mutex>
 #include <new>
 #include <vector>
 
@@ -249,7 +251,9 @@ struct kavg_ctx {
     bool units_ok = false;              // ... or in the one-launch kernel for wide hidden layers on short inputs (fused_units.hip)
     bool fused_on = true;               // ... and the caller has not switched it off (kavg_set_fused)
     unsigned spin_limit = 1u << 20;     // polls a workgroup of that launch spends on one wait before it gives up
-    int compute_units = 0;
+    int compute_units = 0, device = 0;
+    int workgroups = 0;                 // of that launch
+    bool unmarked = false;              // a launch of this context may be in flight with no event behind it
     uint32_t fused_tag = 0;             // steps that launch has exchanged partials for so far (their tags on the scratch)
     // deferred weight updates (kavg_set_refresh): history block, its carve-up, refresh period
     int refresh = 1;
@@ -427,6 +431,106 @@ bool conv_spec(ConvSpec* cv, int H, int W, int n_conv, const int* channels) {
     return true;
 }
 
+// ---- one-launch kernels of several contexts ----
+// A one-launch kernel (fused_small.hip, fused_units.hip) waits for workgroups of its own launch, up to one per compute unit.
+// Several at a time could each hold a part of the chip and wait for what another one holds, until all gave up.  So where
+// the launches that the streams of a process can have in flight together do not all fit on a device, they run one after
+// another there: each waits for the one before.  Where they fit (one stream, or small models) nothing is recorded or
+// waited for; an event costs 3 us of a round (6 learners of 256-256-10: 46.6 -> 49.9).
+struct OneLaunchLine {
+    std::vector<kavg_ctx*> contexts;             // those that may take the path
+    bool crowded = false;                        // their launches do not fit together
+    hipStream_t last = nullptr;                  // the stream of the latest launch since it got crowded ...
+    bool any = false;                            // ... if there is one; `done` is recorded behind it
+    hipEvent_t done = nullptr;
+};
+std::mutex g_line_mutex;                         // held from a launch's wait to its mark
+OneLaunchLine g_line[MAX_DEVICES];
+
+// The largest launch of each stream's contexts, all streams together, by XCD: a launch takes at most its share, rounded up, of each.
+bool crowded(const std::vector<kavg_ctx*>& contexts) {
+    int total = 0, streams = 0, units = 0;
+    for (size_t i = 0; i < contexts.size(); ++i) {
+        bool largest = true;                     // of its stream (of equals the first)
+        for (size_t k = 0; k < contexts.size(); ++k) {
+            const kavg_ctx *c = contexts[i], *o = contexts[k];
+            if (o->stream == c->stream && (o->workgroups > c->workgroups || (o->workgroups == c->workgroups && k < i))) largest = false;
+        }
+        if (!largest) continue;
+        total += (contexts[i]->workgroups + 7) / 8 * 8;
+        ++streams;
+        units = contexts[i]->compute_units;
+    }
+    return streams > 1 && total > units;
+}
+
+void line_up(kavg_ctx* c) {
+    std::lock_guard<std::mutex> lock(g_line_mutex);
+    OneLaunchLine& n = g_line[c->device];
+    n.contexts.push_back(c);
+    n.crowded = crowded(n.contexts);
+}
+
+// c's stream has been waited for
+void leave_line(kavg_ctx* c) {
+    std::lock_guard<std::mutex> lock(g_line_mutex);
+    OneLaunchLine& n = g_line[c->device];
+    n.contexts.erase(std::remove(n.contexts.begin(), n.contexts.end(), c), n.contexts.end());
+    const bool was = n.crowded;
+    n.crowded = crowded(n.contexts);
+    if (was && !n.crowded) {                     // (those that remain fit together, whatever is in flight)
+        n.any = false;
+        for (kavg_ctx* o : n.contexts) o->unmarked = true;
+    }
+    bool known = false;
+    for (const kavg_ctx* o : n.contexts) known = known || o->stream == n.last;
+    if (!known) n.any = false;                   // the latest launch is over, and those before it
+    if (n.contexts.empty() && n.done) {
+        (void)hipEventDestroy(n.done);
+        n.done = nullptr;
+    }
+}
+
+// The caller is recording the stream into a graph of their own.  (The null stream cannot be recorded.)
+bool recording(hipStream_t st) {
+    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
+    return st != nullptr && (hipStreamIsCapturing(st, &s) != hipSuccess || s != hipStreamCaptureStatusNone);
+}
+
+// *ok = false: a launch in flight cannot be waited for, its stream is being recorded (the steps then run as separate launches)
+hipError_t wait_in_line(kavg_ctx* c, bool* ok) {
+    OneLaunchLine& n = g_line[c->device];
+    *ok = true;
+    if (!n.crowded) return hipSuccess;
+    if (!n.done) {
+        const hipError_t e = hipEventCreateWithFlags(&n.done, hipEventDisableTiming);
+        if (e != hipSuccess) return e;
+    }
+    for (const kavg_ctx* o : n.contexts)
+        if (o->unmarked && o->stream != c->stream && recording(o->stream)) { *ok = false; return hipSuccess; }
+    if (n.any && n.last != c->stream) {
+        const hipError_t e = hipStreamWaitEvent(c->stream, n.done, 0);
+        if (e != hipSuccess) return e;
+    }
+    for (const kavg_ctx* o : n.contexts) {       // launches from before it got crowded
+        if (!o->unmarked || o->stream == c->stream) continue;
+        hipError_t e = hipEventRecord(n.done, o->stream);
+        if (e == hipSuccess) e = hipStreamWaitEvent(c->stream, n.done, 0);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+hipError_t launched_in_line(kavg_ctx* c) {
+    OneLaunchLine& n = g_line[c->device];
+    c->unmarked = !n.crowded;
+    if (!n.crowded) return hipSuccess;
+    for (kavg_ctx* o : n.contexts) o->unmarked = false;         // (this launch waits for theirs)
+    n.any = true;
+    n.last = c->stream;
+    return hipEventRecord(n.done, c->stream);
+}
+
 int init_common(kavg_ctx** out, int P, int K, float lr, float mu, int n_layers, const int* dims, int B,
                 int dtype, uint64_t index_seed, void* workspace_dev, size_t workspace_bytes,
                 void* hip_stream, const ConvSpec& cv, bool units = true) {
@@ -471,6 +575,12 @@ int init_common(kavg_ctx** out, int P, int K, float lr, float mu, int n_layers, 
         c->compute_units = cus < 256 ? cus : 256;          // (what the scratch was sized for)
         c->fused_ok = e == hipSuccess && fused_small_shape_ok(P, K, B, dims[0], dims[1], dims[2], c->compute_units);
         c->units_ok = e == hipSuccess && units && fused_units_plan(P, K, B, dims[0], dims[1], dims[2], c->compute_units) > 0;
+        c->device = dev;
+        if (dev < 0 || dev >= MAX_DEVICES) c->fused_ok = c->units_ok = false;
+        if (c->units_ok)
+            c->workgroups = fused_units_workgroups(P, dims[1], fused_units_plan(P, K, B, dims[0], dims[1], dims[2], c->compute_units), c->compute_units);
+        else if (c->fused_ok)
+            c->workgroups = fused_small_workgroups(P, dims[0], dims[1], c->compute_units);
         if (e == hipSuccess) e = hipMemsetAsync(c->ws + lo.off_fused, 0, lo.fused_bytes, c->stream);
     }
     if (e == hipSuccess && lo.off_flat_table) e = launch_flat_table((int32_t*)(c->ws + lo.off_flat_table), B, cv.H, cv.W, c->stream);
@@ -480,6 +590,7 @@ int init_common(kavg_ctx** out, int P, int K, float lr, float mu, int n_layers, 
         delete c;
         return KAVG_EDEVICE;
     }
+    if (c->fused_ok || c->units_ok) line_up(c);
     *out = c;
     return KAVG_OK;
     } catch (...) {
@@ -639,12 +750,6 @@ int issue_steps_conv(kavg_ctx* c);
 
 bool fused_now(const kavg_ctx* c) { return (c->fused_ok || c->units_ok) && c->fused_on && !c->vel; }
 
-// The caller is recording the context's stream into a graph of their own.  (The null stream cannot be recorded.)
-bool recording(hipStream_t st) {
-    hipStreamCaptureStatus s = hipStreamCaptureStatusNone;
-    return st != nullptr && (hipStreamIsCapturing(st, &s) != hipSuccess || s != hipStreamCaptureStatusNone);
-}
-
 // Small fp32 model: indices, all K steps and the per-step losses in one launch (fused_small.hip, fused_units.hip).  The
 // launch carries the step counter (index stream, tags), so it is issued directly, never replayed from a graph.
 // Where both kernels cover a shape the one that splits by hidden units runs: it exchanges C instead of 64 values per row
@@ -671,6 +776,7 @@ int issue_steps_fused(kavg_ctx* c) {
     Bracket br(c, KAVG_CLASS_FORWARD);
     KAVG_HIP(c, c->units_ok ? launch_fused_units(q, st) : launch_fused_small(q, st));
     c->fused_tag += (uint32_t)c->K;
+    KAVG_HIP(c, launched_in_line(c));
     return KAVG_OK;
 }
 
@@ -1181,7 +1287,13 @@ int kavg_local_steps(kavg_ctx* c) {
     KAVG_NOTHROW_BEGIN
     // A recorded launch would be replayed with the tags it was recorded with: a workgroup would then take the partials of
     // the replay before, whose tags are the same, for those of its partners.  Separate launches carry no tags.
-    const bool fused = fused_now(c) && !recording(st);
+    bool fused = fused_now(c) && !recording(st);
+    std::unique_lock<std::mutex> line(g_line_mutex, std::defer_lock);
+    if (fused) {
+        line.lock();
+        KAVG_HIP(c, wait_in_line(c, &fused));
+        if (!fused) line.unlock();
+    }
     {
         Bracket br(c, KAVG_CLASS_INDEX);
         if (c->user_idx)
@@ -1412,6 +1524,7 @@ int kavg_destroy(kavg_ctx* c) {
     if (!c) return KAVG_EINVAL;
     hipError_t e = hipStreamSynchronize(c->stream);
     if (c->static_dev >= 0 && g_static_owner[c->static_dev] == c) g_static_owner[c->static_dev] = nullptr;
+    if (c->fused_ok || c->units_ok) leave_line(c);
     if (c->gexec) (void)hipGraphExecDestroy(c->gexec);
     for (int k = 0; k < KAVG_NCLASS; ++k)
         for (hipEvent_t ev : c->prof_ev[k]) (void)hipEventDestroy(ev);
