@@ -116,13 +116,15 @@ int kavg_init_conv(kavg_ctx** out, int P, int K, float lr, float mu, int H, int 
  * KAVG_STATIC_WORKSPACE_BYTES that lives inside the library's device image (one copy per GPU, held
  * until the process ends) instead of a caller workspace.  Neither this call nor any later call on
  * the context allocates or frees device memory.  Everything else is kavg_init: same arguments,
- * same kernels, same results; data set, index array and velocity block are still the caller's.
+ * same kernels, same results; data set, index array and velocity block are still the caller's.  (One
+ * exception: a small fp32 model that fits the block only without the scratch of kernel 2 of kavg_fused
+ * does without that kernel, and its sums are then taken in another order; kavg_fused tells.)
  * The block keeps whatever the previous context left in it; every piece a context reads is
  * written by it first (the range flag is cleared here, the rest by kavg_set_params / the kernels).
  * One context per device may use the block at a time: a second kavg_init_static on the same
  * device before kavg_destroy of the first returns KAVG_ESTATE (two contexts would race on it).
- * Errors: as kavg_init, plus KAVG_ENOMEM when kavg_workspace_bytes(...) exceeds
- * KAVG_STATIC_WORKSPACE_BYTES (checked before any device call), KAVG_EDEVICE when the block's
+ * Errors: as kavg_init, plus KAVG_ENOMEM when kavg_workspace_bytes(...), without that scratch where
+ * there is one, exceeds KAVG_STATIC_WORKSPACE_BYTES (checked before any device call), KAVG_EDEVICE when the block's
  * address cannot be obtained. */
 #define KAVG_STATIC_WORKSPACE_BYTES ((size_t)32 << 20)
 int kavg_init_static(kavg_ctx** out, int P, int K, float lr, float mu,
@@ -143,22 +145,24 @@ int kavg_set_state(kavg_ctx* ctx, const float* w_host, const float* v_host, uint
  * BORROWED.  N in [1, 2^31). */
 int kavg_set_data(kavg_ctx* ctx, const void* X_dev, const int32_t* y_dev, int64_t N);
 
-/* Small fp32 models (KAVG_FP32, one hidden layer of at most 64 units, at most 16 classes, B <= 64,
- * d_0 a multiple of 4, P * ceil(d_0/64) no larger than the device's number of compute units, no
- * learner-level momentum) run all K local steps of Algorithm 1 in ONE launch that keeps the
- * learners' parameters on chip; workgroups of a learner wait for each other through counters in
- * the workspace, with a bounded number of polls (a wait that gives up makes the next call that
- * synchronises return KAVG_EDEVICE).  Same arithmetic as the launch-per-layer path up to the order
- * of fp32 sums.  kavg_fused: 1 when kavg_local_steps takes that path on this context.
+/* Small fp32 models (KAVG_FP32, one hidden layer, at most 16 classes, B <= 64, K * B <= 1024, no learner-level
+ * momentum) run all K local steps of Algorithm 1 in ONE launch that keeps the learners' parameters on chip.  Two
+ * kernels do this; the workgroups of a learner share its model by
+ *   1  inputs:        at most 64 hidden units, d_0 a multiple of 4, P * ceil(d_0/64) (beyond 1024 inputs: /128, beyond
+ *                     2048: /192) no larger than the device's number of compute units;
+ *   2  hidden units:  4 <= d_0 <= 512, 16, 32 or 64 units per workgroup, at most 16 workgroups per learner and no more
+ *                     than compute units in all, the model's share in the LDS of one (where both cover a shape: this one).
+ * Workgroups of a learner wait for each other through tagged words in the workspace, with a bounded number of polls (a
+ * wait that gives up makes the next call that synchronises return KAVG_EDEVICE).  Same arithmetic as the
+ * launch-per-layer path up to the order of fp32 sums: a pre-activation whose sum falls on the other side of zero that
+ * way (about one in ten million) moves a row of that step's gradient by one sample's share.
+ * kavg_fused: 1 or 2 when kavg_local_steps takes that path on this context, 0 when it runs separate launches.
  * kavg_set_fused(ctx, 0) switches it off (the steps then run as separate launches), 1 on again.  A call made while the
  * caller records the stream into a graph runs separate launches as well: they can be replayed.
  * All workgroups of such a launch have to be on the chip together.  Those of the contexts of one process take turns on a
- * device, whatever their streams and threads; other kernels only delay them.  What holds compute units for longer than the
- * wait limit (a kernel of another process that waits in the same way, a collective whose peers do not come) makes a
- * wait give up: set kavg_set_fused(ctx, 0) beside such work.
- * Wider hidden layers on inputs of at most 512 features (same other limits, any d_0 >= 4) also run their K steps in
- * one launch where a learner's hidden units divide over at most 16 workgroups and all workgroups find a compute unit;
- * kavg_fused does not report that second kernel, kavg_set_fused and kavg_set_wait_limit govern it alike. */
+ * device where they do not fit together, whatever their streams and threads; other kernels only delay them.  What holds
+ * compute units for longer than the wait limit (a kernel of another process that waits in the same way, a collective whose
+ * peers do not come) makes a wait give up: set kavg_set_fused(ctx, 0) beside such work. */
 int kavg_fused(const kavg_ctx* ctx);
 int kavg_set_fused(kavg_ctx* ctx, int on);
 /* Polls a workgroup of that launch spends on one wait for the others before it gives up (default 2^20, about a

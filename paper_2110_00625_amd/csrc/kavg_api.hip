@@ -431,6 +431,8 @@ bool conv_spec(ConvSpec* cv, int H, int W, int n_conv, const int* channels) {
     return true;
 }
 
+bool fused_now(const kavg_ctx* c) { return (c->fused_ok || c->units_ok) && c->fused_on && !c->vel; }
+
 // ---- one-launch kernels of several contexts ----
 // A one-launch kernel (fused_small.hip, fused_units.hip) waits for workgroups of its own launch, up to one per compute unit.
 // Several at a time could each hold a part of the chip and wait for what another one holds, until all gave up.  So where
@@ -717,7 +719,7 @@ int kavg_set_data(kavg_ctx* c, const void* X_dev, const int32_t* y_dev, int64_t 
     return KAVG_OK;
 }
 
-int kavg_fused(const kavg_ctx* c) { return c && c->fused_ok && c->fused_on && !c->vel ? 1 : 0; }
+int kavg_fused(const kavg_ctx* c) { return c && fused_now(c) ? (c->units_ok ? 2 : 1) : 0; }
 
 int kavg_set_fused(kavg_ctx* c, int on) {
     if (!c) return KAVG_EINVAL;
@@ -747,8 +749,6 @@ namespace {
 // lets kavg_local_steps replay this sequence as a graph.
 int issue_steps_deferred(kavg_ctx* c);
 int issue_steps_conv(kavg_ctx* c);
-
-bool fused_now(const kavg_ctx* c) { return (c->fused_ok || c->units_ok) && c->fused_on && !c->vel; }
 
 // Small fp32 model: indices, all K steps and the per-step losses in one launch (fused_small.hip, fused_units.hip).  The
 // launch carries the step counter (index stream, tags), so it is issued directly, never replayed from a graph.

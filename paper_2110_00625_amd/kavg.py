@@ -269,7 +269,12 @@ class MAvg:
     @property
     def fused(self):
         """True when kavg_local_steps runs all K steps of this context in one launch."""
-        return bool(self.lib.kavg_fused(self.ctx))
+        return self.one_launch != 0
+
+    @property
+    def one_launch(self):
+        """0: separate launches; 1: one launch, the workgroups of a learner sharing its inputs; 2: sharing its hidden units."""
+        return int(self.lib.kavg_fused(self.ctx))
 
     def set_fused(self, on):
         _check(self.lib, self.ctx, self.lib.kavg_set_fused(self.ctx, 1 if on else 0))

@@ -89,15 +89,23 @@ def test_a_wait_that_gives_up_ends_the_launch_and_is_reported():
 
 def test_fused_path_is_taken_only_where_it_fits():
     _torch()
-    assert not kavg.MAvg(2, 2, 0.1, 0.5, (64, 65, 10), 8, kavg.KAVG_FP32).fused          # hidden layer too wide
+    assert kavg.MAvg(2, 2, 0.1, 0.5, (64, 65, 10), 8, kavg.KAVG_FP32).one_launch == 2    # hidden layer too wide for the split by inputs
+    assert not kavg.MAvg(2, 2, 0.1, 0.5, (516, 65, 10), 8, kavg.KAVG_FP32).fused         # ... and inputs too long for the split by units
+    assert not kavg.MAvg(2, 2, 0.1, 0.5, (64, 1025, 10), 8, kavg.KAVG_FP32).fused        # more than 16 groups of 64 units
     assert not kavg.MAvg(2, 2, 0.1, 0.5, (64, 32, 17), 8, kavg.KAVG_FP32).fused          # too many classes
     assert not kavg.MAvg(2, 2, 0.1, 0.5, (64, 32, 10), 65, kavg.KAVG_FP32).fused         # batch too large
-    assert not kavg.MAvg(2, 2, 0.1, 0.5, (66, 32, 10), 8, kavg.KAVG_FP32).fused          # d_0 not a multiple of 4
+    assert kavg.MAvg(2, 2, 0.1, 0.5, (66, 32, 10), 8, kavg.KAVG_FP32).one_launch == 2    # d_0 not a multiple of 4: split by units only
+    assert not kavg.MAvg(2, 2, 0.1, 0.5, (602, 32, 10), 8, kavg.KAVG_FP32).fused         # ... and too long for it
     assert not kavg.MAvg(17, 2, 0.1, 0.5, (3072, 32, 10), 8, kavg.KAVG_FP32).fused       # 17 x 16 workgroups: more than compute units
     assert not kavg.MAvg(2, 2, 0.1, 0.5, (64, 32, 32, 10), 8, kavg.KAVG_FP32).fused      # two hidden layers
     assert not kavg.MAvg(2, 33, 0.1, 0.5, (64, 32, 10), 32, kavg.KAVG_FP32).fused        # K*B beyond the index table
     assert not kavg.MAvg(2, 2, 0.1, 0.5, (64, 32, 10), 8, kavg.KAVG_BF16).fused          # mixed precision
+    assert kavg.MAvg(2, 2, 0.1, 0.5, (600, 32, 10), 8, kavg.KAVG_FP32).one_launch == 1
     g = kavg.MAvg(2, 2, 0.1, 0.5, (64, 32, 10), 8, kavg.KAVG_FP32)
+    assert g.fused
+    g.set_fused(False)
+    assert g.one_launch == 0
+    g.set_fused(True)
     assert g.fused
     g.set_learner_momentum(0.9)
     assert not g.fused

@@ -27,6 +27,7 @@ IDS = ["P%d-B%d-%s" % (c[0], c[2], c[3]) for c in CASES]
 @pytest.mark.parametrize("P,K,B,dims", CASES, ids=IDS)
 def test_steps_match_the_oracle(P, K, B, dims):
     g, o = _pair(P, K, 0.05, 0.9, dims, B, False, 191)
+    assert g.one_launch == 2
     _run_and_compare(g, o, dims, 3, TOL_FP32, "units %s" % (dims,))
 
 
@@ -87,6 +88,7 @@ def test_the_librarys_own_block_takes_a_model_whose_scratch_does_not_fit():
     h.set_fused(False)
     assert h.workspace.numel() > 32 << 20
     g = kavg.MAvg(P, K, 0.05, 0.9, dims, B, kavg.KAVG_FP32, index_seed=197, static_workspace=True)
+    assert g.one_launch == 0
     rng = np.random.default_rng(6)
     X = torch.from_numpy(rng.standard_normal((600, 400), dtype=np.float32)).cuda()
     y = torch.from_numpy(rng.integers(0, 10, 600).astype(np.int32)).cuda()
