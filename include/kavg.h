@@ -151,7 +151,8 @@ int kavg_set_data(kavg_ctx* ctx, const void* X_dev, const int32_t* y_dev, int64_
  *   1  inputs:        at most 64 hidden units, d_0 a multiple of 4, P * ceil(d_0/64) (beyond 1024 inputs: /128, beyond
  *                     2048: /192) no larger than the device's number of compute units;
  *   2  hidden units:  4 <= d_0 <= 512, 16, 32 or 64 units per workgroup, at most 16 workgroups per learner and no more
- *                     than compute units in all, the model's share in the LDS of one (where both cover a shape: this one).
+ *                     than compute units in all, the model's share in the LDS of one.
+ * Where both cover a shape the faster one is taken (a rule on P, B and the widths).
  * Workgroups of a learner wait for each other through tagged words in the workspace, with a bounded number of polls (a
  * wait that gives up makes the next call that synchronises return KAVG_EDEVICE).  Same arithmetic as the
  * launch-per-layer path up to the order of fp32 sums: a pre-activation whose sum falls on the other side of zero that

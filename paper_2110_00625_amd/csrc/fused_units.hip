@@ -396,6 +396,20 @@ int fused_units_plan(int P, int K, int B, int d0, int d1, int C, int compute_uni
     return 0;
 }
 
+// Where fused_small.hip covers the shape as well.  That kernel exchanges 64 pre-activations per row and workgroup instead of
+// C logits, but its workgroups hold 64 to 192 inputs of all units where these hold all inputs of few units, and many of
+// these on the chip slow each other's exchange.  Measured at K = 4 on 2 - 250 learners, 8 - 512 inputs, 8 - 64 units and
+// batches of 2 - 64 (1578 shapes; us for the K steps, this kernel / that one): 64-8-10, 2 learners of 32 rows 22 / 42;
+// 256-64-10, 8 of 32 34 / 40; but 512-64-10, 2 of 32 47 / 42; 320-64-10, 24 of 48 67 / 58; 64-64-10, 48 of 24 53 / 39;
+// 128-48-10, 128 of 16 50 / 41.  Inside the lines below it was the faster one at every shape (1.5 times in the mean), outside
+// them not always.
+bool fused_units_faster(int P, int K, int B, int d0, int d1, int C, int compute_units) {
+    const int UN = fused_units_plan(P, K, B, d0, d1, C, compute_units), G = UN ? (d1 + UN - 1) / UN : 0;
+    if (G == 0) return false;
+    if (B <= 16) return G == 1 || 4 * P * G <= 3 * compute_units;
+    return 4 * P * G <= compute_units && (B + 15) / 16 * 16 * d0 <= 12288;
+}
+
 // two buffers of P x G tiles of B x CLS (value, tag) words; UN from fused_units_plan
 size_t fused_units_scratch_bytes(int P, int B, int d1, int UN) { return (size_t)2 * P * ((d1 + UN - 1) / UN) * B * CLS * 8; }
 

@@ -247,8 +247,8 @@ struct kavg_ctx {
     bool warm = false;                  // the sequence has run eagerly once with the current pointers
     hipGraphExec_t gexec = nullptr;
     ConvSpec cv;                        // convolution stack in front of the MLP (empty: plain MLP)
-    bool fused_ok = false;              // the shape and the device allow all K steps in one launch (fused_small.hip)
-    bool units_ok = false;              // ... or in the one-launch kernel for wide hidden layers on short inputs (fused_units.hip)
+    bool fused_ok = false;              // all K steps run in one launch that splits the inputs (fused_small.hip) ...
+    bool units_ok = false;              // ... or in one that splits the hidden units (fused_units.hip); at most one of the two
     bool fused_on = true;               // ... and the caller has not switched it off (kavg_set_fused)
     unsigned spin_limit = 1u << 20;     // polls a workgroup of that launch spends on one wait before it gives up
     int compute_units = 0, device = 0;
@@ -577,6 +577,10 @@ int init_common(kavg_ctx** out, int P, int K, float lr, float mu, int n_layers, 
         c->compute_units = cus < 256 ? cus : 256;          // (what the scratch was sized for)
         c->fused_ok = e == hipSuccess && fused_small_shape_ok(P, K, B, dims[0], dims[1], dims[2], c->compute_units);
         c->units_ok = e == hipSuccess && units && fused_units_plan(P, K, B, dims[0], dims[1], dims[2], c->compute_units) > 0;
+        if (c->fused_ok && c->units_ok) {                  // both cover the shape
+            c->units_ok = fused_units_faster(P, K, B, dims[0], dims[1], dims[2], c->compute_units);
+            c->fused_ok = !c->units_ok;
+        }
         c->device = dev;
         if (dev < 0 || dev >= MAX_DEVICES) c->fused_ok = c->units_ok = false;
         if (c->units_ok)
@@ -752,8 +756,6 @@ int issue_steps_conv(kavg_ctx* c);
 
 // Small fp32 model: indices, all K steps and the per-step losses in one launch (fused_small.hip, fused_units.hip).  The
 // launch carries the step counter (index stream, tags), so it is issued directly, never replayed from a graph.
-// Where both kernels cover a shape the one that splits by hidden units runs: it exchanges C instead of 64 values per row
-// and workgroup.
 int issue_steps_fused(kavg_ctx* c) {
     hipStream_t st = c->stream;
     if (c->fused_tag + (uint32_t)c->K + 1u < c->fused_tag) {    // the tags would wrap: start over on a clean scratch

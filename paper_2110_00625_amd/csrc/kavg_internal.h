@@ -200,6 +200,7 @@ int fused_small_workgroups(int P, int d0, int d1, int compute_units);        // 
 hipError_t launch_fused_small(const FusedSmallCall& c, hipStream_t st);
 // the same for wide hidden layers on short inputs (fused_units.hip; no hints): hidden units per workgroup, 0 = not covered
 int fused_units_plan(int P, int K, int B, int d0, int d1, int C, int compute_units);
+bool fused_units_faster(int P, int K, int B, int d0, int d1, int C, int compute_units);     // ... where both kernels cover the shape
 size_t fused_units_scratch_bytes(int P, int B, int d1, int UN);
 int fused_units_workgroups(int P, int d1, int UN, int compute_units);
 hipError_t launch_fused_units(const FusedSmallCall& c, hipStream_t st);

@@ -12,13 +12,53 @@ pytestmark = pytest.mark.gpu
 CASES = [
     # P, K, B, dims
     (4, 4, 32, (3072, 64, 10)),        # the shape of the smallest workload: 16 workgroups of 192 columns per learner
-    (3, 3, 19, (200, 40, 7)),          # ragged everywhere: last chunk 8 columns wide, odd batch, 40 units
-    (2, 2, 64, (64, 64, 16)),          # one workgroup per learner, every limit reached
-    (5, 3, 7, (132, 8, 3)),            # last chunk 4 columns wide, fewer rows than a matrix-instruction block
+    (3, 3, 19, (200, 40, 7)),          # ragged everywhere: odd batch, 40 units (split by units: three groups, the last one 8)
+    (2, 2, 64, (64, 64, 16)),          # full batch, every class (four groups of units)
+    (5, 3, 7, (132, 8, 3)),            # fewer rows and units than a matrix-instruction block (one group)
     (1, 5, 33, (1000, 33, 2)),         # a single learner, batch one over half the tile
     (2, 3, 64, (4000, 64, 16)),        # 21 chunks of 192 columns (the last one 160 wide), full batch
     (3, 2, 50, (1600, 48, 9)),         # 13 chunks of 128 columns (the last one 64 wide)
 ]
+
+
+# shapes that the split by inputs runs (kavg_fused 1), where its chunks, rows and units end
+BY_INPUTS = [
+    (3, 3, 19, (520, 40, 7)),          # last chunk 8 columns wide, odd batch, 40 units
+    (5, 3, 7, (516, 8, 3)),            # last chunk 4 columns wide, fewer rows than a matrix-instruction block
+    (20, 2, 64, (64, 64, 16)),         # one workgroup per learner, every limit reached
+    (70, 2, 20, (40, 33, 10)),         # one chunk of 40 columns, 70 learners
+    (40, 3, 17, (196, 64, 10)),        # 40 learners of four chunks, the last one 4 columns wide
+]
+
+
+@pytest.mark.parametrize("P,K,B,dims", BY_INPUTS, ids=[str(c[3]) for c in BY_INPUTS])
+def test_split_by_inputs(P, K, B, dims):
+    torch = _torch()
+    g, o = _pair(P, K, 0.05, 0.9, dims, B, False, 95)
+    assert g.one_launch == 1
+    _run_and_compare(g, o, dims, 2, TOL_FP32, "by inputs %s" % (dims,))
+    g, o = _pair(P, K, 0.05, 0.9, dims, B, False, 95)
+    idx = np.random.default_rng(6).integers(0, 600, size=(P, K, B)).astype(np.int32)
+    g.set_indices(torch.from_numpy(idx).cuda())
+    o.set_indices(idx)
+    _run_and_compare(g, o, dims, 2, TOL_FP32, "by inputs %s, caller's indices" % (dims,))
+
+
+LINES = [
+    # P, B, dims, kernel: on either side of the lines of the rule where both kernels cover a shape
+    (48, 16, (256, 64, 10), 2), (49, 16, (256, 64, 10), 1), (200, 9, (64, 64, 10), 2), (128, 9, (64, 64, 10), 1),
+    (24, 16, (512, 64, 10), 2), (20, 17, (512, 64, 10), 1),
+    (16, 17, (128, 64, 10), 2), (17, 17, (128, 64, 10), 1),
+    (2, 32, (384, 64, 10), 2), (2, 32, (388, 64, 10), 1),
+    (2, 64, (192, 20, 10), 2), (2, 64, (196, 20, 10), 1),
+]
+
+
+@pytest.mark.parametrize("P,B,dims,kernel", LINES, ids=["P%d-B%d-%d" % (c[0], c[1], c[2][0]) for c in LINES])
+def test_where_both_splits_cover_a_shape(P, B, dims, kernel):
+    g, o = _pair(P, 2, 0.05, 0.9, dims, B, False, 96)
+    assert g.one_launch == kernel
+    _run_and_compare(g, o, dims, 2, TOL_FP32, "kernel %d %s" % (kernel, dims))
 
 
 @pytest.mark.parametrize("P,K,B,dims", CASES, ids=[str(c[3]) for c in CASES])
