@@ -40,10 +40,13 @@ struct Layout {
     std::vector<int> splits;               // ranges of positions its weight gradient is split over
     std::vector<int> splits_halo;          // the same for the all-taps weight-gradient kernel; 0: shape not covered
     size_t off_draw = 0, off_pool = 0, off_dpool = 0;
-    std::vector<size_t> off_partial, off_pbias;          // per convolution: partial weight gradients
+    // Per convolution: partial weight gradients.  They share one region; where it does not hold those of all layers, the SGD
+    // steps of the layers above run before a layer takes a place of theirs (step_first).
+    std::vector<size_t> off_partial, off_pbias;
+    std::vector<char> step_first;
     bool conv_implicit = false;            // convolutions 2.. form their patch matrices inside the MFMA kernel's loaders
-    // images of any width (conv_flat.hip, conv_flat_wgrad.hip), per convolution: plans (slabs = 0: shape not covered), weights
-    // in operand order, ranges of the weight gradient (0: not covered); one table of positions for all
+    // images of any width (conv_flat.hip, conv_flat_wgrad.hip), per convolution: plans (slabs = 0: other kernels run), weights
+    // in operand order, ranges of the weight gradient (0: other kernels run); one table of positions for all
     std::vector<FlatPlan> flat_f, flat_b;
     std::vector<size_t> off_frag_f, off_frag_b;
     std::vector<int> splits_flat;
@@ -137,42 +140,62 @@ Layout make_layout(int P, int K, int B, int L, const int* dims, int dtype, const
     if (M > 0) {
         const size_t rows = (size_t)B * cv.H * cv.W;
         size_t draw = 0, wrot = 0;
+        std::vector<size_t> part, pbias;                        // per convolution: bytes of its partial weight gradients
         lo.conv_implicit = (size_t)cv.H * cv.W < ((size_t)1 << 14);     // range of the loaders' multiply-shift divisions
         for (int t = 1; t <= M; ++t) {
             const int S1 = (t == 1 && lo.conv_implicit) ? conv_first_splits(P, B, cv.H, cv.W, cv.ch[0], cv.ch[1]) : 0;
-            // explicit patches: every convolution of very large images, and a first convolution (it gathers its images)
-            // that the kernels of conv_first.hip do not cover
+            const int Sh = t == 1 ? S1 : lo.conv_implicit ? conv_wgrad_halo_splits(P, B, cv.H, cv.W, cv.ch[t - 1], cv.ch[t]) : 0;
+            // Which kernels run convolution t: those for images 32 pixels wide where they cover the layer, those for any width
+            // elsewhere.  (The workload's layers on the latter, us per launch against the former: forward 33 / 69 / 174 against
+            // 26 / 71 / 183, data gradient 85 / 226 against 75 / 199, weight gradient 32 / 89 / 260 against 33 / 54 / 168: with the
+            // forward pass of layers 2 and 3 on the latter a round would take 1.4 % less.)
             FlatPlan pf = {}, pb = {};
             int Sf = 0;
             if (lo.conv_implicit) {
-                Sf = conv_flat_wgrad_splits(P, B, cv.H, cv.W, cv.ch[t - 1], cv.ch[t], t == 1);
-                if (t > 1 || Sf) (void)conv_flat_plan(B, cv.H, cv.W, cv.ch[t - 1], cv.ch[t], &pf);
-                if (t > 1) (void)conv_flat_plan(B, cv.H, cv.W, cv.ch[t], cv.ch[t - 1], &pb);
+                const int cin = cv.ch[t - 1], cout = cv.ch[t];
+                if (Sh == 0) Sf = conv_flat_wgrad_splits(P, B, cv.H, cv.W, cin, cout, t == 1);
+                if (t == 1 ? Sf > 0 : !conv_direct_ok(cv.H, cv.W, cin, cout, false)) (void)conv_flat_plan(B, cv.H, cv.W, cin, cout, &pf);
+                if (t > 1 && !conv_direct_ok(cv.H, cv.W, cin, cout, true)) (void)conv_flat_plan(B, cv.H, cv.W, cout, cin, &pb);
                 if (t == 1 && !pf.slabs) Sf = 0;
             }
             lo.splits_flat.push_back(Sf);
             lo.flat_f.push_back(pf); lo.flat_b.push_back(pb);
             lo.off_frag_f.push_back(pf.slabs ? take((size_t)P * pf.frag_elems() * 2) : 0);
             lo.off_frag_b.push_back(pb.slabs ? take((size_t)P * pb.frag_elems() * 2) : 0);
+            // explicit patches: every convolution of very large images, and a first convolution (it gathers its images)
+            // that neither kind of tile kernel covers
             const bool expl = (t == 1 && S1 == 0 && Sf == 0) || !lo.conv_implicit;
             lo.off_patch.push_back(expl ? take((size_t)P * rows * 9 * cv.ch[t - 1] * 2) : 0);
             lo.off_cact.push_back(take((size_t)P * rows * cv.ch[t] * 2));
             lo.off_cdz.push_back(take((size_t)P * rows * cv.ch[t] * 2));
             if (t > 1 && !lo.conv_implicit && (size_t)P * rows * 9 * cv.ch[t - 1] * 4 > draw) draw = (size_t)P * rows * 9 * cv.ch[t - 1] * 4;
-            if (t > 1 && lo.conv_implicit && (size_t)P * 9 * cv.ch[t] * cv.ch[t - 1] * 2 > wrot) wrot = (size_t)P * 9 * cv.ch[t] * cv.ch[t - 1] * 2;
+            if (t > 1 && lo.conv_implicit && !pb.slabs && !conv_direct_ok(cv.H, cv.W, cv.ch[t - 1], cv.ch[t], true) &&
+                (size_t)P * 9 * cv.ch[t] * cv.ch[t - 1] * 2 > wrot)
+                wrot = (size_t)P * 9 * cv.ch[t] * cv.ch[t - 1] * 2;
             // split the weight gradient's contraction until the launch has some hundreds of workgroups,
             // keeping at least 256 positions per range
             const size_t tiles = (size_t)((cv.ch[t] + 127) / 128) * ((9 * cv.ch[t - 1] + 127) / 128) * P;
             int S = 1;
             while (tiles * S < 512 && rows % (2 * (size_t)S) == 0 && rows / (2 * (size_t)S) >= 256) S *= 2;
             lo.splits.push_back(S);
-            const int Sh = t == 1 ? S1 : lo.conv_implicit ? conv_wgrad_halo_splits(P, B, cv.H, cv.W, cv.ch[t - 1], cv.ch[t]) : 0;
             lo.splits_halo.push_back(Sh);
-            if (Sh > S) S = Sh;                                          // (sizes the partial buffers below)
-            if (Sf > S) S = Sf;
-            const size_t nw = (size_t)cv.ch[t] * 9 * cv.ch[t - 1];
-            lo.off_partial.push_back(take((size_t)P * S * nw * 4));
-            lo.off_pbias.push_back(take((size_t)P * S * cv.ch[t] * 4));
+            if (Sf > 0) S = Sf; else if (Sh > 0) S = Sh;
+            part.push_back(round_up((size_t)P * S * cv.ch[t] * 9 * cv.ch[t - 1] * 4, ALIGN));
+            pbias.push_back(round_up((size_t)P * S * cv.ch[t] * 4, ALIGN));
+        }
+        // One region for the partial sums of all layers: of at most 64 MiB or a thirty-second of the rest of the workspace,
+        // or what the largest layer takes.  (One launch for the SGD steps of all layers gains 2 % of a round of small nets;
+        // for that a deep net is not to take half as much memory again.)
+        size_t all = 0, largest = 0;
+        for (int t = 0; t < M; ++t) { all += part[t] + pbias[t]; largest = std::max(largest, part[t] + pbias[t]); }
+        const size_t region = std::max(largest, std::min(all, std::max((size_t)64 << 20, p / 32 / ALIGN * ALIGN))), base = take(region);
+        lo.off_partial.resize(M); lo.off_pbias.resize(M); lo.step_first.assign(M, 0);
+        size_t used = 0;
+        for (int t = M - 1; t >= 0; --t) {                      // in the order of the backward pass
+            if (used + part[t] + pbias[t] > region) { lo.step_first[t] = 1; used = 0; }
+            lo.off_partial[t] = base + used;
+            lo.off_pbias[t] = base + used + part[t];
+            used += part[t] + pbias[t];
         }
         lo.off_draw = draw ? take(draw) : 0;
         lo.off_wrot = wrot ? take(wrot) : 0;
@@ -966,14 +989,6 @@ int issue_steps_conv(kavg_ctx* c) {
         v.splits = lo.splits_halo[0];
         return v;
     };
-    // Which kernels run convolution t: those for images 32 pixels wide where they cover the layer, those for any width
-    // elsewhere.  (The workload's layers on the latter, us per launch against the former: forward 33 / 69 / 174 against
-    // 26 / 71 / 183, data gradient 85 / 226 against 75 / 199, weight gradient 32 / 89 / 260 against 33 / 54 / 168.)
-    auto flat_forward = [&](int t) {
-        return lo.flat_f[t - 1].slabs && !(t == 1 ? first_direct : conv_direct_ok(H, W, cv.ch[t - 1], cv.ch[t], false));
-    };
-    auto flat_backward = [&](int t) { return lo.flat_b[t - 1].slabs && !conv_direct_ok(H, W, cv.ch[t - 1], cv.ch[t], true); };
-    auto flat_update = [&](int t) { return lo.splits_flat[t - 1] > 0 && lo.splits_halo[t - 1] == 0; };
     const int32_t* table = (const int32_t*)(c->ws + lo.off_flat_table);
     std::vector<PackLayer> pack;                                    // weights in the operand order of conv_flat.hip
     for (int t = 1; t <= M; ++t) {
@@ -982,8 +997,8 @@ int issue_steps_conv(kavg_ctx* c) {
         q.c_in = cv.ch[t - 1]; q.c_out = cv.ch[t];
         q.fwd_plan = lo.flat_f[t - 1]; q.fwd_lstride = q.fwd_plan.frag_elems();
         q.bwd_plan = lo.flat_b[t - 1]; q.bwd_lstride = q.bwd_plan.frag_elems();
-        q.fwd = flat_forward(t) ? (uint16_t*)(c->ws + lo.off_frag_f[t - 1]) : nullptr;
-        q.bwd = flat_backward(t) ? (uint16_t*)(c->ws + lo.off_frag_b[t - 1]) : nullptr;
+        q.fwd = q.fwd_plan.slabs ? (uint16_t*)(c->ws + lo.off_frag_f[t - 1]) : nullptr;
+        q.bwd = q.bwd_plan.slabs ? (uint16_t*)(c->ws + lo.off_frag_b[t - 1]) : nullptr;
         pack.push_back(q);
     }
     for (int k = 0; k < c->K; ++k) {
@@ -1053,8 +1068,8 @@ int issue_steps_conv(kavg_ctx* c) {
         }
         // The gradient of the mean over the positions: written out for the generic kernels; the tile kernels of
         // the last convolution form it while loading (both of them must be in use, or the buffer is needed).
-        const bool pool_fused = M > 1 && lo.conv_implicit && (flat_backward(M) || conv_direct_ok(H, W, cv.ch[M - 1], cv.ch[M], true)) &&
-                                (flat_update(M) || (lo.splits_halo[M - 1] > 0 &&
+        const bool pool_fused = M > 1 && lo.conv_implicit && (lo.flat_b[M - 1].slabs || conv_direct_ok(H, W, cv.ch[M - 1], cv.ch[M], true)) &&
+                                (lo.splits_flat[M - 1] > 0 || (lo.splits_halo[M - 1] > 0 &&
                                                     B / lo.splits_halo[M - 1] <= conv_wgrad_halo_pool_images()));
         const void* dpool_M = c->ws + lo.off_dpool;
         if (!pool_fused) {
@@ -1062,8 +1077,18 @@ int issue_steps_conv(kavg_ctx* c) {
             KAVG_HIP(c, launch_pool_backward(c->ws + lo.off_dpool, c->ws + lo.off_cact[M - 1], c->ws + lo.off_cdz[M - 1],
                                              P, B, H * W, cv.ch[M], st));
         }
-        std::vector<ConvStep> steps;                                // SGD steps of all convolutions, after their data gradients
+        std::vector<ConvStep> steps;                                // SGD steps of the convolutions, after their data gradients
+        auto take_steps = [&]() -> int {
+            Bracket br(c, KAVG_CLASS_UPDATE);
+            KAVG_HIP(c, launch_conv_steps(steps.data(), (int)steps.size(), lo.stride, P, c->lr, st));
+            steps.clear();
+            return KAVG_OK;
+        };
         for (int t = M; t >= 1; --t) {                              // convolutions, backward
+            if (lo.step_first[t - 1]) {                             // (the layers above are done with their weights)
+                const int rc = take_steps();
+                if (rc != KAVG_OK) return rc;
+            }
             if (t > 1 && lo.conv_implicit) {
                 ConvCall v = implicit_call(t);
                 {
@@ -1080,7 +1105,7 @@ int issue_steps_conv(kavg_ctx* c) {
                     }
                 }
                 Bracket br(c, KAVG_CLASS_UPDATE);
-                if (flat_update(t)) {
+                if (lo.splits_flat[t - 1] > 0) {
                     v.splits = lo.splits_flat[t - 1];
                     KAVG_HIP(c, conv_flat_wgrad(v, table, nullptr, nullptr, 0, (pool_fused && t == M) ? dpool_M : nullptr, st));
                 } else if (lo.splits_halo[t - 1] > 0) {
@@ -1092,10 +1117,10 @@ int issue_steps_conv(kavg_ctx* c) {
                 steps.push_back({v.ws, v.wlo, (uint16_t*)v.bhi, (uint16_t*)v.blo, v.partial, v.partial_bias, v.splits, v.c_out * 9 * v.c_in, v.c_out});
                 continue;
             }
-            if (t == 1 && (flat_update(1) || first_direct)) {
+            if (t == 1 && (lo.splits_flat[0] > 0 || first_direct)) {
                 Bracket br(c, KAVG_CLASS_UPDATE);
                 ConvCall v = first_call();
-                if (flat_update(1)) {
+                if (lo.splits_flat[0] > 0) {
                     v.splits = lo.splits_flat[0];
                     KAVG_HIP(c, conv_flat_wgrad(v, table, c->X, idx_k, idx_ls, nullptr, st));
                 } else {
@@ -1121,8 +1146,8 @@ int issue_steps_conv(kavg_ctx* c) {
             KAVG_HIP(c, bf16_update(q, st));
             steps.push_back({q.ws, q.wlo, q.bhi, q.blo, q.partial, q.partial_bias, q.splits, q.d_out * q.d_in, q.d_out});
         }
-        Bracket br(c, KAVG_CLASS_UPDATE);
-        KAVG_HIP(c, launch_conv_steps(steps.data(), M, lo.stride, P, c->lr, st));
+        const int rc = take_steps();
+        if (rc != KAVG_OK) return rc;
     }
     return KAVG_OK;
 }

@@ -56,6 +56,22 @@ def test_workspace_holds_state_and_replicas(lib):
     assert kavg.kavg_workspace_bytes(1, 1, 1, (8, 16, 3), 1) > 0
 
 
+def test_conv_workspace_grows_with_depth_by_the_layers_own_data(lib):
+    """The partial sums of the weight gradients share one region: a convolution more costs its parameters, its images and
+    their gradient, and its weights once per direction in operand order."""
+    P, B = 8, 32
+
+    def need(H, c, M):
+        ch, dims = (8,) + (c,) * M, (c, 10)
+        return lib.kavg_workspace_bytes_conv(P, 8, B, H, H, M, kavg._dims_array(ch), 1, kavg._dims_array(dims))
+
+    for H, c in ((28, 128), (32, 128), (8, 512), (56, 64)):
+        weights, images = 9 * c * c + c, 2 * 2 * P * B * H * H * c
+        layer = (P + 2) * 4 * weights + images + 2 * 2 * P * weights
+        grown = need(H, c, 24) - need(H, c, 12)
+        assert grown < 1.05 * 12 * layer, (H, c, grown / (12 * layer))
+
+
 @pytest.mark.parametrize("kw, code", [
     (dict(P=0), kavg.KAVG_EINVAL), (dict(K=0), kavg.KAVG_EINVAL), (dict(B=0), kavg.KAVG_EINVAL),
     (dict(B=70000), kavg.KAVG_EINVAL), (dict(lr=-0.1), kavg.KAVG_EINVAL), (dict(mu=1.0), kavg.KAVG_EINVAL),

@@ -20,6 +20,7 @@ CASES = [
     (1, 2, 6, 10, (8, 136, 24), (24, 10)),           # 136 channels: one side of each layer on the generic kernels
     (1, 1, 3, 150, (8, 16, 48), (48, 10)),           # wide and low
     (1, 40, 1, 1, (8, 32, 32), (32, 10)),            # images of one pixel: margins everywhere
+    (1, 16, 28, 28, (8, 128, 128, 128, 128), (128, 10)),     # partial sums of 30 MB per layer: the SGD steps in two launches
 ]
 
 
