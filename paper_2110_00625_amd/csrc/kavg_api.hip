@@ -1343,7 +1343,8 @@ int kavg_local_steps(kavg_ctx* c) {
         if (!c->gexec) {
             hipGraph_t g = nullptr;
             KAVG_HIP(c, hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal));
-            const int rc = issue_steps(c);
+            int rc;
+            try { rc = issue_steps(c); } catch (...) { rc = fail(c, KAVG_ENOMEM, "host allocation failed"); }
             const hipError_t e = hipStreamEndCapture(st, &g);      // always ends the capture
             if (rc != KAVG_OK) { if (g) (void)hipGraphDestroy(g); return rc; }
             KAVG_HIP(c, e);
