@@ -25,7 +25,7 @@
 // Measured on 28x28 images, channels 8-32-64, 8 learners of 32 images (us per launch; before: the generic kernel on an
 // implicit patch matrix, the first layer on a written one): forward 15 + 17 -> 11 (first layer) and 27 -> 19, data gradient
 // 37 and a rotated weight copy -> 22, weight gradient 17 -> 12 and 49 -> 33 (conv_flat_wgrad.hip), a round of four steps
-// 980 -> 605.  At 64 -> 128 channels (32x32, 700 TFLOP/s) 17.6 k of a workgroup's 34 k cycles are the contraction, 6.8 k
+// 980 -> 605 (552 with one launch for the SGD steps of all layers).  At 64 -> 128 channels (32x32, 700 TFLOP/s) 17.6 k of a workgroup's 34 k cycles are the contraction, 6.8 k
 // bring in pixels, 9.4 k write the outputs; the clock stands near 1.6 GHz.
 #include "kavg_internal.h"
 #include "conv_flat.h"
@@ -278,13 +278,8 @@ __global__ void __launch_bounds__(NT) pack_weights_kernel(PackArgs a) {
     const uint16_t* w = d.w + (size_t)blockIdx.y * a.w_lstride;
     u32x4 v = {0u, 0u, 0u, 0u};
     if (!d.back) {
-        if (x < d.c_out && k < d.c_in) {                      // (the weights of a layer need not start at a multiple of 16 bytes)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const uint16_t* p = w + ((size_t)x * 9 + tap) * d.c_in + k + 2 * q;
-                v[q] = (uint32_t)p[0] | ((uint32_t)p[1] << 16);
-            }
-        }
+        if (x < d.c_out && k < d.c_in)                        // (all channel counts are multiples of 8, so layers and rows start at 16 bytes)
+            v = *(const u32x4*)(w + ((size_t)x * 9 + tap) * d.c_in + k);
     } else if (x < d.c_in && k < d.c_out) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {

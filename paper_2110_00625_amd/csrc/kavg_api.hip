@@ -991,6 +991,7 @@ int issue_steps_conv(kavg_ctx* c) {
     };
     const int32_t* table = (const int32_t*)(c->ws + lo.off_flat_table);
     std::vector<PackLayer> pack;                                    // weights in the operand order of conv_flat.hip
+    bool packed = false;
     for (int t = 1; t <= M; ++t) {
         PackLayer q{};
         q.w = c->hi_planes() + lo.cw_off[t - 1];
@@ -999,13 +1000,17 @@ int issue_steps_conv(kavg_ctx* c) {
         q.bwd_plan = lo.flat_b[t - 1]; q.bwd_lstride = q.bwd_plan.frag_elems();
         q.fwd = q.fwd_plan.slabs ? (uint16_t*)(c->ws + lo.off_frag_f[t - 1]) : nullptr;
         q.bwd = q.bwd_plan.slabs ? (uint16_t*)(c->ws + lo.off_frag_b[t - 1]) : nullptr;
+        packed = packed || q.fwd || q.bwd;
         pack.push_back(q);
     }
     for (int k = 0; k < c->K; ++k) {
         const int32_t* idx_k = c->idx() + (size_t)k * B;
         const long idx_ls = (long)c->K * B;
         float* rowloss_k = c->rowloss() + (size_t)k * P * B;
-        KAVG_HIP(c, launch_pack_weights(pack.data(), M, lo.stride, P, st));
+        if (packed) {
+            Bracket br(c, KAVG_CLASS_FORWARD);
+            KAVG_HIP(c, launch_pack_weights(pack.data(), M, lo.stride, P, st));
+        }
         for (int t = 1; t <= M; ++t) {                              // convolutions, forward
             Bracket br(c, KAVG_CLASS_FORWARD);
             if (pack[t - 1].fwd) {

@@ -38,3 +38,15 @@ def test_one_step(P, B, H, W, channels, dims):
             e = np.max(np.abs(got[sl] - want[sl])) / max(np.max(np.abs(want[sl])), 1e-30)
             print("  learner %d %-8s %.3g" % (j, name, e))
             assert e < 2.0 ** -8, "%s of learner %d: %.3g" % (name, j, e)
+
+
+def test_profile_counts_the_packing_of_the_weights():
+    """A step's forward launches: the packed weights, two convolutions, the mean over the positions (the last layer of ten
+    classes runs in the head kernels)."""
+    g, _, _ = _setup(2, 2, 4, 9, 28, (8, 32, 64), (64, 10), 77)
+    g.profile(["forward"])
+    g.local_steps()
+    assert g.profile_read()["forward"][1] == 2 * 4
+    g.profile([])
+    g.local_steps()
+    assert np.all(np.isfinite(g.losses()))
