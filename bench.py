@@ -9,7 +9,8 @@ the fused meta step (kavg_meta_update).  Prints ONE JSON line:
               (inputs resident in device memory before the clock starts)
   roofline    the dominant kernel class of the round, its algorithmic bytes
               per launch over its average launch duration (HIP events on the
-              library's stream, recorded inside the timed region)
+              library's stream in as many rounds again behind the timed ones,
+              which carry no events: observed updates run layer by layer)
   cpu_baseline  the CPU oracle, as it stands, on a bounded sample of the same
               workload (reported for context, not a target)
   other_workloads  the remaining training workloads, same measurements,
@@ -43,9 +44,10 @@ MFMA_BF16_PEAK_TFLOPS = 2500.0  # dense bf16 MFMA, published
 FP32_PEAK_TFLOPS = 157.3
 
 
-def class_model(w, learner_momentum=False):
+def class_model(w, learner_momentum=False, strips=False):
     """Algorithmic bytes and flops of one launch-set (all layers) of each kernel
-    class for ONE local step of all P learners, and of one meta pass."""
+    class for ONE local step of all P learners, and of one meta pass.
+    strips: the layers above the first form their data gradient in the update's pass over the weights."""
     P, B, d = w.P, w.B, w.dims
     L = len(d) - 1
     bf = w.dtype == kavg.KAVG_BF16
@@ -70,7 +72,10 @@ def class_model(w, learner_momentum=False):
         # write, dZ and A once
         by["update"] += P * ((8 + vel) * wsz + (8 + vel) * d[l] + e * B * (ld_out + d[l - 1]))
         fl["update"] += P * 2 * B * wsz
-        if l > 1:   # data gradient: weights once, dZ_l, mask read, dZ_{l-1} written
+        if l > 1 and strips:   # ... and the data gradient, from what the update has at hand: dZ_{l-1} written
+            by["update"] += P * e * B * d[l - 1]
+            fl["update"] += P * 2 * B * wsz
+        elif l > 1:   # data gradient: weights once, dZ_l, mask read, dZ_{l-1} written
             by["backward"] += P * (e * wsz + e * B * ld_out + 2 * e * B * d[l - 1])
             fl["backward"] += P * 2 * B * wsz
     n = num_params(d)
@@ -238,11 +243,9 @@ def run_workload(torch, w, steps, warmup, learner_momentum=0.0, copy_calibration
     if fused:
         heavy = "forward"
 
-    # timed region: only the dominant class carries events, and only one launch in EVERY of it
-    # (an event pair costs ~10 us of stream time; 17 is coprime with the launches per round, so
-    # the sample walks evenly over the layers)
-    EVERY = 17
-    g.profile([heavy], every=EVERY)
+    # timed region: no events.  (Observing the updates would also change what is timed: unobserved, those of all layers of
+    # a model whose weights stay in the cache are one launch, with the loss means.)
+    g.profile([])
     torch.cuda.synchronize()
     t0 = time.perf_counter()
     for _ in range(steps):
@@ -250,21 +253,30 @@ def run_workload(torch, w, steps, warmup, learner_momentum=0.0, copy_calibration
         g.meta_update()
     torch.cuda.synchronize()
     dt = time.perf_counter() - t0
+    loss_last = float(g.losses()[-1].mean())
+    # the dominant class in as many rounds again, one launch in EVERY of it (an event pair costs ~10 us of stream time;
+    # 17 is coprime with the launches per round, so the sample walks evenly over the layers)
+    EVERY = 17
+    g.profile([heavy], every=EVERY)
+    for _ in range(steps):
+        g.local_steps()
+        g.meta_update()
     prof = g.profile_read()
     g.profile([])
-    loss_last = float(g.losses()[-1].mean())
     g.close()
     del X, y
     torch.cuda.empty_cache()
 
     samples = w.P * w.K * w.B * steps
-    by, fl = class_model(w, learner_momentum > 0)
-    ms_sampled, sampled = prof[heavy]
-    per_round = w.K if heavy != "meta" else 1
     n_layers = len(w.dims) - 1
     head = w.dims[-1] <= 16
+    n_back = n_layers - 1 - (1 if head else 0)                 # layers with a data gradient outside the head kernels
+    strips = not fused and refresh == 1 and n_back > 0 and breakdown["backward"][1] == 0
+    by, fl = class_model(w, learner_momentum > 0, strips)
+    ms_sampled, sampled = prof[heavy]
+    per_round = w.K if heavy != "meta" else 1
     per_step = {"meta": 1, "update": n_layers - (1 if head else 0), "forward": n_layers - (1 if head else 0),
-                "backward": n_layers - 1 - (1 if head else 0)}[heavy]
+                "backward": n_back}[heavy]
     launches = per_step * per_round * steps
     if fused:                                                  # the one launch does the work of every class of the K steps
         launches = steps
@@ -272,7 +284,7 @@ def run_workload(torch, w, steps, warmup, learner_momentum=0.0, copy_calibration
         fl = dict(fl, forward=sum(fl[c] for c in ("forward", "backward", "update")) * w.K)
         per_round = 1
     ms_heavy = ms_sampled / max(sampled, 1) * launches         # sampled mean launch time x all launches of the class
-    bytes_heavy = by[heavy] * per_round * steps                # all launches of the class in the timed region
+    bytes_heavy = by[heavy] * per_round * steps                # all launches of the class in the sampled rounds
     flops_heavy = fl[heavy] * per_round * steps
     t_hbm = bytes_heavy / (HBM_PEAK_GBS * 1e9)
     peak_flops = (MFMA_BF16_PEAK_TFLOPS if bf else FP32_PEAK_TFLOPS) * 1e12
@@ -285,6 +297,8 @@ def run_workload(torch, w, steps, warmup, learner_momentum=0.0, copy_calibration
         achieved = flops_heavy / (ms_heavy * 1e-3) / 1e12
         roof = {"bound": "mfma", "achieved": achieved, "peak": peak_flops / 1e12, "unit": "TFLOP/s",
                 "frac": achieved / (peak_flops / 1e12)}
+    if strips and heavy == "update":
+        roof["note"] = "update launches of the layers above the first include their data gradients"
     roof.update({"traffic": stored_traffic(w.name, heavy) if refresh == 1 else None, "kernel_class": heavy, "launches": launches,
                  "launches_timed": sampled, "avg_launch_us": 1e3 * ms_heavy / max(launches, 1),
                  "algorithmic_bytes_per_launch": bytes_heavy / max(launches, 1),

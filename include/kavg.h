@@ -241,9 +241,10 @@ int kavg_set_refresh(kavg_ctx* ctx, int refresh, void* history_dev, size_t bytes
  * method): while a class's bit is set in class_mask, one launch in `every` of
  * that class (the first, the every+1-th, ...) is bracketed by a HIP event pair
  * on the context's stream; an event costs a few microseconds of stream time, so
- * a sparse sample keeps the timed region close to an unobserved one.  Updates that otherwise
- * run as one launch for all layers, with the loss means, are launched layer by layer while the
- * update, head or loss class is observed; a layer whose data gradient and update are one launch counts as update.
+ * a sparse sample keeps a timed region close to an unobserved one where the class's launches stay
+ * what they are.  Updates that otherwise run as one launch for all layers, with the loss means, are
+ * launched layer by layer while the update, head or loss class is in the mask, sampled or not: time such
+ * models unobserved.  A layer whose data gradient and update are one launch counts as update.
  * kavg_profile waits for the stream, clears the totals and installs the mask
  * (0 = off); kavg_profile_read waits for the stream and returns, per class, the
  * summed elapsed milliseconds and the number of bracketed launches since then
