@@ -424,6 +424,8 @@ def test_graph_replay_matches_the_eager_path_bit_for_bit(tag, dims, bf16, P, K, 
             if beta > 0:
                 g.set_learner_momentum(beta)
             g.set_params(w0)
+            g.set_fused(False)                           # (the fp32 model would run its steps in one launch, which is not recorded)
+            assert g.one_launch == 0
             if use_graph:
                 g.graph(True)
             trace = []
@@ -455,6 +457,7 @@ def test_graph_replay_against_the_oracle():
     dims = (96, 72, 10)
     with torch.cuda.stream(torch.cuda.Stream()):
         g, o = _pair(3, 3, 0.05, 0.5, dims, 20, False, 41)
+        g.set_fused(False)                               # (one launch is not recorded)
         g.graph(True)
         _run_and_compare(g, o, dims, 5, TOL_FP32, "graph")
         g.close()
