@@ -29,7 +29,8 @@
 // alternate between two buffers: a workgroup overwrites the buffer of step k only when it computes step k+2,
 // which it starts after it has read every partial of step k+1, each of which was written after its
 // writer had read the partials of step k.  All workgroups must be resident at once: the host
-// launches this kernel only when their number does not exceed the number of compute units.  A reader that
+// launches this kernel only when their number does not exceed the number of compute units, and launches of several
+// contexts that do not fit on the chip together take turns (kavg_api.hip).  A reader that
 // runs out of polls raises an error word and carries on, so every wavefront reaches the end of the
 // kernel whatever happens.
 //

@@ -14,8 +14,9 @@
 //      (identically everywhere) b_2.
 // With G = 1 nothing is exchanged.  Tags, buffers and the bounded polls are those of fused_small.hip: a word (value, tag)
 // validates itself, two buffers alternate (one is overwritten at step k+2, which its writer reaches only after every reader
-// has finished step k), all P*G workgroups are resident because there are no more of them than compute units, and a wait
-// that runs out of polls raises an error word and carries on, so every wavefront reaches the end.
+// has finished step k), all P*G workgroups are resident because there are no more of them than compute units (launches of
+// several contexts that do not fit together take turns, kavg_api.hip), and a wait that runs out of polls raises an error word
+// and carries on, so every wavefront reaches the end.
 //
 // What bounds it: the chain of phases inside a step, each of them a few dependent LDS round trips and matrix instructions on
 // eight wavefronts, not a throughput.  Measured per step on 256-256-10 with 6 learners, B = 32 (16 groups of 16 units), us:

@@ -12,7 +12,7 @@
 //
 // Measured, all updates of a step, us (one launch per layer, the velocity read after the contraction -> this kernel):
 // 3072-1024-1024-10, 16 learners of 128 samples 80 + 31 + 9 -> 103 (5.3 TB/s); 3080-1032-520-24 with momentum, 5 learners of
-// 70: 84 + 19 + 8 -> 66; models of a few hundred units: 4 - 6 per layer -> 5 - 6 in all (a step 1.2 - 1.5x faster).  What bounds
+// 70: 84 + 19 + 8 -> 59 (5.0 TB/s); models of a few hundred units: 4 - 6 per layer -> 5 - 6 in all (a step 1.2 - 1.5x faster).  What bounds
 // it: the traffic of the planes on large models, latency on small ones.  Where the hi planes stream as well the one-layer
 // kernel and the head's are as fast (4096 wide, 32 learners: 630 against 595 + 23) and stay.
 #include "kavg_internal.h"
