@@ -19,6 +19,7 @@
 // / master update in fp32; the master is read and written as its two 16-bit
 // planes (split.h), of which the bf16 one is the operand of the products.
 #include "kavg_internal.h"
+#include "head_update.h"
 #include "split.h"
 
 namespace kavg {
@@ -48,15 +49,6 @@ __device__ __forceinline__ float wave_sum(float x) {
     const float r2 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(xi, 47));
     const float r3 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(xi, 63));
     return (r0 + r1) + (r2 + r3);
-}
-// Sum over the 16 lanes that differ in bits 2..5 of the lane index (same low two bits), in every lane:
-// rotations by 4 and 8 inside a row keep the low bits; the rows are joined by two shuffles.
-__device__ __forceinline__ float groups_sum(float x) {
-    x += dpp_move<0x124>(x);       // row_ror:4
-    x += dpp_move<0x128>(x);       // row_ror:8
-    x += __shfl_xor(x, 16, 64);
-    x += __shfl_xor(x, 32, 64);
-    return x;
 }
 __device__ __forceinline__ uint16_t bf16_bits(float x) {
     __bf16 h = (__bf16)x;                         // round to nearest even
@@ -100,8 +92,7 @@ struct HeadArgs {
     const void* wmul; size_t wmul_lstride;                // weights as multiplied: bf16 (hi) plane or fp32, [C][d]
     float* wmaster; size_t w_lstride;                     // fp32 mode: the layer's weights
     float* bias;                                          // fp32 mode: its bias (stride w_lstride)
-    uint16_t* whi; uint16_t* wlo; size_t ws_lstride;      // bf16 mode: hi / lo planes of the weights (split.h)
-    uint16_t* bhi; uint16_t* blo;                         // bf16 mode: hi / lo planes of the bias (stride ws_lstride)
+    const uint16_t* bhi; const uint16_t* blo; size_t ws_lstride;     // bf16 mode: hi / lo planes of the bias (split.h)
     const int32_t* y;                                     // labels of the data set
     void* dz; int ldz; size_t dz_lstride;                 // dZ_L [P][B][ldz]
     void* dz_prev; size_t dz_prev_lstride;                // dZ_{L-1} [P][B][d], null for a single-layer model
@@ -259,160 +250,63 @@ __global__ void __launch_bounds__(256) head_forward_backward_kernel(HeadArgs a) 
     }
 }
 
-// One row of dZ_L (ldz <= 16 values) as floats; entries beyond ldz are zero.
-template <bool BF16>
-__device__ __forceinline__ void load_dz_row(const void* dz, size_t at, int ldz, float* out /*[16]*/) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) out[i] = 0.f;
-    if (BF16) {
-        const u32x4 lo = *(const u32x4*)((const uint16_t*)dz + at);
-        u32x4 hi = {0u, 0u, 0u, 0u};
-        if (ldz > 8) hi = *(const u32x4*)((const uint16_t*)dz + at + 8);
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            out[2 * i] = __builtin_bit_cast(float, lo[i] << 16);
-            out[2 * i + 1] = __builtin_bit_cast(float, lo[i] & 0xFFFF0000u);
-            out[8 + 2 * i] = __builtin_bit_cast(float, hi[i] << 16);
-            out[8 + 2 * i + 1] = __builtin_bit_cast(float, hi[i] & 0xFFFF0000u);
-        }
-    } else {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            if (4 * i < ldz) {                                // ldz is a multiple of 8
-                const f32x4 v = *(const f32x4*)((const float*)dz + at + 4 * i);
-                out[4 * i] = v.x; out[4 * i + 1] = v.y; out[4 * i + 2] = v.z; out[4 * i + 3] = v.w;
-            }
-        }
-    }
+__global__ void __launch_bounds__(256) head_update_bf16_kernel(HeadStep a) {
+    __shared__ __align__(16) float xch[HEAD_LDS / 4];
+    head_step(a, blockIdx.x, gridDim.z > 1 ? (int)blockIdx.z : -1, blockIdx.y, xch);
 }
 
-// 256 threads = 4 wavefronts.  Lane = 4*g + pl: sample group g (samples s = g mod 16) and piece
-// blockIdx.x*16 + 4*wave + pl of the layer's input units.  Every lane sums dZ_L[s][c] * A[s][piece]
-// over its samples in ascending order; a butterfly over the group bits of the lane index adds the
-// sixteen groups, after which lane group g applies the update of class c = g.
-constexpr int XCH_CS = 16 * 32 + 36;      // floats between classes in a wavefront's exchange patch (36: classes fall on different banks)
-
-template <bool BF16, int CT>
-__global__ void __launch_bounds__(256) head_update_kernel(HeadArgs a) {
-    constexpr int N = Piece<BF16>::N;
+// fp32: 256 threads = 4 wavefronts.  Lane = 4*g + pl: sample group g (samples s = g mod 16) and input unit
+// blockIdx.x*16 + 4*wave + pl.  Every lane sums dZ_L[s][c] * A[s][unit] over its samples in ascending order; a
+// butterfly over the group bits of the lane index adds the sixteen groups, after which lane group g applies the
+// update of class c = g.
+template <int CT>
+__global__ void __launch_bounds__(256) head_update_f32_kernel(HeadArgs a) {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int grp = lane >> 2, pl = lane & 3;
     const int q = blockIdx.x * 16 + wave * 4 + pl;
     const int learner = blockIdx.y;
-    const int pieces = a.d / N;
-    const bool live = q < pieces;
-    const int qq = live ? q : pieces - 1;                     // out-of-range lanes shadow the last piece, never store
+    const bool live = q < a.d;
+    const int qq = live ? q : a.d - 1;                        // out-of-range lanes shadow the last unit, never store
     const int32_t* g = a.gather + (long)learner * a.gather_lstride;
+    const float* act = (const float*)a.act;
+    const float* dz = (const float*)a.dz + (size_t)learner * a.dz_lstride;
 
-    float acc[CT][N], bsum[CT];
+    float acc[CT], bsum[CT];
 #pragma unroll
-    for (int c = 0; c < CT; ++c) {
-        bsum[c] = 0.f;
-#pragma unroll
-        for (int e = 0; e < N; ++e) acc[c][e] = 0.f;
-    }
+    for (int c = 0; c < CT; ++c) acc[c] = bsum[c] = 0.f;
 #pragma unroll 4
     for (int s = grp; s < a.B; s += 16) {
         const size_t arow = a.act_lstride ? (size_t)learner * a.act_lstride + (size_t)s * a.ld_act
                                           : (size_t)g[s] * a.ld_act;
-        Piece<BF16> x;
-        x.load(a.act, arow + (size_t)qq * N);
-        float gz[16];
-        load_dz_row<BF16>(a.dz, (size_t)learner * a.dz_lstride + (size_t)s * a.ldz, a.ldz, gz);
+        const float x = act[arow + qq];
+        float gz[16];                                         // one row of dZ_L; entries beyond ldz are zero
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            f32x4 v = {0.f, 0.f, 0.f, 0.f};
+            if (4 * i < a.ldz) v = *(const f32x4*)(dz + (size_t)s * a.ldz + 4 * i);      // ldz is a multiple of 8
+            gz[4 * i] = v.x; gz[4 * i + 1] = v.y; gz[4 * i + 2] = v.z; gz[4 * i + 3] = v.w;
+        }
 #pragma unroll
         for (int c = 0; c < CT; ++c) {
             bsum[c] += gz[c];                                  // bias gradient: column sum of dZ_L
-#pragma unroll
-            for (int e = 0; e < N; ++e) acc[c][e] = fmaf(gz[c], x.v[e], acc[c][e]);
+            acc[c] = fmaf(gz[c], x, acc[c]);
         }
     }
+    float mine = 0.f, sum = 0.f;
 #pragma unroll
     for (int c = 0; c < CT; ++c) {
-        float b = bsum[c];
-        bsum[c] = groups_sum(b);
-    }
-    float mine[N];
-    if constexpr (BF16) {
-        // Lane group g needs class g's gradient of the wavefront's four pieces, summed over the sixteen sample
-        // groups: each lane leaves its CT x 8 partial sums in the wavefront's LDS patch and lane group g adds
-        // the sixteen partials of class g in ascending group order (a butterfly would move every value four
-        // times, this moves it twice).  A wavefront's LDS accesses complete in order: no barrier.
-        extern __shared__ __align__(16) float head_xch[];
-        float* patch = head_xch + wave * (CT * XCH_CS);
-#pragma unroll
-        for (int c = 0; c < CT; ++c) {
-            *(f32x4*)(patch + c * XCH_CS + lane * 8) = (f32x4){acc[c][0], acc[c][1], acc[c][2], acc[c][3]};
-            *(f32x4*)(patch + c * XCH_CS + lane * 8 + 4) = (f32x4){acc[c][4], acc[c][5], acc[c][6], acc[c][7]};
-        }
-#pragma unroll
-        for (int e = 0; e < N; ++e) mine[e] = 0.f;
-        const float* src = patch + min(grp, CT - 1) * XCH_CS + pl * 8;
-#pragma unroll
-        for (int g2 = 0; g2 < 16; ++g2) {
-            const f32x4 lo4 = *(const f32x4*)(src + g2 * 32), hi4 = *(const f32x4*)(src + g2 * 32 + 4);
-            mine[0] += lo4.x; mine[1 % N] += lo4.y; mine[2 % N] += lo4.z; mine[3 % N] += lo4.w;
-            mine[4 % N] += hi4.x; mine[5 % N] += hi4.y; mine[6 % N] += hi4.z; mine[7 % N] += hi4.w;
-        }
-    } else {
-#pragma unroll
-        for (int c = 0; c < CT; ++c)
-#pragma unroll
-            for (int e = 0; e < N; ++e) {
-                float v = acc[c][e];
-                acc[c][e] = groups_sum(v);
-            }
-#pragma unroll
-        for (int e = 0; e < N; ++e) mine[e] = 0.f;
-#pragma unroll
-        for (int c = 0; c < CT; ++c)
-            if (c == grp) {
-#pragma unroll
-                for (int e = 0; e < N; ++e) mine[e] = acc[c][e];
-            }
+        const float bs = groups_sum(bsum[c]), v = groups_sum(acc[c]);
+        if (c == grp) { mine = v; sum = bs; }
     }
     if (live && grp < a.C) {
-        const size_t uat = (size_t)learner * a.w_lstride + (size_t)grp * a.d + (size_t)q * N;   // velocity (fp32 layout)
-        if (a.u) {                                            // heavy ball inside the learner
-#pragma unroll
-            for (int e = 0; e < N; ++e) { mine[e] = a.beta * a.u[uat + e] + mine[e]; a.u[uat + e] = mine[e]; }
-        }
-        if (BF16) {
-            // the master lives in two 16-bit planes; the hi plane is what the next products read
-            const size_t at = (size_t)learner * a.ws_lstride + (size_t)grp * a.d + (size_t)q * N;
-            const u32x4 h = *(const u32x4*)(a.whi + at), l = *(const u32x4*)(a.wlo + at);
-            u32x4 oh, ol;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                uint32_t b0, b1;
-                split_join2(h[i], l[i], b0, b1);
-                const float w0 = __builtin_bit_cast(float, b0) - a.lr * mine[(2 * i) % N];
-                const float w1 = __builtin_bit_cast(float, b1) - a.lr * mine[(2 * i + 1) % N];
-                uint32_t h2, l2;
-                split_pack2(__builtin_bit_cast(uint32_t, w0), __builtin_bit_cast(uint32_t, w1), h2, l2);
-                oh[i] = h2; ol[i] = l2;
-            }
-            *(u32x4*)(a.whi + at) = oh;
-            *(u32x4*)(a.wlo + at) = ol;
-        } else {
-            float* wm = a.wmaster + uat;
-#pragma unroll
-            for (int e = 0; e < N; ++e) wm[e] = wm[e] - a.lr * mine[e];
-        }
+        const size_t uat = (size_t)learner * a.w_lstride + (size_t)grp * a.d + q;
+        if (a.u) { mine = a.beta * a.u[uat] + mine; a.u[uat] = mine; }     // heavy ball inside the learner
+        a.wmaster[uat] = a.wmaster[uat] - a.lr * mine;
     }
     if (blockIdx.x == 0 && wave == 0 && pl == 0 && grp < a.C) {   // every lane holds the full column sums
-        float mine = 0.f;
-#pragma unroll
-        for (int c = 0; c < CT; ++c) if (c == grp) mine = bsum[c];
         const size_t at = (size_t)learner * a.w_lstride + grp;
-        if (a.ub) { mine = a.beta * a.ub[at] + mine; a.ub[at] = mine; }
-        if (BF16) {
-            const size_t sat = (size_t)learner * a.ws_lstride + grp;
-            const float b = __builtin_bit_cast(float, split_join(a.bhi[sat], a.blo[sat])) - a.lr * mine;
-            a.bhi[sat] = (uint16_t)split_hi(__builtin_bit_cast(uint32_t, b));
-            a.blo[sat] = (uint16_t)split_lo(__builtin_bit_cast(uint32_t, b));
-        } else {
-            a.bias[at] = a.bias[at] - a.lr * mine;
-        }
+        if (a.ub) { sum = a.beta * a.ub[at] + sum; a.ub[at] = sum; }
+        a.bias[at] = a.bias[at] - a.lr * sum;
     }
 }
 
@@ -423,7 +317,7 @@ HeadArgs make_args(const LayerCall& c, const int32_t* y, const int32_t* idx, lon
     a.wmul = bf16 ? (const void*)c.ws : (const void*)c.w;
     a.wmul_lstride = bf16 ? c.ws_stride : c.w_stride;
     a.wmaster = c.w; a.w_lstride = c.w_stride; a.bias = c.b;
-    a.whi = c.ws; a.wlo = c.wlo; a.ws_lstride = c.ws_stride; a.bhi = c.bhi; a.blo = c.blo;
+    a.bhi = c.bhi; a.blo = c.blo; a.ws_lstride = c.ws_stride;
     a.y = y;
     a.dz = (void*)c.dz; a.ldz = c.ld_dz; a.dz_lstride = c.dz_stride;
     a.dz_prev = c.dz_prev; a.dz_prev_lstride = c.dz_prev_stride;
@@ -450,25 +344,6 @@ void launch_fb(const HeadArgs& a, dim3 grid, hipStream_t st) {
     const int pieces = a.d / Piece<BF16>::N;
     if (pieces <= 128) launch_fb2<BF16, true>(a, grid, st); else launch_fb2<BF16, false>(a, grid, st);
 }
-template <bool BF16, int CT>
-hipError_t launch_upd_ct(const HeadArgs& a, dim3 grid, hipStream_t st) {
-    constexpr int SMEM = BF16 ? 4 * CT * XCH_CS * 4 : 0;       // one exchange patch per wavefront
-    if (SMEM > 64 * 1024) {
-        static hipError_t raised = hipFuncSetAttribute((const void*)head_update_kernel<BF16, CT>,
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
-        if (raised != hipSuccess) return raised;
-    }
-    hipLaunchKernelGGL((head_update_kernel<BF16, CT>), grid, dim3(256), SMEM, st, a);
-    return hipSuccess;
-}
-template <bool BF16>
-hipError_t launch_upd(const HeadArgs& a, dim3 grid, hipStream_t st) {
-    if (a.C <= 4) return launch_upd_ct<BF16, 4>(a, grid, st);
-    if (a.C <= 8) return launch_upd_ct<BF16, 8>(a, grid, st);
-    if (a.C <= 12) return launch_upd_ct<BF16, 12>(a, grid, st);
-    return launch_upd_ct<BF16, 16>(a, grid, st);
-}
-
 }  // namespace
 
 hipError_t head_forward_backward(const LayerCall& c, const int32_t* y, const int32_t* idx, long idx_lstride,
@@ -480,11 +355,18 @@ hipError_t head_forward_backward(const LayerCall& c, const int32_t* y, const int
 }
 
 hipError_t head_update(const LayerCall& c, const int32_t* idx, long idx_lstride, int bf16, hipStream_t st) {
-    HeadArgs a = make_args(c, nullptr, idx, idx_lstride, nullptr, bf16 != 0);
-    const int pieces = c.d_in / (bf16 ? 8 : 1);
-    dim3 grid((pieces + 15) / 16, c.P);
-    const hipError_t e = bf16 ? launch_upd<true>(a, grid, st) : launch_upd<false>(a, grid, st);
-    return e != hipSuccess ? e : hipGetLastError();
+    if (bf16) {
+        hipLaunchKernelGGL(head_update_bf16_kernel, dim3(head_blocks(c.d_in), c.P, head_class_groups(c.P, c.d_in, c.d_out)), dim3(256), 0, st,
+                           head_step_args(c, idx, idx_lstride));
+    } else {
+        const HeadArgs a = make_args(c, nullptr, idx, idx_lstride, nullptr, false);
+        const dim3 grid((c.d_in + 15) / 16, c.P);
+        if (c.d_out <= 4) hipLaunchKernelGGL(head_update_f32_kernel<4>, grid, dim3(256), 0, st, a);
+        else if (c.d_out <= 8) hipLaunchKernelGGL(head_update_f32_kernel<8>, grid, dim3(256), 0, st, a);
+        else if (c.d_out <= 12) hipLaunchKernelGGL(head_update_f32_kernel<12>, grid, dim3(256), 0, st, a);
+        else hipLaunchKernelGGL(head_update_f32_kernel<16>, grid, dim3(256), 0, st, a);
+    }
+    return hipGetLastError();
 }
 
 }  // namespace kavg

@@ -415,6 +415,7 @@ LayerCall layer_call(const kavg_ctx* c, int l /*1..L*/, int k) {
     q.out_stride = (size_t)c->B * q.ld_out;
     q.dz = c->ws + lo.off_dz[l - 1]; q.ld_dz = l == L ? lo.ldz : c->dims[l];
     q.dz_stride = (size_t)c->B * q.ld_dz;
+    q.head = l == L && head_supported(c->dims[L]);
     q.lr = c->lr;
     q.beta = c->beta;
     q.u = c->vel ? c->vel + lo.w_off[l - 1] : nullptr;

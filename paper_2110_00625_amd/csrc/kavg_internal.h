@@ -75,6 +75,7 @@ struct LayerCall {
     // learner-level momentum: velocity of this layer's weights (learner 0; stride w_stride) and of its
     // bias, null when off.  u <- beta u + g, w <- w - lr u.
     float* u; float* ub; float beta;
+    int head;              // the last layer, of few classes: its update takes its sums in the order of head_update
     // deferred weight updates (bf16 mode):
     int shared_w;          // forward / backward-data: every learner's stored weights equal learner 0's (round start): read those
     int bwd_raw;           // backward-data: write the unmasked fp32 product to dz_prev instead of the masked bf16 one
@@ -128,6 +129,7 @@ hipError_t f32_update(const LayerCall* layers, int n, const LossMeans* losses, h
 hipError_t bf16_forward(const LayerCall& c, hipStream_t st);
 hipError_t bf16_backward_data(const LayerCall& c, hipStream_t st);
 hipError_t bf16_update(const LayerCall& c, hipStream_t st);
+bool bf16_backward_splits(int P, int B, int d_in, int d_out);        // bf16_backward_data sums every 64 units in two halves, joined at the end
 // data gradient and update of a layer in one pass over its weights (strip_bf16.hip); which calls it takes
 bool bf16_strip_ok(const LayerCall& c);
 hipError_t bf16_strip(const LayerCall& c, hipStream_t st);

@@ -7,22 +7,29 @@
 //
 // A workgroup owns a strip of 128 input units and walks down the output units RC at a time.  The strip's activations
 // (up to 256 samples) stay in LDS; a chunk brings in RC columns of dZ, which both products use, and RC x 128 weights, which
-// are multiplied, updated and written back while they are at hand.  Chunks are requested two ahead in registers.
+// are multiplied, updated and written back while they are at hand.  Chunks are requested ahead in registers.
 //
-//   data gradient: MFMA 32x32x16, rows = input units (transpose reads of the weights in LDS), columns = samples, k = units of
-//                  the chunk; the sums of the whole strip stay in accumulators (BT/64 blocks per wavefront);
-//   update:        rows = input units, columns = output units, k = samples (two halves of them, added up on the way); the
-//                  chunk's gradient passes through LDS so that a thread then holds eight consecutive columns of both
-//                  planes (256 bytes per row and plane).
+//   update:        four wavefronts; rows = input units (32 each), columns = output units, k = samples, MFMA 32x32x16.  The
+//                  activations stay in registers; the chunk's gradient passes through LDS so that a thread then holds
+//                  eight consecutive columns of both planes (256 bytes per row and plane).
+//   data gradient: four wavefronts; rows = input units (transpose reads of the weights in LDS), columns = samples, k = units
+//                  of the chunk; the sums of the whole strip stay in accumulators (BT/32 blocks per wavefront).
+//
+// Every sum is one chain over ascending samples or units, as in the separate kernels (gemm_bf16.hip; their data gradient
+// splits its contraction where a launch is small): with the samples split over two wavefronts instead, both kinds of
+// product on each, the results moved by half a per cent of the block momentum within a round, and with 256 samples it was
+// slower (2048 -> 2048, 16 learners: 87 against 75 us).
 //
 // Why: with the weights streaming from memory the separate kernels read the hi plane twice (2 of 12 bytes per weight and
 // step), and with 256 samples what they pull out of L2 for each tile of weights -- both operands of every tile, 128 KB per
 // 128 KB of master traffic -- held the update to 4.5 - 5 TB/s.  Here a chunk costs its dZ columns only.
-// Measured, both products of a layer, us (separate kernels -> this one): 4096 -> 4096, 32 learners of 64 samples 976 -> 861;
-// 8 of 256: 340 -> 308; 4096 -> 1000, 8 of 256: 99 -> 79; 1024 -> 1024, 32 of 128: 74 -> 54; 32 of 64: 61 -> 48.
+// Measured, both products of a layer, us (separate kernels -> this one): 4096 -> 4096, 32 learners of 64 samples 745 + 207 ->
+// 787; 8 of 256, mean with 4096 -> 1000: 149 + 70 -> 165.  Rounds of four steps, 256-1024-1024-1024-40: 24 learners of 128 936 ->
+// 881, of 200 1198 -> 1085.
 // What bounds it: up to 128 samples the traffic of the weights itself (5.0 - 5.9 TB/s; without the products the same time);
-// with 256 samples the two barriers per chunk cost a quarter on top (237 us without the products).
+// with 256 samples the two barriers per chunk on top.
 #include "kavg_internal.h"
+#include "column_sum.h"
 #include "split.h"
 
 namespace kavg {
@@ -45,12 +52,11 @@ constexpr int PP = SC + 4;                   // LDS rows of the gradient (fp32)
 
 constexpr int RC = 32;                       // output units per chunk
 constexpr int ZP = RC + 16;                  // LDS rows of dZ: read along the units and across them
-constexpr int SETS = 3;                      // chunks in registers: the one at hand and two requested ahead (four and five: the same time)
 
 template <int BT>
 struct StripShape {
     static constexpr int ZN = (BT * RC / 8 + NT - 1) / NT, AN = BT * SC / 8 / NT;
-    static constexpr int SMEM = BT * XP * 2 + BT * ZP * 2 + RC * XP * 2 + 2 * RC * (PP + 1) * 4;
+    static constexpr int SMEM = BT * XP * 2 + BT * ZP * 2 + RC * XP * 2 + RC * (PP + 1) * 4;
 };
 static_assert(RC * SC / 8 == NT, "one 16-byte piece of each plane per thread and chunk");
 
@@ -78,20 +84,25 @@ __device__ __forceinline__ bf16x8 frag_tr(const uint16_t* tile, int pitch, int k
     return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-// STREAM: the hi planes of all learners do not stay in the memory-side cache (the lo planes never do)
-template <int BT, bool STREAM>
+// STREAM: the hi planes of all learners do not stay in the memory-side cache (the lo planes never do).  CHAINS: the data
+// gradient's sums, one chain over the units, or two (even and odd chunks) that are added up at the end.
+template <int BT, bool STREAM, int CHAINS>
 __global__ void __launch_bounds__(NT) strip_kernel(StripArgs a) {
     typedef StripShape<BT> SH;
-    constexpr int ZN = SH::ZN, KS = BT / 16 / 2;             // slabs of 16 samples in one half
-    // blocks of a wavefront's data gradient: input units x samples (two by two where there are enough: four operand reads
-    // per four matrix instructions instead of five)
-    constexpr int CBW = BT == 256 ? 2 : 1, SBW = BT / 32 * 4 / 8 / CBW;
+    constexpr int ZN = SH::ZN, KS = BT / 16;                 // slabs of 16 samples
+    // Chunks in registers, the one at hand and those requested ahead.  (Three: 70 against 66 us with 1024 -> 1024, 32 learners
+    // of 128 samples, and no registers left for the accumulators with 256; with 64 samples three are 58 against 59 us where
+    // the planes stay cached, and cost the second workgroup per compute unit, 0.3 % of a round, where they stream.)
+    constexpr int SETS = BT == 64 && !STREAM && CHAINS == 1 ? 3 : 2;
+    static_assert(CHAINS == 1 || SETS == 2, "a chunk's set is its parity");
+    // blocks of a wavefront's data gradient: input units x samples
+    constexpr int CBW = BT == 64 ? 1 : 2, SBW = BT / 32 / CBW;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     uint16_t* const X = (uint16_t*)smem;                     // [BT][XP] activations
     uint16_t* const Z = X + BT * XP;                         // [BT][ZP] dZ of the chunk
     uint16_t* const W = Z + BT * ZP;                         // [RC][XP] hi plane of the chunk
-    float* const G = (float*)(W + RC * XP);                  // [2][RC][PP] gradient of the chunk, halves of the samples
-    float* const GB = G + 2 * RC * PP;                       // [2][RC] column sums of dZ
+    float* const G = (float*)(W + RC * XP);                  // [RC][PP] gradient of the chunk
+    float* const GB = G + RC * PP;                           // [RC] column sums of dZ
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // workgroup g runs on XCD g mod 8: each XCD gets one contiguous range of (learner, strip)
     const int at = (blockIdx.x & 7) * (a.padded >> 3) + (blockIdx.x >> 3);
@@ -141,28 +152,11 @@ __global__ void __launch_bounds__(NT) strip_kernel(StripArgs a) {
         }
     }
 
-    // update: input units 32 cb .. +31 of the strip, one half of the samples
-    const int cb = wave & 3, half = wave >> 2;
-    // data gradient: input units 32 bc .. and samples 32 bs .. , CBW x SBW blocks
-    const int bc = wave % (4 / CBW) * CBW, bs = wave / (4 / CBW) * SBW;
-    f32x16 back[CBW][SBW];
-#pragma unroll
-    for (int c = 0; c < CBW; ++c)
-#pragma unroll
-        for (int s = 0; s < SBW; ++s)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) back[c][s][e] = 0.f;
-    // the activations that this wavefront multiplies in every chunk
     __syncthreads();
-    bf16x8 xf[KS];
-#pragma unroll
-    for (int k = 0; k < KS; ++k) xf[k] = frag_tr(X, XP, (half * KS + k) * 16, cb * 32, lane);
 
-    const bool bias = strip == 0 && cb == 0;                 // (uniform) this wavefront sums dZ as well: its product with ones
-    bf16x8 ones;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
-    auto chunk = [&](int set, int r0) __attribute__((always_inline)) {
+    // A chunk: its pieces from registers to LDS, the next one requested, the products (each kind of wavefront its own), and
+    // the master's step from the gradient in LDS.
+    auto stage = [&](int set, int r0) __attribute__((always_inline)) {
 #pragma unroll
         for (int i = 0; i < ZN; ++i) {
             const int e = tid + NT * i, s = e / (RC / 8), r = r0 + (e % (RC / 8)) * 8;
@@ -173,43 +167,13 @@ __global__ void __launch_bounds__(NT) strip_kernel(StripArgs a) {
         __syncthreads();
         load((set + SETS - 1) % SETS, r0 + (SETS - 1) * RC);
         __builtin_amdgcn_sched_barrier(0);                   // (left alone, the compiler moves the requests to their use)
-#pragma unroll
-        for (int k = 0; k < RC / 16; ++k) {
-            bf16x8 wf[CBW], zf[SBW];
-#pragma unroll
-            for (int c = 0; c < CBW; ++c) wf[c] = frag_tr(W, XP, k * 16, (bc + c) * 32, lane);
-#pragma unroll
-            for (int s = 0; s < SBW; ++s) zf[s] = *(const bf16x8*)(Z + ((bs + s) * 32 + (lane & 31)) * ZP + k * 16 + (lane >> 5) * 8);
-#pragma unroll
-            for (int c = 0; c < CBW; ++c)
-#pragma unroll
-                for (int s = 0; s < SBW; ++s)
-                    back[c][s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[c], zf[s], back[c][s], 0, 0, 0);
-        }
-        f32x16 g;
-#pragma unroll
-        for (int e = 0; e < 16; ++e) g[e] = 0.f;
-#pragma unroll
-        for (int k = 0; k < KS; ++k) {
-            const bf16x8 zf = frag_tr(Z, ZP, (half * KS + k) * 16, 0, lane);
-            g = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf[k], zf, g, 0, 0, 0);
-        }
-        // accumulator e: input unit 8 (e/4) + 4 (lane/32) + e%4 of the block, output unit lane%32
-        float* p = G + (half * RC + (lane & 31)) * PP + cb * 32 + 4 * (lane >> 5);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) *(f32x4*)(p + 8 * q) = (f32x4){g[4 * q], g[4 * q + 1], g[4 * q + 2], g[4 * q + 3]};
-        if (bias) {                                          // (a loop of its own: a branch inside the one above would serialise it)
-            f32x16 gb;
-#pragma unroll
-            for (int e = 0; e < 16; ++e) gb[e] = 0.f;
-#pragma unroll
-            for (int k = 0; k < KS; ++k)
-                gb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, frag_tr(Z, ZP, (half * KS + k) * 16, 0, lane), gb, 0, 0, 0);
-            if (lane < 32) GB[half * RC + lane] = gb[0];         // (every row holds the same sums)
-        }
+    };
+    // The bias of a chunk's units belongs to one of the learner's strips, in turn.
+    auto owns_bias = [&](int r0) __attribute__((always_inline)) { return r0 / RC % a.strips == strip; };
+    auto step = [&](int set, int r0) __attribute__((always_inline)) {
         __syncthreads();
         const float* gp = G + wrow * PP + wcol;
-        const f32x4 g0 = *(const f32x4*)gp + *(const f32x4*)(gp + RC * PP), g1 = *(const f32x4*)(gp + 4) + *(const f32x4*)(gp + RC * PP + 4);
+        const f32x4 g0 = *(const f32x4*)gp, g1 = *(const f32x4*)(gp + 4);
         const float gs[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
         u32x4 oh, ol;
 #pragma unroll
@@ -225,14 +189,76 @@ __global__ void __launch_bounds__(NT) strip_kernel(StripArgs a) {
             if (STREAM) __builtin_nontemporal_store(oh, (u32x4*)(hi + p)); else *(u32x4*)(hi + p) = oh;
             __builtin_nontemporal_store(ol, (u32x4*)(lo + p));
         }
-        if (strip == 0 && tid < RC && r0 + tid < a.d_out) {
-            const float b = __builtin_bit_cast(float, split_join(br[set][0], br[set][1])) - a.lr * (GB[tid] + GB[RC + tid]);
+        if (tid < RC && r0 + tid < a.d_out && owns_bias(r0)) {
+            const float b = __builtin_bit_cast(float, split_join(br[set][0], br[set][1])) - a.lr * GB[tid];
             bhi[r0 + tid] = (uint16_t)split_hi(__builtin_bit_cast(uint32_t, b));
             blo[r0 + tid] = (uint16_t)split_lo(__builtin_bit_cast(uint32_t, b));
         }
     };
-    // (chunks beyond the last unit multiply zeros and store nothing; leaving the loop at each of the three costs the compiler
+    // (chunks beyond the last unit multiply zeros and store nothing; leaving the loop at each of them costs the compiler
     // a copy of the accumulators per exit)
+
+    if (wave < 4) {
+        // update: input units 32 wave .. +31 of the strip, all samples in one chain; its activations stay in registers
+        const int cb = wave;
+        bf16x8 xf[KS];
+#pragma unroll
+        for (int k = 0; k < KS; ++k) xf[k] = frag_tr(X, XP, k * 16, cb * 32, lane);
+        auto chunk = [&](int set, int r0) __attribute__((always_inline)) {
+            stage(set, r0);
+            f32x16 g;
+#pragma unroll
+            for (int e = 0; e < 16; ++e) g[e] = 0.f;
+#pragma unroll
+            for (int k = 0; k < KS; ++k) g = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xf[k], frag_tr(Z, ZP, k * 16, 0, lane), g, 0, 0, 0);
+            // accumulator e: input unit 8 (e/4) + 4 (lane/32) + e%4 of the block, output unit lane%32
+            float* p = G + (lane & 31) * PP + cb * 32 + 4 * (lane >> 5);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) *(f32x4*)(p + 8 * q) = (f32x4){g[4 * q], g[4 * q + 1], g[4 * q + 2], g[4 * q + 3]};
+            if (cb == 0 && owns_bias(r0)) {
+                float sum = 0.f;
+#pragma unroll
+                for (int k = 0; k < KS; ++k) sum = column_sum16(frag_tr(Z, ZP, k * 16, 0, lane), sum);
+                if (lane < RC) GB[lane] = sum;
+            }
+            step(set, r0);
+        };
+        for (int r0 = 0; r0 < a.d_out; r0 += SETS * RC) {
+#pragma unroll
+            for (int s = 0; s < SETS; ++s) chunk(s, r0 + s * RC);
+        }
+        return;
+    }
+
+    // data gradient: input units 32 bc .. and samples 32 bs .. , CBW x SBW blocks
+    const int bc = (wave - 4) % (4 / CBW) * CBW, bs = (wave - 4) / (4 / CBW) * SBW;
+    f32x16 back[CHAINS][CBW][SBW];
+#pragma unroll
+    for (int h = 0; h < CHAINS; ++h)
+#pragma unroll
+        for (int c = 0; c < CBW; ++c)
+#pragma unroll
+            for (int s = 0; s < SBW; ++s)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) back[h][c][s][e] = 0.f;
+    auto chunk = [&](int set, int r0) __attribute__((always_inline)) {
+        stage(set, r0);
+        const int h = CHAINS == 2 ? set : 0;
+#pragma unroll
+        for (int k = 0; k < RC / 16; ++k) {
+            bf16x8 wf[CBW], zf[SBW];
+#pragma unroll
+            for (int c = 0; c < CBW; ++c) wf[c] = frag_tr(W, XP, k * 16, (bc + c) * 32, lane);
+#pragma unroll
+            for (int s = 0; s < SBW; ++s) zf[s] = *(const bf16x8*)(Z + ((bs + s) * 32 + (lane & 31)) * ZP + k * 16 + (lane >> 5) * 8);
+#pragma unroll
+            for (int c = 0; c < CBW; ++c)
+#pragma unroll
+                for (int s = 0; s < SBW; ++s)
+                    back[h][c][s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[c], zf[s], back[h][c][s], 0, 0, 0);
+        }
+        step(set, r0);
+    };
     for (int r0 = 0; r0 < a.d_out; r0 += SETS * RC) {
 #pragma unroll
         for (int s = 0; s < SETS; ++s) chunk(s, r0 + s * RC);
@@ -244,7 +270,7 @@ __global__ void __launch_bounds__(NT) strip_kernel(StripArgs a) {
 #pragma unroll
         for (int s = 0; s < SBW; ++s) {
             const int row = (bs + s) * 32 + (lane & 31);
-            const f32x16& d = back[cc][s];
+            const f32x16 d = CHAINS == 2 ? back[0][cc][s] + back[CHAINS - 1][cc][s] : back[0][cc][s];
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int cl = (bc + cc) * 32 + 8 * q + 4 * (lane >> 5);
@@ -258,21 +284,21 @@ __global__ void __launch_bounds__(NT) strip_kernel(StripArgs a) {
         }
 }
 
-template <int BT, bool STREAM>
+template <int BT, bool STREAM, int CHAINS>
 hipError_t launch(const StripArgs& a, hipStream_t st) {
     constexpr int SMEM = StripShape<BT>::SMEM;
     static_assert(SMEM <= 160 * 1024, "more LDS than a compute unit has");
     if (SMEM > 64 * 1024) {
-        static hipError_t raised = hipFuncSetAttribute((const void*)strip_kernel<BT, STREAM>,
+        static hipError_t raised = hipFuncSetAttribute((const void*)strip_kernel<BT, STREAM, CHAINS>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
         if (raised != hipSuccess) return raised;
     }
-    hipLaunchKernelGGL((strip_kernel<BT, STREAM>), dim3(a.padded), dim3(NT), SMEM, st, a);
+    hipLaunchKernelGGL((strip_kernel<BT, STREAM, CHAINS>), dim3(a.padded), dim3(NT), SMEM, st, a);
     return hipGetLastError();
 }
-template <int BT>
+template <int BT, int CHAINS>
 hipError_t launch_stream(const StripArgs& a, bool stream, hipStream_t st) {
-    return stream ? launch<BT, true>(a, st) : launch<BT, false>(a, st);
+    return stream ? launch<BT, true, CHAINS>(a, st) : launch<BT, false, CHAINS>(a, st);
 }
 
 }  // namespace
@@ -280,8 +306,9 @@ hipError_t launch_stream(const StripArgs& a, bool stream, hipStream_t st) {
 bool bf16_strip_ok(const LayerCall& c) {
     if (c.gather || !c.dz_prev || c.B > 256 || c.u || c.rows || c.partial || c.skip_bias || c.shared_w || c.d_in < 8 || c.ld_dz < 8) return false;
     // One workgroup per strip, so the strips have to fill the 256 compute units: at three quarters of the last round and more
-    // this is the faster one (192 strips of 1024 -> 1024, 128 samples: 54 against 64 us; 384: 97 / 103; 448: 107 / 121),
-    // below it is not (128: 50 / 42; 320: 95 / 93; 264 strips of 4104 -> 2056: 173 / 160).
+    // this is at least as fast (rounds of 256-1024-1024-1024-40, separate kernels against this one, us: 192 strips, 128 samples
+    // 936 / 881, 64 samples 769 / 760; 384 strips 1709 / 1708, 1470 / 1481; 448 of 64 1685 / 1582), below it is not (a layer: 128
+    // strips 42 / 50; 320: 93 / 95; 264 strips of 4104 -> 2056: 160 / 173).
     const long strips = (long)((c.d_in + SC - 1) / SC) * c.P, rounds = (strips + 255) / 256;
     return 4 * strips >= 3 * 256 * rounds;
 }
@@ -297,9 +324,13 @@ hipError_t bf16_strip(const LayerCall& c, hipStream_t st) {
     a.strips = (c.d_in + SC - 1) / SC;
     a.total = a.strips * c.P;
     a.padded = (a.total + 7) / 8 * 8;
-    if (c.B <= 64) return launch_stream<64>(a, !c.shadow_cached, st);
-    if (c.B <= 128) return launch_stream<128>(a, !c.shadow_cached, st);
-    return launch_stream<256>(a, !c.shadow_cached, st);
+    // where the separate data gradient would split its contraction (small launches, up to 128 samples), so does this one
+    const bool two = bf16_backward_splits(c.P, c.B, c.d_in, c.d_out);
+    const bool stream = !c.shadow_cached;
+    if (c.B <= 64) return two ? launch_stream<64, 2>(a, stream, st) : launch_stream<64, 1>(a, stream, st);
+    if (c.B <= 128) return two ? launch_stream<128, 2>(a, stream, st) : launch_stream<128, 1>(a, stream, st);
+    if (two) return hipErrorInvalidValue;                    // (never: 192 strips of more than 128 samples are 384 tiles)
+    return launch_stream<256, 1>(a, stream, st);
 }
 
 }  // namespace kavg

@@ -8,14 +8,19 @@
 // Workgroup = 64 output x 128 input units of one layer of one learner, four wavefronts of 32 x 64.  MFMA 32x32x16 bf16,
 // rows = input units, columns = output units, k = samples, both operands by transpose reads out of LDS in slices of 64
 // samples.  The master -- and the velocity -- are requested right after the first slice and arrive under the contraction;
-// the gradient passes through LDS so that a thread then holds eight consecutive columns of a row.
+// the gradient passes through LDS so that a thread then holds eight consecutive columns of a row.  A last layer of few
+// classes is stepped by workgroups of head_update.h.  Every sum is taken in the order of the one-layer kernels (gemm_bf16.hip,
+// head.hip): with the head as a matrix-core tile the same steps were up to 4 % faster and moved the results by half a per
+// cent of the block momentum within a round.
 //
 // Measured, all updates of a step, us (one launch per layer, the velocity read after the contraction -> this kernel):
-// 3072-1024-1024-10, 16 learners of 128 samples 80 + 31 + 9 -> 103 (5.3 TB/s); 3080-1032-520-24 with momentum, 5 learners of
-// 70: 84 + 19 + 8 -> 59 (5.0 TB/s); models of a few hundred units: 4 - 6 per layer -> 5 - 6 in all (a step 1.2 - 1.5x faster).  What bounds
+// 3072-1024-1024-10, 16 learners of 128 samples 79 + 31 + 9 -> 104 (5.3 TB/s); 3080-1032-520-24 with momentum, 5 learners of
+// 70: 84 + 27 -> 58 (5.2 TB/s); models of a few hundred units: 4 - 6 per layer -> 5 - 8 in all.  What bounds
 // it: the traffic of the planes on large models, latency on small ones.  Where the hi planes stream as well the one-layer
-// kernel and the head's are as fast (4096 wide, 32 learners: 630 against 595 + 23) and stay.
+// kernel is as fast (4096 wide, 32 learners: 630 against 595 + 23) and stays.
 #include "kavg_internal.h"
+#include "column_sum.h"
+#include "head_update.h"
 #include "loss_mean.h"
 #include "split.h"
 
@@ -34,8 +39,10 @@ constexpr int TR = 64, TC = 128, BK = 64;    // output units, input units, sampl
 constexpr int ZP = TR + 32, XP = TC + 32;    // LDS rows of the operands: 64 bytes of padding (transpose reads)
 constexpr int GP = TC + 4;                   // LDS rows of the gradient (fp32)
 constexpr int ZN = BK * TR / 8 / NT, XN = BK * TC / 8 / NT, WN = TR * TC / 8 / NT;
-constexpr int OPERANDS = BK * (ZP + XP) * 2, GRADIENT = TR * (GP + 1) * 4;
-constexpr int SMEM = OPERANDS > GRADIENT ? OPERANDS : GRADIENT;   // (the gradient lies over the operands)
+constexpr int OPERANDS = BK * (ZP + XP) * 2, GRADIENT = TR * GP * 4;
+constexpr int TILE_LDS = OPERANDS > GRADIENT ? OPERANDS : GRADIENT;    // (the gradient lies over the operands)
+constexpr int SMEM = TILE_LDS > HEAD_LDS ? TILE_LDS : HEAD_LDS;
+static_assert(HEAD_PIECES * 8 == TC, "a workgroup of the head takes as many input units as a tile");
 constexpr int GROUP = 8;                     // layers per launch
 
 struct Layer {
@@ -44,10 +51,12 @@ struct Layer {
     const int32_t* gather; const int32_t* next_gather; long gather_lstride;       // (this step's and the next's)
     uint16_t* hi; uint16_t* lo; uint16_t* bhi; uint16_t* blo; float* u; float* ub;
     int d_out, d_in, tiles_r, tiles_c, total, padded;
+    int head;                                // head_step (tiles_r: groups of classes)
 };
 struct Args {
     Layer layer[GROUP];
     int n_layers, B;
+    int head_every;                          // > 0: layer 0 is the head, its workgroups (latency, hardly any traffic) are spread over the launch
     size_t lstride;                          // between learners, in planes and velocities
     float lr, beta;
     LossMeans losses;                        // n > 0: computed by the workgroups behind those of the layers, four each
@@ -73,10 +82,16 @@ __global__ void __launch_bounds__(NT, 2) update_group_kernel(Args a) {
     uint16_t* const Z = (uint16_t*)smem;                     // [BK][ZP] dZ
     uint16_t* const X = Z + BK * ZP;                         // [BK][XP] activations
     float* const G = (float*)smem;                           // [TR][GP] gradient
-    float* const GB = G + TR * GP;                           // [TR] column sums of dZ
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int g = blockIdx.x, li = 0;
-    while (li + 1 < a.n_layers && g >= a.layer[li].padded) g -= a.layer[li++].padded;
+    bool head = false;
+    if (a.head_every) {                                      // layer 0 is the head: one octet of workgroups in head_every
+        const int octet = g >> 3, t = octet / a.head_every, heads = a.layer[0].padded >> 3;
+        head = t < heads && octet - t * a.head_every == a.head_every - 1;
+        g = head ? t * 8 + (g & 7) : g - min(t, heads) * 8;
+        li = head ? 0 : 1;
+    }
+    while (!head && li + 1 < a.n_layers && g >= a.layer[li].padded) g -= a.layer[li++].padded;
     const Layer& q = a.layer[li];
     if (g >= q.padded) {
         const int r = (g - q.padded) * 4 + wave;
@@ -88,6 +103,16 @@ __global__ void __launch_bounds__(NT, 2) update_group_kernel(Args a) {
     if (at >= q.total) return;
     const int rt = at % q.tiles_r; at /= q.tiles_r;
     const int ct = at % q.tiles_c, learner = at / q.tiles_c;
+    if (q.head) {
+        HeadStep h = {};
+        h.act = q.in; h.ld_act = q.ld_in; h.act_lstride = q.in_lstride; h.gather = q.gather; h.gather_lstride = q.gather_lstride;
+        h.dz = q.dz; h.ldz = q.ld_dz; h.dz_lstride = q.dz_lstride;
+        h.whi = q.hi; h.wlo = q.lo; h.bhi = q.bhi; h.blo = q.blo; h.lstride = a.lstride;
+        if (MOMENTUM) { h.u = q.u; h.ub = q.ub; h.beta = a.beta; }
+        h.B = a.B; h.d = q.d_in; h.C = q.d_out; h.lr = a.lr;
+        head_step(h, ct, q.tiles_r > 1 ? rt : -1, learner, (float*)smem);
+        return;
+    }
     const int r0 = rt * TR, c0 = ct * TC, B = a.B;
     const uint16_t* dz = q.dz + (size_t)learner * q.dz_lstride;
     const uint16_t* in = q.in + (size_t)learner * q.in_lstride;
@@ -146,13 +171,11 @@ __global__ void __launch_bounds__(NT, 2) update_group_kernel(Args a) {
     }
 
     const int rb = wave >> 1, cb = (wave & 1) * 2;           // 32 output units, two blocks of 32 input units
-    const bool bias = ct == 0 && cb == 0;                    // (uniform) this wavefront sums dZ as well: its product with ones
-    f32x16 acc[2], gb;
-    bf16x8 ones;
+    const bool bias = ct == 0 && cb == 0;                    // (uniform) this wavefront sums dZ as well: unit rb*32 + lane%32
+    float bsum = 0.f;
+    f32x16 acc[2];
 #pragma unroll
-    for (int e = 0; e < 16; ++e) { acc[0][e] = 0.f; acc[1][e] = 0.f; gb[e] = 0.f; }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) ones[e] = (__bf16)1.0f;
+    for (int e = 0; e < 16; ++e) { acc[0][e] = 0.f; acc[1][e] = 0.f; }
     auto contract = [&]() __attribute__((always_inline)) {
 #pragma unroll
         for (int k = 0; k < BK / 16; ++k) {
@@ -163,7 +186,7 @@ __global__ void __launch_bounds__(NT, 2) update_group_kernel(Args a) {
         }
         if (bias) {
 #pragma unroll
-            for (int k = 0; k < BK / 16; ++k) gb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ones, frag_tr(Z, ZP, k * 16, rb * 32, lane), gb, 0, 0, 0);
+            for (int k = 0; k < BK / 16; ++k) bsum = column_sum16(frag_tr(Z, ZP, k * 16, rb * 32, lane), bsum);
         }
     };
     // the first slice outside the loop: its waits leave the master in flight
@@ -186,7 +209,6 @@ __global__ void __launch_bounds__(NT, 2) update_group_kernel(Args a) {
         for (int t = 0; t < 4; ++t)
             *(f32x4*)(G + (rb * 32 + (lane & 31)) * GP + (cb + j) * 32 + 8 * t + 4 * (lane >> 5)) =
                 (f32x4){acc[j][4 * t], acc[j][4 * t + 1], acc[j][4 * t + 2], acc[j][4 * t + 3]};
-    if (bias && lane < 32) GB[rb * 32 + lane] = gb[0];       // (every row holds the same sums)
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < WN; ++i) {
@@ -210,11 +232,10 @@ __global__ void __launch_bounds__(NT, 2) update_group_kernel(Args a) {
             if constexpr (MOMENTUM) { put<STREAM>((f32x4*)(q.u + p), g0); put<STREAM>((f32x4*)(q.u + p + 4), g1); }
         }
     }
-    if (ct == 0 && tid < TR && r0 + tid < q.d_out) {
-        const size_t p = lat + r0 + tid;
-        float gsum = GB[tid];
-        if constexpr (MOMENTUM) { gsum = a.beta * q.ub[p] + gsum; q.ub[p] = gsum; }
-        const float b = __builtin_bit_cast(float, split_join(q.bhi[p], q.blo[p])) - a.lr * gsum;
+    if (bias && lane < 32 && r0 + rb * 32 + lane < q.d_out) {
+        const size_t p = lat + r0 + rb * 32 + lane;
+        if constexpr (MOMENTUM) { bsum = a.beta * q.ub[p] + bsum; q.ub[p] = bsum; }
+        const float b = __builtin_bit_cast(float, split_join(q.bhi[p], q.blo[p])) - a.lr * bsum;
         q.bhi[p] = (uint16_t)split_hi(__builtin_bit_cast(uint32_t, b));
         q.blo[p] = (uint16_t)split_lo(__builtin_bit_cast(uint32_t, b));
     }
@@ -250,11 +271,15 @@ hipError_t bf16_update_group(const LayerCall* calls, int n, const LossMeans* los
             q.gather = c.gather; q.next_gather = c.gather ? c.next_gather : nullptr; q.gather_lstride = c.gather_stride;
             q.hi = c.ws; q.lo = c.wlo; q.bhi = c.bhi; q.blo = c.blo; q.u = c.u; q.ub = c.ub;
             q.d_out = c.d_out; q.d_in = c.d_in;
-            q.tiles_r = (c.d_out + TR - 1) / TR; q.tiles_c = (c.d_in + TC - 1) / TC;
+            q.head = c.head;
+            q.tiles_r = c.head ? head_class_groups(c.P, c.d_in, c.d_out) : (c.d_out + TR - 1) / TR; q.tiles_c = (c.d_in + TC - 1) / TC;
             q.total = q.tiles_r * q.tiles_c * c.P;
             q.padded = (q.total + 7) / 8 * 8;
             wgs += q.padded;
         }
+        // Long launches spread the head's workgroups, which fetch little and wait much (3072-1024-1024-10, 16 learners: a round 1.5 %
+        // faster than with the head in front); in short ones the head would be the tail.
+        if (a.n_layers > 1 && a.layer[0].head && wgs >= 9 * a.layer[0].padded) a.head_every = wgs / a.layer[0].padded;
         if (losses && at + a.n_layers == n) {
             a.losses = *losses;
             wgs += (losses->n + 3) / 4;
