@@ -84,7 +84,7 @@ def class_model(w, learner_momentum=False, strips=False):
     return by, fl
 
 
-KERNEL_SOURCES = ("gemm_bf16.hip", "strip_bf16.hip", "update_bf16.hip", "meta_update.hip", "head.hip", "head_update.h", "sampling_loss.hip", "split.h", "kavg_internal.h")
+KERNEL_SOURCES = ("gemm_bf16.hip", "strip_bf16.hip", "update_bf16.hip", "meta_update.hip", "head.hip", "head_update.h", "column_sum.h", "sampling_loss.hip", "split.h", "kavg_internal.h")
 
 
 def source_digest():

@@ -90,11 +90,12 @@ template <int BT, bool STREAM, int CHAINS>
 __global__ void __launch_bounds__(NT) strip_kernel(StripArgs a) {
     typedef StripShape<BT> SH;
     constexpr int ZN = SH::ZN, KS = BT / 16;                 // slabs of 16 samples
-    // Chunks in registers, the one at hand and those requested ahead.  (Three: 70 against 66 us with 1024 -> 1024, 32 learners
-    // of 128 samples, and no registers left for the accumulators with 256; with 64 samples three are 58 against 59 us where
-    // the planes stay cached, and cost the second workgroup per compute unit, 0.3 % of a round, where they stream.)
-    constexpr int SETS = BT == 64 && !STREAM && CHAINS == 1 ? 3 : 2;
-    static_assert(CHAINS == 1 || SETS == 2, "a chunk's set is its parity");
+    // Chunks in registers, the one at hand and those requested ahead.  More than 64 samples: a third is slower (70 against 66 us
+    // with 1024 -> 1024, 32 learners of 128) or has no registers left beside the accumulators.  64: two where a second
+    // workgroup per compute unit counts for more (planes that stream: 0.3 % of a round), else three (58 against 59 us); with
+    // two chains there are hardly more strips than compute units, and four are 1 - 2 % of a round faster than two.
+    constexpr int SETS = BT > 64 ? 2 : CHAINS == 2 ? 4 : STREAM ? 2 : 3;
+    static_assert(CHAINS == 1 || SETS % 2 == 0, "a chunk's set has its parity");
     // blocks of a wavefront's data gradient: input units x samples
     constexpr int CBW = BT == 64 ? 1 : 2, SBW = BT / 32 / CBW;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -243,7 +244,7 @@ __global__ void __launch_bounds__(NT) strip_kernel(StripArgs a) {
                 for (int e = 0; e < 16; ++e) back[h][c][s][e] = 0.f;
     auto chunk = [&](int set, int r0) __attribute__((always_inline)) {
         stage(set, r0);
-        const int h = CHAINS == 2 ? set : 0;
+        const int h = CHAINS == 2 ? set & 1 : 0;
 #pragma unroll
         for (int k = 0; k < RC / 16; ++k) {
             bf16x8 wf[CBW], zf[SBW];
