@@ -149,8 +149,8 @@ pool_backward_kernel(const uint16_t* __restrict__ dpool, const uint16_t* __restr
 
 // W[j][e] -= lr * sum_s partial[(j*S+s)][e]  and  b[j][r] -= lr * sum_s pbias[(j*S+s)][r]  on the master's planes, for several
 // convolutions: adds up the S partial gradients of an element (eight requested together, added in ascending order).  One
-// launch for all layers of a step: with one launch each and one partial sum requested at a time it took 14 us per layer on
-// 28x28 images with channels 8-32-64, now 10.5 us for both.
+// launch for all layers whose partial sums lie side by side in the workspace: with one launch each and one partial sum
+// requested at a time it took 14 us per layer on 28x28 images with channels 8-32-64, now 10.5 us for both.
 constexpr int STEP_GROUP = 8;
 struct StepArgs { ConvStep layer[STEP_GROUP]; int n; size_t lstride; float lr; };
 

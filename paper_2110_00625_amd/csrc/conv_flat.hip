@@ -25,8 +25,8 @@
 // Measured on 28x28 images, channels 8-32-64, 8 learners of 32 images (us per launch; before: the generic kernel on an
 // implicit patch matrix, the first layer on a written one): forward 15 + 17 -> 11 (first layer) and 27 -> 19, data gradient
 // 37 and a rotated weight copy -> 22, weight gradient 17 -> 12 and 49 -> 33 (conv_flat_wgrad.hip), a round of four steps
-// 980 -> 605 (552 with one launch for the SGD steps of all layers).  At 64 -> 128 channels (32x32, 700 TFLOP/s) 17.6 k of a workgroup's 34 k cycles are the contraction, 6.8 k
-// bring in pixels, 9.4 k write the outputs; the clock stands near 1.6 GHz.
+// 980 -> 605 (555 with one launch for the SGD steps of all layers).  At 64 -> 128 channels (32x32, 700 TFLOP/s) 17.6 k of a
+// workgroup's 34 k cycles are the contraction, 6.8 k bring in pixels, 9.4 k write the outputs; the clock stands near 1.6 GHz.
 #include "kavg_internal.h"
 #include "conv_flat.h"
 #include "conv_pool.h"
