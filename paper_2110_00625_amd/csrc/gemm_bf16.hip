@@ -1063,6 +1063,7 @@ hipError_t bf16_forward(const LayerCall& c, hipStream_t st) {
     return launch_tiled<MODE_FWD, false, false>(a, c.P, pick_tile(MODE_FWD, a.nR, a.nC, a.nK, c.P), st);
 }
 
+bool bf16_forward_splits(int P, int B, int d_in, int d_out) { return pick_tile(MODE_FWD, B, d_out, d_in, P) == T64x64_K2; }
 bool bf16_backward_splits(int P, int B, int d_in, int d_out) { return pick_tile(MODE_BWD, B, d_in, d_out, P) == T64x64_K2; }
 
 hipError_t bf16_backward_data(const LayerCall& c, hipStream_t st) {

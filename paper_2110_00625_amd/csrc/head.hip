@@ -21,6 +21,7 @@
 #include "kavg_internal.h"
 #include "head_update.h"
 #include "split.h"
+#include "wave_sum.h"
 
 namespace kavg {
 
@@ -30,26 +31,6 @@ constexpr int CMAX = 16;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// Data-parallel-primitive moves inside a row of 16 lanes: no LDS round trip, unlike a general shuffle.
-template <int CTRL>
-__device__ __forceinline__ float dpp_move(float x) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
-}
-// Sum over the 64 lanes, the same value in every lane.  Inside a row: neighbours, pairs, mirrored halves,
-// mirrored row (every lane then holds its row's sum); across the four rows: their last lanes are read
-// as scalars and added in a fixed order.
-__device__ __forceinline__ float wave_sum(float x) {
-    x += dpp_move<0xB1>(x);        // quad_perm [1,0,3,2]
-    x += dpp_move<0x4E>(x);        // quad_perm [2,3,0,1]
-    x += dpp_move<0x141>(x);       // row_half_mirror
-    x += dpp_move<0x140>(x);       // row_mirror
-    const int xi = __builtin_bit_cast(int, x);
-    const float r0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(xi, 15));
-    const float r1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(xi, 31));
-    const float r2 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(xi, 47));
-    const float r3 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(xi, 63));
-    return (r0 + r1) + (r2 + r3);
-}
 __device__ __forceinline__ uint16_t bf16_bits(float x) {
     __bf16 h = (__bf16)x;                         // round to nearest even
     return __builtin_bit_cast(uint16_t, h);
@@ -176,7 +157,7 @@ __global__ void __launch_bounds__(256) head_forward_backward_kernel(HeadArgs a) 
     float mx = -INFINITY;
 #pragma unroll
     for (int c = 0; c < CT; ++c) {
-        acc[c] = wave_sum(acc[c]) + bias_c[c];
+        acc[c] = dpp_wave_sum(acc[c]) + bias_c[c];
         if (c < a.C) mx = fmaxf(mx, acc[c]);
     }
     float sum = 0.f;

@@ -18,6 +18,7 @@
 #include "conv_direct.h"
 #include "conv_flat.h"
 #include "conv_first.h"
+#include "chain_bf16.h"
 #include "split.h"
 
 using namespace kavg;
@@ -831,6 +832,21 @@ int issue_update_group(kavg_ctx* c, const std::vector<LayerCall>& group, bool he
     return KAVG_OK;
 }
 
+// The layers above `from` of a small bf16 MLP, from their forward pass to their data gradients, as one launch.  While one of
+// its classes is profiled they run as separate launches.
+int chained_layers(const kavg_ctx* c) {
+    const unsigned apart = (1u << KAVG_CLASS_FORWARD) | (1u << KAVG_CLASS_BACKWARD) | (1u << KAVG_CLASS_HEAD) | (1u << KAVG_CLASS_LOSS);
+    if (c->dtype != KAVG_BF16 || (c->prof_mask & apart)) return 0;
+    return chain_layers(c->P, c->B, c->L, c->dims.data(), !c->cv.ch.empty());
+}
+int issue_chain(kavg_ctx* c, int from, int k) {
+    LayerCall calls[CHAIN_LAYERS];
+    for (int l = from + 1; l <= c->L; ++l) calls[l - from - 1] = layer_call(c, l, k);
+    KAVG_HIP(c, bf16_chain(calls, c->L - from, c->y, c->idx() + (size_t)k * c->B, (long)c->K * c->B, c->rowloss() + (size_t)k * c->P * c->B,
+                           c->stream));
+    return KAVG_OK;
+}
+
 int issue_steps(kavg_ctx* c) {
     if (!c->cv.ch.empty()) return issue_steps_conv(c);
     if (c->refresh > 1) return issue_steps_deferred(c);
@@ -841,16 +857,20 @@ int issue_steps(kavg_ctx* c) {
     // With few classes the last layer runs as two dedicated kernels (forward + loss + data gradient,
     // then its update) instead of four generic launches.
     const bool head = head_supported(c->dims[L]);
+    const int chained = chained_layers(c), below = L - chained;          // layers 1 .. below run one by one
     for (int k = 0; k < c->K; ++k) {
         const int32_t* idx_k = c->idx() + (size_t)k * c->B;
         const long idx_ls = (long)c->K * c->B;
         float* rowloss_k = c->rowloss() + (size_t)k * c->P * c->B;
-        for (int l = 1; l <= (head ? L - 1 : L); ++l) {      // forward
+        for (int l = 1; l <= (head && !chained ? L - 1 : below); ++l) {      // forward
             LayerCall q = layer_call(c, l, k);
             Bracket br(c, KAVG_CLASS_FORWARD);
             KAVG_HIP(c, bf ? bf16_forward(q, st) : f32_forward(q, st));
         }
-        if (head) {
+        if (chained) {
+            const int rc = issue_chain(c, below, k);
+            if (rc != KAVG_OK) return rc;
+        } else if (head) {
             LayerCall q = layer_call(c, L, k);
             Bracket br(c, KAVG_CLASS_HEAD);
             KAVG_HIP(c, head_forward_backward(q, c->y, idx_k, idx_ls, rowloss_k, bf ? 1 : 0, st));
@@ -878,7 +898,7 @@ int issue_steps(kavg_ctx* c) {
         std::vector<LayerCall> group;                        // updates that run as one launch after the backward pass
         for (int l = L; l >= 1; --l) {                       // backward; W_l is read before it is updated
             LayerCall q = layer_call(c, l, k);
-            if (!(head && l == L)) {
+            if (l <= below && !(head && l == L)) {
                 if (bf16_strip_ok(q)) {                      // data gradient and update in one pass over the weights
                     Bracket br(c, KAVG_CLASS_UPDATE);
                     KAVG_HIP(c, bf16_strip(q, st));
@@ -1004,6 +1024,7 @@ int issue_steps_conv(kavg_ctx* c) {
         packed = packed || q.fwd || q.bwd;
         pack.push_back(q);
     }
+    const int chained = chained_layers(c), below = L - chained;          // layers 1 .. below of the MLP run one by one
     for (int k = 0; k < c->K; ++k) {
         const int32_t* idx_k = c->idx() + (size_t)k * B;
         const long idx_ls = (long)c->K * B;
@@ -1039,11 +1060,14 @@ int issue_steps_conv(kavg_ctx* c) {
             Bracket br(c, KAVG_CLASS_FORWARD);
             KAVG_HIP(c, launch_pool_forward(c->ws + lo.off_cact[M - 1], c->ws + lo.off_pool, P, B, H * W, cv.ch[M], st));
         }
-        for (int l = 1; l <= (head ? L - 1 : L); ++l) {             // MLP, forward
+        for (int l = 1; l <= (head && !chained ? L - 1 : below); ++l) {             // MLP, forward
             Bracket br(c, KAVG_CLASS_FORWARD);
             KAVG_HIP(c, bf16_forward(layer_call(c, l, k), st));
         }
-        if (head) {
+        if (chained) {
+            const int rc = issue_chain(c, below, k);
+            if (rc != KAVG_OK) return rc;
+        } else if (head) {
             Bracket br(c, KAVG_CLASS_HEAD);
             KAVG_HIP(c, head_forward_backward(layer_call(c, L, k), c->y, idx_k, idx_ls, rowloss_k, 1, st));
         } else {
@@ -1054,7 +1078,7 @@ int issue_steps_conv(kavg_ctx* c) {
         std::vector<LayerCall> group;                               // updates that run as one launch after the backward pass
         for (int l = L; l >= 1; --l) {                              // MLP, backward; layer 1 hands dL/d(pooled) on
             LayerCall q = layer_call(c, l, k);
-            if (!(head && l == L)) {
+            if (l <= below && !(head && l == L)) {
                 Bracket br(c, KAVG_CLASS_BACKWARD);
                 KAVG_HIP(c, bf16_backward_data(q, st));
             }

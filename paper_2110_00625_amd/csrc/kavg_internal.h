@@ -129,6 +129,7 @@ hipError_t f32_update(const LayerCall* layers, int n, const LossMeans* losses, h
 hipError_t bf16_forward(const LayerCall& c, hipStream_t st);
 hipError_t bf16_backward_data(const LayerCall& c, hipStream_t st);
 hipError_t bf16_update(const LayerCall& c, hipStream_t st);
+bool bf16_forward_splits(int P, int B, int d_in, int d_out);         // bf16_forward sums every 128 inputs in two halves, joined at the end
 bool bf16_backward_splits(int P, int B, int d_in, int d_out);        // bf16_backward_data sums every 64 units in two halves, joined at the end
 // data gradient and update of a layer in one pass over its weights (strip_bf16.hip); which calls it takes
 bool bf16_strip_ok(const LayerCall& c);
