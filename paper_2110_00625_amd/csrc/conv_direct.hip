@@ -65,8 +65,9 @@ struct DirectArgs {
     const uint16_t* act;                                 // data gradient: activations of the layer below (CN channels, same strides as out)
     uint16_t* out; size_t out_lstride;
     int H, tiles;                                        // tiles (of 8 rows) per learner
-    // data gradient of the last convolution: dpool != null means `in` holds that layer's activations and the
-    // gradient images are formed from them and dpool[learner][image][c_k] while loading (conv_pool.h)
+    // data gradient of the last convolution: dpool != null means the gradient images are formed from the bits that its
+    // forward pass left and dpool[learner][image][c_k] while loading (conv_pool.h)
+    const uint8_t* bits; size_t bits_lstride; int bits_pitch;        // bytes
     const uint16_t* dpool; size_t dpool_lstride; float inv;
 };
 
@@ -85,7 +86,7 @@ __device__ __forceinline__ bf16x8 frag_tr(const uint16_t* tile, int pitch, int r
     return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-// POOL (data gradient only): the gradient images are formed from activations and dpool while the tile is loaded
+// POOL (data gradient only): the gradient images are formed from bits and dpool while the tile is loaded
 template <int CK, int CN, bool BWD, bool POOL = false>
 __global__ void __launch_bounds__(NT, 4) conv_direct_kernel(DirectArgs a) {
     typedef DirectShape<CK, CN, BWD> SH;
@@ -141,14 +142,10 @@ __global__ void __launch_bounds__(NT, 4) conv_direct_kernel(DirectArgs a) {
     };
     // the tile's rows row0 - 1 .. row0 + 8 of channel group g: global -> registers -> LDS
     auto load_tile = [&](int g) {
-        u32x4 v[SH::INN], gp[POOL ? SH::INN : 1];
-        if constexpr (POOL) {                    // requested first, all at once
-#pragma unroll
-            for (int i = 0; i < SH::INN; ++i) {
-                const int e = min(tid + NT * i, SH::IN_PIECES - 1);
-                gp[i] = *(const u32x4*)(a.dpool + (size_t)learner * a.dpool_lstride + (size_t)b * a.c_k + g * CK + (e % (CK / 8)) * 8);
-            }
-        }
+        u32x4 v[SH::INN], gp;
+        uint8_t bt[POOL ? SH::INN : 1];
+        static_assert(NT % (CK / 8) == 0, "a thread's pieces are the same channels of their pixels");
+        if constexpr (POOL) gp = *(const u32x4*)(a.dpool + (size_t)learner * a.dpool_lstride + (size_t)b * a.c_k + g * CK + (tid % (CK / 8)) * 8);
 #pragma unroll
         for (int i = 0; i < SH::INN; ++i) {
             const int e = min(tid + NT * i, SH::IN_PIECES - 1);
@@ -156,13 +153,18 @@ __global__ void __launch_bounds__(NT, 4) conv_direct_kernel(DirectArgs a) {
             const int px = rest / (CK / 8), ch8 = rest - px * (CK / 8);
             const int h = row0 - 1 + row;
             const bool ok = h >= 0 && h < H;
-            const u32x4 x = *(const u32x4*)(in + ((size_t)(ok ? h : row0) * IMG_W + px) * a.c_k + g * CK + ch8 * 8);
             const u32x4 zero = {0u, 0u, 0u, 0u};
-            v[i] = ok ? x : zero;                // (zero activations give a zero gradient below)
+            if constexpr (POOL) {
+                const uint8_t m = a.bits[(size_t)learner * a.bits_lstride + (((size_t)b * H + (ok ? h : row0)) * IMG_W + px) * a.bits_pitch + g * (CK / 8) + ch8];
+                bt[i] = ok ? m : (uint8_t)0;
+            } else {
+                const u32x4 x = *(const u32x4*)(in + ((size_t)(ok ? h : row0) * IMG_W + px) * a.c_k + g * CK + ch8 * 8);
+                v[i] = ok ? x : zero;
+            }
         }
         if constexpr (POOL) {
 #pragma unroll
-            for (int i = 0; i < SH::INN; ++i) v[i] = pool_grad_piece(v[i], gp[i], a.inv);
+            for (int i = 0; i < SH::INN; ++i) v[i] = pool_grad_bits(bt[i], gp, a.inv);
         }
 #pragma unroll
         for (int i = 0; i < SH::INN; ++i) {
@@ -310,8 +312,9 @@ hipError_t conv_direct_backward_data(const ConvCall& c, const void* dpool, hipSt
     if (!shape_ok(c) || !conv_direct_ok(c.H, c.W, c.c_in, c.c_out, true)) return hipErrorInvalidValue;
     const size_t rows = (size_t)c.B * c.H * c.W;
     DirectArgs a = {};
-    if (dpool && !c.out) return hipErrorInvalidValue;
-    a.in = (const uint16_t*)(dpool ? c.out : c.dz); a.in_lstride = rows * c.c_out; a.c_k = c.c_out;
+    if (dpool && !c.bits) return hipErrorInvalidValue;
+    a.bits = (const uint8_t*)c.bits; a.bits_pitch = conv_bits_pitch(c.c_out) * 4; a.bits_lstride = rows * a.bits_pitch;
+    a.in = (const uint16_t*)c.dz; a.in_lstride = rows * c.c_out; a.c_k = c.c_out;
     a.dpool = (const uint16_t*)dpool; a.dpool_lstride = (size_t)c.B * c.c_out; a.inv = 1.0f / (float)(c.H * c.W);
     a.w = c.ws; a.w_lstride = c.ws_stride;
     a.act = (const uint16_t*)c.in;

@@ -27,12 +27,18 @@ struct PackLayer {
 };
 hipError_t launch_pack_weights(const PackLayer* layers, int n, size_t w_lstride, int P, hipStream_t st);
 
-// c.out = relu(conv(c.in, W) + b); gather != null: the images are rows gather[learner * gstride + n] of the data set X
+// Partial sums over the positions (ConvCall::pool_sums): places of images, of `channels` floats each, per 128 positions;
+// elements in all; 0: images too small.  pooled[P][B][c] = bf16(mean) out of them.
+int conv_pool_slots(int H, int W);
+size_t conv_pool_elems(int P, int B, int H, int W, const FlatPlan& plan);
+hipError_t launch_pool_finish(const float* sums, const FlatPlan& plan, void* pooled, int P, int B, int H, int W, int c, hipStream_t st);
+
+// c.out = relu(conv(c.in, W) + b), or c.bits and c.pool_sums; gather != null: the images are rows gather[learner * gstride + n] of the data set X
 hipError_t conv_flat_forward(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag, const int32_t* table, const void* X, const int32_t* gather,
                              long gstride, hipStream_t st);
 // c.dz_in = [c.in > 0] * (transposed convolution of c.dz with W).  dpool != null (the last convolution, below the
-// mean over the positions): c.dz is not read; the gradient images are formed while loading from the layer's own
-// activations c.out and dpool [P][B][c_out], as pool_backward_kernel would.
+// mean over the positions): c.dz is not read; the gradient images are formed while loading from c.bits and
+// dpool [P][B][c_out], as pool_backward_kernel would.
 hipError_t conv_flat_backward_data(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag, const int32_t* table, const void* dpool,
                                    hipStream_t st);
 

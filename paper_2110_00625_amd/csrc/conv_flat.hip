@@ -27,6 +27,12 @@
 // 37 and a rotated weight copy -> 22, weight gradient 17 -> 12 and 49 -> 33 (conv_flat_wgrad.hip), a round of four steps
 // 980 -> 605 (555 with one launch for the SGD steps of all layers).  At 64 -> 128 channels (32x32, 700 TFLOP/s) 17.6 k of a
 // workgroup's 34 k cycles are the contraction, 6.8 k bring in pixels, 9.4 k write the outputs; the clock stands near 1.6 GHz.
+//
+// The last convolution, below the mean over the positions, writes no activations: what is read of them afterwards is their
+// ReLU mask, one bit each, and their sums.  The sums of an image are a product with ones out of the epilogue's patch, 128
+// positions at a time, joined in ascending order (pool_finish_kernel).  16 learners of 64 images of 32x32, channels
+// 8-32-64-128: 268 MB of activations were written once and read three times; without them the mean takes 5 us instead of 47 and
+// the data gradient 184 instead of 203, a round 6.92 -> 6.28 ms; one convolution on 60x32 images 141 -> 97 us, 28x28 536 -> 514.
 #include "kavg_internal.h"
 #include "conv_flat.h"
 #include "conv_pool.h"
@@ -59,7 +65,9 @@ struct FlatArgs {
     const int32_t* table; int table_len;                 // pixel of position i - W - 2
     uint32_t div_hw_m; int div_hw_s;
     int tiles, total, padded;                            // tiles per learner; workgroups
-    const uint16_t* dpool; size_t dpool_lstride; float inv;          // BWD_POOL: `in` holds activations
+    const uint16_t* dpool; size_t dpool_lstride; float inv;          // BWD_POOL: gradients from the bits and these
+    uint32_t* bits; int bits_pitch; size_t bits_lstride;             // words per pixel; LAST: written, BWD_POOL: read
+    float* sums; int slots, image;                                   // LAST: places of images per 128 positions; positions of an image
 };
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
@@ -68,12 +76,24 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){lo, hi}, bf16x2));      // round to nearest even
 }
 
+// fragment of a [position][channel] patch by transpose reads: lane l receives channel x0 + l%32 at positions 8 (l/32) .. +7
+__device__ __forceinline__ bf16x8 frag_tr(const uint16_t* patch, int pitch, int x0, int lane) {
+    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    typedef bf16x4 __attribute__((address_space(3))) * lds_ptr;
+    const int t = lane & 15, grp = lane >> 4;
+    const uint16_t* p = patch + ((grp >> 1) * 8 + (t >> 2)) * pitch + x0 + (grp & 1) * 16 + (t & 3) * 4;
+    const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr)p);
+    const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr)(p + 4 * pitch));
+    return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
 // bytes of the pixels of a tile, which the output patches of the four wavefronts lie over
 __host__ __device__ constexpr int tile_area(int n_px, int CK, int NB) {
     return n_px * (CK + 8) * 2 > 4 * 32 * (NB * 32 + 8) * 2 ? n_px * (CK + 8) * 2 : 4 * 32 * (NB * 32 + 8) * 2;
 }
 
-template <int CK, int NB, int PWAVES, int KIND>
+// LAST (forward): the layer below the mean over the positions; bits and partial sums instead of activations
+template <int CK, int NB, int PWAVES, int KIND, bool LAST>
 __global__ void __launch_bounds__(NT, 2) conv_flat_kernel(FlatArgs a) {
     constexpr int IP = CK + 8;                            // LDS pixel: its channels plus 16 bytes
     constexpr int TP = PWAVES * PB * 32, SL = CK / 16, C8 = CK / 8;
@@ -85,6 +105,7 @@ __global__ void __launch_bounds__(NT, 2) conv_flat_kernel(FlatArgs a) {
     typedef typename std::conditional<KIND == FWD_GATHER, int64_t, int2>::type Source;
     Source* const SRC = (Source*)(smem + tile_area(n_px, CK, NB));      // where a pixel lies: int2 (pixel, image) or pixel of the data set; -1: margin
     float* const BIAS = (float*)(SRC + n_px);
+    uint8_t* const SLOT = (uint8_t*)(BIAS + 128);         // LAST: place of a position's image among those of its wavefront; 255: margin
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int pw = wave % PWAVES, cw = wave / PWAVES;
     // workgroup g runs on XCD g mod 8: each XCD gets one contiguous range of (learner, tile)
@@ -112,6 +133,13 @@ __global__ void __launch_bounds__(NT, 2) conv_flat_kernel(FlatArgs a) {
         else
             SRC[i] = make_int2(px, n);
     }
+    if constexpr (LAST) {
+        for (int p = tid; p < TP; p += NT) {
+            const int px = a.table[min(q0 + p + pitch + 1, a.table_len - 1)];
+            const int first = (q0 + (p & ~(PB * 32 - 1))) / a.image;
+            SLOT[p] = px < 0 ? 255 : (uint8_t)((int)fastdiv((uint32_t)px, a.div_hw_m, a.div_hw_s) - first);
+        }
+    }
     if constexpr (!BACK) {
         for (int i = tid; i < 128; i += NT) {
             const size_t at_b = (size_t)learner * a.b_lstride + min(i, a.c_n - 1);
@@ -123,9 +151,10 @@ __global__ void __launch_bounds__(NT, 2) conv_flat_kernel(FlatArgs a) {
     // all pixels of channel group g: every request of a thread is in flight before the first is waited for
     const int pieces = n_px * C8;
     auto load_tile = [&](int g) __attribute__((always_inline)) {
-        constexpr int ALL = ((TP + 132) * C8 + NT - 1) / NT, MAX = KIND == BWD_POOL ? 6 : 11, N = ALL < MAX ? ALL : MAX;
+        constexpr int ALL = ((TP + 132) * C8 + NT - 1) / NT, MAX = KIND == BWD_POOL ? 8 : 11, N = ALL < MAX ? ALL : MAX;
         for (int e0 = tid; e0 < pieces; e0 += NT * N) {
-            u32x4 v[N], gp[KIND == BWD_POOL ? N : 1];
+            u32x4 v[KIND == BWD_POOL ? 1 : N], gp[KIND == BWD_POOL ? N : 1];
+            uint8_t bt[KIND == BWD_POOL ? N : 1];
             unsigned ok = 0;
 #pragma unroll
             for (int i = 0; i < N; ++i) {
@@ -136,16 +165,20 @@ __global__ void __launch_bounds__(NT, 2) conv_flat_kernel(FlatArgs a) {
                 if constexpr (KIND == FWD_GATHER) px = src; else px = src.x;
                 const bool in_ok = px >= 0 && ch < a.c_k;
                 if (in_ok) ok |= 1u << i;
-                v[i] = *(const u32x4*)(in + (in_ok ? px * a.c_k + ch : 0));
-                if constexpr (KIND == BWD_POOL)
+                if constexpr (KIND == BWD_POOL) {
+                    bt[i] = ((const uint8_t*)(a.bits + (size_t)learner * a.bits_lstride))[in_ok ? px * a.bits_pitch * 4 + (ch >> 3) : 0];
                     gp[i] = *(const u32x4*)(a.dpool + (size_t)learner * a.dpool_lstride + (in_ok ? (size_t)src.y * a.c_k + ch : 0));
+                } else {
+                    v[i] = *(const u32x4*)(in + (in_ok ? px * a.c_k + ch : 0));
+                }
             }
 #pragma unroll
             for (int i = 0; i < N; ++i) {
                 const int e = e0 + NT * i;
                 const u32x4 zero = {0u, 0u, 0u, 0u};
-                u32x4 x = (ok >> i) & 1u ? v[i] : zero;                // (zero activations give a zero gradient)
-                if constexpr (KIND == BWD_POOL) x = pool_grad_piece(x, gp[i], a.inv);
+                u32x4 x;
+                if constexpr (KIND == BWD_POOL) x = pool_grad_bits((ok >> i) & 1u ? bt[i] : 0u, gp[i], a.inv);
+                else x = (ok >> i) & 1u ? v[i] : zero;
                 if (e < pieces) *(u32x4*)(IN + (e / C8) * IP + (e % C8) * 8) = x;
             }
         }
@@ -215,10 +248,19 @@ __global__ void __launch_bounds__(NT, 2) conv_flat_kernel(FlatArgs a) {
             }
     };
     if constexpr (BACK) fetch_mask(0);
-#pragma unroll
-    for (int b = 0; b < PB; ++b) {
+    f32x16 sums[LAST ? NB : 1];                               // [place of an image][channel] of the wavefront's positions
+    if constexpr (LAST) {
 #pragma unroll
         for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) sums[j][e] = 0.f;
+    }
+#pragma unroll
+    for (int b = 0; b < PB; ++b) {
+        uint32_t word[NB];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            word[j] = 0;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 float v0 = acc[j][b][4 * q + 0], v1 = acc[j][b][4 * q + 1], v2 = acc[j][b][4 * q + 2], v3 = acc[j][b][4 * q + 3];
@@ -236,8 +278,41 @@ __global__ void __launch_bounds__(NT, 2) conv_flat_kernel(FlatArgs a) {
                     v2 = fmaxf(v2 + bias.z, 0.f);
                     v3 = fmaxf(v3 + bias.w, 0.f);
                 }
-                *(u32x2*)(patch + (lane & 31) * OP + j * 32 + q * 8 + (lane >> 5) * 4) = (u32x2){pack_bf16x2(v0, v1), pack_bf16x2(v2, v3)};
+                const u32x2 o = {pack_bf16x2(v0, v1), pack_bf16x2(v2, v3)};
+                *(u32x2*)(patch + (lane & 31) * OP + j * 32 + q * 8 + (lane >> 5) * 4) = o;
+                if constexpr (LAST) {
+                    const uint32_t four = (o.x & 0x7FFFu ? 1u : 0u) | (o.x & 0x7FFF0000u ? 2u : 0u) | (o.y & 0x7FFFu ? 4u : 0u) | (o.y & 0x7FFF0000u ? 8u : 0u);
+                    word[j] |= four << (q * 8 + (lane >> 5) * 4);
+                }
             }
+        }
+        if constexpr (LAST) {
+            // The sum over the positions of an image is a product with ones where a position is of that image (margins: of none).
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const u32x2 sl = *(const u32x2*)(SLOT + (pw * PB + b) * 32 + t * 16 + (lane >> 5) * 8);
+                u32x4 ones;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t w = i < 2 ? sl.x : sl.y;
+                    ones[i] = (((w >> (i & 1) * 16) & 0xFFu) == (uint32_t)(lane & 31) ? 0x3F80u : 0u) |
+                              (((w >> ((i & 1) * 16 + 8)) & 0xFFu) == (uint32_t)(lane & 31) ? 0x3F800000u : 0u);
+                }
+#pragma unroll
+                for (int j = 0; j < NB; ++j)
+                    sums[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, ones), frag_tr(patch + t * 16 * OP, OP, j * 32, lane), sums[j], 0, 0, 0);
+            }
+            const int to = position(b, lane & 31);
+#pragma unroll
+            for (int j = 0; j < NB; ++j) {
+                const auto h = __builtin_amdgcn_permlane32_swap(word[j], word[j], false, false);
+                if (lane < 32 && to >= 0 && cw * NB + j < a.bits_pitch)
+                    a.bits[(size_t)learner * a.bits_lstride + (size_t)to * a.bits_pitch + cw * NB + j] = (uint32_t)h[0] | (uint32_t)h[1];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            continue;
+        }
         if constexpr (BACK) { if (b + 1 < PB) fetch_mask(b + 1); }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -249,6 +324,32 @@ __global__ void __launch_bounds__(NT, 2) conv_flat_kernel(FlatArgs a) {
         }
         __builtin_amdgcn_sched_barrier(0);
     }
+    if constexpr (LAST) {
+        const int group = q0 / (PB * 32) + pw, first = (q0 + pw * PB * 32) / a.image, n = (q0 + pw * PB * 32 + PB * 32 - 1) / a.image - first;
+        float* to = a.sums + ((size_t)learner * a.tiles * PWAVES + group) * a.slots * (a.blocks * 32) + cw * NB * 32 + (lane & 31);
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const int slot = 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
+                if (slot <= n) to[(size_t)slot * (a.blocks * 32) + j * 32] = sums[j][e];
+            }
+    }
+}
+
+// pooled[image][channel] = bf16(mean): one lane per output adds the image's partial sums in ascending order
+__global__ void __launch_bounds__(NT) pool_finish_kernel(const float* sums, uint16_t* pooled, int B, int image, int last, int slots, int groups, int pitch, int c, float inv,
+                                                         int total) {
+    const int e = blockIdx.x * NT + threadIdx.x;
+    if (e >= total) return;
+    const int ch = e % c, img = e / c, learner = img / B, n = img - learner * B;
+    const int g1 = (n * image + last) / (PB * 32);
+    const float* p = sums + (size_t)learner * groups * slots * pitch + ch;
+    float s = 0.f;
+#pragma unroll 4
+    for (int g = n * image / (PB * 32); g <= g1; ++g) s += p[((size_t)g * slots + n - g * (PB * 32) / image) * pitch];
+    const __bf16 h = (__bf16)(s * inv);                       // round to nearest even
+    pooled[e] = __builtin_bit_cast(uint16_t, h);
 }
 
 __global__ void __launch_bounds__(NT) flat_table_kernel(int32_t* table, int len, int end, int H, int W) {
@@ -290,10 +391,10 @@ __global__ void __launch_bounds__(NT) pack_weights_kernel(PackArgs a) {
     *(u32x4*)(d.frag + (size_t)blockIdx.y * d.frag_lstride + (size_t)e * 8) = v;
 }
 
-// the tile, where its pixels lie, the bias
+// the tile, where its pixels lie, the bias, the places of images
 size_t lds_bytes(const FlatPlan& p, int W) {
     const int n_px = p.PWAVES * PB * 32 + 2 * (W + 1) + 2;
-    return (size_t)tile_area(n_px, p.CK, p.NB) + (size_t)n_px * 8 + 128 * 4;
+    return (size_t)tile_area(n_px, p.CK, p.NB) + (size_t)n_px * 8 + 128 * 4 + p.PWAVES * PB * 32;
 }
 
 FlatArgs make_args(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag, const int32_t* table) {
@@ -310,34 +411,34 @@ FlatArgs make_args(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag
     return a;
 }
 
-template <int CK, int NB, int PWAVES, int KIND>
+template <int CK, int NB, int PWAVES, int KIND, bool LAST>
 hipError_t launch(const FlatArgs& a, size_t smem, hipStream_t st) {
     if (smem > 64 * 1024) {
-        static hipError_t raised = hipFuncSetAttribute((const void*)conv_flat_kernel<CK, NB, PWAVES, KIND>,
+        static hipError_t raised = hipFuncSetAttribute((const void*)conv_flat_kernel<CK, NB, PWAVES, KIND, LAST>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
         if (raised != hipSuccess) return raised;
     }
-    hipLaunchKernelGGL((conv_flat_kernel<CK, NB, PWAVES, KIND>), dim3(a.padded), dim3(NT), smem, st, a);
+    hipLaunchKernelGGL((conv_flat_kernel<CK, NB, PWAVES, KIND, LAST>), dim3(a.padded), dim3(NT), smem, st, a);
     return hipGetLastError();
 }
 
-template <int KIND>
+template <int KIND, bool LAST = false>
 hipError_t run(const FlatArgs& a, const FlatPlan& p, hipStream_t st) {
     const size_t smem = lds_bytes(p, a.W);
     if (p.PWAVES == 2) {
-        if (p.CK == 64) return launch<64, 2, 2, KIND>(a, smem, st);
-        if (p.CK == 48) return launch<48, 2, 2, KIND>(a, smem, st);
-        if (p.CK == 32) return launch<32, 2, 2, KIND>(a, smem, st);
-        return launch<16, 2, 2, KIND>(a, smem, st);
+        if (p.CK == 64) return launch<64, 2, 2, KIND, LAST>(a, smem, st);
+        if (p.CK == 48) return launch<48, 2, 2, KIND, LAST>(a, smem, st);
+        if (p.CK == 32) return launch<32, 2, 2, KIND, LAST>(a, smem, st);
+        return launch<16, 2, 2, KIND, LAST>(a, smem, st);
     }
     if (p.NB == 2) {
-        if (p.CK == 48) return launch<48, 2, 4, KIND>(a, smem, st);
-        if (p.CK == 32) return launch<32, 2, 4, KIND>(a, smem, st);
-        return launch<16, 2, 4, KIND>(a, smem, st);
+        if (p.CK == 48) return launch<48, 2, 4, KIND, LAST>(a, smem, st);
+        if (p.CK == 32) return launch<32, 2, 4, KIND, LAST>(a, smem, st);
+        return launch<16, 2, 4, KIND, LAST>(a, smem, st);
     }
-    if (p.CK == 48) return launch<48, 1, 4, KIND>(a, smem, st);
-    if (p.CK == 32) return launch<32, 1, 4, KIND>(a, smem, st);
-    return launch<16, 1, 4, KIND>(a, smem, st);
+    if (p.CK == 48) return launch<48, 1, 4, KIND, LAST>(a, smem, st);
+    if (p.CK == 32) return launch<32, 1, 4, KIND, LAST>(a, smem, st);
+    return launch<16, 1, 4, KIND, LAST>(a, smem, st);
 }
 
 }  // namespace
@@ -397,6 +498,23 @@ hipError_t launch_pack_weights(const PackLayer* layers, int n, size_t w_lstride,
     return flush();
 }
 
+int conv_pool_slots(int H, int W) {
+    const int image = (H + 1) * (W + 1);
+    return image < 5 ? 0 : PB * 32 / image + 2;               // (at most the 32 rows of a matrix instruction)
+}
+
+size_t conv_pool_elems(int P, int B, int H, int W, const FlatPlan& plan) {
+    const int end = ((B - 1) * (H + 1) + H - 1) * (W + 1) + W, TP = plan.PWAVES * PB * 32;
+    return (size_t)P * ((end + TP - 1) / TP) * plan.PWAVES * conv_pool_slots(H, W) * plan.blocks * 32;
+}
+
+hipError_t launch_pool_finish(const float* sums, const FlatPlan& plan, void* pooled, int P, int B, int H, int W, int c, hipStream_t st) {
+    const int end = ((B - 1) * (H + 1) + H - 1) * (W + 1) + W, TP = plan.PWAVES * PB * 32, total = P * B * c;
+    hipLaunchKernelGGL(pool_finish_kernel, dim3((total + NT - 1) / NT), dim3(NT), 0, st, sums, (uint16_t*)pooled, B, (H + 1) * (W + 1),
+                       (H - 1) * (W + 1) + W - 1, conv_pool_slots(H, W), (end + TP - 1) / TP * plan.PWAVES, plan.blocks * 32, c, 1.0f / (float)(H * W), total);
+    return hipGetLastError();
+}
+
 hipError_t conv_flat_forward(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag, const int32_t* table, const void* X,
                              const int32_t* gather, long gstride, hipStream_t st) {
     FlatArgs a = make_args(c, plan, frag, table);
@@ -406,15 +524,22 @@ hipError_t conv_flat_forward(const ConvCall& c, const FlatPlan& plan, const uint
     a.bhi = c.bhi; a.blo = c.blo; a.b_lstride = c.ws_stride;
     a.out = (uint16_t*)c.out; a.out_lstride = rows * c.c_out; a.c_n = c.c_out;
     a.sign = 1;
+    if (c.bits) {
+        a.bits = c.bits; a.bits_pitch = conv_bits_pitch(c.c_out); a.bits_lstride = rows * a.bits_pitch;
+        a.sums = c.pool_sums; a.slots = conv_pool_slots(c.H, c.W); a.image = (c.H + 1) * (c.W + 1);
+        if (!a.sums || !a.slots) return hipErrorInvalidValue;
+        return gather ? run<FWD_GATHER, true>(a, plan, st) : run<FWD, true>(a, plan, st);
+    }
     return gather ? run<FWD_GATHER>(a, plan, st) : run<FWD>(a, plan, st);
 }
 
 hipError_t conv_flat_backward_data(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag, const int32_t* table, const void* dpool,
                                    hipStream_t st) {
-    if (dpool && !c.out) return hipErrorInvalidValue;
+    if (dpool && !c.bits) return hipErrorInvalidValue;
     FlatArgs a = make_args(c, plan, frag, table);
     const size_t rows = (size_t)c.B * c.H * c.W;
-    a.in = (const uint16_t*)(dpool ? c.out : c.dz); a.in_lstride = rows * c.c_out; a.c_k = c.c_out;
+    a.in = (const uint16_t*)c.dz; a.in_lstride = rows * c.c_out; a.c_k = c.c_out;
+    a.bits = c.bits; a.bits_pitch = conv_bits_pitch(c.c_out); a.bits_lstride = rows * a.bits_pitch;
     a.dpool = (const uint16_t*)dpool; a.dpool_lstride = (size_t)c.B * c.c_out; a.inv = 1.0f / (float)(c.H * c.W);
     a.act = (const uint16_t*)c.in;
     a.out = (uint16_t*)c.dz_in; a.out_lstride = rows * c.c_in; a.c_n = c.c_in;

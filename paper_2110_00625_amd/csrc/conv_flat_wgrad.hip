@@ -55,7 +55,8 @@ struct WgradArgs {
     int ring, lead;                                      // rows of the ring (a power of two); slices of pixels that the first slice needs
     uint32_t div_hw_m; int div_hw_s;
     float* partial; float* partial_bias;
-    const uint16_t* dpool; size_t dpool_lstride; float inv;          // POOL: dz holds this layer's activations
+    const uint16_t* dpool; size_t dpool_lstride; float inv;          // POOL: dZ from the bits and these
+    const uint8_t* bits; size_t bits_lstride; int bits_pitch;        // bytes
 };
 
 // Fragment of a [position][channel] LDS tile for one 16-position slab: lane l receives channel x0 + l%32 at positions
@@ -91,7 +92,8 @@ __global__ void __launch_bounds__(64 * 3 * OB) conv_flat_wgrad_kernel(WgradArgs 
 
     // piece i of this thread: row of the slice and 16-byte chunk, for dZ and for the pixels
     const int mask = a.ring - 1;
-    u32x4 zr[SH::ZN], ar[SH::AN], gr[POOL ? SH::ZN : 1];
+    u32x4 zr[POOL ? 1 : SH::ZN], ar[SH::AN], gr[POOL ? SH::ZN : 1];
+    uint8_t br[POOL ? SH::ZN : 1];
     int zi[SH::ZN], ai[SH::AN];                          // pixels of the slice that is requested next
     unsigned z_ok = 0, a_ok = 0;
     auto look_up = [&](int s) __attribute__((always_inline)) {       // dZ slice s, pixel slice s + lead
@@ -135,7 +137,8 @@ __global__ void __launch_bounds__(64 * 3 * OB) conv_flat_wgrad_kernel(WgradArgs 
             const bool ok = zi[i] >= 0 && ch < a.c_out && q < q_end;
             if (ok) z_ok |= 1u << i;
             const int px = ok ? zi[i] : 0, c = ok ? ch : 0;
-            zr[i] = *(const u32x4*)(dz + (int64_t)px * a.c_out + c);
+            if constexpr (!POOL) zr[i] = *(const u32x4*)(dz + (int64_t)px * a.c_out + c);
+            if constexpr (POOL) br[i] = a.bits[(size_t)learner * a.bits_lstride + (size_t)px * a.bits_pitch + (c >> 3)];
             if constexpr (POOL)
                 gr[i] = *(const u32x4*)(a.dpool + (size_t)learner * a.dpool_lstride +
                                         (size_t)fastdiv((uint32_t)px, a.div_hw_m, a.div_hw_s) * a.c_out + c);
@@ -152,8 +155,9 @@ __global__ void __launch_bounds__(64 * 3 * OB) conv_flat_wgrad_kernel(WgradArgs 
 #pragma unroll
         for (int i = 0; i < SH::ZN; ++i) {
             const int e = tid + NT * i;
-            u32x4 v = (z_ok >> i) & 1u ? zr[i] : zero;
-            if constexpr (POOL) v = pool_grad_piece(v, gr[i], a.inv);      // (zero activations give a zero gradient)
+            u32x4 v;
+            if constexpr (POOL) v = pool_grad_bits((z_ok >> i) & 1u ? br[i] : 0u, gr[i], a.inv);
+            else v = (z_ok >> i) & 1u ? zr[i] : zero;
             if (e < SLP * OB * 4) *(u32x4*)(Z + (buf * SLP + e / (OB * 4)) * ZP + (e % (OB * 4)) * 8) = v;
         }
     };
@@ -299,11 +303,11 @@ int conv_flat_wgrad_splits(int P, int B, int H, int W, int c_in, int c_out, bool
 
 hipError_t conv_flat_wgrad(const ConvCall& c, const int32_t* table, const void* X, const int32_t* gather, long gstride,
                            const void* dpool, hipStream_t st) {
-    if (c.splits < 1 || !c.partial || !c.partial_bias || (dpool && !c.out) || (gather && c.c_in != 8))
+    if (c.splits < 1 || !c.partial || !c.partial_bias || (dpool && !c.bits) || (gather && c.c_in != 8))
         return hipErrorInvalidValue;
     WgradArgs a = {};
     const size_t rows = (size_t)c.B * c.H * c.W;
-    a.dz = (const uint16_t*)(dpool ? c.out : c.dz); a.dz_lstride = rows * c.c_out; a.c_out = c.c_out;
+    a.dz = (const uint16_t*)c.dz; a.dz_lstride = rows * c.c_out; a.c_out = c.c_out;
     a.in = (const uint16_t*)(gather ? X : c.in); a.in_lstride = gather ? 0 : rows * c.c_in; a.c_in = c.c_in;
     a.gather = gather; a.gather_lstride = gstride;
     a.table = table; a.table_len = conv_flat_table_len(c.B, c.H, c.W);
@@ -315,8 +319,9 @@ hipError_t conv_flat_wgrad(const ConvCall& c, const int32_t* table, const void* 
     fastdiv_make((uint32_t)a.HW, &a.div_hw_m, &a.div_hw_s);
     a.partial = c.partial; a.partial_bias = c.partial_bias;
     a.dpool = (const uint16_t*)dpool; a.dpool_lstride = (size_t)c.B * c.c_out; a.inv = 1.0f / (float)a.HW;
+    a.bits = (const uint8_t*)c.bits; a.bits_pitch = conv_bits_pitch(c.c_out) * 4; a.bits_lstride = rows * a.bits_pitch;
     const int OB = (c.c_out + 31) / 32, wgs = c.P * a.splits * a.groups;
-    if (gather) return launch_ob<1, true, false>(a, OB, wgs, st);
+    if (gather) return dpool ? launch_ob<1, true, true>(a, OB, wgs, st) : launch_ob<1, true, false>(a, OB, wgs, st);
     if (c.c_in <= 32) return dpool ? launch_ob<1, false, true>(a, OB, wgs, st) : launch_ob<1, false, false>(a, OB, wgs, st);
     return dpool ? launch_ob<2, false, true>(a, OB, wgs, st) : launch_ob<2, false, false>(a, OB, wgs, st);
 }

@@ -26,4 +26,16 @@ __device__ __forceinline__ pool_u32x4 pool_grad_piece(pool_u32x4 m, pool_u32x4 g
     return o;
 }
 
+// The same from one byte of the bits that the last convolution's forward pass leaves in place of its activations (bit c:
+// channel c of the eight is positive; ConvCall::bits).
+__device__ __forceinline__ pool_u32x4 pool_grad_bits(uint32_t m, pool_u32x4 g, float inv) {
+    pool_u32x4 o;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const float g0 = __builtin_bit_cast(float, g[q] << 16) * inv, g1 = __builtin_bit_cast(float, g[q] & 0xFFFF0000u) * inv;
+        o[q] = pool_pack2(m & (1u << 2 * q) ? g0 : 0.f, m & (2u << 2 * q) ? g1 : 0.f);
+    }
+    return o;
+}
+
 }  // namespace kavg

@@ -50,8 +50,9 @@ struct WgradArgs {
     const uint16_t* in; size_t in_lstride;       // [learner][B*H*W][C_IN]
     float* partial; float* partial_bias;
     int H, images, splits;                       // images per workgroup; ranges per learner
-    // dpool != null: dz holds this layer's activations, and the gradient is formed from them and
+    // dpool != null: the gradient is formed from the bits that the layer's forward pass left and
     // dpool[learner][image][C_OUT] while loading (conv_pool.h)
+    const uint8_t* bits; size_t bits_lstride;    // bytes
     const uint16_t* dpool; size_t dpool_lstride; float inv;
 };
 
@@ -69,7 +70,7 @@ __device__ __forceinline__ bf16x8 frag_tr(const uint16_t* tile, int pitch, int r
 
 constexpr int POOL_IMAGES_MAX = 64;          // images of a workgroup whose dpool rows are kept in LDS
 
-// POOL: dZ is formed from the layer's activations and dpool while the slice is written to LDS
+// POOL: dZ is formed from the layer's bits and dpool while the slice is written to LDS
 template <int C_IN, int C_OUT, bool POOL>
 __global__ void __launch_bounds__(64 * 3 * (C_OUT / 32)) conv_wgrad_halo_kernel(WgradArgs a) {
     typedef WgradShape<C_IN, C_OUT> SH;
@@ -105,7 +106,9 @@ __global__ void __launch_bounds__(64 * 3 * (C_OUT / 32)) conv_wgrad_halo_kernel(
         const uint16_t* dpool = a.dpool + (size_t)learner * a.dpool_lstride + (size_t)range * a.images * C_OUT;
         for (int e = tid; e < a.images * (C_OUT / 8); e += NT) *(u32x4*)(gl + e * 8) = *(const u32x4*)(dpool + (size_t)e * 8);
     }
-    u32x4 zr[SH::ZN], ar[SH::AN];
+    u32x4 zr[POOL ? 1 : SH::ZN], ar[SH::AN];
+    uint8_t br[POOL ? SH::ZN : 1];
+    const uint8_t* bits = POOL ? a.bits + (size_t)learner * a.bits_lstride + pos0 * (C_OUT / 8) : nullptr;
     unsigned a_ok = 0;                           // bit i: piece i of the halo in the registers lies inside the image
     auto fetch = [&](int s) {
         const int b = s / half, h0 = (s - b * half) * 2;
@@ -113,7 +116,8 @@ __global__ void __launch_bounds__(64 * 3 * (C_OUT / 32)) conv_wgrad_halo_kernel(
 #pragma unroll
         for (int i = 0; i < SH::ZN; ++i) {
             const int e = min(tid + NT * i, SH::Z_PIECES - 1);
-            zr[i] = *(const u32x4*)(zsrc + (size_t)e * 8);
+            if constexpr (POOL) br[i] = bits[((size_t)b * H + h0) * IMG_W * (C_OUT / 8) + e];      // (whole words per pixel: C_OUT is a multiple of 32)
+            else zr[i] = *(const u32x4*)(zsrc + (size_t)e * 8);
         }
         a_ok = 0;
 #pragma unroll
@@ -134,8 +138,9 @@ __global__ void __launch_bounds__(64 * 3 * (C_OUT / 32)) conv_wgrad_halo_kernel(
         for (int i = 0; i < SH::ZN; ++i) {
             const int e = tid + NT * i;
             if (e < SH::Z_PIECES) {
-                u32x4 v = zr[i];
-                if constexpr (POOL) v = pool_grad_piece(v, *(const u32x4*)(gl + b * C_OUT + (e % (C_OUT / 8)) * 8), a.inv);
+                u32x4 v;
+                if constexpr (!POOL) v = zr[i];
+                if constexpr (POOL) v = pool_grad_bits(br[i], *(const u32x4*)(gl + b * C_OUT + (e % (C_OUT / 8)) * 8), a.inv);
                 *(u32x4*)(Z + (e / (C_OUT / 8)) * ZP + (e % (C_OUT / 8)) * 8) = v;
             }
         }
@@ -261,15 +266,16 @@ int conv_wgrad_halo_splits(int P, int B, int H, int W, int c_in, int c_out) {
 }
 
 hipError_t conv_wgrad_halo(const ConvCall& c, const void* dpool, hipStream_t st) {
-    if (conv_wgrad_halo_splits(c.P, c.B, c.H, c.W, c.c_in, c.c_out) == 0 || c.splits < 1 || c.B % c.splits != 0 || !c.partial || (dpool && (!c.out || c.B / c.splits > POOL_IMAGES_MAX)) ||
+    if (conv_wgrad_halo_splits(c.P, c.B, c.H, c.W, c.c_in, c.c_out) == 0 || c.splits < 1 || c.B % c.splits != 0 || !c.partial || (dpool && (!c.bits || c.B / c.splits > POOL_IMAGES_MAX)) ||
         !c.partial_bias)
         return hipErrorInvalidValue;
     WgradArgs a;
     const size_t rows = (size_t)c.B * c.H * c.W;
-    a.dz = (const uint16_t*)(dpool ? c.out : c.dz); a.dz_lstride = rows * c.c_out;
+    a.dz = (const uint16_t*)c.dz; a.dz_lstride = rows * c.c_out;
     a.in = (const uint16_t*)c.in; a.in_lstride = rows * c.c_in;
     a.partial = c.partial; a.partial_bias = c.partial_bias;
     a.H = c.H; a.images = c.B / c.splits; a.splits = c.splits;
+    a.bits = (const uint8_t*)c.bits; a.bits_lstride = rows * (c.c_out / 8);
     a.dpool = (const uint16_t*)dpool; a.dpool_lstride = (size_t)c.B * c.c_out; a.inv = 1.0f / (float)(c.H * c.W);
     if (c.c_in == 32) {
         if (c.c_out == 32) return launch_wgrad<32, 32>(a, c.P, st);

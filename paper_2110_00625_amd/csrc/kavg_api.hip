@@ -52,6 +52,9 @@ struct Layout {
     std::vector<size_t> off_frag_f, off_frag_b;
     std::vector<int> splits_flat;
     size_t off_flat_table = 0;
+    // the last convolution leaves bits and partial sums in place of its activations (ConvCall::bits)
+    bool pool_bits = false;
+    size_t off_bits = 0, off_sums = 0;
     size_t off_wrot = 0;                   // ... and their data gradient reads the weights as [(tap, o)][c_in]
     // all K steps of a small fp32 model in one launch (fused_small.hip, fused_units.hip): scratch; 0 bytes = shape not eligible
     size_t off_fused = 0, fused_bytes = 0;
@@ -145,7 +148,7 @@ Layout make_layout(int P, int K, int B, int L, const int* dims, int dtype, const
         lo.conv_implicit = (size_t)cv.H * cv.W < ((size_t)1 << 14);     // range of the loaders' multiply-shift divisions
         for (int t = 1; t <= M; ++t) {
             const int S1 = (t == 1 && lo.conv_implicit) ? conv_first_splits(P, B, cv.H, cv.W, cv.ch[0], cv.ch[1]) : 0;
-            const int Sh = t == 1 ? S1 : lo.conv_implicit ? conv_wgrad_halo_splits(P, B, cv.H, cv.W, cv.ch[t - 1], cv.ch[t]) : 0;
+            int Sh = t == 1 ? S1 : lo.conv_implicit ? conv_wgrad_halo_splits(P, B, cv.H, cv.W, cv.ch[t - 1], cv.ch[t]) : 0;
             // Which kernels run convolution t: those for images 32 pixels wide where they cover the layer, those for any width
             // elsewhere.  (The workload's layers on the latter, us per launch against the former: forward 33 / 69 / 174 against
             // 26 / 71 / 183, data gradient 85 / 226 against 75 / 199, weight gradient 32 / 89 / 260 against 33 / 54 / 168: with the
@@ -159,16 +162,33 @@ Layout make_layout(int P, int K, int B, int L, const int* dims, int dtype, const
                 if (t > 1 && !conv_direct_ok(cv.H, cv.W, cin, cout, true)) (void)conv_flat_plan(B, cv.H, cv.W, cout, cin, &pb);
                 if (t == 1 && !pf.slabs) Sf = 0;
             }
+            // The last convolution: bits and partial sums where its forward pass runs on images of any width and kernels that
+            // form their dZ cover both of its gradients.
+            if (t == M && lo.conv_implicit && conv_pool_slots(cv.H, cv.W)) {
+                const int cin = cv.ch[t - 1], cout = cv.ch[t];
+                FlatPlan p = {};
+                const int S = t == 1 ? conv_flat_wgrad_splits(P, B, cv.H, cv.W, cin, cout, true) : 0;
+                const bool gradients = t == 1 ? S > 0 : (pb.slabs || conv_direct_ok(cv.H, cv.W, cin, cout, true)) &&
+                                                        (Sf > 0 || (Sh > 0 && B / Sh <= conv_wgrad_halo_pool_images()));
+                lo.pool_bits = gradients && conv_flat_plan(B, cv.H, cv.W, cin, cout, &p);
+                if (lo.pool_bits) {
+                    pf = p;
+                    if (t == 1) { Sf = S; Sh = 0; }
+                    lo.off_bits = take((size_t)P * rows * conv_bits_pitch(cout) * 4);
+                    lo.off_sums = take(conv_pool_elems(P, B, cv.H, cv.W, p) * 4);
+                }
+            }
             lo.splits_flat.push_back(Sf);
             lo.flat_f.push_back(pf); lo.flat_b.push_back(pb);
             lo.off_frag_f.push_back(pf.slabs ? take((size_t)P * pf.frag_elems() * 2) : 0);
             lo.off_frag_b.push_back(pb.slabs ? take((size_t)P * pb.frag_elems() * 2) : 0);
             // explicit patches: every convolution of very large images, and a first convolution (it gathers its images)
             // that neither kind of tile kernel covers
-            const bool expl = (t == 1 && S1 == 0 && Sf == 0) || !lo.conv_implicit;
+            const bool expl = (t == 1 && Sh == 0 && Sf == 0) || !lo.conv_implicit;
             lo.off_patch.push_back(expl ? take((size_t)P * rows * 9 * cv.ch[t - 1] * 2) : 0);
-            lo.off_cact.push_back(take((size_t)P * rows * cv.ch[t] * 2));
-            lo.off_cdz.push_back(take((size_t)P * rows * cv.ch[t] * 2));
+            const bool written = !(t == M && lo.pool_bits);                 // its activations and their gradient
+            lo.off_cact.push_back(written ? take((size_t)P * rows * cv.ch[t] * 2) : 0);
+            lo.off_cdz.push_back(written ? take((size_t)P * rows * cv.ch[t] * 2) : 0);
             if (t > 1 && !lo.conv_implicit && (size_t)P * rows * 9 * cv.ch[t - 1] * 4 > draw) draw = (size_t)P * rows * 9 * cv.ch[t - 1] * 4;
             if (t > 1 && lo.conv_implicit && !pb.slabs && !conv_direct_ok(cv.H, cv.W, cv.ch[t - 1], cv.ch[t], true) &&
                 (size_t)P * 9 * cv.ch[t] * cv.ch[t - 1] * 2 > wrot)
@@ -997,6 +1017,7 @@ int issue_steps_conv(kavg_ctx* c) {
         v.wrot = (const uint16_t*)(c->ws + lo.off_wrot); v.wrot_stride = (size_t)9 * v.c_out * v.c_in;
         v.partial = (float*)(c->ws + lo.off_partial[t - 1]); v.partial_bias = (float*)(c->ws + lo.off_pbias[t - 1]);
         v.splits = lo.splits[t - 1];
+        if (t == M && lo.pool_bits) { v.bits = (uint32_t*)(c->ws + lo.off_bits); v.pool_sums = (float*)(c->ws + lo.off_sums); }
         return v;
     };
     const bool first_direct = lo.conv_implicit && lo.splits_halo[0] > 0;   // the first convolution straight from the gathered images
@@ -1008,6 +1029,7 @@ int issue_steps_conv(kavg_ctx* c) {
         v.out = c->ws + lo.off_cact[0]; v.dz = c->ws + lo.off_cdz[0];
         v.partial = (float*)(c->ws + lo.off_partial[0]); v.partial_bias = (float*)(c->ws + lo.off_pbias[0]);
         v.splits = lo.splits_halo[0];
+        if (M == 1 && lo.pool_bits) { v.bits = (uint32_t*)(c->ws + lo.off_bits); v.pool_sums = (float*)(c->ws + lo.off_sums); }
         return v;
     };
     const int32_t* table = (const int32_t*)(c->ws + lo.off_flat_table);
@@ -1058,7 +1080,10 @@ int issue_steps_conv(kavg_ctx* c) {
         }
         {
             Bracket br(c, KAVG_CLASS_FORWARD);
-            KAVG_HIP(c, launch_pool_forward(c->ws + lo.off_cact[M - 1], c->ws + lo.off_pool, P, B, H * W, cv.ch[M], st));
+            if (lo.pool_bits)
+                KAVG_HIP(c, launch_pool_finish((const float*)(c->ws + lo.off_sums), lo.flat_f[M - 1], c->ws + lo.off_pool, P, B, H, W, cv.ch[M], st));
+            else
+                KAVG_HIP(c, launch_pool_forward(c->ws + lo.off_cact[M - 1], c->ws + lo.off_pool, P, B, H * W, cv.ch[M], st));
         }
         for (int l = 1; l <= (head && !chained ? L - 1 : below); ++l) {             // MLP, forward
             Bracket br(c, KAVG_CLASS_FORWARD);
@@ -1096,11 +1121,8 @@ int issue_steps_conv(kavg_ctx* c) {
             const int rc = issue_update_group(c, group, head, k == c->K - 1);
             if (rc != KAVG_OK) return rc;
         }
-        // The gradient of the mean over the positions: written out for the generic kernels; the tile kernels of
-        // the last convolution form it while loading (both of them must be in use, or the buffer is needed).
-        const bool pool_fused = M > 1 && lo.conv_implicit && (lo.flat_b[M - 1].slabs || conv_direct_ok(H, W, cv.ch[M - 1], cv.ch[M], true)) &&
-                                (lo.splits_flat[M - 1] > 0 || (lo.splits_halo[M - 1] > 0 &&
-                                                    B / lo.splits_halo[M - 1] <= conv_wgrad_halo_pool_images()));
+        // The gradient of the mean over the positions: formed by the gradients of the last convolution from its bits, or written out.
+        const bool pool_fused = lo.pool_bits;
         const void* dpool_M = c->ws + lo.off_dpool;
         if (!pool_fused) {
             Bracket br(c, KAVG_CLASS_BACKWARD);
@@ -1152,7 +1174,7 @@ int issue_steps_conv(kavg_ctx* c) {
                 ConvCall v = first_call();
                 if (lo.splits_flat[0] > 0) {
                     v.splits = lo.splits_flat[0];
-                    KAVG_HIP(c, conv_flat_wgrad(v, table, c->X, idx_k, idx_ls, nullptr, st));
+                    KAVG_HIP(c, conv_flat_wgrad(v, table, c->X, idx_k, idx_ls, (pool_fused && M == 1) ? dpool_M : nullptr, st));
                 } else {
                     KAVG_HIP(c, conv_first_wgrad(v, c->X, idx_k, idx_ls, st));
                 }

@@ -171,7 +171,12 @@ struct ConvCall {
     void* dz_in;                                       // backward: gradient w.r.t. the input layer's pre-activation (masked by in > 0)
     const uint16_t* wrot; size_t wrot_stride;          // backward: weights as [(tap, o)][c_in] (launch_rotate_weights), learner stride
     float* partial; float* partial_bias; int splits;   // update: fp32 partials [P*splits][c_out][9 c_in] / [P*splits][c_out]
+    // The last convolution, below the mean over the positions: nothing but that mean and the ReLU masks are read of its
+    // activations, so its forward pass leaves bits [P][B*H*W][ceil(c_out / 32)] (bit c%32 of word c/32: positive) and
+    // partial sums (launch_pool_finish), and its gradients form dZ from the bits.  null: activations in `out`.
+    uint32_t* bits; float* pool_sums;
 };
+inline int conv_bits_pitch(int c) { return (c + 31) / 32; }
 hipError_t bf16_conv_forward(const ConvCall& c, hipStream_t st);
 hipError_t bf16_conv_backward_data(const ConvCall& c, hipStream_t st);
 hipError_t bf16_conv_update_partial(const ConvCall& c, hipStream_t st);

@@ -40,6 +40,23 @@ def test_one_step(P, B, H, W, channels, dims):
             assert e < 2.0 ** -8, "%s of learner %d: %.3g" % (name, j, e)
 
 
+LAST = [
+    # the last convolution: bits and partial sums in place of its activations
+    (2, 9, 1, 2, (8, 16), (16, 10)),                 # images of six positions: 23 of them in the 128 of a wavefront
+    (2, 70, 2, 1, (8, 8, 128), (128, 3)),        # more images than a tile holds; two tiles per learner
+    (1, 3, 3, 4, (8, 8, 72), (72, 40)),              # a last word of eight channels
+    (3, 3, 32, 32, (8, 32), (32, 10)),               # one convolution, 32 pixels wide: its gradient from the bits as well
+    (2, 5, 32, 32, (8, 32, 32, 64), (64, 10)),       # an odd batch: the gradients of the kernels for any width
+    (2, 4, 16, 32, (8, 64, 64, 128), (128, 17)),     # an even one: those for 32 pixels, from bits
+    (1, 2, 13, 47, (8, 40, 104), (104, 10)),
+]
+
+
+@pytest.mark.parametrize("P,B,H,W,channels,dims", LAST, ids=["%dx%d-%s" % (c[2], c[3], "-".join(map(str, c[4]))) for c in LAST])
+def test_last_convolution(P, B, H, W, channels, dims):
+    test_one_step(P, B, H, W, channels, dims)
+
+
 def test_profile_counts_the_packing_of_the_weights():
     """A step's forward launches: the packed weights, two convolutions, the mean over the positions (the last layer of ten
     classes runs in the head kernels)."""
