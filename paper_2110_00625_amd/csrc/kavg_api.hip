@@ -157,10 +157,14 @@ Layout make_layout(int P, int K, int B, int L, const int* dims, int dtype, const
             int Sf = 0;
             if (lo.conv_implicit) {
                 const int cin = cv.ch[t - 1], cout = cv.ch[t];
-                if (Sh == 0) Sf = conv_flat_wgrad_splits(P, B, cv.H, cv.W, cin, cout, t == 1);
-                if (t == 1 ? Sf > 0 : !conv_direct_ok(cv.H, cv.W, cin, cout, false)) (void)conv_flat_plan(B, cv.H, cv.W, cin, cout, &pf);
+                Sf = conv_flat_wgrad_splits(P, B, cv.H, cv.W, cin, cout, t == 1);
+                // The kernels for 32 pixels split a learner into equal numbers of whole images, down to one range where the batch
+                // is odd; where that leaves them a third fewer compute units than the others' ranges, which end anywhere, those
+                // run.  (15 learners of 6 images, 64 -> 64 channels: 76 against 24 us; 16 learners of 64, 64 -> 128: 168 / 260.)
+                if (Sh > 0 && std::min(256, P * Sh) * 3 >= std::min(256, P * Sf) * 2) Sf = 0;
+                if (t == 1 ? Sf > 0 && Sh == 0 : !conv_direct_ok(cv.H, cv.W, cin, cout, false)) (void)conv_flat_plan(B, cv.H, cv.W, cin, cout, &pf);
                 if (t > 1 && !conv_direct_ok(cv.H, cv.W, cin, cout, true)) (void)conv_flat_plan(B, cv.H, cv.W, cout, cin, &pb);
-                if (t == 1 && !pf.slabs) Sf = 0;
+                if (t == 1 && !pf.slabs && Sh == 0) Sf = 0;
             }
             // The last convolution: bits and partial sums where its forward pass runs on images of any width and kernels that
             // form their dZ cover both of its gradients.
