@@ -78,6 +78,19 @@ struct Operand {
     uint32_t div_c_m, div_w_m, div_hw_m; int div_c_s, div_w_s, div_hw_s;
 };
 
+// Rows of all learners as one operand (MERGED below): row x is row x mod B of learner x / B.
+struct Rows { int B; uint32_t div_m; int div_s; };
+__device__ __forceinline__ int learner_of(const Rows& r, int x) { return (int)fastdiv((uint32_t)x, r.div_m, r.div_s); }
+// its start, as an element offset from the operand's base
+template <bool MERGED>
+__device__ __forceinline__ long row_start(const Operand& o, const Rows& r, const int32_t* gather, int x) {
+    if constexpr (MERGED) {
+        const int j = learner_of(r, x), i = x - j * r.B;
+        return gather ? (long)gather[(long)j * o.gstride + i] * o.ld : (long)j * (long)o.lstride + (long)i * o.ld;
+    }
+    return (gather ? (long)gather[x] : (long)x) * o.ld;
+}
+
 inline void operand_conv(Operand& o, int c, int H, int W, int sign) {
     o.cv_c = c; o.cv_H = H; o.cv_W = W; o.cv_sign = sign;
     fastdiv_make((uint32_t)c, &o.div_c_m, &o.div_c_s);
@@ -115,6 +128,7 @@ struct Args {
     //                  the master; "learners" are then ranges of rows of the real learners
     float* partial; float* partial_bias;
     int cv_splits;                               // implicit C operand with partial outputs: ranges per real learner
+    Rows rows;                                   // MERGED: nR = rows of all learners
     int c_stream;                                // forward: the C operand (weights) is read once and does not stay in the memory-side cache
                                                  // (measured: noisy_wide forward 5.9 -> 5.5 ms per round; no gain on the transposed reads of backward-data)
 };
@@ -146,14 +160,15 @@ struct DirectLoader {
     static constexpr int N = X * BK / 8 / NT;
     const uint16_t* rowp[N];     // null: row outside the operand
     int kc[N];
-    __device__ __forceinline__ void init(const Operand& o, const uint16_t* base, const int32_t* gather, int x0, int tid) {
+    template <bool MERGED = false>
+    __device__ __forceinline__ void init(const Operand& o, const uint16_t* base, const int32_t* gather, int x0, int tid, const Rows& rows = Rows()) {
 #pragma unroll
         for (int i = 0; i < N; ++i) {
             const int e = tid + NT * i;
             const int x = x0 + e / (BK / 8);
             kc[i] = (e % (BK / 8)) * 8;
             rowp[i] = nullptr;
-            if (x < o.n_rows) rowp[i] = base + (gather ? (long)gather[x] : (long)x) * o.ld + kc[i];
+            if (x < o.n_rows) rowp[i] = base + row_start<MERGED>(o, rows, gather, x) + kc[i];
         }
     }
     // STREAM: the operand is read once per launch and comes from memory (weights that do not fit the
@@ -374,7 +389,8 @@ struct DmaLoader {
     const uint16_t* row[N];      // start of the (clamped) memory row of piece i, plus the piece's chunk offset
     int chunk8[N];               // first element of the piece's memory chunk within a slice
     int wave;                    // wavefront index, uniform (kept in a scalar register)
-    __device__ __forceinline__ void init(const Operand& o, const uint16_t* base, const int32_t* gather, int x0, int tid) {
+    template <bool MERGED = false>
+    __device__ __forceinline__ void init(const Operand& o, const uint16_t* base, const int32_t* gather, int x0, int tid, const Rows& rows = Rows()) {
         const int lane = tid & 63;
         wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 #pragma unroll
@@ -383,7 +399,7 @@ struct DmaLoader {
             const int xr = slot / CPR;
             const int x = min(x0 + xr, o.n_rows - 1);
             chunk8[i] = ((slot % CPR) ^ dma_swizzle<BK>(xr)) * 8;
-            row[i] = base + (gather ? (long)gather[x] : (long)x) * o.ld + chunk8[i];
+            row[i] = base + row_start<MERGED>(o, rows, gather, x) + chunk8[i];
         }
     }
     // FULL: the slice lies inside the contraction (k0 + BK <= n_cont), no clamping needed
@@ -444,9 +460,11 @@ struct Shape {
 // summed through LDS at the end, in fixed order).  BK = slice length.  One slice is always in
 // flight in registers ahead of the one being multiplied; with PIPE_LDS2 the LDS tiles are double-buffered,
 // so the next slice is written while the current one is read and a slice costs one barrier, not two.
+// MERGED (forward, backward-data): all learners multiply by the same weights, so their rows are those of one product: each tile of
+// weights is read once per 256 or 128 rows instead of once per learner (learner strides of R, bias, mask and output by row).
 // CONV_R / CONV_C: that operand is the implicit patch matrix of a convolution (Operand::cv_c).
 template <int MODE, int TR, int TC, int WR, int WC, int WK, int BK, bool RTRANS, bool CTRANS, int PIPE, bool SHADOW_CACHED = false,
-          bool GATHER_C = false, bool CONV_R = false, bool CONV_C = false>
+          bool GATHER_C = false, bool CONV_R = false, bool CONV_C = false, bool MERGED = false>
 __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING_LOADERS : 0))) gemm_bf16_kernel(Args a) {
     static_assert(!CONV_R || (!RTRANS && PIPE != PIPE_DMA), "implicit R operand: k-contiguous, staged through registers");
     static_assert(!CONV_C || (CTRANS && !GATHER_C && MODE == MODE_UPD), "implicit C operand: the update's transposed operand");
@@ -501,7 +519,7 @@ __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING
     DirectLoader<TC, BK, NT> cdl; TransLoader<TC, BK, NT, GATHER_C> ctl; ConvTransLoader<TC, BK, NT> ccl;
     if constexpr (!DIRECT) {                    // (direct global->LDS pipelines set up their own loaders below)
         if constexpr (CONV_R) rcl.init(a.R, Rbase, r0, tid);
-        else if (RTRANS) rtl.init(a.R, Rbase, Rg, r0, tid); else rdl.init(a.R, Rbase, Rg, r0, tid);
+        else if (RTRANS) rtl.init(a.R, Rbase, Rg, r0, tid); else rdl.template init<MERGED>(a.R, Rbase, Rg, r0, tid, a.rows);
         if constexpr (CONV_C) ccl.init(a.C, Cbase, c_koff, c0, tid);
         else if (CTRANS) ctl.init(a.C, Cbase, Cg, c0, tid); else cdl.init(a.C, Cbase, Cg, c0, tid);
     }
@@ -579,9 +597,14 @@ __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING
     constexpr bool EARLY = MR * MC == 1;
     // bias of four columns: raw hi / lo words (requested early, joined only where they are used: joining
     // at once would make every request wait for its own answer)
-    auto bias_raw = [&](int j, int q, u32x2& h, u32x2& l) {
-        const uint16_t* bh = a.bias_hi + (size_t)learner * a.bias_lstride;
-        const uint16_t* bl = a.bias_lo + (size_t)learner * a.bias_lstride;
+    // learner and row inside it of output row r
+    auto place_of = [&](int r, int& j, int& i) {
+        j = MERGED ? learner_of(a.rows, min(r, a.nR - 1)) : learner;
+        i = MERGED ? r - j * a.rows.B : r;
+    };
+    auto bias_raw = [&](int of, int j, int q, u32x2& h, u32x2& l) {          // of: learner
+        const uint16_t* bh = a.bias_hi + (size_t)of * a.bias_lstride;
+        const uint16_t* bl = a.bias_lo + (size_t)of * a.bias_lstride;
         const int c = c0 + (wc * MC + j) * 32 + q * 8 + (lane >> 5) * 4;
         h = (u32x2){0u, 0u}; l = (u32x2){0u, 0u};
         if (!a.bias_hi) return;                   // product without a bias term
@@ -606,8 +629,10 @@ __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING
         const int r = r0 + (wr * MR + i) * 32 + (lane & 31);
         const int c = c0 + (wc * MC + j) * 32 + q * 8 + (lane >> 5) * 4;
         u32x2 m = {0u, 0u};
+        int of, row;
+        place_of(r, of, row);
         if (a.act_prev && r < a.nR && c < a.nC)
-            m = *(const u32x2*)(a.act_prev + (size_t)learner * a.act_lstride + (size_t)r * a.ld_act + c);
+            m = *(const u32x2*)(a.act_prev + (size_t)of * a.act_lstride + (size_t)row * a.ld_act + c);
         return m;
     };
     u32x2 ebh[4], ebl[4];
@@ -615,7 +640,7 @@ __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING
     if (EARLY && wk == 0) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            if (MODE == MODE_FWD) bias_raw(0, q, ebh[q], ebl[q]);
+            if (MODE == MODE_FWD) bias_raw(learner, 0, q, ebh[q], ebl[q]);
             if (MODE == MODE_BWD) emask[q] = mask_of(0, 0, q);
         }
     }
@@ -635,7 +660,7 @@ __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING
         const int slices = a.nK / BK;               // (whole slices: checked by the launcher)
         if (__builtin_amdgcn_readfirstlane(wave) >= NW) {
             DmaLoader<TR, BK, 64 * RING_LOADERS> rdma; DmaLoader<TC, BK, 64 * RING_LOADERS> cdma;
-            rdma.init(a.R, Rbase, Rg, r0, tid - NT);
+            rdma.template init<MERGED>(a.R, Rbase, Rg, r0, tid - NT, a.rows);
             cdma.init(a.C, Cbase, Cg, c0, tid - NT);
 #pragma unroll
             for (int d = 0; d < D; ++d)
@@ -675,7 +700,7 @@ __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING
     } else if constexpr (PIPE == PIPE_DMA) {
         static_assert(!RTRANS && !CTRANS && MODE != MODE_UPD, "direct LDS loads: k-contiguous operands only");
         DmaLoader<TR, BK, NT> rdma; DmaLoader<TC, BK, NT> cdma;
-        rdma.init(a.R, Rbase, Rg, r0, tid);
+        rdma.template init<MERGED>(a.R, Rbase, Rg, r0, tid, a.rows);
         cdma.init(a.C, Cbase, Cg, c0, tid);
         rdma.load(a.R, 0, Rs, tid);
         cdma.load(a.C, 0, Cs, tid, a.c_stream);
@@ -814,10 +839,12 @@ __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING
         u32x2 pmk[MODE == MODE_BWD ? MR : 1][MODE == MODE_BWD ? MC : 1][4];
         if (!EARLY) {
             if constexpr (MODE == MODE_FWD) {
+                if constexpr (!MERGED) {
 #pragma unroll
-                for (int j = 0; j < MC; ++j)
+                    for (int j = 0; j < MC; ++j)
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) bias_raw(j, q, pbh[j][q], pbl[j][q]);
+                        for (int q = 0; q < 4; ++q) bias_raw(learner, j, q, pbh[j][q], pbl[j][q]);
+                }
             } else {
 #pragma unroll
                 for (int i = 0; i < MR; ++i)
@@ -841,6 +868,14 @@ __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING
         for (int i = 0; i < MR; ++i) {
             const int r = r0 + (wr * MR + i) * 32 + (lane & 31);
             const bool r_ok = r < a.nR;
+            int of, row_of;                                     // (of this lane's row)
+            place_of(r, of, row_of);
+            if constexpr (MODE == MODE_FWD && MERGED) {
+#pragma unroll
+                for (int j = 0; j < MC; ++j)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) bias_raw(of, j, q, pbh[j][q], pbl[j][q]);
+            }
 #pragma unroll
             for (int j = 0; j < MC; ++j) {
 #pragma unroll
@@ -860,16 +895,16 @@ __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING
                         } else if (a.relu) {
                             o = (u32x2){pack2(fmaxf(v0, 0.f), fmaxf(v1, 0.f)), pack2(fmaxf(v2, 0.f), fmaxf(v3, 0.f))};
                         } else {
-                            if (ok) *(f32x4*)((float*)a.out + (size_t)learner * a.out_lstride + (size_t)r * a.ld_out + c) = (f32x4){v0, v1, v2, v3};
+                            if (ok) *(f32x4*)((float*)a.out + (size_t)of * a.out_lstride + (size_t)row_of * a.ld_out + c) = (f32x4){v0, v1, v2, v3};
                             continue;
                         }
                     } else {
                         if (a.base && ok) {
-                            const f32x4 bs = *(const f32x4*)(a.base + (size_t)learner * a.base_lstride + (size_t)r * a.ld_base + c);
+                            const f32x4 bs = *(const f32x4*)(a.base + (size_t)of * a.base_lstride + (size_t)row_of * a.ld_base + c);
                             v0 += bs.x; v1 += bs.y; v2 += bs.z; v3 += bs.w;
                         }
                         if (a.epi == EPI_RAW || a.epi == EPI_LOGITS) {
-                            if (ok) *(f32x4*)((float*)a.out + (size_t)learner * a.out_lstride + (size_t)r * a.ld_out + c) = (f32x4){v0, v1, v2, v3};
+                            if (ok) *(f32x4*)((float*)a.out + (size_t)of * a.out_lstride + (size_t)row_of * a.ld_out + c) = (f32x4){v0, v1, v2, v3};
                             continue;
                         }
                         if (a.epi == EPI_RELU) {
@@ -885,7 +920,7 @@ __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING
                         o = (u32x2){pack2(v0, v1), pack2(v2, v3)};
                     }
                     if (staged) *(u32x2*)(opatch + (lane & 31) * OP + j * 32 + q * 8 + (lane >> 5) * 4) = o;
-                    else if (ok) *(u32x2*)((uint16_t*)a.out + (size_t)learner * a.out_lstride + (size_t)r * a.ld_out + c) = o;
+                    else if (ok) *(u32x2*)((uint16_t*)a.out + (size_t)of * a.out_lstride + (size_t)row_of * a.ld_out + c) = o;
                 }
             }
             if (staged) {
@@ -897,8 +932,10 @@ __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING
                     const int row = pass * RPP + lane / CPRW, ch = lane % CPRW;
                     const int rr = rblk + row, cc = c0 + wc * WTC + ch * 8;
                     const u32x4 v = *(const u32x4*)(opatch + row * OP + ch * 8);
+                    int pj, pi;
+                    place_of(rr, pj, pi);
                     if (rr < a.nR && cc < c_end)
-                        *(u32x4*)((uint16_t*)a.out + (size_t)learner * a.out_lstride + (size_t)rr * a.ld_out + cc) = v;
+                        *(u32x4*)((uint16_t*)a.out + (size_t)pj * a.out_lstride + (size_t)pi * a.ld_out + cc) = v;
                 }
             }
         }
@@ -982,7 +1019,7 @@ __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING
 }
 
 template <int MODE, int TR, int TC, int WR, int WC, int WK, int BK, bool RT, bool CT, int PIPE, bool SC = false, bool GC = false,
-          bool CVR = false, bool CVC = false>
+          bool CVR = false, bool CVC = false, bool MG = false>
 hipError_t launch(Args a, int P, hipStream_t st) {
     a.tiles_c = (a.nC + TC - 1) / TC;
     a.tiles_r = (a.nR + TR - 1) / TR;
@@ -993,12 +1030,12 @@ hipError_t launch(Args a, int P, hipStream_t st) {
     static_assert(SMEM <= 160 * 1024, "more LDS than a compute unit has");
     if (SMEM > 64 * 1024) {                     // beyond the default limit: raise it once for this kernel
         static hipError_t raised = hipFuncSetAttribute(
-            (const void*)gemm_bf16_kernel<MODE, TR, TC, WR, WC, WK, BK, RT, CT, PIPE, SC, GC, CVR, CVC>,
+            (const void*)gemm_bf16_kernel<MODE, TR, TC, WR, WC, WK, BK, RT, CT, PIPE, SC, GC, CVR, CVC, MG>,
             hipFuncAttributeMaxDynamicSharedMemorySize, SMEM);
         if (raised != hipSuccess) return raised;
     }
     if (PIPE == PIPE_RING && (a.nK % BK != 0 || a.nK > a.R.n_cont || a.nK > a.C.n_cont)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((gemm_bf16_kernel<MODE, TR, TC, WR, WC, WK, BK, RT, CT, PIPE, SC, GC, CVR, CVC>), grid,
+    hipLaunchKernelGGL((gemm_bf16_kernel<MODE, TR, TC, WR, WC, WK, BK, RT, CT, PIPE, SC, GC, CVR, CVC, MG>), grid,
                        dim3(Shape<MODE, TR, TC, WR, WC, WK, BK, RT, CT, PIPE>::THREADS), SMEM, st, a);
     return hipGetLastError();
 }
@@ -1052,6 +1089,21 @@ hipError_t launch_tiled(const Args& a, int P, int tile, hipStream_t st) {
 
 }  // namespace
 
+namespace {
+// Products whose weights all learners share (round start of deferred updates): one product over the rows of all learners where
+// its tiles fill the chip (no sum is split there; the same bits wherever none was before).  (32 learners of 64 samples, us per launch: forward,
+// mean of 3072 -> 4096 -> 4096, 103 -> 73 = 840 TFLOP/s; data gradient of 4096 -> 4096 134 -> 93.)
+bool merge_rows(const LayerCall& c, Args& a, int tr, int tc) {
+    if (!c.shared_w || c.P < 2 || c.B >= 1 << 14 || (long)c.P * c.B >= 1 << 30) return false;
+    const long rows = (long)c.P * c.B, tiles = (rows + tr - 1) / tr;
+    if (tiles * ((a.nC + tc - 1) / tc) < 192 || tiles * tr * 8 > rows * 9) return false;      // (at most an eighth of the rows padding)
+    a.rows.B = c.B;
+    fastdiv_make((uint32_t)c.B, &a.rows.div_m, &a.rows.div_s);
+    a.R.n_rows = a.nR = (int)rows;
+    return true;
+}
+}  // namespace
+
 hipError_t bf16_forward(const LayerCall& c, hipStream_t st) {
     Args a = {};
     a.R = {(const uint16_t*)c.in, c.gather ? 0 : c.in_stride, c.ld_in, c.gather, c.gather_stride, c.B, c.d_in};
@@ -1060,6 +1112,8 @@ hipError_t bf16_forward(const LayerCall& c, hipStream_t st) {
     a.bias_hi = c.bhi; a.bias_lo = c.blo; a.bias_lstride = c.ws_stride;
     a.out = c.out; a.out_lstride = c.out_stride; a.ld_out = c.ld_out; a.relu = c.relu;
     a.c_stream = !c.shadow_cached && !c.shared_w;
+    if (a.nK % 64 == 0 && a.nK >= 128 && merge_rows(c, a, 256, 128))
+        return launch<MODE_FWD, 256, 128, 2, 2, 1, 64, false, false, PIPE_RING, false, false, false, false, true>(a, 1, st);
     return launch_tiled<MODE_FWD, false, false>(a, c.P, pick_tile(MODE_FWD, a.nR, a.nC, a.nK, c.P), st);
 }
 
@@ -1074,6 +1128,8 @@ hipError_t bf16_backward_data(const LayerCall& c, hipStream_t st) {
     a.act_prev = (const uint16_t*)c.in; a.act_lstride = c.in_stride; a.ld_act = c.ld_in;
     a.out = c.dz_prev; a.out_lstride = c.dz_prev_stride; a.ld_out = c.ld_in;
     if (c.bwd_raw) { a.epi = EPI_RAW; a.act_prev = nullptr; }
+    if (merge_rows(c, a, 128, 128))
+        return launch<MODE_BWD, 128, 128, 2, 2, 1, 64, false, true, PIPE_PLAIN, false, false, false, false, true>(a, 1, st);
     return launch_tiled<MODE_BWD, false, true>(a, c.P, pick_tile(MODE_BWD, a.nR, a.nC, a.nK, c.P), st);
 }
 
