@@ -455,7 +455,7 @@ int chain_layers(int P, int B, int L, const int* dims, bool into_input) {
                 one += product(d_in, d_out); many += 43 + 2 * d_out / 64;
             }
         }
-        if (many - one > gain) { best = n; gain = many - one; }
+        if (many - one > gain && !(head && n == 1)) { best = n; gain = many - one; }     // (alone the head is one launch anyway)
     }
     return best;
 }
