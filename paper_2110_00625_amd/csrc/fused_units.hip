@@ -24,7 +24,8 @@
 // and storing the parameters 10 per launch.  A round (K = 4) with the meta step and the read-back of the losses: 79 us, as
 // launches per layer (six dependent kernels of 4-17 us per step) 180 us; 48 learners, B = 4, K = 8: 153 against 419 us.
 // What it took: all workgroups of a learner on one XCD (88 -> 79), no division by a run-time number in a phase (64 -> 42 us for
-// the launch), the next step's rows written to a second LDS buffer while the partial logits travel, biases as a column of the
+// the launch), parameters requested all at once (48 learners: 9 -> 4 us per launch), sums over the rows that exist and not
+// over whole blocks (minibatches of 4), the next step's rows written to a second LDS buffer while the partial logits travel, biases as a column of the
 // products instead of serial sums at the end of a step.
 #include "kavg_internal.h"
 #include "fused_common.h"
@@ -98,6 +99,31 @@ __global__ void __launch_bounds__(NT) fused_units_kernel(FusedSmallCall a, int s
     float *b2 = sm + q.b2, *rowloss = sm + q.rowloss;
     int *idx = (int*)(sm + q.idx), *gave_up_word = (int*)(sm + q.gave_up);
 
+    // ---- parameters: requested together, ahead of everything else; places outside the model are read from inside and dropped
+    constexpr int RW = UN / NW, W2N = (CLS * UN + NT - 1) / NT;
+    f32x4 wv[2][RW];
+    float bv[RW], w2v[W2N];
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int i = 0; i < RW; ++i) {
+            const float* src = rep + a.w1_off + (size_t)(ub + min(wave + NW * i, un - 1)) * a.d0;
+            const int c = h * 256 + lane * 4;
+            if (VEC) wv[h][i] = *(const f32x4*)(src + min(c, a.d0 - 4));
+            else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) wv[h][i][e] = src[min(c + e, a.d0 - 1)];
+            }
+        }
+#pragma unroll
+    for (int i = 0; i < RW; ++i) bv[i] = rep[a.b1_off + ub + min(wave + NW * i, un - 1)];
+#pragma unroll
+    for (int i = 0; i < W2N; ++i) {
+        const int e = tid + NT * i;
+        w2v[i] = rep[a.w2_off + (size_t)min(e / UN, a.C - 1) * a.d1 + ub + min(e % UN, un - 1)];
+    }
+    const float b2v = rep[a.b2_off + min(tid, a.C - 1)];
+
     // ---- the learner's minibatch indices: draw (j, t0 + k, m) of the counter-based stream, or the caller's ----
     for (int e = tid; e < a.K * a.B; e += NT) {
         int32_t v;
@@ -112,26 +138,28 @@ __global__ void __launch_bounds__(NT) fused_units_kernel(FusedSmallCall a, int s
 
     // ---- parameters into LDS; positions outside the model (and rows of the minibatch beyond B) are zero throughout.
     // Column d_0 of W_1 is b_1 and column d_0 of every row of X is 1: the bias is added and stepped by the products. ----
-    for (int r = wave; r < UN; r += NW)
-        for (int c = lane * 4; c < q.D; c += 256) {
-            f32x4 v = {0.f, 0.f, 0.f, 0.f};
-            if (r < un) {
-                const float* src = rep + a.w1_off + (size_t)(ub + r) * a.d0 + c;
-                if (VEC && c < a.d0) v = *(const f32x4*)src;
+    static_assert(D0MAX + 16 <= 2 * 256 + 16, "two pieces per lane and row, and the last sixteen columns");
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    if (!VEC && c + i < a.d0) v[i] = src[i];
-                    if (c + i == a.d0) v[i] = rep[a.b1_off + ub + r];
-                }
-            }
-            *(f32x4*)(W1 + r * PW + c) = v;
+    for (int i = 0; i < RW; ++i) {
+        const int r = wave + NW * i;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int c = h * 256 + lane * 4;
+            f32x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = r < un ? (c + e < a.d0 ? wv[h][i][e] : c + e == a.d0 ? bv[i] : 0.f) : 0.f;
+            if (c < q.D) *(f32x4*)(W1 + r * PW + c) = v;
         }
-    for (int e = tid; e < CLS * UN; e += NT) {
-        const int c = e / UN, u = e % UN;
-        sm[q.W2 + c * PU + u] = (c < a.C && u < un) ? rep[a.w2_off + (size_t)c * a.d1 + ub + u] : 0.f;
+        const int c = 512 + lane;                               // (columns 512 .. 527 of inputs of 512)
+        if (c < q.D) W1[r * PW + c] = r < un && c == a.d0 ? bv[i] : 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < W2N; ++i) {
+        const int e = tid + NT * i, c = e / UN, u = e % UN;
+        if (e < CLS * UN) sm[q.W2 + c * PU + u] = (c < a.C && u < un) ? w2v[i] : 0.f;
     }
     if (tid == 0) *gave_up_word = 0;
-    if (tid < CLS) b2[tid] = tid < a.C ? rep[a.b2_off + tid] : 0.f;
+    if (tid < CLS) b2[tid] = tid < a.C ? b2v : 0.f;
     for (int e = tid; e < q.R * PD; e += NT) D2[e] = 0.f;
     for (int r = wave; r < q.NX * q.R; r += NW)
         for (int c = lane; c < q.D; c += 64) sm[q.X + r * PW + c] = c == a.d0 ? 1.f : 0.f;
@@ -311,7 +339,7 @@ __global__ void __launch_bounds__(NT) fused_units_kernel(FusedSmallCall a, int s
             const bool bias = ublk == ublocks;
             f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll 4
-            for (int m = 0; m < q.R; m += 4)
+            for (int m = 0; m < a.B; m += 4)                    // (beyond B: zeros)
                 acc = __builtin_amdgcn_mfma_f32_16x16x4f32(D2[(m + lq) * PD + l16], bias ? 1.f : A1[(m + lq) * PU + u0 + l16], acc, 0, 0, 0);
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
@@ -341,7 +369,7 @@ __global__ void __launch_bounds__(NT) fused_units_kernel(FusedSmallCall a, int s
                 for (int i = 0; i < NB; ++i) acc[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
                 const float* xp = X + lq * PW + cb + l16;
 #pragma unroll 4
-                for (int m = 0; m < q.R; m += 4) {
+                for (int m = 0; m < a.B; m += 4) {              // (beyond B dZ_1 is zero)
                     const float d = dp[m * PU];
 #pragma unroll
                     for (int i = 0; i < NB; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(d, xp[m * PW + i * cstep], acc[i], 0, 0, 0);
