@@ -114,6 +114,7 @@ Layout make_layout(int P, int K, int B, int L, const int* dims, int dtype, const
     lo.off_shadow = dtype == KAVG_BF16 ? take((size_t)P * lo.stride * 2) : 0;
     lo.off_idx = take((size_t)P * K * B * 4);
     lo.off_flag = take(ALIGN);
+    lo.off_losses = take((size_t)K * P * 4);                // right behind the flags: read back together (kavg_losses)
     for (int l = 1; l <= L; ++l) {
         const size_t ld = l == L ? (size_t)lo.ldz : (size_t)dims[l];
         lo.off_act.push_back(l < L ? take((size_t)P * B * ld * esz) : 0);
@@ -121,7 +122,6 @@ Layout make_layout(int P, int K, int B, int L, const int* dims, int dtype, const
     }
     lo.off_logits = take((size_t)P * B * lo.ldz * 4);
     lo.off_rowloss = take((size_t)K * P * B * 4);
-    lo.off_losses = take((size_t)K * P * 4);
     if (dtype == KAVG_FP32) {          // partial tiles of the split forward contractions
         size_t need = 0;
         for (int l = 1; l <= L; ++l) {
@@ -340,13 +340,10 @@ int fail(kavg_ctx* c, int code, const char* fmt, ...) {
         if (e_ != hipSuccess) return fail(ctx, KAVG_EDEVICE, "%s: %s", #call, hipGetErrorString(e_)); \
     } while (0)
 
-// wait for the stream, then report (and clear) the device-side range flag
-int sync_and_check(kavg_ctx* c) {
-    int flag[2] = {0, 0};                   // [0] range error, [1] a wait between workgroups gave up
-    KAVG_HIP(c, hipMemcpyAsync(flag, c->flag(), sizeof(flag), hipMemcpyDeviceToHost, c->stream));
-    KAVG_HIP(c, hipStreamSynchronize(c->stream));
+// report (and clear) the device-side flags that a finished stream left: [0] range error, [1] a wait between workgroups gave up
+int check_flags(kavg_ctx* c, const int flag[2]) {
     if (flag[0] || flag[1]) {
-        KAVG_HIP(c, hipMemsetAsync(c->flag(), 0, sizeof(flag), c->stream));
+        KAVG_HIP(c, hipMemsetAsync(c->flag(), 0, 2 * sizeof(int), c->stream));
         KAVG_HIP(c, hipStreamSynchronize(c->stream));
         if (flag[1])
             return fail(c, KAVG_EDEVICE, "a wait between the workgroups of the fused local steps ran out of polls; "
@@ -354,6 +351,14 @@ int sync_and_check(kavg_ctx* c) {
         return fail(c, KAVG_EINVAL, "an index or label outside its range was found on the device");
     }
     return KAVG_OK;
+}
+
+// wait for the stream, then report (and clear) the flags
+int sync_and_check(kavg_ctx* c) {
+    int flag[2] = {0, 0};
+    KAVG_HIP(c, hipMemcpyAsync(flag, c->flag(), sizeof(flag), hipMemcpyDeviceToHost, c->stream));
+    KAVG_HIP(c, hipStreamSynchronize(c->stream));
+    return check_flags(c, flag);
 }
 
 int install_global(kavg_ctx* c, const float* w_host, const float* v_host) {
@@ -1484,7 +1489,18 @@ int kavg_losses(kavg_ctx* c, float* out_host) {
     if (!c) return KAVG_EINVAL;
     if (!out_host) return fail(c, KAVG_EINVAL, "out_host is null");
     if (!c->have_steps) return fail(c, KAVG_ESTATE, "no local steps taken yet");
-    return copy_out(c, c->losses(), out_host, (size_t)c->K * c->P * 4);
+    // flags and losses in one copy: on small models each copy takes as long as a local step (256-256-10, rounds with read-back:
+    // 6 learners 75.5 -> 64.6 us, 48 learners 134 -> 123)
+    KAVG_NOTHROW_BEGIN
+    const size_t at = c->lo.off_losses - c->lo.off_flag, bytes = (size_t)c->K * c->P * 4;
+    std::vector<char> both(at + bytes);
+    KAVG_HIP(c, hipMemcpyAsync(both.data(), c->flag(), at + bytes, hipMemcpyDeviceToHost, c->stream));
+    KAVG_HIP(c, hipStreamSynchronize(c->stream));
+    int flag[2];
+    memcpy(flag, both.data(), sizeof(flag));
+    memcpy(out_host, both.data() + at, bytes);
+    return check_flags(c, flag);
+    KAVG_NOTHROW_END(c)
 }
 
 int kavg_indices(kavg_ctx* c, int32_t* out_host) {
