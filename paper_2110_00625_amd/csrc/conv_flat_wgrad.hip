@@ -293,12 +293,23 @@ int conv_flat_wgrad_splits(int P, int B, int H, int W, int c_in, int c_out, bool
     const int IB = c_in <= 32 ? 1 : 2, OB = (c_out + 31) / 32, groups = (c_in + 63) / 64;
     const int smem = smem_of(IB, OB, first, ring_rows(W, nullptr));
     if (smem > LDS_MAX) return 0;
-    // ranges: one round of workgroups over the 256 compute units, as many as fit into the LDS of each (at most 16
-    // wavefronts), and at least four slices each, since every range brings in its margins and writes its partial sums
+    // Ranges: one round of workgroups over the 256 compute units, f of them on each, and at least four slices each, since every
+    // range brings in its margins.  More workgroups per compute unit hide more of each other's waits (up to as many as fit
+    // into its LDS, 16 wavefronts at most), but each writes partial sums that conv_step_kernel reads again.  The better f: a slice
+    // takes 1 us of a compute unit, f workgroups are 1 .. 1.7 times as fast as one, the sums move at 3.5 TB/s.  (us per step of
+    // nets, f as many as fit / 1: 28x28 32 -> 64, 8 learners of 32 images 130 / 123; 32x32 64 -> 64, 15 of 6 177 / 149; but
+    // 60x32 8 -> 32, 8 of 62 98 / 119; 32x32 24 -> 24 -> 40, 12 of 35 244 / 251.)
     const int end = ((B - 1) * (H + 1) + H - 1) * (W + 1) + W, all = (end + SLP - 1) / SLP;
-    const int fit = std::max(1, std::min(LDS_MAX / smem, 16 / (3 * OB)));
-    int S = std::max(1, 256 * fit / (P * groups));
-    return std::max(1, std::min(S, all / 4));
+    const int fit = std::max(1, std::min({LDS_MAX / smem, 16 / (3 * OB), 5}));
+    const double faster[6] = {0, 1, 1.35, 1.5, 1.6, 1.7}, slices = (double)all * P * groups / 256, sums = (double)P * c_out * 9 * c_in * 8 / 3.5e6;
+    int best = 1;
+    double least = 0;
+    for (int f = 1; f <= fit; ++f) {
+        const int S = std::max(1, std::min(std::max(1, 256 * f / (P * groups)), all / 4));
+        const double us = slices / faster[f] + S * sums;
+        if (f == 1 || us < least) { best = S; least = us; }
+    }
+    return best;
 }
 
 hipError_t conv_flat_wgrad(const ConvCall& c, const int32_t* table, const void* X, const int32_t* gather, long gstride,
