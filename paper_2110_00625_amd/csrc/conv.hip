@@ -30,6 +30,7 @@
 // and the pooling and the master step serve all.
 #include "kavg_internal.h"
 #include "split.h"
+#include "fastdiv.h"
 #include "conv_pool.h"
 
 namespace kavg {
@@ -151,8 +152,16 @@ pool_backward_kernel(const uint16_t* __restrict__ dpool, const uint16_t* __restr
 // convolutions: adds up the S partial gradients of an element (eight requested together, added in ascending order).  One
 // launch for all layers whose partial sums lie side by side in the workspace: with one launch each and one partial sum
 // requested at a time it took 14 us per layer on 28x28 images with channels 8-32-64, now 10.5 us for both.
+// The stepped bf16 values are also left in operand order for the next step's products (conv_flat.hip), two bytes at a time: a
+// launch of its own for that was 4 - 5 us of a step (28x28: a round of four steps PACK_FIGURES).
 constexpr int STEP_GROUP = 8;
-struct StepArgs { ConvStep layer[STEP_GROUP]; int n; size_t lstride; float lr; };
+struct StepArgs { ConvStep layer[STEP_GROUP]; uint32_t div_m[STEP_GROUP]; int div_s[STEP_GROUP]; int n; size_t lstride; float lr; };
+
+// element (output x, contraction k, tap) of a layer's weights in operand order (launch_pack_weights)
+__device__ __forceinline__ void put_frag(const FragPlace& f, int j, int x, int k, int tap, uint16_t v) {
+    const int slab = k >> 4, grp = slab / f.SL, it = grp * 9 * f.SL + tap * f.SL + slab - grp * f.SL;
+    f.frag[(size_t)j * f.lstride + ((size_t)(it * f.blocks + (x >> 5)) * 64 + (x & 31) + ((k >> 3) & 1) * 32) * 8 + (k & 7)] = v;
+}
 
 __global__ void __launch_bounds__(256) conv_step_kernel(StepArgs a) {
     int b = blockIdx.x, i0 = 0;
@@ -178,8 +187,14 @@ __global__ void __launch_bounds__(256) conv_step_kernel(StepArgs a) {
     uint16_t* hi = (is_w ? q.whi : q.bhi) + (size_t)j * a.lstride + i;
     uint16_t* lo = (is_w ? q.wlo : q.blo) + (size_t)j * a.lstride + i;
     const float v = __builtin_bit_cast(float, split_join(*hi, *lo)) - a.lr * s;
-    *hi = (uint16_t)split_hi(__builtin_bit_cast(uint32_t, v));
+    const uint16_t h = (uint16_t)split_hi(__builtin_bit_cast(uint32_t, v));
+    *hi = h;
     *lo = (uint16_t)split_lo(__builtin_bit_cast(uint32_t, v));
+    if (is_w && (q.fwd.frag || q.bwd.frag)) {
+        const int ot = (int)fastdiv((uint32_t)i, a.div_m[i0], a.div_s[i0]), c = i - ot * q.c_in, o = ot / 9, tap = ot - 9 * o;
+        if (q.fwd.frag) put_frag(q.fwd, j, o, c, tap, h);
+        if (q.bwd.frag) put_frag(q.bwd, j, c, o, tap, h);
+    }
 }
 
 // one lane per 16-byte piece of the rotated weights
@@ -248,6 +263,7 @@ hipError_t launch_conv_steps(const ConvStep* layers, int n, size_t lstride, int 
         unsigned wgs = 0;
         for (int i = 0; i < a.n; ++i) {
             a.layer[i] = layers[at + i];
+            fastdiv_make((uint32_t)a.layer[i].c_in, &a.div_m[i], &a.div_s[i]);
             wgs += blocks((size_t)a.layer[i].n_w + a.layer[i].n_b);
         }
         hipLaunchKernelGGL(conv_step_kernel, dim3(wgs, P), dim3(256), 0, st, a);

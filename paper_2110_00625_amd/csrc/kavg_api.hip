@@ -1055,12 +1055,23 @@ int issue_steps_conv(kavg_ctx* c) {
         packed = packed || q.fwd || q.bwd;
         pack.push_back(q);
     }
+    // The weights in operand order: packed before the first step, then left by the SGD steps (while forward launches are
+    // profiled: packed before every step).
+    const bool pack_each = (c->prof_mask & (1u << KAVG_CLASS_FORWARD)) != 0;
+    auto frag_place = [&](int t, bool back, int k) {
+        const PackLayer& q = pack[t - 1];
+        const FlatPlan& p = back ? q.bwd_plan : q.fwd_plan;
+        FragPlace f = {};
+        if (pack_each || k == c->K - 1 || !(back ? q.bwd : q.fwd)) return f;
+        f.frag = back ? q.bwd : q.fwd; f.lstride = back ? q.bwd_lstride : q.fwd_lstride; f.SL = p.CK / 16; f.blocks = p.blocks;
+        return f;
+    };
     const int chained = chained_layers(c), below = L - chained;          // layers 1 .. below of the MLP run one by one
     for (int k = 0; k < c->K; ++k) {
         const int32_t* idx_k = c->idx() + (size_t)k * B;
         const long idx_ls = (long)c->K * B;
         float* rowloss_k = c->rowloss() + (size_t)k * P * B;
-        if (packed) {
+        if (packed && (k == 0 || pack_each)) {
             Bracket br(c, KAVG_CLASS_FORWARD);
             KAVG_HIP(c, launch_pack_weights(pack.data(), M, lo.stride, P, st));
         }
@@ -1175,7 +1186,7 @@ int issue_steps_conv(kavg_ctx* c) {
                 } else {
                     KAVG_HIP(c, bf16_conv_update_partial(v, st));
                 }
-                steps.push_back({v.ws, v.wlo, (uint16_t*)v.bhi, (uint16_t*)v.blo, v.partial, v.partial_bias, v.splits, v.c_out * 9 * v.c_in, v.c_out});
+                steps.push_back({v.ws, v.wlo, (uint16_t*)v.bhi, (uint16_t*)v.blo, v.partial, v.partial_bias, v.splits, v.c_out * 9 * v.c_in, v.c_out, v.c_in, frag_place(t, false, k), frag_place(t, true, k)});
                 continue;
             }
             if (t == 1 && (lo.splits_flat[0] > 0 || first_direct)) {
@@ -1187,7 +1198,7 @@ int issue_steps_conv(kavg_ctx* c) {
                 } else {
                     KAVG_HIP(c, conv_first_wgrad(v, c->X, idx_k, idx_ls, st));
                 }
-                steps.push_back({v.ws, v.wlo, (uint16_t*)v.bhi, (uint16_t*)v.blo, v.partial, v.partial_bias, v.splits, v.c_out * 9 * v.c_in, v.c_out});
+                steps.push_back({v.ws, v.wlo, (uint16_t*)v.bhi, (uint16_t*)v.blo, v.partial, v.partial_bias, v.splits, v.c_out * 9 * v.c_in, v.c_out, v.c_in, frag_place(t, false, k), frag_place(t, true, k)});
                 continue;
             }
             LayerCall q = conv_call(t);
@@ -1205,7 +1216,7 @@ int issue_steps_conv(kavg_ctx* c) {
             q.partial_bias = (float*)(c->ws + lo.off_pbias[t - 1]);
             q.splits = lo.splits[t - 1];
             KAVG_HIP(c, bf16_update(q, st));
-            steps.push_back({q.ws, q.wlo, q.bhi, q.blo, q.partial, q.partial_bias, q.splits, q.d_out * q.d_in, q.d_out});
+            steps.push_back({q.ws, q.wlo, q.bhi, q.blo, q.partial, q.partial_bias, q.splits, q.d_out * q.d_in, q.d_out, cv.ch[t - 1], frag_place(t, false, k), frag_place(t, true, k)});
         }
         const int rc = take_steps();
         if (rc != KAVG_OK) return rc;

@@ -156,7 +156,13 @@ hipError_t launch_col2im_mask(const float* draw, const void* act, void* dprev, i
 hipError_t launch_pool_forward(const void* act, void* pooled, int P, int B, int HW, int c, hipStream_t st);
 hipError_t launch_pool_backward(const void* dpool, const void* act, void* dz, int P, int B, int HW, int c, hipStream_t st);
 // master -= lr * (sum of the S fp32 partial gradients) for n layers, weights [n_w] and bias [n_b] of each, planes of split.h
-struct ConvStep { uint16_t* whi; uint16_t* wlo; uint16_t* bhi; uint16_t* blo; const float* partial; const float* pbias; int S, n_w, n_b; };
+// fwd, bwd: where not null, the stepped weights go to those places as well, in the operand order of conv_flat.hip (the zeros around
+// them stay)
+struct FragPlace { uint16_t* frag; size_t lstride; int SL, blocks; };
+struct ConvStep {
+    uint16_t* whi; uint16_t* wlo; uint16_t* bhi; uint16_t* blo; const float* partial; const float* pbias; int S, n_w, n_b, c_in;
+    FragPlace fwd, bwd;
+};
 hipError_t launch_conv_steps(const ConvStep* layers, int n, size_t lstride, int P, float lr, hipStream_t st);
 
 // ---- 3x3 convolution (stride 1, zero padding 1) on channels-last images [P][B][H][W][c], the patch matrix formed
