@@ -24,14 +24,15 @@
 // What bounds these kernels: 3072-512 with 64 rows and 8 learners is 1.6 GFLOP per product, 10 us of the matrix
 // cores' fp32 rate; the update also moves 100 MB of weights, 15 us out of the memory-side cache.  Measured on
 // 3072-512-256-10 (8 learners, 64 rows): split forward product 24 -> 14 us per launch (mean of the two layers),
-// backward-data 24 -> 11 us, the updates of a step 75 -> 29 + 5 us; a round of four steps 657 -> 358 us.  (Before: 64x64
+// backward-data 24 -> 11 us, the updates of a step 75 -> 30 us; a round of four steps 657 -> 331 us.  (Before: 64x64
 // tiles everywhere, operands moved word by word, one slice ahead, the weights read after the contraction.)
 //
 // The forward pass may split the contraction over several workgroups where a layer has few output tiles: each writes
 // its partial tile to a scratch buffer and a second small kernel adds the partials in ascending split order, then
-// applies bias and ReLU.  The updates of all layers of a step (but a thin last one, head.hip) are one launch: they depend
+// applies bias and ReLU.  The updates of all layers of a step are one launch: they depend
 // on nothing but the backward pass, and on small models each launch is a few microseconds of latency.
 #include "kavg_internal.h"
+#include "head_update.h"
 #include "loss_mean.h"
 
 namespace kavg {
@@ -286,6 +287,7 @@ struct UpdLayer {
     const float* in; size_t in_lstride; int ld_in; const int32_t* gather; long gather_lstride;   // [k][c]
     float* w; float* b; float* u; float* ub;                        // u, ub: velocities, null: plain SGD
     int d_out, d_in, tiles_r, tiles_c, total, padded;
+    int head;                                                       // the last layer, of few classes: head_tile
 };
 constexpr int GROUP = 8;       // layers per launch
 struct UpdArgs {
@@ -417,6 +419,69 @@ __device__ __forceinline__ void update_tile(const UpdArgs& a, const UpdLayer& q,
     }
 }
 
+// The step of a last layer of at most CT classes on sixteen of its input units.  Lane = 4*g + pl: sample group g (samples
+// s = g mod 16) and input unit 16 block + 4 wave + pl.  Every lane sums dZ_L[s][c] * A[s][unit] over its samples in ascending
+// order; a butterfly over the group bits of the lane index adds the sixteen groups, after which lane group g applies the update
+// of class c = g.  What waits here is a chain of latencies; as a launch of its own it was 5 us and a gap of every step
+// (rounds, us, with that launch and without: 3072-512-256-10, 8 learners of 64 346 / 331; 300-500-10, 2 of 16 236 / 208;
+// 500-700-16, 30 of 20 203 / 188).
+template <int CT>
+__device__ __forceinline__ void head_tile(const UpdArgs& a, const UpdLayer& q, int learner, int block) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int grp = lane >> 2, pl = lane & 3;
+    const int unit = block * 16 + wave * 4 + pl;
+    const bool live = unit < q.d_in;
+    const int uu = live ? unit : q.d_in - 1;                        // out-of-range lanes shadow the last unit, never store
+    const int32_t* g = q.gather + (long)learner * q.gather_lstride;
+    const float* in = q.in + (size_t)learner * q.in_lstride;
+    const float* dz = q.dz + (size_t)learner * q.dz_lstride;
+    const size_t lat = (size_t)learner * a.lstride;
+
+    float acc[CT], bsum[CT];
+#pragma unroll
+    for (int c = 0; c < CT; ++c) acc[c] = bsum[c] = 0.f;
+#pragma unroll 4
+    for (int s = grp; s < a.B; s += 16) {
+        const float x = in[(size_t)(q.gather ? g[s] : s) * q.ld_in + uu];
+        float gz[CT];                                               // one row of dZ_L; entries beyond ld_dz are zero
+#pragma unroll
+        for (int i = 0; i < CT / 4; ++i) {
+            f32x4 v = {0.f, 0.f, 0.f, 0.f};
+            if (4 * i < q.ld_dz) v = *(const f32x4*)(dz + (size_t)s * q.ld_dz + 4 * i);      // (ld_dz is a multiple of 8)
+            gz[4 * i] = v.x; gz[4 * i + 1] = v.y; gz[4 * i + 2] = v.z; gz[4 * i + 3] = v.w;
+        }
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            bsum[c] += gz[c];                                       // bias gradient: column sum of dZ_L
+            acc[c] = fmaf(gz[c], x, acc[c]);
+        }
+    }
+    float mine = 0.f;
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+        const float v = groups_sum(acc[c]);
+        if (c == grp) mine = v;
+    }
+    if (live && grp < q.d_out) {
+        const size_t at = lat + (size_t)grp * q.d_in + unit;
+        if (q.u) { mine = a.beta * q.u[at] + mine; q.u[at] = mine; }       // heavy ball inside the learner
+        q.w[at] = q.w[at] - a.lr * mine;
+    }
+    if (block == 0 && wave == 0) {
+        float sum = 0.f;
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+            const float v = groups_sum(bsum[c]);
+            if (c == grp) sum = v;
+        }
+        if (pl == 0 && grp < q.d_out) {
+            const size_t at = lat + grp;
+            if (q.ub) { sum = a.beta * q.ub[at] + sum; q.ub[at] = sum; }
+            q.b[at] = q.b[at] - a.lr * sum;
+        }
+    }
+}
+
 template <bool WORDS>
 __global__ void __launch_bounds__(256, WORDS ? 2 : 3) update_kernel(UpdArgs a) {
     __shared__ __align__(16) float lds[2 * BK * (xpitch(UR) + xpitch(UC))];
@@ -432,6 +497,10 @@ __global__ void __launch_bounds__(256, WORDS ? 2 : 3) update_kernel(UpdArgs a) {
     if (at >= q.total) return;
     const int rt = at % q.tiles_r; at /= q.tiles_r;
     const int ct = at % q.tiles_c, learner = at / q.tiles_c;
+    if (q.head) {
+        if (q.d_out <= 8) head_tile<8>(a, q, learner, ct); else head_tile<16>(a, q, learner, ct);
+        return;
+    }
     if (!WORDS && (rt + 1) * UR <= q.d_out && (ct + 1) * UC <= q.d_in) update_tile<WORDS, !WORDS>(a, q, learner, rt, ct, lds);
     else update_tile<WORDS, false>(a, q, learner, rt, ct, lds);
 }
@@ -550,11 +619,12 @@ hipError_t f32_update(const LayerCall* calls, int n, const LossMeans* losses, hi
             q.gather = c.gather; q.gather_lstride = c.gather_stride;
             q.w = c.w; q.b = c.b; q.u = c.u; q.ub = c.ub;
             q.d_out = c.d_out; q.d_in = c.d_in;
-            q.tiles_r = div_up(c.d_out, UR); q.tiles_c = div_up(c.d_in, UC);
+            q.head = c.head;
+            q.tiles_r = c.head ? 1 : div_up(c.d_out, UR); q.tiles_c = div_up(c.d_in, c.head ? 16 : UC);
             q.total = q.tiles_r * q.tiles_c * c.P;
             q.padded = div_up(q.total, 8) * 8;
             wgs += q.padded;
-            words = words || c.d_in < 4 || c.ld_dz < 4 || c.d_in >= 1 << 24;     // (2^24: reach of lane_at)
+            words = words || (!c.head && (c.d_in < 4 || c.ld_dz < 4 || c.d_in >= 1 << 24));      // (2^24: reach of lane_at)
         }
         if (losses && at + a.n_layers == n) {
             a.losses = *losses;

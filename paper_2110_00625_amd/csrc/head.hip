@@ -11,7 +11,7 @@
 //        dZ_{L-1}[s] = (dZ_L[s] W_L) * [A_{L-1}[s] > 0]
 //  head_update             W_L <- W_L - lr * dZ_L^T A_{L-1},  b_L <- b_L - lr * colsum(dZ_L)
 //        (the learner update of Algorithm 1 for the last layer; runs after the kernel above
-//        because that one reads the weights of before the step)
+//        because that one reads the weights of before the step; fp32: head_tile of gemm_f32.hip)
 //
 // Mixed precision follows the same rounding points as the generic kernels:
 // products of bf16 operands accumulated in fp32, dZ_L and dZ_{L-1} rounded to
@@ -71,16 +71,13 @@ struct HeadArgs {
     const void* act; int ld_act; size_t act_lstride;      // A_{L-1} [P][B][ld_act], or the data set when gather != null
     const int32_t* gather; long gather_lstride;           // row s of learner j is data row gather[j*gather_lstride + s]
     const void* wmul; size_t wmul_lstride;                // weights as multiplied: bf16 (hi) plane or fp32, [C][d]
-    float* wmaster; size_t w_lstride;                     // fp32 mode: the layer's weights
-    float* bias;                                          // fp32 mode: its bias (stride w_lstride)
+    const float* bias; size_t w_lstride;                  // fp32 mode: the bias
     const uint16_t* bhi; const uint16_t* blo; size_t ws_lstride;     // bf16 mode: hi / lo planes of the bias (split.h)
     const int32_t* y;                                     // labels of the data set
     void* dz; int ldz; size_t dz_lstride;                 // dZ_L [P][B][ldz]
     void* dz_prev; size_t dz_prev_lstride;                // dZ_{L-1} [P][B][d], null for a single-layer model
     float* rowloss;                                       // [P][B]
     int P, B, d, C;
-    float lr;
-    float* u; float* ub; float beta;                      // velocities of W_L / b_L (stride w_lstride), null: plain SGD
 };
 
 // CT = compile-time bound on the class count (4, 8, 12 or 16): every loop over classes is fully
@@ -236,75 +233,19 @@ __global__ void __launch_bounds__(256) head_update_bf16_kernel(HeadStep a) {
     head_step(a, blockIdx.x, gridDim.z > 1 ? (int)blockIdx.z : -1, blockIdx.y, xch);
 }
 
-// fp32: 256 threads = 4 wavefronts.  Lane = 4*g + pl: sample group g (samples s = g mod 16) and input unit
-// blockIdx.x*16 + 4*wave + pl.  Every lane sums dZ_L[s][c] * A[s][unit] over its samples in ascending order; a
-// butterfly over the group bits of the lane index adds the sixteen groups, after which lane group g applies the
-// update of class c = g.
-template <int CT>
-__global__ void __launch_bounds__(256) head_update_f32_kernel(HeadArgs a) {
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int grp = lane >> 2, pl = lane & 3;
-    const int q = blockIdx.x * 16 + wave * 4 + pl;
-    const int learner = blockIdx.y;
-    const bool live = q < a.d;
-    const int qq = live ? q : a.d - 1;                        // out-of-range lanes shadow the last unit, never store
-    const int32_t* g = a.gather + (long)learner * a.gather_lstride;
-    const float* act = (const float*)a.act;
-    const float* dz = (const float*)a.dz + (size_t)learner * a.dz_lstride;
-
-    float acc[CT], bsum[CT];
-#pragma unroll
-    for (int c = 0; c < CT; ++c) acc[c] = bsum[c] = 0.f;
-#pragma unroll 4
-    for (int s = grp; s < a.B; s += 16) {
-        const size_t arow = a.act_lstride ? (size_t)learner * a.act_lstride + (size_t)s * a.ld_act
-                                          : (size_t)g[s] * a.ld_act;
-        const float x = act[arow + qq];
-        float gz[16];                                         // one row of dZ_L; entries beyond ldz are zero
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            f32x4 v = {0.f, 0.f, 0.f, 0.f};
-            if (4 * i < a.ldz) v = *(const f32x4*)(dz + (size_t)s * a.ldz + 4 * i);      // ldz is a multiple of 8
-            gz[4 * i] = v.x; gz[4 * i + 1] = v.y; gz[4 * i + 2] = v.z; gz[4 * i + 3] = v.w;
-        }
-#pragma unroll
-        for (int c = 0; c < CT; ++c) {
-            bsum[c] += gz[c];                                  // bias gradient: column sum of dZ_L
-            acc[c] = fmaf(gz[c], x, acc[c]);
-        }
-    }
-    float mine = 0.f, sum = 0.f;
-#pragma unroll
-    for (int c = 0; c < CT; ++c) {
-        const float bs = groups_sum(bsum[c]), v = groups_sum(acc[c]);
-        if (c == grp) { mine = v; sum = bs; }
-    }
-    if (live && grp < a.C) {
-        const size_t uat = (size_t)learner * a.w_lstride + (size_t)grp * a.d + q;
-        if (a.u) { mine = a.beta * a.u[uat] + mine; a.u[uat] = mine; }     // heavy ball inside the learner
-        a.wmaster[uat] = a.wmaster[uat] - a.lr * mine;
-    }
-    if (blockIdx.x == 0 && wave == 0 && pl == 0 && grp < a.C) {   // every lane holds the full column sums
-        const size_t at = (size_t)learner * a.w_lstride + grp;
-        if (a.ub) { sum = a.beta * a.ub[at] + sum; a.ub[at] = sum; }
-        a.bias[at] = a.bias[at] - a.lr * sum;
-    }
-}
-
 HeadArgs make_args(const LayerCall& c, const int32_t* y, const int32_t* idx, long idx_lstride, float* rowloss, bool bf16) {
     HeadArgs a = {};
     a.act = c.in; a.ld_act = c.ld_in; a.act_lstride = c.gather ? 0 : c.in_stride;
     a.gather = idx; a.gather_lstride = idx_lstride;
     a.wmul = bf16 ? (const void*)c.ws : (const void*)c.w;
     a.wmul_lstride = bf16 ? c.ws_stride : c.w_stride;
-    a.wmaster = c.w; a.w_lstride = c.w_stride; a.bias = c.b;
+    a.bias = c.b; a.w_lstride = c.w_stride;
     a.bhi = c.bhi; a.blo = c.blo; a.ws_lstride = c.ws_stride;
     a.y = y;
     a.dz = (void*)c.dz; a.ldz = c.ld_dz; a.dz_lstride = c.dz_stride;
     a.dz_prev = c.dz_prev; a.dz_prev_lstride = c.dz_prev_stride;
     a.rowloss = rowloss;
-    a.P = c.P; a.B = c.B; a.d = c.d_in; a.C = c.d_out; a.lr = c.lr;
-    a.u = c.u; a.ub = c.ub; a.beta = c.beta;
+    a.P = c.P; a.B = c.B; a.d = c.d_in; a.C = c.d_out;
     return a;
 }
 
@@ -335,18 +276,9 @@ hipError_t head_forward_backward(const LayerCall& c, const int32_t* y, const int
     return hipGetLastError();
 }
 
-hipError_t head_update(const LayerCall& c, const int32_t* idx, long idx_lstride, int bf16, hipStream_t st) {
-    if (bf16) {
-        hipLaunchKernelGGL(head_update_bf16_kernel, dim3(head_blocks(c.d_in), c.P, head_class_groups(c.P, c.d_in, c.d_out)), dim3(256), 0, st,
-                           head_step_args(c, idx, idx_lstride));
-    } else {
-        const HeadArgs a = make_args(c, nullptr, idx, idx_lstride, nullptr, false);
-        const dim3 grid((c.d_in + 15) / 16, c.P);
-        if (c.d_out <= 4) hipLaunchKernelGGL(head_update_f32_kernel<4>, grid, dim3(256), 0, st, a);
-        else if (c.d_out <= 8) hipLaunchKernelGGL(head_update_f32_kernel<8>, grid, dim3(256), 0, st, a);
-        else if (c.d_out <= 12) hipLaunchKernelGGL(head_update_f32_kernel<12>, grid, dim3(256), 0, st, a);
-        else hipLaunchKernelGGL(head_update_f32_kernel<16>, grid, dim3(256), 0, st, a);
-    }
+hipError_t head_update(const LayerCall& c, const int32_t* idx, long idx_lstride, hipStream_t st) {
+    hipLaunchKernelGGL(head_update_bf16_kernel, dim3(head_blocks(c.d_in), c.P, head_class_groups(c.P, c.d_in, c.d_out)), dim3(256), 0, st,
+                       head_step_args(c, idx, idx_lstride));
     return hipGetLastError();
 }
 

@@ -909,17 +909,13 @@ int issue_steps(kavg_ctx* c) {
                                           c->ws + c->lo.off_dz[L - 1], (long)c->B * c->lo.ldz, bf ? 1 : 0, rowloss_k, st));
         }
         if (!bf) {
-            // the data gradients of all layers, then the updates: of a thin last layer, and of all others in one launch
+            // the data gradients of all layers, then the updates of all in one launch
             for (int l = head ? L - 1 : L; l > 1; --l) {
                 Bracket br(c, KAVG_CLASS_BACKWARD);
                 KAVG_HIP(c, f32_backward_data(layer_call(c, l, k), st));
             }
-            if (head) {
-                Bracket br(c, KAVG_CLASS_HEAD);
-                KAVG_HIP(c, head_update(layer_call(c, L, k), idx_k, idx_ls, 0, st));
-            }
             std::vector<LayerCall> updates;
-            for (int l = head ? L - 1 : L; l >= 1; --l) updates.push_back(layer_call(c, l, k));
+            for (int l = L; l >= 1; --l) updates.push_back(layer_call(c, l, k));
             const int rc = issue_update_group(c, updates, head, k == c->K - 1);
             if (rc != KAVG_OK) return rc;
             continue;
@@ -942,7 +938,7 @@ int issue_steps(kavg_ctx* c) {
                 group.push_back(q);
             } else if (head && l == L) {
                 Bracket br(c, KAVG_CLASS_HEAD);
-                KAVG_HIP(c, head_update(q, idx_k, idx_ls, 1, st));
+                KAVG_HIP(c, head_update(q, idx_k, idx_ls, st));
             } else {
                 Bracket br(c, KAVG_CLASS_UPDATE);
                 KAVG_HIP(c, bf16_update(q, st));
@@ -1131,7 +1127,7 @@ int issue_steps_conv(kavg_ctx* c) {
                 group.push_back(q);
             } else if (head && l == L) {
                 Bracket br(c, KAVG_CLASS_HEAD);
-                KAVG_HIP(c, head_update(q, idx_k, idx_ls, 1, st));
+                KAVG_HIP(c, head_update(q, idx_k, idx_ls, st));
             } else {
                 Bracket br(c, KAVG_CLASS_UPDATE);
                 KAVG_HIP(c, bf16_update(q, st));
@@ -1313,7 +1309,7 @@ int issue_steps_deferred(kavg_ctx* c) {
             LayerCall q = call(l, k, slot);
             if (head && l == L) {
                 Bracket br(c, KAVG_CLASS_HEAD);
-                KAVG_HIP(c, head_update(q, idx_k, idx_ls, 1, st));       // the thin last layer is stepped at once
+                KAVG_HIP(c, head_update(q, idx_k, idx_ls, st));       // the thin last layer is stepped at once
                 continue;
             }
             if (l > 1) {

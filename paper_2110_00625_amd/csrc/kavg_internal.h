@@ -144,7 +144,7 @@ bool head_supported(int C);
 // idx: this step's indices of learner 0, idx_lstride elements between learners
 hipError_t head_forward_backward(const LayerCall& c, const int32_t* y, const int32_t* idx, long idx_lstride,
                                  float* rowloss, int bf16, hipStream_t st);
-hipError_t head_update(const LayerCall& c, const int32_t* idx, long idx_lstride, int bf16, hipStream_t st);
+hipError_t head_update(const LayerCall& c, const int32_t* idx, long idx_lstride, hipStream_t st);
 
 // ---- convolutional layers (conv.hip): 3x3, stride 1, zero padding 1, channels-last bf16 images ----
 // patches[j][(n,h,w)][(kh,kw,c)] from images in[j][n][h][w][c] (or, with gather, from rows gather[j*gstride+n] of a shared set)

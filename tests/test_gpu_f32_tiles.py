@@ -32,3 +32,13 @@ def test_learner_loop_at_tile_edges(P, K, B, dims, beta):
         g.set_params(g.params())                 # velocities start at zero
         o.beta, o.u = beta, np.zeros((o.P, o.n))
     _run_and_compare(g, o, dims, 2, TOL_FP32, "tiles %s" % (dims,))
+
+
+@pytest.mark.parametrize("P,K,B,dims,beta", [
+    (2, 2, 1, (20, 17, 8), 0.9),                 # one sample, one unit over a workgroup's sixteen, classes as one row of eight
+    (3, 2, 17, (33, 15, 9), 0.0),                # one sample over the sixteen groups, fewer units than a workgroup, nine classes
+    (2, 2, 80, (40, 64, 31, 16), 0.9),           # five samples per lane, sixteen classes
+    (3, 2, 65, (100, 12), 0.0),                  # the head alone, on gathered rows
+], ids=lambda v: "-".join(map(str, v)) if isinstance(v, tuple) else str(v))
+def test_head_in_the_update_launch(P, K, B, dims, beta):
+    test_learner_loop_at_tile_edges(P, K, B, dims, beta)
