@@ -569,6 +569,15 @@ int f32_forward_plan(int P, int B, int d_in, int d_out, int* chunk_out) {
     return (d_in + chunk - 1) / chunk;               // splits that actually receive work
 }
 
+// Up to sixteen partial products of a unit arrive in one round trip, beside the head's weights; more would be a round trip each
+// eight of every 64 units, in one wavefront per sample, where finish_forward_kernel has a lane for every unit.  Rounds, us, with
+// that launch and with the sums in the head: 3072-512-256-10, 8 learners of 64 (8 splits) 331 / 324; 300-500-10, 2 of 16 (4)
+// 210 / 196; 784-300-10, 4 of 16 (9) 103 / 97; 900-100-16, 2 of 32 (10) 95.5 / 85.5; 1024-1000-8, 2 of 32 (16) 132 / 131.
+bool f32_head_finishes(int P, int B, int d_in, int d_out) {
+    const int splits = f32_forward_plan(P, B, d_in, d_out, nullptr);
+    return splits > 1 && splits <= HEAD_SPLITS;
+}
+
 hipError_t f32_forward(const LayerCall& c, hipStream_t st) {
     RowArgs a = {};
     a.R = (const float*)c.in; a.r_lstride = c.gather ? 0 : c.in_stride; a.ldR = c.ld_in;    // gathered: one data set for all
@@ -586,7 +595,7 @@ hipError_t f32_forward(const LayerCall& c, hipStream_t st) {
     a.out = (float*)c.scratch;
     a.split_stride = (size_t)c.P * c.out_stride;
     hipError_t e = run_rows<EPI_PARTIAL>(a, c.P, st);
-    if (e != hipSuccess) return e;
+    if (e != hipSuccess || c.unfinished) return e;
     const size_t total = (size_t)c.P * c.out_stride;
     hipLaunchKernelGGL(finish_forward_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
                        (const float*)c.scratch, a.split_stride, a.splits, c.b, c.w_stride, (float*)c.out, c.P, c.B,

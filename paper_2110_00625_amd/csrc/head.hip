@@ -77,6 +77,9 @@ struct HeadArgs {
     void* dz; int ldz; size_t dz_lstride;                 // dZ_L [P][B][ldz]
     void* dz_prev; size_t dz_prev_lstride;                // dZ_{L-1} [P][B][d], null for a single-layer model
     float* rowloss;                                       // [P][B]
+    // fp32, FINISH > 0: A_{L-1} = relu(sum of the splits' partial products + bias of layer L-1), formed and written here
+    const float* partial; size_t split_stride; int splits;
+    const float* below_bias;                              // (stride w_lstride)
     int P, B, d, C;
 };
 
@@ -85,7 +88,9 @@ struct HeadArgs {
 // so that a lane's loads of a step go out together instead of one round trip per class.
 // KEEP: the row has at most 128 pieces (two per lane); they are fetched once and stay in registers for
 // the second pass (the data gradient) instead of being fetched again.
-template <bool BF16, int CT, bool KEEP>
+// FINISH: a row's activations are added up from the (at most FINISH) partial products of the layer below, in the order of
+// finish_forward_kernel (gemm_f32.hip), whose launch this saves: every unit is read by one lane here anyway.
+template <bool BF16, int CT, bool KEEP, int FINISH>
 __global__ void __launch_bounds__(256) head_forward_backward_kernel(HeadArgs a) {
     constexpr int N = Piece<BF16>::N;
     const int lane = threadIdx.x & 63;
@@ -115,21 +120,40 @@ __global__ void __launch_bounds__(256) head_forward_backward_kernel(HeadArgs a) 
 #pragma unroll
     for (int c = 0; c < CT; ++c) wrow[c] = (size_t)(c < a.C ? c : a.C - 1) * a.d;
 
+    // the partial products of a unit, requested together (those beyond the last re-read it and are not added)
+    auto request = [&](float (&t)[FINISH + 1], size_t unit) __attribute__((always_inline)) {
+#pragma unroll
+        for (int s = 0; s < FINISH; ++s) t[s] = a.partial[min(s, a.splits - 1) * a.split_stride + arow + unit];
+        t[FINISH] = a.below_bias[(size_t)learner * a.w_lstride + unit];
+    };
+    auto finish = [&](const float (&t)[FINISH + 1]) __attribute__((always_inline)) {
+        float z = 0.f;
+#pragma unroll
+        for (int s = 0; s < FINISH; ++s) if (s < a.splits) z += t[s];
+        return fmaxf(z + t[FINISH], 0.f);
+    };
+    float* const act_out = FINISH ? (float*)const_cast<void*>(a.act) : nullptr;
+
     float acc[CT];
 #pragma unroll
     for (int c = 0; c < CT; ++c) acc[c] = 0.f;
     Piece<BF16> xs[KEEP ? 2 : 1], ws[CT][KEEP ? 2 : 1];
     if constexpr (KEEP) {
+        float parts[2][FINISH + 1];
 #pragma unroll
         for (int it = 0; it < 2; ++it) {
             const int q = lane + 64 * it;
             const size_t qq = (size_t)(q < pieces ? q : pieces - 1) * N;      // clamped: no predicated loads
-            xs[it].fetch(a.act, arow + qq);
+            if constexpr (FINISH > 0) request(parts[it], qq); else xs[it].fetch(a.act, arow + qq);
 #pragma unroll
             for (int c = 0; c < CT; ++c) ws[c][it].fetch(W, wrow[c] + qq);
         }
 #pragma unroll
         for (int it = 0; it < 2; ++it) {
+            if constexpr (FINISH > 0) {
+                xs[it].r = finish(parts[it]);
+                if (lane + 64 * it < pieces) act_out[arow + lane + 64 * it] = xs[it].r;
+            }
             if (lane + 64 * it >= pieces) xs[it].clear();                      // contributes nothing to either pass
             xs[it].unpack();
 #pragma unroll
@@ -142,9 +166,11 @@ __global__ void __launch_bounds__(256) head_forward_backward_kernel(HeadArgs a) 
     } else {
         for (int q = lane; q < pieces; q += 64) {
             Piece<BF16> x, w[CT];
-            x.load(a.act, arow + (size_t)q * N);
+            float parts[FINISH + 1];
+            if constexpr (FINISH > 0) request(parts, q); else x.load(a.act, arow + (size_t)q * N);
 #pragma unroll
             for (int c = 0; c < CT; ++c) w[c].load(W, wrow[c] + (size_t)q * N);
+            if constexpr (FINISH > 0) { x.r = finish(parts); x.unpack(); act_out[arow + q] = x.r; }
 #pragma unroll
             for (int c = 0; c < CT; ++c)
 #pragma unroll
@@ -254,25 +280,35 @@ HeadArgs make_args(const LayerCall& c, const int32_t* y, const int32_t* idx, lon
 bool head_supported(int C) { return C <= CMAX; }
 
 namespace {
-template <bool BF16, bool KEEP>
+template <bool BF16, bool KEEP, int FINISH>
 void launch_fb2(const HeadArgs& a, dim3 grid, hipStream_t st) {
-    if (a.C <= 4) hipLaunchKernelGGL((head_forward_backward_kernel<BF16, 4, KEEP>), grid, dim3(256), 0, st, a);
-    else if (a.C <= 8) hipLaunchKernelGGL((head_forward_backward_kernel<BF16, 8, KEEP>), grid, dim3(256), 0, st, a);
-    else if (a.C <= 12) hipLaunchKernelGGL((head_forward_backward_kernel<BF16, 12, KEEP>), grid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((head_forward_backward_kernel<BF16, 16, KEEP && !BF16>), grid, dim3(256), 0, st, a);   // bf16 x 16 classes: too many registers to keep
+    if (a.C <= 4) hipLaunchKernelGGL((head_forward_backward_kernel<BF16, 4, KEEP, FINISH>), grid, dim3(256), 0, st, a);
+    else if (a.C <= 8) hipLaunchKernelGGL((head_forward_backward_kernel<BF16, 8, KEEP, FINISH>), grid, dim3(256), 0, st, a);
+    else if (a.C <= 12) hipLaunchKernelGGL((head_forward_backward_kernel<BF16, 12, KEEP, FINISH>), grid, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((head_forward_backward_kernel<BF16, 16, KEEP && !BF16, FINISH>), grid, dim3(256), 0, st, a);   // bf16 x 16 classes: too many registers to keep
 }
-template <bool BF16>
+template <bool BF16, int FINISH>
 void launch_fb(const HeadArgs& a, dim3 grid, hipStream_t st) {
     const int pieces = a.d / Piece<BF16>::N;
-    if (pieces <= 128) launch_fb2<BF16, true>(a, grid, st); else launch_fb2<BF16, false>(a, grid, st);
+    if (pieces <= 128) launch_fb2<BF16, true, FINISH>(a, grid, st); else launch_fb2<BF16, false, FINISH>(a, grid, st);
 }
 }  // namespace
 
 hipError_t head_forward_backward(const LayerCall& c, const int32_t* y, const int32_t* idx, long idx_lstride,
-                                 float* rowloss, int bf16, hipStream_t st) {
+                                 float* rowloss, int bf16, const LayerCall* below, hipStream_t st) {
     HeadArgs a = make_args(c, y, idx, idx_lstride, rowloss, bf16 != 0);
     dim3 grid((c.B + 3) / 4, c.P);
-    if (bf16) launch_fb<true>(a, grid, st); else launch_fb<false>(a, grid, st);
+    if (below) {
+        a.splits = f32_forward_plan(c.P, c.B, below->d_in, below->d_out, nullptr);
+        if (bf16 || c.gather || c.in != below->out || !below->scratch || a.splits < 2 || a.splits > HEAD_SPLITS) return hipErrorInvalidValue;
+        a.partial = (const float*)below->scratch; a.split_stride = (size_t)c.P * below->out_stride;
+        a.below_bias = below->b;
+        if (a.splits <= HEAD_SPLITS / 2) launch_fb<false, HEAD_SPLITS / 2>(a, grid, st); else launch_fb<false, HEAD_SPLITS>(a, grid, st);
+    } else if (bf16) {
+        launch_fb<true, 0>(a, grid, st);
+    } else {
+        launch_fb<false, 0>(a, grid, st);
+    }
     return hipGetLastError();
 }
 

@@ -33,6 +33,7 @@ __device__ __forceinline__ float groups_sum(float x) {
     return x;
 }
 
+constexpr int HEAD_SPLITS = 16;           // partial tiles of the layer below that head_forward_backward adds up at most
 constexpr int HEAD_CT = 4;                // classes at a time
 constexpr int HEAD_PIECES = 16;           // pieces of 8 input units per workgroup
 // floats between classes in a wavefront's exchange patch (36: classes fall on different banks); the patches of four wavefronts

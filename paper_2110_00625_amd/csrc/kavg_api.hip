@@ -887,12 +887,15 @@ int issue_steps(kavg_ctx* c) {
     // then its update) instead of four generic launches.
     const bool head = head_supported(c->dims[L]);
     const int chained = chained_layers(c), below = L - chained;          // layers 1 .. below run one by one
+    const unsigned apart = (1u << KAVG_CLASS_FORWARD) | (1u << KAVG_CLASS_HEAD);
+    const bool finish = !bf && head && L > 1 && !(c->prof_mask & apart) && f32_head_finishes(c->P, c->B, c->dims[L - 2], c->dims[L - 1]);
     for (int k = 0; k < c->K; ++k) {
         const int32_t* idx_k = c->idx() + (size_t)k * c->B;
         const long idx_ls = (long)c->K * c->B;
         float* rowloss_k = c->rowloss() + (size_t)k * c->P * c->B;
         for (int l = 1; l <= (head && !chained ? L - 1 : below); ++l) {      // forward
             LayerCall q = layer_call(c, l, k);
+            q.unfinished = finish && l == L - 1;
             Bracket br(c, KAVG_CLASS_FORWARD);
             KAVG_HIP(c, bf ? bf16_forward(q, st) : f32_forward(q, st));
         }
@@ -900,9 +903,9 @@ int issue_steps(kavg_ctx* c) {
             const int rc = issue_chain(c, below, k);
             if (rc != KAVG_OK) return rc;
         } else if (head) {
-            LayerCall q = layer_call(c, L, k);
+            const LayerCall q = layer_call(c, L, k), q_below = finish ? layer_call(c, L - 1, k) : q;
             Bracket br(c, KAVG_CLASS_HEAD);
-            KAVG_HIP(c, head_forward_backward(q, c->y, idx_k, idx_ls, rowloss_k, bf ? 1 : 0, st));
+            KAVG_HIP(c, head_forward_backward(q, c->y, idx_k, idx_ls, rowloss_k, bf ? 1 : 0, finish ? &q_below : nullptr, st));
         } else {
             Bracket br(c, KAVG_CLASS_LOSS);
             KAVG_HIP(c, launch_softmax_ce(c->logits(), c->lo.ldz, c->dims[L], c->y, idx_k, idx_ls, c->B, c->P,
@@ -1110,7 +1113,7 @@ int issue_steps_conv(kavg_ctx* c) {
             if (rc != KAVG_OK) return rc;
         } else if (head) {
             Bracket br(c, KAVG_CLASS_HEAD);
-            KAVG_HIP(c, head_forward_backward(layer_call(c, L, k), c->y, idx_k, idx_ls, rowloss_k, 1, st));
+            KAVG_HIP(c, head_forward_backward(layer_call(c, L, k), c->y, idx_k, idx_ls, rowloss_k, 1, nullptr, st));
         } else {
             Bracket br(c, KAVG_CLASS_LOSS);
             KAVG_HIP(c, launch_softmax_ce(c->logits(), lo.ldz, c->dims[L], c->y, idx_k, idx_ls, B, P,
@@ -1299,7 +1302,7 @@ int issue_steps_deferred(kavg_ctx* c) {
         if (head) {
             LayerCall q = call(L, k, slot);
             Bracket br(c, KAVG_CLASS_HEAD);
-            KAVG_HIP(c, head_forward_backward(q, c->y, idx_k, idx_ls, rowloss_k, 1, st));
+            KAVG_HIP(c, head_forward_backward(q, c->y, idx_k, idx_ls, rowloss_k, 1, nullptr, st));
         } else {
             Bracket br(c, KAVG_CLASS_LOSS);
             KAVG_HIP(c, launch_softmax_ce(c->logits(), lo.ldz, c->dims[L], c->y, idx_k, idx_ls, B, P, dzH(L, slot),

@@ -71,6 +71,7 @@ struct LayerCall {
     void* dz_prev; size_t dz_prev_stride;
     int relu;              // forward: apply ReLU (hidden layer) / keep fp32 logits (last layer)
     void* scratch;         // fp32 forward: partial tiles of a split contraction (see f32_forward_plan)
+    int unfinished;        // fp32 forward: leave them there, head_forward_backward adds them up (f32_head_finishes)
     float lr;
     // learner-level momentum: velocity of this layer's weights (learner 0; stride w_stride) and of its
     // bias, null when off.  u <- beta u + g, w <- w - lr u.
@@ -122,6 +123,8 @@ hipError_t launch_bias_step(uint16_t* bhi, uint16_t* blo, size_t b_stride, const
 // splits of the forward contraction of a layer and the contraction range of each; shapes only
 int f32_forward_plan(int P, int B, int d_in, int d_out, int* chunk_out);
 hipError_t f32_forward(const LayerCall& c, hipStream_t st);
+// whether a head above the layer d_in -> d_out adds up the partial tiles of that layer's split forward product
+bool f32_head_finishes(int P, int B, int d_in, int d_out);
 hipError_t f32_backward_data(const LayerCall& c, hipStream_t st);
 // all n layers in one launch, and the mean losses of a round where `losses` is not null
 hipError_t f32_update(const LayerCall* layers, int n, const LossMeans* losses, hipStream_t st);
@@ -141,9 +144,10 @@ hipError_t bf16_update_group(const LayerCall* layers, int n, const LossMeans* lo
 
 // ---- classifier head for small class counts (last layer: forward + loss + data gradient, then update) ----
 bool head_supported(int C);
-// idx: this step's indices of learner 0, idx_lstride elements between learners
+// idx: this step's indices of learner 0, idx_lstride elements between learners; below: the layer whose activations this one
+// finishes and writes (LayerCall::unfinished), null: none
 hipError_t head_forward_backward(const LayerCall& c, const int32_t* y, const int32_t* idx, long idx_lstride,
-                                 float* rowloss, int bf16, hipStream_t st);
+                                 float* rowloss, int bf16, const LayerCall* below, hipStream_t st);
 hipError_t head_update(const LayerCall& c, const int32_t* idx, long idx_lstride, hipStream_t st);
 
 // ---- convolutional layers (conv.hip): 3x3, stride 1, zero padding 1, channels-last bf16 images ----

@@ -42,3 +42,14 @@ def test_learner_loop_at_tile_edges(P, K, B, dims, beta):
 ], ids=lambda v: "-".join(map(str, v)) if isinstance(v, tuple) else str(v))
 def test_head_in_the_update_launch(P, K, B, dims, beta):
     test_learner_loop_at_tile_edges(P, K, B, dims, beta)
+
+
+@pytest.mark.parametrize("P,K,B,dims", [
+    (3, 2, 9, (129, 64, 4)),                     # two splits, one unit per lane
+    (2, 2, 5, (512, 130, 10)),                   # eight splits, units beyond two per lane, odd batch
+    (2, 2, 6, (70, 784, 127, 16)),               # nine splits, an odd number of units
+    (1, 2, 33, (1024, 65, 2)),                   # sixteen splits
+    (1, 2, 33, (2112, 65, 2)),                   # more: added up by a launch of their own
+])
+def test_split_product_finished_by_the_head(P, K, B, dims):
+    test_learner_loop_at_tile_edges(P, K, B, dims, 0.0)
