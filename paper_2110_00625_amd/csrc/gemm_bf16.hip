@@ -58,8 +58,10 @@ enum { MODE_FWD = 0, MODE_BWD = 1, MODE_UPD = 2 };
 // direct global->LDS loads (no registers, no LDS store instructions); k-contiguous operands only.
 // RING: a ring of LDS buffers filled, slices ahead, by two extra wavefronts that do nothing else
 // (the wavefronts that multiply never issue a memory load, so none of them stands in the queue of the
-// memory pipeline while its MFMAs could run); whole slices only.
-enum { PIPE_PLAIN = 0, PIPE_LDS2 = 1, PIPE_DMA = 2, PIPE_RING = 3 };
+// memory pipeline while its MFMAs could run); whole slices only.  LATE (update, long contractions): as PLAIN, but
+// the master is requested under the last slice, which leaves registers for a third workgroup per compute unit, and the tiles
+// of eight tile rows follow each other column by column.
+enum { PIPE_PLAIN = 0, PIPE_LDS2 = 1, PIPE_DMA = 2, PIPE_RING = 3, PIPE_LATE = 4 };
 constexpr int RING_LOADERS = 2, RING_BYTES = 144 * 1024;
 
 struct Operand {
@@ -447,7 +449,7 @@ struct Shape {
     static constexpr int R_ELEMS = DIRECT ? TR * BK : RTRANS ? BK * tpitch(TR) : TR * dpitch(BK);
     static constexpr int C_ELEMS = DIRECT ? TC * BK : CTRANS ? BK * tpitch(TC) : TC * dpitch(BK);
     static constexpr int RING_BUFS = RING_BYTES / ((R_ELEMS + C_ELEMS) * 2);
-    static constexpr int OPER_BYTES = (PIPE == PIPE_PLAIN ? 1 : PIPE == PIPE_RING ? RING_BUFS : 2) * (R_ELEMS + C_ELEMS) * 2;
+    static constexpr int OPER_BYTES = (PIPE == PIPE_PLAIN || PIPE == PIPE_LATE ? 1 : PIPE == PIPE_RING ? RING_BUFS : 2) * (R_ELEMS + C_ELEMS) * 2;
     static constexpr int STAGE_BYTES = MODE == MODE_UPD ? 4 * 32 * SPITCH * 4 : 0;
     static constexpr int KRED_BYTES = WK > 1 ? WR * WC * MR * MC * 16 * 64 * 4 : 0;   // one k group's partial tiles
     static constexpr int SMEM1 = OPER_BYTES > STAGE_BYTES ? OPER_BYTES : STAGE_BYTES;
@@ -465,14 +467,14 @@ struct Shape {
 // CONV_R / CONV_C: that operand is the implicit patch matrix of a convolution (Operand::cv_c).
 template <int MODE, int TR, int TC, int WR, int WC, int WK, int BK, bool RTRANS, bool CTRANS, int PIPE, bool SHADOW_CACHED = false,
           bool GATHER_C = false, bool CONV_R = false, bool CONV_C = false, bool MERGED = false>
-__global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING_LOADERS : 0))) gemm_bf16_kernel(Args a) {
+__global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING_LOADERS : 0)), PIPE == PIPE_LATE ? 3 : 1) gemm_bf16_kernel(Args a) {
     static_assert(!CONV_R || (!RTRANS && PIPE != PIPE_DMA), "implicit R operand: k-contiguous, staged through registers");
     static_assert(!CONV_C || (CTRANS && !GATHER_C && MODE == MODE_UPD), "implicit C operand: the update's transposed operand");
     constexpr int NW = WR * WC * WK, NT = 64 * NW;
     constexpr int MR = TR / (32 * WR), MC = TC / (32 * WC);
     static_assert(MR >= 1 && MC >= 1, "tile too small for the wave grid");
     static_assert((BK / 16) % WK == 0, "slice must split evenly over the k groups");
-    static_assert(MODE != MODE_UPD || (WK == 1 && NW == 4 && PIPE == PIPE_PLAIN), "the update epilogue assumes 4 wavefronts, no k split, one LDS buffer");
+    static_assert(MODE != MODE_UPD || (WK == 1 && NW == 4 && (PIPE == PIPE_PLAIN || PIPE == PIPE_LATE)), "the update epilogue assumes 4 wavefronts, no k split, one LDS buffer");
     constexpr bool DIRECT = PIPE == PIPE_DMA || PIPE == PIPE_RING;
     static_assert(PIPE != PIPE_RING || (WK == 1 && MODE != MODE_UPD), "ring pipeline: forward / backward-data without a k split");
     static_assert(NT % (TR / 8) == 0 && NT % (TC / 8) == 0, "loader column mapping");
@@ -494,7 +496,14 @@ __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING
     if (logical >= a.total_wg) return;
     const int learner = logical / (a.tiles_r * a.tiles_c);
     const int tile = logical - learner * (a.tiles_r * a.tiles_c);
-    const int tile_r = tile / a.tiles_c, tile_c = tile - tile_r * a.tiles_c;
+    int tile_r = tile / a.tiles_c, tile_c = tile - tile_r * a.tiles_c;
+    if (MODE == MODE_UPD && PIPE == PIPE_LATE) {
+        // (row by row, the workgroups that run on an XCD together would read eight megabytes of the C operand again for every two
+        // tile rows; 8 x 8 tiles share four)
+        const int first = tile / (8 * a.tiles_c) * 8, n = min(8, a.tiles_r - first), in = tile - first * a.tiles_c;
+        tile_c = in / n;
+        tile_r = first + in - tile_c * n;
+    }
     const int r0 = tile_r * TR, c0 = tile_c * TC;
 
     const uint16_t* Rbase = a.R.base + (size_t)learner * a.R.lstride;
@@ -742,10 +751,9 @@ __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING
             if constexpr (CONV_C) touch_at = (const uint32_t*)Cbase;     // nothing to prefetch: the images are this launch's own operand
         }
         fetch(0);
-        if (MODE == MODE_UPD) {
-            __builtin_amdgcn_sched_barrier(0);          // keep the operand loads the oldest
+        auto master = [&]() __attribute__((always_inline)) {
             // The master tile (both planes) is independent of the product: its loads go out right after
-            // the first operand slice and are in flight during the contraction.  They are issued
+            // the first operand slice (LATE: the last one) and are in flight during the contraction.  They are issued
             // without predicates (rows and columns beyond the layer are clamped; those lanes store
             // nothing later), so that the compiler can count them: the wait for the operand slice is
             // then "all but these", not "everything".
@@ -766,20 +774,42 @@ __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING
                                                : __builtin_nontemporal_load((const u32x4*)(hbase + (size_t)r * a.nC + c));
                     mlo[i][it] = __builtin_nontemporal_load((const u32x4*)(lbase + (size_t)r * a.nC + c));
                 }
+        };
+        if (MODE == MODE_UPD) {
+            __builtin_amdgcn_sched_barrier(0);          // keep the operand loads the oldest
+            if (PIPE != PIPE_LATE) master();
             __builtin_amdgcn_sched_barrier(0);
             touched = *touch_at;
         }
-        if (PIPE == PIPE_PLAIN) {
+        // R tile of the update is dZ as [sample][unit]: column tid summed over the slice's samples
+        auto add_bias = [&]() __attribute__((always_inline)) {
+            if (MODE == MODE_UPD && tile_c == 0 && tid < TR) {
+#pragma unroll 8
+                for (int k = 0; k < BK; ++k) bias_sum += bf16_to_f32(Rs[k * tpitch(TR) + tid]);
+            }
+        };
+        if (PIPE == PIPE_LATE) {
+            auto slice = [&](auto request) __attribute__((always_inline)) {
+                stash(0);
+                __syncthreads();
+                request();
+                multiply(0);
+                add_bias();
+                __syncthreads();
+            };
+            for (int k0 = BK; k0 < a.nK; k0 += BK) slice([&]() __attribute__((always_inline)) { fetch(k0); });
+            slice([&]() __attribute__((always_inline)) {
+                __builtin_amdgcn_sched_barrier(0);
+                master();
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        } else if (PIPE == PIPE_PLAIN) {
             auto slice = [&](int k0) {
                 stash(0);
                 __syncthreads();
                 if (k0 + BK < a.nK) fetch(k0 + BK);     // next slice in flight during the MFMAs
                 multiply(0);
-                if (MODE == MODE_UPD && tile_c == 0 && tid < TR) {
-                    // R tile of the update is dZ as [sample][unit]: column tid summed over the slice's samples
-#pragma unroll 8
-                    for (int k = 0; k < BK; ++k) bias_sum += bf16_to_f32(Rs[k * tpitch(TR) + tid]);
-                }
+                add_bias();
                 __syncthreads();
             };
             // The first slice stands outside the loop: there the compiler knows that the operand loads
@@ -1155,6 +1185,20 @@ hipError_t bf16_update(const LayerCall& c, hipStream_t st) {
     // Tile shapes from measured sweeps (whole rounds, same box): wavefront tiles of 32x64 in both regimes
     // (128-byte row segments per plane), as 128x64 where the bf16 planes stay in the memory-side
     // cache (CIFAR-MLP) and as 64x128 where they stream (the 4096-wide workloads with batches up to 128).
+    if (rows > 256 && !c.partial) {
+        // Here the contraction is the longer part, its operands come from memory, and one slice of look-ahead in two workgroups per
+        // compute unit does not cover that: a third workgroup instead of an early master.  (Refresh of 32 learners, 1024 rows, us:
+        // 4096 -> 4096 2139 / 1785 = 615 TFLOP/s, 3072 -> 4096 1631 / 1319.  Rounds, without / with it: 3072-4096-10, 32 learners,
+        // 320 rows 4020 / 4000; 4000-2000-100, 8 learners, 300 rows 1100 / 1094; planes in the cache: 1032-2056-520-12, 5 learners,
+        // 1000 rows 1645 / 1602, 3072-1024-1024-10, 16 learners, 512 rows 1238 / 1215; with 256 rows, every step of the 4096-wide
+        // model, 22 200 / 22 380.)
+        if (c.shadow_cached) {
+            if (c.gather) return launch<MODE_UPD, 128, 128, 2, 2, 1, 64, true, true, PIPE_LATE, true, true>(a, P, st);
+            return launch<MODE_UPD, 128, 128, 2, 2, 1, 64, true, true, PIPE_LATE, true, false>(a, P, st);
+        }
+        if (c.gather) return launch<MODE_UPD, 128, 128, 2, 2, 1, 64, true, true, PIPE_LATE, false, true>(a, P, st);
+        return launch<MODE_UPD, 128, 128, 2, 2, 1, 64, true, true, PIPE_LATE, false, false>(a, P, st);
+    }
     if (c.shadow_cached) {
         if (c.gather) return launch<MODE_UPD, 128, 64, 4, 1, 1, 64, true, true, PIPE_PLAIN, true, true>(a, P, st);
         return launch<MODE_UPD, 128, 64, 4, 1, 1, 64, true, true, PIPE_PLAIN, true, false>(a, P, st);
