@@ -1185,13 +1185,15 @@ hipError_t bf16_update(const LayerCall& c, hipStream_t st) {
     // Tile shapes from measured sweeps (whole rounds, same box): wavefront tiles of 32x64 in both regimes
     // (128-byte row segments per plane), as 128x64 where the bf16 planes stay in the memory-side
     // cache (CIFAR-MLP) and as 64x128 where they stream (the 4096-wide workloads with batches up to 128).
-    if (rows > 256 && !c.partial) {
+    const long tiles128 = (long)((a.nR + 127) / 128) * ((a.nC + 127) / 128) * P;
+    if (rows > 256 && !c.partial && (!c.shadow_cached || tiles128 >= 512)) {
         // Here the contraction is the longer part, its operands come from memory, and one slice of look-ahead in two workgroups per
         // compute unit does not cover that: a third workgroup instead of an early master.  (Refresh of 32 learners, 1024 rows, us:
         // 4096 -> 4096 2139 / 1785 = 615 TFLOP/s, 3072 -> 4096 1631 / 1319.  Rounds, without / with it: 3072-4096-10, 32 learners,
-        // 320 rows 4020 / 4000; 4000-2000-100, 8 learners, 300 rows 1100 / 1094; planes in the cache: 1032-2056-520-12, 5 learners,
-        // 1000 rows 1645 / 1602, 3072-1024-1024-10, 16 learners, 512 rows 1238 / 1215; with 256 rows, every step of the 4096-wide
-        // model, 22 200 / 22 380.)
+        // 320 rows 4020 / 4000; 4000-2000-100, 8 learners, 300 rows 1100 / 1094; with 256 rows, every step of the 4096-wide model,
+        // 22 200 / 22 380.)  Where the planes are cached the other choice is a tile half as large, which wins below two
+        // workgroups per compute unit: 3072-1024-1024-10, 16 learners, 512 rows, 1024 and more tiles 1243 / 1220; 567 tiles, 7
+        // learners, 1000 rows 1217 / 1213; 384, 6 learners, 768 rows 653 / 660; 126 and 315, 7 learners, 1248 rows 803 / 812.
         if (c.shadow_cached) {
             if (c.gather) return launch<MODE_UPD, 128, 128, 2, 2, 1, 64, true, true, PIPE_LATE, true, true>(a, P, st);
             return launch<MODE_UPD, 128, 128, 2, 2, 1, 64, true, true, PIPE_LATE, true, false>(a, P, st);
