@@ -24,13 +24,13 @@
 // What bounds these kernels: 3072-512 with 64 rows and 8 learners is 1.6 GFLOP per product, 10 us of the matrix
 // cores' fp32 rate; the update also moves 100 MB of weights, 15 us out of the memory-side cache.  Measured on
 // 3072-512-256-10 (8 learners, 64 rows): split forward product 24 -> 14 us per launch (mean of the two layers),
-// backward-data 24 -> 11 us, the updates of a step 75 -> 30 us; a round of four steps 657 -> 331 us.  (Before: 64x64
+// backward-data 24 -> 11 us, the updates of a step 75 -> 30 us; a round of four steps 657 -> 325 us.  (Before: 64x64
 // tiles everywhere, operands moved word by word, one slice ahead, the weights read after the contraction.)
 //
 // The forward pass may split the contraction over several workgroups where a layer has few output tiles: each writes
-// its partial tile to a scratch buffer and a second small kernel adds the partials in ascending split order, then
-// applies bias and ReLU.  The updates of all layers of a step are one launch: they depend
-// on nothing but the backward pass, and on small models each launch is a few microseconds of latency.
+// its partial tile to a scratch buffer and a second small kernel (below a head: the head's, f32_head_finishes) adds the
+// partials in ascending split order, then applies bias and ReLU.  The updates of all layers of a step are one launch: they
+// depend on nothing but the backward pass, and on small models each launch is a few microseconds of latency.
 #include "kavg_internal.h"
 #include "head_update.h"
 #include "loss_mean.h"
