@@ -369,11 +369,15 @@ __global__ void __launch_bounds__(NT, 2) chain_kernel(Args a) {
                 *(u32x4*)(zbelow + wave * pitch(d) + p) = o;
             }
     }
-    __syncthreads();
+    // These rows leave LDS before the barrier: with a head the first product below it writes to the place of the last layer's
+    // gradients again.  A wavefront copies the row that it wrote itself, and its LDS accesses complete in order.
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     copy_out(ztop, ldz, top.dz);
     if (HEAD && below) copy_out(zbelow, top.d_in, below);
+    __syncthreads();
 
-    // data gradients
+    // Data gradients.  The two places take turns: a product reads one and writes the other, the copy out of the one written stands
+    // between the barrier behind that product and the barrier behind the next, and only the product after that writes there again.
 #pragma unroll 1
     for (int i = HEAD ? a.L - 2 : a.L - 1; i >= downto; --i) {
         const Layer l = a.layer[i];

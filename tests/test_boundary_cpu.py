@@ -203,3 +203,18 @@ def test_multiply_shift_division_is_exact_over_its_stated_range(tmp_path):
     rng = np.random.default_rng(11)
     n = np.concatenate([rng.integers(0, 1 << 30, size=3000, dtype=np.uint64), np.arange(0, 70000, 7, dtype=np.uint64)]).astype(np.uint32)
     assert lib.check(n.ctypes.data, n.size, 1 << 14) == 0
+
+
+def test_rows_leave_lds_before_their_place_is_written_again():
+    """chain_bf16.hip: with a head the first data gradient goes to the place of the last layer's gradients (the two places take
+    turns), so the rows of all wavefronts must have been copied out of it before the barrier that lets the first of them go on."""
+    text = open(os.path.join(ROOT, "paper_2110_00625_amd", "csrc", "chain_bf16.hip")).read()
+    kernel = text[text.index("chain_kernel(Args a)"):text.index("size_t lds_plan")]
+    rest = kernel[kernel.index("// loss and the gradients"):]
+    loss, products = re.split(r"for \(int i = HEAD \? a\.L - 2 : a\.L - 1; i >= downto; --i\)", rest)
+    assert loss.count("__syncthreads()") == 1
+    copies = [m.start() for m in re.finditer(r"copy_out\((?:ztop|zbelow),", loss)]
+    assert len(copies) == 2 and max(copies) < loss.index("__syncthreads()")
+    # in the loop: a product, a barrier, the copy out of what it wrote
+    assert products.index("product(yes") < products.index("__syncthreads()") < products.index("copy_out(to")
+    assert products.count("__syncthreads()") == 1 and products.count("copy_out(") == 1
