@@ -218,3 +218,14 @@ def test_rows_leave_lds_before_their_place_is_written_again():
     # in the loop: a product, a barrier, the copy out of what it wrote
     assert products.index("product(yes") < products.index("__syncthreads()") < products.index("copy_out(to")
     assert products.count("__syncthreads()") == 1 and products.count("copy_out(") == 1
+
+
+def test_cases_of_the_one_launch_test_run_as_one_launch(lib):
+    """tests/test_gpu_chain.py compares the launch with separate ones: a shape that the rule leaves apart would compare those
+    with themselves."""
+    from tests.test_gpu_chain import CASES, CONVOLUTIONS
+    from tests.util import chained_layers
+    for P, _, B, dims, _, layers in CASES:
+        assert 0 < layers == chained_layers(P, B, dims), dims
+    for channels, hidden, B, C, layers in CONVOLUTIONS:
+        assert 0 < layers == chained_layers(2, B, (channels[-1],) + hidden + (C,), True), (channels, hidden, C)

@@ -1,5 +1,19 @@
 """Helpers shared by the parity tests (no arithmetic of the method)."""
+import ctypes
+
 import numpy as np
+
+from paper_2110_00625_amd import kavg
+
+
+def chained_layers(P, B, dims, behind_convolutions=False):
+    """How many of the last layers of a bf16 MLP run in one launch: the library's own rule (chain_layers in
+    csrc/chain_bf16.h, `int chain_layers(int, int, int, const int*, bool)`), on the host."""
+    rule = kavg.load_library()._ZN4kavg12chain_layersEiiiPKib
+    rule.restype = ctypes.c_int
+    rule.argtypes = [ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_void_p, ctypes.c_bool]
+    d = (ctypes.c_int * len(dims))(*dims)
+    return rule(P, B, len(dims) - 1, ctypes.addressof(d), behind_convolutions)
 
 
 def layer_slices(dims):
