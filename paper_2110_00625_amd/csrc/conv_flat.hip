@@ -337,19 +337,20 @@ __global__ void __launch_bounds__(NT, 2) conv_flat_kernel(FlatArgs a) {
     }
 }
 
-// pooled[image][channel] = bf16(mean): one lane per output adds the image's partial sums in ascending order
-__global__ void __launch_bounds__(NT) pool_finish_kernel(const float* sums, uint16_t* pooled, int B, int image, int last, int slots, int groups, int pitch, int c, float inv,
-                                                         int total) {
-    const int e = blockIdx.x * NT + threadIdx.x;
-    if (e >= total) return;
-    const int ch = e % c, img = e / c, learner = img / B, n = img - learner * B;
+// pooled[learner][image][channel] = bf16(mean): one lane per output adds the image's partial sums in ascending order.  (One row of
+// the grid per learner: all learners' outputs together may be more than 2^31.)
+__global__ void __launch_bounds__(NT) pool_finish_kernel(const float* sums, uint16_t* pooled, int image, int last, int slots, int groups, int pitch, int c, float inv,
+                                                         int outputs) {
+    const int e = blockIdx.x * NT + threadIdx.x, learner = blockIdx.y;
+    if (e >= outputs) return;
+    const int ch = e % c, n = e / c;
     const int g1 = (n * image + last) / (PB * 32);
     const float* p = sums + (size_t)learner * groups * slots * pitch + ch;
     float s = 0.f;
 #pragma unroll 4
     for (int g = n * image / (PB * 32); g <= g1; ++g) s += p[((size_t)g * slots + n - g * (PB * 32) / image) * pitch];
     const __bf16 h = (__bf16)(s * inv);                       // round to nearest even
-    pooled[e] = __builtin_bit_cast(uint16_t, h);
+    pooled[(size_t)learner * outputs + e] = __builtin_bit_cast(uint16_t, h);
 }
 
 __global__ void __launch_bounds__(NT) flat_table_kernel(int32_t* table, int len, int end, int H, int W) {
@@ -509,9 +510,9 @@ size_t conv_pool_elems(int P, int B, int H, int W, const FlatPlan& plan) {
 }
 
 hipError_t launch_pool_finish(const float* sums, const FlatPlan& plan, void* pooled, int P, int B, int H, int W, int c, hipStream_t st) {
-    const int end = ((B - 1) * (H + 1) + H - 1) * (W + 1) + W, TP = plan.PWAVES * PB * 32, total = P * B * c;
-    hipLaunchKernelGGL(pool_finish_kernel, dim3((total + NT - 1) / NT), dim3(NT), 0, st, sums, (uint16_t*)pooled, B, (H + 1) * (W + 1),
-                       (H - 1) * (W + 1) + W - 1, conv_pool_slots(H, W), (end + TP - 1) / TP * plan.PWAVES, plan.blocks * 32, c, 1.0f / (float)(H * W), total);
+    const int end = ((B - 1) * (H + 1) + H - 1) * (W + 1) + W, TP = plan.PWAVES * PB * 32, outputs = B * c;      // (at most 2^16 images of 128 channels)
+    hipLaunchKernelGGL(pool_finish_kernel, dim3((outputs + NT - 1) / NT, P), dim3(NT), 0, st, sums, (uint16_t*)pooled, (H + 1) * (W + 1),
+                       (H - 1) * (W + 1) + W - 1, conv_pool_slots(H, W), (end + TP - 1) / TP * plan.PWAVES, plan.blocks * 32, c, 1.0f / (float)(H * W), outputs);
     return hipGetLastError();
 }
 

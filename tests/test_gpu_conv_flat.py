@@ -57,6 +57,22 @@ def test_last_convolution(P, B, H, W, channels, dims):
     test_one_step(P, B, H, W, channels, dims)
 
 
+def test_mean_over_more_than_2_to_the_31_outputs():
+    """256 learners of 65 536 images of two pixels and 128 channels: 2^31 means."""
+    P, B, channels, dims = 256, 65536, (8, 128), (128, 10)
+    g, o, spec = _setup(P, 1, B, 1, 2, channels, dims, 78, lr=0.5)
+    start = g.params().astype(np.float64)
+    g.local_steps()
+    sample = [0, 127, 128, P - 1]
+    o.local_steps(learners=sample)
+    for j in sample:
+        got, want = g.replica(j) - start, np.asarray(o.replica(j)) - start
+        for name, sl in conv_slices(spec):
+            e = np.max(np.abs(got[sl] - want[sl])) / max(np.max(np.abs(want[sl])), 1e-30)
+            assert e < 2.0 ** -8, "%s of learner %d: %.3g" % (name, j, e)      # (as above)
+    g.close()
+
+
 def test_profile_counts_the_packing_of_the_weights():
     """A step's forward launches: the packed weights, two convolutions, the mean over the positions (the last layer of ten
     classes runs in the head kernels)."""
