@@ -87,9 +87,11 @@ __device__ __forceinline__ bf16x8 frag_tr(const uint16_t* patch, int pitch, int 
     return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-// bytes of the pixels of a tile, which the output patches of the four wavefronts lie over
+// bytes of the output patches of the four wavefronts, and of the pixels of a tile, which those lie over; behind the patches
+// a byte for each position of each wavefront (LAST: in the tile, for LDS beyond it would cost the widest images a kernel)
+__host__ __device__ constexpr int patch_area(int NB) { return 4 * 32 * (NB * 32 + 8) * 2; }
 __host__ __device__ constexpr int tile_area(int n_px, int CK, int NB) {
-    return n_px * (CK + 8) * 2 > 4 * 32 * (NB * 32 + 8) * 2 ? n_px * (CK + 8) * 2 : 4 * 32 * (NB * 32 + 8) * 2;
+    return n_px * (CK + 8) * 2 > patch_area(NB) + 4 * PB * 32 ? n_px * (CK + 8) * 2 : patch_area(NB) + 4 * PB * 32;
 }
 
 // LAST (forward): the layer below the mean over the positions; bits and partial sums instead of activations
@@ -105,7 +107,6 @@ __global__ void __launch_bounds__(NT, 2) conv_flat_kernel(FlatArgs a) {
     typedef typename std::conditional<KIND == FWD_GATHER, int64_t, int2>::type Source;
     Source* const SRC = (Source*)(smem + tile_area(n_px, CK, NB));      // where a pixel lies: int2 (pixel, image) or pixel of the data set; -1: margin
     float* const BIAS = (float*)(SRC + n_px);
-    uint8_t* const SLOT = (uint8_t*)(BIAS + 128);         // LAST: place of a position's image among those of its wavefront; 255: margin
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int pw = wave % PWAVES, cw = wave / PWAVES;
     // workgroup g runs on XCD g mod 8: each XCD gets one contiguous range of (learner, tile)
@@ -132,13 +133,6 @@ __global__ void __launch_bounds__(NT, 2) conv_flat_kernel(FlatArgs a) {
             SRC[i] = px < 0 ? -1 : ((int64_t)a.gather[(long)learner * a.gather_lstride + n] - n) * (a.H * a.W) + px;
         else
             SRC[i] = make_int2(px, n);
-    }
-    if constexpr (LAST) {
-        for (int p = tid; p < TP; p += NT) {
-            const int px = a.table[min(q0 + p + pitch + 1, a.table_len - 1)];
-            const int first = (q0 + (p & ~(PB * 32 - 1))) / a.image;
-            SLOT[p] = px < 0 ? 255 : (uint8_t)((int)fastdiv((uint32_t)px, a.div_hw_m, a.div_hw_s) - first);
-        }
     }
     if constexpr (!BACK) {
         for (int i = tid; i < 128; i += NT) {
@@ -249,7 +243,15 @@ __global__ void __launch_bounds__(NT, 2) conv_flat_kernel(FlatArgs a) {
     };
     if constexpr (BACK) fetch_mask(0);
     f32x16 sums[LAST ? NB : 1];                               // [place of an image][channel] of the wavefront's positions
+    uint8_t* const SLOT = (uint8_t*)smem + patch_area(NB) + wave * (PB * 32);      // LAST: place of a position's image among those of its wavefront; 255: margin
     if constexpr (LAST) {
+        const int first = (q0 + pw * PB * 32) / a.image;
+#pragma unroll
+        for (int h = 0; h < PB / 2; ++h) {
+            const int px = position(2 * h + (lane >> 5), lane & 31);
+            SLOT[h * 64 + lane] = px < 0 ? 255 : (uint8_t)((int)fastdiv((uint32_t)px, a.div_hw_m, a.div_hw_s) - first);
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 #pragma unroll
         for (int j = 0; j < NB; ++j)
 #pragma unroll
@@ -291,7 +293,7 @@ __global__ void __launch_bounds__(NT, 2) conv_flat_kernel(FlatArgs a) {
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
-                const u32x2 sl = *(const u32x2*)(SLOT + (pw * PB + b) * 32 + t * 16 + (lane >> 5) * 8);
+                const u32x2 sl = *(const u32x2*)(SLOT + b * 32 + t * 16 + (lane >> 5) * 8);
                 u32x4 ones;
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
@@ -392,10 +394,10 @@ __global__ void __launch_bounds__(NT) pack_weights_kernel(PackArgs a) {
     *(u32x4*)(d.frag + (size_t)blockIdx.y * d.frag_lstride + (size_t)e * 8) = v;
 }
 
-// the tile, where its pixels lie, the bias, the places of images
+// the tile, where its pixels lie, the bias
 size_t lds_bytes(const FlatPlan& p, int W) {
     const int n_px = p.PWAVES * PB * 32 + 2 * (W + 1) + 2;
-    return (size_t)tile_area(n_px, p.CK, p.NB) + (size_t)n_px * 8 + 128 * 4 + p.PWAVES * PB * 32;
+    return (size_t)tile_area(n_px, p.CK, p.NB) + (size_t)n_px * 8 + 128 * 4;
 }
 
 FlatArgs make_args(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag, const int32_t* table) {

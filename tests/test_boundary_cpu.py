@@ -229,3 +229,21 @@ def test_cases_of_the_one_launch_test_run_as_one_launch(lib):
         assert 0 < layers == chained_layers(P, B, dims), dims
     for channels, hidden, B, C, layers in CONVOLUTIONS:
         assert 0 < layers == chained_layers(2, B, (channels[-1],) + hidden + (C,), True), (channels, hidden, C)
+
+
+def test_convolutions_of_wide_images_keep_their_kernels(lib):
+    """conv_flat_plan (conv_flat.hip): the channels of a group are the most whose tile -- positions and two margins of a row and
+    a pixel each, 16 bytes behind the channels, 8 bytes per pixel for where it lies, 512 for the bias -- leaves room for two
+    workgroups per compute unit.  The widths are those where 512 bytes more would take a group or the whole kernel away."""
+    plan = lib._ZN4kavg14conv_flat_planEiiiiiPNS_8FlatPlanE
+    plan.restype = ctypes.c_bool
+    for W in (64, 80, 81, 137, 202, 204, 209, 332, 464, 465, 468, 469, 594, 596, 597):
+        for c_in, c_out in ((16, 16), (48, 64), (64, 64), (64, 128)):
+            positions, most = (512, 3) if c_out <= 64 else (256, 4)
+            pixels, slabs = positions + 2 * (W + 1) + 2, c_in // 16
+            fit = [n for n in range(1, min(most, slabs) + 1) if slabs % n == 0 and pixels * ((16 * n + 8) * 2 + 8) + 512 <= 80 * 1024]
+            got = (ctypes.c_int * 5)()
+            ok = plan(2, 8, W, c_in, c_out, got)
+            assert ok == bool(fit), (W, c_in, c_out)
+            if ok:
+                assert got[0] == 16 * max(fit) and got[3] == slabs, (W, c_in, c_out, list(got))

@@ -49,6 +49,9 @@ LAST = [
     (2, 5, 32, 32, (8, 32, 32, 64), (64, 10)),       # an odd batch: the gradients of the kernels for any width
     (2, 4, 16, 32, (8, 64, 64, 128), (128, 17)),     # an even one: those for 32 pixels, from bits
     (1, 2, 13, 47, (8, 40, 104), (104, 10)),
+    (1, 2, 3, 80, (8, 48, 64), (64, 10)),            # the widest images whose three slabs come at once
+    (1, 3, 2, 468, (8, 16), (16, 10)),               # the widest images of all, four wavefronts side by side
+    (1, 2, 2, 596, (8, 16, 72), (72, 10)),           # ... and two
 ]
 
 
