@@ -76,6 +76,14 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
     return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){lo, hi}, bf16x2));      // round to nearest even
 }
 
+// Two bf16 numbers, the largest finite one in place of infinity: in a product with ones and zeros an infinity would reach every
+// sum (its zeros are NaN).  A sum that holds such a number is at least as large, and infinite again in pool_finish_kernel.
+constexpr uint32_t BF16_MAX = 0x7F7Fu;
+__device__ __forceinline__ uint32_t finite2(uint32_t two) {
+    typedef short i16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_min(__builtin_bit_cast(i16x2, two), (i16x2){(short)BF16_MAX, (short)BF16_MAX}));
+}
+
 // fragment of a [position][channel] patch by transpose reads: lane l receives channel x0 + l%32 at positions 8 (l/32) .. +7
 __device__ __forceinline__ bf16x8 frag_tr(const uint16_t* patch, int pitch, int x0, int lane) {
     typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
@@ -280,7 +288,8 @@ __global__ void __launch_bounds__(NT, 2) conv_flat_kernel(FlatArgs a) {
                     v2 = fmaxf(v2 + bias.z, 0.f);
                     v3 = fmaxf(v3 + bias.w, 0.f);
                 }
-                const u32x2 o = {pack_bf16x2(v0, v1), pack_bf16x2(v2, v3)};
+                u32x2 o = {pack_bf16x2(v0, v1), pack_bf16x2(v2, v3)};
+                if constexpr (LAST) o = (u32x2){finite2(o.x), finite2(o.y)};
                 *(u32x2*)(patch + (lane & 31) * OP + j * 32 + q * 8 + (lane >> 5) * 4) = o;
                 if constexpr (LAST) {
                     const uint32_t four = (o.x & 0x7FFFu ? 1u : 0u) | (o.x & 0x7FFF0000u ? 2u : 0u) | (o.y & 0x7FFFu ? 4u : 0u) | (o.y & 0x7FFF0000u ? 8u : 0u);
@@ -350,7 +359,10 @@ __global__ void __launch_bounds__(NT) pool_finish_kernel(const float* sums, uint
     const float* p = sums + (size_t)learner * groups * slots * pitch + ch;
     float s = 0.f;
 #pragma unroll 4
-    for (int g = n * image / (PB * 32); g <= g1; ++g) s += p[((size_t)g * slots + n - g * (PB * 32) / image) * pitch];
+    for (int g = n * image / (PB * 32); g <= g1; ++g) {
+        const float x = p[((size_t)g * slots + n - g * (PB * 32) / image) * pitch];
+        s += x < __builtin_bit_cast(float, BF16_MAX << 16) ? x : INFINITY;      // (finite2)
+    }
     const __bf16 h = (__bf16)(s * inv);                       // round to nearest even
     pooled[(size_t)learner * outputs + e] = __builtin_bit_cast(uint16_t, h);
 }

@@ -3,6 +3,8 @@ against the oracle, on the scale of one local step: replica - start = -lr * grad
 import numpy as np
 import pytest
 
+from oracle import conv_oracle as C
+from paper_2110_00625_amd import kavg
 from tests.test_gpu_conv import _setup, conv_slices
 
 pytestmark = pytest.mark.gpu
@@ -58,6 +60,40 @@ LAST = [
 @pytest.mark.parametrize("P,B,H,W,channels,dims", LAST, ids=["%dx%d-%s" % (c[2], c[3], "-".join(map(str, c[4]))) for c in LAST])
 def test_last_convolution(P, B, H, W, channels, dims):
     test_one_step(P, B, H, W, channels, dims)
+
+
+@pytest.mark.parametrize("size,bad", [(3, 0), (3, 7), (12, 2)], ids=["first-of-eight", "last-of-eight", "two-tiles"])
+def test_an_infinite_activation_stays_in_its_image(size, bad):
+    """One image whose first output channel overflows bf16.  Every hidden unit takes that channel with a negative weight, so
+    the image's hidden layer is zero and its loss log C, and the losses of the other images, whose sums over the positions are
+    formed beside its own, are what they are without it."""
+    torch = pytest.importorskip("torch")
+    B, channels, dims = 9, (8, 16), (16, 8, 3)
+    spec = C.ConvSpec(size, size, channels, dims)
+    rng = np.random.default_rng(21)
+    X = torch.from_numpy(rng.standard_normal((B, size, size, 8)).astype(np.float32)).to(torch.bfloat16)
+    X[bad] = 0.0
+    X[bad, :, :, 0] = 3e38
+    y = rng.integers(0, 3, size=B).astype(np.int32)
+    w = (rng.standard_normal(spec.num_params()) * 0.3).astype(np.float32)
+    convs, Ws, bs = C.unpack(w, spec)                        # (views into w)
+    convs[0][0][...] *= np.arange(8) > 0                     # input channel 0: the centre tap of output channel 0 alone
+    convs[0][0][0, 1, 1, 0] = 4.0
+    Ws[0][:, 0] = -0.5
+    bs[0][:], bs[1][:] = 1.0, 0.0
+    w = w.astype(np.float32)
+
+    g = kavg.MAvg(2, 1, 0.0, 0.0, dims, B, kavg.KAVG_BF16, index_seed=1, conv=(size, size, channels))
+    g.set_data(X.cuda(), torch.from_numpy(y).cuda())
+    g.set_params(w)
+    g.set_indices(torch.arange(B, dtype=torch.int32, device="cuda").repeat(2))
+    g.local_steps()
+    others = [i for i in range(B) if i != bad]
+    loss, _ = C.minibatch_gradient(w.astype(np.float64), spec, X.float().numpy().reshape(B, -1)[others], y[others], bf16=True)
+    want = (loss * (B - 1) + np.log(3.0)) / B
+    assert abs(loss - np.log(3.0)) > 0.02                    # (what the others would have if their hidden layers were lost)
+    assert np.max(np.abs(g.losses() - want)) < 1e-3, (g.losses(), want, loss)
+    g.close()
 
 
 def test_mean_over_more_than_2_to_the_31_outputs():
