@@ -290,7 +290,7 @@ bool conv_direct_ok(int H, int W, int c_in, int c_out, bool backward) {
 }
 
 hipError_t conv_direct_forward(const ConvCall& c, hipStream_t st) {
-    if (!shape_ok(c) || !conv_direct_ok(c.H, c.W, c.c_in, c.c_out, false)) return hipErrorInvalidValue;
+    if (!shape_ok(c) || !conv_direct_ok(c.H, c.W, c.c_in, c.c_out, false) || !c.out) return hipErrorInvalidValue;
     const size_t rows = (size_t)c.B * c.H * c.W;
     DirectArgs a = {};
     a.in = (const uint16_t*)c.in; a.in_lstride = rows * c.c_in; a.c_k = c.c_in;
@@ -312,7 +312,7 @@ hipError_t conv_direct_backward_data(const ConvCall& c, const void* dpool, hipSt
     if (!shape_ok(c) || !conv_direct_ok(c.H, c.W, c.c_in, c.c_out, true)) return hipErrorInvalidValue;
     const size_t rows = (size_t)c.B * c.H * c.W;
     DirectArgs a = {};
-    if (dpool && !c.bits) return hipErrorInvalidValue;
+    if (dpool ? !c.bits : !c.dz) return hipErrorInvalidValue;
     a.bits = (const uint8_t*)c.bits; a.bits_pitch = conv_bits_pitch(c.c_out) * 4; a.bits_lstride = rows * a.bits_pitch;
     a.in = (const uint16_t*)c.dz; a.in_lstride = rows * c.c_out; a.c_k = c.c_out;
     a.dpool = (const uint16_t*)dpool; a.dpool_lstride = (size_t)c.B * c.c_out; a.inv = 1.0f / (float)(c.H * c.W);

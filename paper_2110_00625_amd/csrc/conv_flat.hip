@@ -532,6 +532,7 @@ hipError_t launch_pool_finish(const float* sums, const FlatPlan& plan, void* poo
 
 hipError_t conv_flat_forward(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag, const int32_t* table, const void* X,
                              const int32_t* gather, long gstride, hipStream_t st) {
+    if (!c.bits && !c.out) return hipErrorInvalidValue;
     FlatArgs a = make_args(c, plan, frag, table);
     const size_t rows = (size_t)c.B * c.H * c.W;
     a.in = (const uint16_t*)(gather ? X : c.in); a.in_lstride = gather ? 0 : rows * c.c_in; a.c_k = c.c_in;
@@ -550,7 +551,7 @@ hipError_t conv_flat_forward(const ConvCall& c, const FlatPlan& plan, const uint
 
 hipError_t conv_flat_backward_data(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag, const int32_t* table, const void* dpool,
                                    hipStream_t st) {
-    if (dpool && !c.bits) return hipErrorInvalidValue;
+    if (dpool ? !c.bits : !c.dz) return hipErrorInvalidValue;
     FlatArgs a = make_args(c, plan, frag, table);
     const size_t rows = (size_t)c.B * c.H * c.W;
     a.in = (const uint16_t*)c.dz; a.in_lstride = rows * c.c_out; a.c_k = c.c_out;

@@ -314,7 +314,7 @@ int conv_flat_wgrad_splits(int P, int B, int H, int W, int c_in, int c_out, bool
 
 hipError_t conv_flat_wgrad(const ConvCall& c, const int32_t* table, const void* X, const int32_t* gather, long gstride,
                            const void* dpool, hipStream_t st) {
-    if (c.splits < 1 || !c.partial || !c.partial_bias || (dpool && !c.bits) || (gather && c.c_in != 8))
+    if (c.splits < 1 || !c.partial || !c.partial_bias || (dpool ? !c.bits : !c.dz) || (gather && c.c_in != 8))
         return hipErrorInvalidValue;
     WgradArgs a = {};
     const size_t rows = (size_t)c.B * c.H * c.W;

@@ -266,7 +266,7 @@ int conv_wgrad_halo_splits(int P, int B, int H, int W, int c_in, int c_out) {
 }
 
 hipError_t conv_wgrad_halo(const ConvCall& c, const void* dpool, hipStream_t st) {
-    if (conv_wgrad_halo_splits(c.P, c.B, c.H, c.W, c.c_in, c.c_out) == 0 || c.splits < 1 || c.B % c.splits != 0 || !c.partial || (dpool && (!c.bits || c.B / c.splits > POOL_IMAGES_MAX)) ||
+    if (conv_wgrad_halo_splits(c.P, c.B, c.H, c.W, c.c_in, c.c_out) == 0 || c.splits < 1 || c.B % c.splits != 0 || !c.partial || (dpool ? !c.bits || c.B / c.splits > POOL_IMAGES_MAX : !c.dz) ||
         !c.partial_bias)
         return hipErrorInvalidValue;
     WgradArgs a;

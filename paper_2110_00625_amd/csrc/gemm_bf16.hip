@@ -1225,7 +1225,7 @@ bool conv_call_ok(const ConvCall& c) {
 }  // namespace
 
 hipError_t bf16_conv_forward(const ConvCall& c, hipStream_t st) {
-    if (!conv_call_ok(c) || c.H * c.W >= (1 << 14)) return hipErrorInvalidValue;
+    if (!conv_call_ok(c) || !c.out || c.H * c.W >= (1 << 14)) return hipErrorInvalidValue;
     const int rows = c.B * c.H * c.W;
     Args a = {};
     a.R = {(const uint16_t*)c.in, (size_t)rows * c.c_in, c.c_in, nullptr, 0, rows, 9 * c.c_in};
@@ -1240,7 +1240,7 @@ hipError_t bf16_conv_forward(const ConvCall& c, hipStream_t st) {
 
 // dZ_in[n,h,w,ci] = [act_in > 0] * sum_{tap,o} dZ[n, h-(kh-1), w-(kw-1), o] * Wrot[(tap,o)][ci]
 hipError_t bf16_conv_backward_data(const ConvCall& c, hipStream_t st) {
-    if (!conv_call_ok(c) || c.H * c.W >= (1 << 14)) return hipErrorInvalidValue;
+    if (!conv_call_ok(c) || !c.dz || c.H * c.W >= (1 << 14)) return hipErrorInvalidValue;
     const int rows = c.B * c.H * c.W;
     Args a = {};
     a.R = {(const uint16_t*)c.dz, (size_t)rows * c.c_out, c.c_out, nullptr, 0, rows, 9 * c.c_out};
@@ -1256,7 +1256,7 @@ hipError_t bf16_conv_backward_data(const ConvCall& c, hipStream_t st) {
 // fp32 partial weight gradients of `splits` ranges of positions per learner (conv_step_kernel adds them)
 hipError_t bf16_conv_update_partial(const ConvCall& c, hipStream_t st) {
     const int rows = c.B * c.H * c.W;
-    if (!conv_call_ok(c) || c.H * c.W >= (1 << 14) || c.splits < 1 || rows % c.splits != 0 || !c.partial || !c.partial_bias)
+    if (!conv_call_ok(c) || !c.dz || c.H * c.W >= (1 << 14) || c.splits < 1 || rows % c.splits != 0 || !c.partial || !c.partial_bias)
         return hipErrorInvalidValue;
     const int range = rows / c.splits;
     Args a = {};

@@ -998,6 +998,9 @@ int issue_steps_conv(kavg_ctx* c) {
     const int L = c->L, M = (int)cv.ch.size() - 1, P = c->P, B = c->B, H = cv.H, W = cv.W;
     const int rows = B * H * W;
     const bool head = head_supported(c->dims[L]);
+    // activations of convolution t and their gradient; null where the layer leaves bits and partial sums instead
+    auto act_of = [&](int t) { return t == M && lo.pool_bits ? (char*)nullptr : c->ws + lo.off_cact[t - 1]; };
+    auto dz_of = [&](int t) { return t == M && lo.pool_bits ? (char*)nullptr : c->ws + lo.off_cdz[t - 1]; };
     auto conv_call = [&](int t) {
         LayerCall q{};
         const int cin = 9 * cv.ch[t - 1], cout = cv.ch[t];
@@ -1009,9 +1012,9 @@ int issue_steps_conv(kavg_ctx* c) {
         q.blo = c->lo_planes() + lo.cb_off[t - 1];
         q.shadow_cached = shadows_stay_cached(P, lo.stride);
         q.in = c->ws + lo.off_patch[t - 1]; q.ld_in = cin; q.in_stride = (size_t)rows * cin;
-        q.out = c->ws + lo.off_cact[t - 1]; q.ld_out = cout; q.out_stride = (size_t)rows * cout;
+        q.out = act_of(t); q.ld_out = cout; q.out_stride = (size_t)rows * cout;
         q.relu = 1;
-        q.dz = c->ws + lo.off_cdz[t - 1]; q.ld_dz = cout; q.dz_stride = (size_t)rows * cout;
+        q.dz = dz_of(t); q.ld_dz = cout; q.dz_stride = (size_t)rows * cout;
         q.lr = c->lr;
         return q;
     };
@@ -1020,8 +1023,8 @@ int issue_steps_conv(kavg_ctx* c) {
         v.P = P; v.B = B; v.H = H; v.W = W; v.c_in = cv.ch[t - 1]; v.c_out = cv.ch[t];
         v.ws = c->hi_planes() + lo.cw_off[t - 1]; v.wlo = c->lo_planes() + lo.cw_off[t - 1]; v.ws_stride = lo.stride;
         v.bhi = c->hi_planes() + lo.cb_off[t - 1]; v.blo = c->lo_planes() + lo.cb_off[t - 1];
-        v.in = c->ws + lo.off_cact[t - 2]; v.out = c->ws + lo.off_cact[t - 1];
-        v.dz = c->ws + lo.off_cdz[t - 1]; v.dz_in = c->ws + lo.off_cdz[t - 2];
+        v.in = act_of(t - 1); v.out = act_of(t);
+        v.dz = dz_of(t); v.dz_in = dz_of(t - 1);
         v.wrot = (const uint16_t*)(c->ws + lo.off_wrot); v.wrot_stride = (size_t)9 * v.c_out * v.c_in;
         v.partial = (float*)(c->ws + lo.off_partial[t - 1]); v.partial_bias = (float*)(c->ws + lo.off_pbias[t - 1]);
         v.splits = lo.splits[t - 1];
@@ -1034,7 +1037,7 @@ int issue_steps_conv(kavg_ctx* c) {
         v.P = P; v.B = B; v.H = H; v.W = W; v.c_in = cv.ch[0]; v.c_out = cv.ch[1];
         v.ws = c->hi_planes() + lo.cw_off[0]; v.wlo = c->lo_planes() + lo.cw_off[0]; v.ws_stride = lo.stride;
         v.bhi = c->hi_planes() + lo.cb_off[0]; v.blo = c->lo_planes() + lo.cb_off[0];
-        v.out = c->ws + lo.off_cact[0]; v.dz = c->ws + lo.off_cdz[0];
+        v.out = act_of(1); v.dz = dz_of(1);
         v.partial = (float*)(c->ws + lo.off_partial[0]); v.partial_bias = (float*)(c->ws + lo.off_pbias[0]);
         v.splits = lo.splits_halo[0];
         if (M == 1 && lo.pool_bits) { v.bits = (uint32_t*)(c->ws + lo.off_bits); v.pool_sums = (float*)(c->ws + lo.off_sums); }

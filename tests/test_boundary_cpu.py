@@ -247,3 +247,32 @@ def test_convolutions_of_wide_images_keep_their_kernels(lib):
             assert ok == bool(fit), (W, c_in, c_out)
             if ok:
                 assert got[0] == 16 * max(fit) and got[3] == slabs, (W, c_in, c_out, list(got))
+
+
+def test_convolution_launchers_refuse_images_that_are_not_there(lib):
+    """The last convolution leaves bits and partial sums in place of its activations and their gradient; a launch that would read
+    or write those images then has no buffer, and says so before it reaches a device."""
+    vp = ctypes.c_void_p
+
+    class ConvCall(ctypes.Structure):                            # csrc/kavg_internal.h
+        _fields_ = ([(n, ctypes.c_int) for n in "P B H W c_in c_out".split()] + [("ws", vp), ("wlo", vp), ("ws_stride", ctypes.c_size_t)] +
+                    [(n, vp) for n in "bhi blo in_ out dz dz_in wrot".split()] + [("wrot_stride", ctypes.c_size_t), ("partial", vp),
+                     ("partial_bias", vp), ("splits", ctypes.c_int), ("bits", vp), ("pool_sums", vp)])
+
+    some = 4096
+    plan = (ctypes.c_int * 5)()
+    lib._ZN4kavg14conv_flat_planEiiiiiPNS_8FlatPlanE(2, 8, 32, 32, 64, plan)
+    call = ConvCall(P=1, B=2, H=8, W=32, c_in=32, c_out=64, ws=some, wlo=some, ws_stride=1 << 16, bhi=some, blo=some, in_=some, dz_in=some,
+                    wrot=some, wrot_stride=1 << 16, partial=some, partial_bias=some, splits=1)
+    c, invalid, long = ctypes.byref(call), 1, ctypes.c_long(0)   # hipErrorInvalidValue
+    assert lib._ZN4kavg17conv_flat_forwardERKNS_8ConvCallERKNS_8FlatPlanEPKtPKiPKvS9_lP12ihipStream_t(
+        c, plan, vp(some), vp(some), None, None, long, None) == invalid
+    assert lib._ZN4kavg23conv_flat_backward_dataERKNS_8ConvCallERKNS_8FlatPlanEPKtPKiPKvP12ihipStream_t(
+        c, plan, vp(some), vp(some), None, None) == invalid
+    assert lib._ZN4kavg15conv_flat_wgradERKNS_8ConvCallEPKiPKvS4_lS6_P12ihipStream_t(c, vp(some), None, None, long, None, None) == invalid
+    assert lib._ZN4kavg15conv_wgrad_haloERKNS_8ConvCallEPKvP12ihipStream_t(c, None, None) == invalid
+    assert lib._ZN4kavg19conv_direct_forwardERKNS_8ConvCallEP12ihipStream_t(c, None) == invalid
+    assert lib._ZN4kavg25conv_direct_backward_dataERKNS_8ConvCallEPKvP12ihipStream_t(c, None, None) == invalid
+    assert lib._ZN4kavg17bf16_conv_forwardERKNS_8ConvCallEP12ihipStream_t(c, None) == invalid
+    assert lib._ZN4kavg23bf16_conv_backward_dataERKNS_8ConvCallEP12ihipStream_t(c, None) == invalid
+    assert lib._ZN4kavg24bf16_conv_update_partialERKNS_8ConvCallEP12ihipStream_t(c, None) == invalid
