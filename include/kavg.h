@@ -244,7 +244,12 @@ int kavg_set_refresh(kavg_ctx* ctx, int refresh, void* history_dev, size_t bytes
  * a sparse sample keeps a timed region close to an unobserved one where the class's launches stay
  * what they are.  Updates that otherwise run as one launch for all layers, with the loss means, are
  * launched layer by layer while the update, head or loss class is in the mask, sampled or not: time such
- * models unobserved.  A layer whose data gradient and update are one launch counts as update.
+ * models unobserved.  In the same way the last layers of small KAVG_BF16 models, otherwise one launch from
+ * their forward pass to their data gradients, are launches of their own while the forward, backward, head or
+ * loss class is in the mask; a KAVG_FP32 head adds up no partial products of the layer below while forward or
+ * head is; and while forward is, the weights of convolutions are packed before every step instead of by the
+ * SGD step before it.  What such classes report are then launches that an unobserved round does not make.
+ * A layer whose data gradient and update are one launch counts as update.
  * kavg_profile waits for the stream, clears the totals and installs the mask
  * (0 = off); kavg_profile_read waits for the stream and returns, per class, the
  * summed elapsed milliseconds and the number of bracketed launches since then

@@ -59,8 +59,8 @@ enum { MODE_FWD = 0, MODE_BWD = 1, MODE_UPD = 2 };
 // RING: a ring of LDS buffers filled, slices ahead, by two extra wavefronts that do nothing else
 // (the wavefronts that multiply never issue a memory load, so none of them stands in the queue of the
 // memory pipeline while its MFMAs could run); whole slices only.  LATE (update, long contractions): as PLAIN, but
-// the master is requested under the last slice, which leaves registers for a third workgroup per compute unit, and the tiles
-// of eight tile rows follow each other column by column.
+// the master is requested under the last slice, which leaves registers for a third workgroup per compute unit but for eight
+// (166 - 168 used, 36 bytes of scratch per lane), and the tiles of eight tile rows follow each other column by column.
 enum { PIPE_PLAIN = 0, PIPE_LDS2 = 1, PIPE_DMA = 2, PIPE_RING = 3, PIPE_LATE = 4 };
 constexpr int RING_LOADERS = 2, RING_BYTES = 144 * 1024;
 

@@ -1,6 +1,6 @@
 """Updates that contract over more than 256 rows (gemm_bf16.hip, LATE), as a refresh of deferred updates does: a last slice
 of few rows, ragged tiles on both sides, tile rows behind the last whole group of eight, both kinds of access to the bf16 plane --
-against the oracle."""
+against the oracle.  Cases of few tiles run in the tiles of shorter updates."""
 import pytest
 
 from tests.test_gpu_deferred import TOL_BF16, _setup
@@ -13,7 +13,8 @@ CASES = [
     (2, 5, 53, (136, 1032, 264, 24), 5),         # 265 rows, few tiles
     (3, 4, 65, (264, 200, 136, 10), 4),          # 260 rows, a thin last layer (few tiles: 128x64, as with fewer rows)
     (13, 2, 131, (136, 2568, 264, 24), 2),       # 262 rows; 546 and 819 tiles, 21 tile rows, planes in the cache
-    (2, 3, 256, (8, 16, 40), 2),                 # operands narrower than a tile; 512 rows, then 256
+    (2, 3, 256, (8, 16, 40), 2),                 # operands narrower than a tile; 512 rows, then 256 (few tiles)
+    (520, 2, 131, (8, 16, 40), 2),               # ... many tiles of one layer each
     # planes of all learners beyond the cache; 262 rows.  (Two steps: over five steps of 57 rows at this width, with the same
     # bits as a kernel that requests the master first, roundings that fall the other way flip ReLU masks: 3.6e-2 off the
     # oracle.  Two steps: 5.4e-3.)
