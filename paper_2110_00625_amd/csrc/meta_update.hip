@@ -9,11 +9,12 @@
 // Traffic per parameter and pass: read P replicas + w~ + v, write w~ + v + P
 // replicas = (2P+4)*4 bytes (+2P bytes when bf16 shadows are refreshed).
 // Each lane owns four consecutive parameters (16-byte accesses), on long vectors
-// eight such pieces 4 KB apart, on short ones two or one, so that there are some
-// hundred workgroups; the replica loads are issued sixteen at a time so that many
-// are in flight per lane, on short vectors the last of them for the last replica
-// over and over (one by one they cost a round trip to memory each).  us per pass:
-// 48 replicas of 68 362 12.9 -> 9.1; 31 of 268 000 in planes, with one local step, 54 -> 48.
+// eight such pieces 4 KB apart, on short ones a single parameter (two in planes),
+// so that there are some hundred workgroups; the replica loads are issued sixteen
+// at a time so that many are in flight per lane.  TOGETHER: so are the last of
+// them, those beyond the last replica for that one over and over (one by one they
+// cost a round trip to memory each; on long vectors other workgroups hide it).
+// us per pass: 48 replicas of 68 362 floats 11.2 -> 5.0, in planes 16.4 -> 7.0.
 // Replica loads and stores are streaming (non-temporal): nothing is reused.
 #include "kavg_internal.h"
 #include "split.h"
@@ -48,7 +49,7 @@ __device__ __forceinline__ void meta_scalar_element(float* w_tilde, float* v, fl
 
 // V: pieces of W parameters per lane, 256 lanes apart, so that a workgroup covers V*W KB of consecutive
 // addresses in every replica (longer runs inside one DRAM row per stream).
-template <bool SHADOW, int UNROLL, bool SHADOW_CACHED, int V, int W>
+template <bool SHADOW, int UNROLL, bool SHADOW_CACHED, int V, int W, bool TOGETHER>
 __global__ void __launch_bounds__(256)
 meta_update_vec_kernel(float* __restrict__ w_tilde, float* __restrict__ v, float* __restrict__ reps,
                        size_t stride, uint16_t* __restrict__ shadow, size_t sstride, int P,
@@ -74,7 +75,7 @@ meta_update_vec_kernel(float* __restrict__ w_tilde, float* __restrict__ v, float
 #pragma unroll
                 for (int q = 0; q < V; ++q) acc[q] += t[u][q] - wt[q];
         }
-        if constexpr (W == 4) {                             // (many workgroups: no load for nothing)
+        if constexpr (!TOGETHER) {
             for (; j < P; ++j)
 #pragma unroll
                 for (int q = 0; q < V; ++q) acc[q] += __builtin_nontemporal_load(r + (size_t)j * s4 + q * 256) - wt[q];
@@ -119,6 +120,7 @@ meta_update_vec_kernel(float* __restrict__ w_tilde, float* __restrict__ v, float
         }
         return;
     }
+    if constexpr (V * W == 1) return;                       // (nothing is smaller than a parameter)
     // the last workgroups: piece by piece, whole vectors first, then the ragged tail of at most 3 parameters
     for (int q = 0; q < V; ++q) {
         const size_t i = i0 + (size_t)q * 256;
@@ -150,20 +152,29 @@ hipError_t launch_meta_update(float* w_tilde, float* v, float* reps, size_t stri
     if (vec) {
         // Long vectors: eight pieces per lane, so that a workgroup reads and writes 32 KB of consecutive
         // addresses per replica (meta-only workload, 64 replicas: 0.665 -> 0.70 of the HBM peak); others one piece per
-        // lane, of as many parameters as leave two workgroups per compute unit.
+        // lane.  A parameter per lane up to four workgroups per compute unit: beyond, four times as many requests cost more than
+        // the workgroups hide; up to three of very few replicas, whose latency is soon hidden, and of many in whole pieces, where
+        // the requests count sooner.  us, four per lane / one: 31 replicas of 250 001 18.1 / 8.4, 16 of 196 607 5.3 / 4.2, 48 of 68 362
+        // 11.2 / 5.0; 64 of 230 000 16.7 / 21.7, 48 of 210 000 11.8 / 13.9, 2 of 230 000 2.7 / 3.2; 64 of 410 000 (and two per lane)
+        // 35.6 / 43.9 (40.7); rounds of one step on 504-504-10, 259 570 parameters, 48 learners 78.9 / 76.2.
+        // The last replicas together: one by one / together, a parameter per lane: 31 of 68 362 5.2 / 4.2, 33 4.3 / 4.6 (rounds of
+        // four steps on 3072-64-10, 4 learners, 72.4 / 72.1); four per lane: 12 of 410 000 6.6 / 6.0, 31 of 350 001 26.8 / 17.2, but 17
+        // of 410 000 9.9 / 11.0, 24 of 700 000 23.0 / 26.3.
         const bool wide = n / 4 >= (size_t)256 * 8 * 1024;
-        const int W = wide || n >= (size_t)4 * 256 * 512 ? 4 : n >= (size_t)2 * 256 * 512 ? 2 : 1;
+        const int W = n < (size_t)(P >= 4 && (P < 32 || n % 4) ? 4 : 3) * 256 * 256 ? 1 : 4, rest = P % 16;
+        const bool together = W == 1 ? rest >= 4 : rest >= 8 && n < (size_t)2 * 256 * 1024;
         const size_t nw = n / W, threads = nw + (n - W * nw);
         const unsigned grid = (unsigned)((threads + (wide ? 2048 : 256) - 1) / (wide ? 2048 : 256));
-#define KAVG_META_AS(SH, SC, U, V, W)                                                                         \
-        hipLaunchKernelGGL((meta_update_vec_kernel<SH, U, SC, V, W>), dim3(grid), dim3(256), 0, st, w_tilde, v, reps, stride, \
+#define KAVG_META_AS(SH, SC, U, V, W, T)                                                                      \
+        hipLaunchKernelGGL((meta_update_vec_kernel<SH, U, SC, V, W, T>), dim3(grid), dim3(256), 0, st, w_tilde, v, reps, stride, \
                            shadow, sstride, P, nw, n, mu, invP)
 #define KAVG_META_LAUNCH(SH, SC)                                                                              \
         do {                                                                                                  \
-            if (wide) KAVG_META_AS(SH, SC, 2, 8, 4);                                                          \
-            else if (W == 4) KAVG_META_AS(SH, SC, 16, 1, 4);                                                  \
-            else if (W == 2) KAVG_META_AS(SH, SC, 16, 1, 2);                                                  \
-            else KAVG_META_AS(SH, SC, 16, 1, 1);                                                              \
+            if (wide) KAVG_META_AS(SH, SC, 2, 8, 4, false);                                                   \
+            else if (W == 4 && together) KAVG_META_AS(SH, SC, 16, 1, 4, true);                                \
+            else if (W == 4) KAVG_META_AS(SH, SC, 16, 1, 4, false);                                           \
+            else if (together) KAVG_META_AS(SH, SC, 16, 1, 1, true);                                          \
+            else KAVG_META_AS(SH, SC, 16, 1, 1, false);                                                       \
         } while (0)
         if (shadow && shadow_cached) KAVG_META_LAUNCH(true, true);
         else if (shadow) KAVG_META_LAUNCH(true, false);
@@ -206,7 +217,7 @@ __device__ __forceinline__ void meta_split_scalar_element(float* w_tilde, float*
 }
 
 // W: parameters per lane
-template <int UNROLL, bool HI_CACHED, int W>
+template <int UNROLL, bool HI_CACHED, int W, bool TOGETHER>
 __global__ void __launch_bounds__(256)
 meta_update_split_kernel(float* __restrict__ w_tilde, float* __restrict__ v, uint16_t* __restrict__ hi,
                          uint16_t* __restrict__ lo, size_t stride, int P, size_t nw, size_t n, float mu,
@@ -250,7 +261,7 @@ meta_update_split_kernel(float* __restrict__ w_tilde, float* __restrict__ v, uin
             for (int u = 0; u < UNROLL; ++u) if (whole || j + u < P) add(th[u], tl[u]);
         };
         for (; j + UNROLL <= P; j += UNROLL) batch(std::true_type{});
-        if constexpr (W == 8) {                                 // (many workgroups: no load for nothing)
+        if constexpr (!TOGETHER) {
             for (; j < P; ++j)
                 add(HI_CACHED ? ph[(size_t)j * s8] : __builtin_nontemporal_load(ph + (size_t)j * s8),
                     __builtin_nontemporal_load(pl + (size_t)j * s8));
@@ -294,15 +305,21 @@ hipError_t launch_meta_update_split(float* w_tilde, float* v, uint16_t* hi, uint
                                     int P, size_t n, float mu, int hi_cached, hipStream_t st) {
     // planes and vectors come out of the 256-byte aligned workspace; stride is a multiple of 64
     const float invP = 1.0f / (float)P;
-    const int W = !hi_cached || n >= (size_t)8 * 256 * 512 ? 8 : n >= (size_t)4 * 256 * 512 ? 4 : 2;       // two workgroups per compute unit
+    // Two parameters per lane up to two workgroups per compute unit, beyond that the requests cost more than the workgroups hide
+    // (us, eight per lane / two: 16 replicas of 240 001 7.5 / 5.5, 48 of 68 362 16.4 / 7.0; 64 of 470 000 36.4 / 45.0, 33 of 410 000
+    // 17.2 / 20.9; four per lane: 8 of 1 000 000 10.5 / 13.3).  The last replicas together: one by one / together, eight per lane:
+    // 12 of 300 000 7.7 / 7.4, 31 of 410 000 18.6 / 16.5; but 37 of 817 000 40.0 / 46.7.
+    const int W = hi_cached && n < (size_t)2 * 256 * 512 ? 2 : 8;
+    const bool together = W == 2 ? P % 16 > 4 : P % 8 >= 4 && hi_cached && n < (size_t)2 * 256 * 1024;
     const size_t nw = n / W, threads = nw + (n - W * nw);
     const dim3 grid((unsigned)((threads + 255) / 256));
-#define KAVG_META_SPLIT(U, HC, W) \
-    hipLaunchKernelGGL((meta_update_split_kernel<U, HC, W>), grid, dim3(256), 0, st, w_tilde, v, hi, lo, stride, P, nw, n, mu, invP)
-    if (!hi_cached) KAVG_META_SPLIT(8, false, 8);
-    else if (W == 8) KAVG_META_SPLIT(8, true, 8);
-    else if (W == 4) KAVG_META_SPLIT(8, true, 4);
-    else KAVG_META_SPLIT(16, true, 2);
+#define KAVG_META_SPLIT(U, HC, W, T) \
+    hipLaunchKernelGGL((meta_update_split_kernel<U, HC, W, T>), grid, dim3(256), 0, st, w_tilde, v, hi, lo, stride, P, nw, n, mu, invP)
+    if (!hi_cached) KAVG_META_SPLIT(8, false, 8, false);
+    else if (W == 8 && together) KAVG_META_SPLIT(8, true, 8, true);
+    else if (W == 8) KAVG_META_SPLIT(8, true, 8, false);
+    else if (together) KAVG_META_SPLIT(16, true, 2, true);
+    else KAVG_META_SPLIT(16, true, 2, false);
 #undef KAVG_META_SPLIT
     return hipGetLastError();
 }

@@ -1,5 +1,5 @@
-"""The meta step where the parameters per lane change (1, 2, 4 of a float replica; 2, 4, 8 of one in planes), with numbers of
-replicas around the sixteen (eight) whose loads go out together, against 64-bit arithmetic."""
+"""The meta step where the parameters per lane change (1, 4 of a float replica; 2, 8 of one in planes), with ragged ends and
+numbers of replicas around the sixteen (eight) whose loads go out together, against 64-bit arithmetic."""
 import numpy as np
 import pytest
 import torch
@@ -22,8 +22,8 @@ def _close(got, want, terms):
     assert np.max(np.abs(np.asarray(got, dtype=np.float64) - want)) <= bound
 
 
-@pytest.mark.parametrize("n", [1, 3, 255, 20001, 262143, 262145, 524287, 524290])
-@pytest.mark.parametrize("P,shadow", [(1, False), (15, True), (17, False), (33, True)])
+@pytest.mark.parametrize("n", [1, 3, 255, 20001, 196607, 196610, 262143, 262145, 524287, 524290])
+@pytest.mark.parametrize("P,shadow", [(1, False), (15, True), (17, False), (26, True), (33, True)])
 def test_float_replicas(n, P, shadow):
     gen = torch.Generator(device="cuda").manual_seed(n + P)
     stride = (n + 63) // 64 * 64
@@ -43,7 +43,7 @@ def test_float_replicas(n, P, shadow):
 
 
 @pytest.mark.parametrize("P", [1, 7, 17])
-@pytest.mark.parametrize("dims", [(8, 8, 3), (256, 1000, 8, 5), (512, 1016, 8, 6), (1024, 512, 7), (1024, 1016, 8, 9)], ids=lambda d: "-".join(map(str, d)))
+@pytest.mark.parametrize("dims", [(8, 8, 3), (256, 1000, 8, 5), (512, 600, 8, 6), (512, 1016, 8, 6), (1024, 512, 7), (1024, 1016, 8, 9)], ids=lambda d: "-".join(map(str, d)))
 def test_replicas_in_planes(P, dims):
     g, _ = _pair(P, 1, 0.05, 0.9, dims, 8, True, 31)
     for _ in range(2):
