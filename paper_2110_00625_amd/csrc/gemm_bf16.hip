@@ -751,33 +751,34 @@ __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING
             if constexpr (CONV_C) touch_at = (const uint32_t*)Cbase;     // nothing to prefetch: the images are this launch's own operand
         }
         fetch(0);
-        auto master = [&]() __attribute__((always_inline)) {
-            // The master tile (both planes) is independent of the product: its loads go out right after
-            // the first operand slice (LATE: the last one) and are in flight during the contraction.  They are issued
-            // without predicates (rows and columns beyond the layer are clamped; those lanes store
-            // nothing later), so that the compiler can count them: the wait for the operand slice is
-            // then "all but these", not "everything".
-            // (with partial outputs nothing is stepped; the loads then go to learner 0's tile and are ignored,
-            // so that the load sequence keeps its branch-free shape)
+        // The master tile (both planes) is independent of the product: its loads go out right after
+        // the first operand slice (LATE: the last one) and are in flight during the contraction.  They are issued
+        // without predicates (rows and columns beyond the layer are clamped; those lanes store
+        // nothing later), so that the compiler can count them: the wait for the operand slice is
+        // then "all but these", not "everything".
+        // (with partial outputs nothing is stepped; the loads then go to learner 0's tile and are ignored,
+        // so that the load sequence keeps its branch-free shape)
+        // (a piece at a time: as one function over both arrays the early form took four to nine instructions more)
+        auto master_piece = [&](int i, int it, u32x4& hi, u32x4& lo) __attribute__((always_inline)) {
             const size_t mlearner = a.partial ? 0 : (size_t)learner;
             const uint16_t* hbase = a.ws + mlearner * a.ws_lstride;
             const uint16_t* lbase = a.wlo + mlearner * a.ws_lstride;
             const int c = min(c0 + wc * WTC + (lane % L8_PER_ROW) * 8, a.nC - 8);
-#pragma unroll
-            for (int i = 0; i < MR; ++i)
-#pragma unroll
-                for (int it = 0; it < ITS; ++it) {
-                    const int r = min(r0 + (wr * MR + i) * 32 + it * ROWS_PER_IT + lane / L8_PER_ROW, a.nR - 1);
-                    // hi was left in the memory-side cache by the previous writer when it fits there
-                    // (otherwise it is streamed like lo, so as not to push anything else out)
-                    mhi[i][it] = SHADOW_CACHED ? *(const u32x4*)(hbase + (size_t)r * a.nC + c)
-                                               : __builtin_nontemporal_load((const u32x4*)(hbase + (size_t)r * a.nC + c));
-                    mlo[i][it] = __builtin_nontemporal_load((const u32x4*)(lbase + (size_t)r * a.nC + c));
-                }
+            const int r = min(r0 + (wr * MR + i) * 32 + it * ROWS_PER_IT + lane / L8_PER_ROW, a.nR - 1);
+            // hi was left in the memory-side cache by the previous writer when it fits there
+            // (otherwise it is streamed like lo, so as not to push anything else out)
+            hi = SHADOW_CACHED ? *(const u32x4*)(hbase + (size_t)r * a.nC + c)
+                               : __builtin_nontemporal_load((const u32x4*)(hbase + (size_t)r * a.nC + c));
+            lo = __builtin_nontemporal_load((const u32x4*)(lbase + (size_t)r * a.nC + c));
         };
         if (MODE == MODE_UPD) {
             __builtin_amdgcn_sched_barrier(0);          // keep the operand loads the oldest
-            if (PIPE != PIPE_LATE) master();
+            if constexpr (PIPE != PIPE_LATE) {
+#pragma unroll
+                for (int i = 0; i < MR; ++i)
+#pragma unroll
+                    for (int it = 0; it < ITS; ++it) master_piece(i, it, mhi[i][it], mlo[i][it]);
+            }
             __builtin_amdgcn_sched_barrier(0);
             touched = *touch_at;
         }
@@ -800,7 +801,10 @@ __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING
             for (int k0 = BK; k0 < a.nK; k0 += BK) slice([&]() __attribute__((always_inline)) { fetch(k0); });
             slice([&]() __attribute__((always_inline)) {
                 __builtin_amdgcn_sched_barrier(0);
-                master();
+#pragma unroll
+                for (int i = 0; i < MR; ++i)
+#pragma unroll
+                    for (int it = 0; it < ITS; ++it) master_piece(i, it, mhi[i][it], mlo[i][it]);
                 __builtin_amdgcn_sched_barrier(0);
             });
         } else if (PIPE == PIPE_PLAIN) {
