@@ -26,16 +26,23 @@ __device__ __forceinline__ pool_u32x4 pool_grad_piece(pool_u32x4 m, pool_u32x4 g
     return o;
 }
 
-// The same from one byte of the bits that the last convolution's forward pass leaves in place of its activations (bit c:
-// channel c of the eight is positive; ConvCall::bits).
-__device__ __forceinline__ pool_u32x4 pool_grad_bits(uint32_t m, pool_u32x4 g, float inv) {
+// The same in two parts, for kernels that scale a channel's gradient once and mask it at every position: bf16(g / (H W)) ...
+__device__ __forceinline__ pool_u32x4 pool_scale(pool_u32x4 g, float inv) {
     pool_u32x4 o;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        const float g0 = __builtin_bit_cast(float, g[q] << 16) * inv, g1 = __builtin_bit_cast(float, g[q] & 0xFFFF0000u) * inv;
-        o[q] = pool_pack2(m & (1u << 2 * q) ? g0 : 0.f, m & (2u << 2 * q) ? g1 : 0.f);
-    }
+    for (int q = 0; q < 4; ++q) o[q] = pool_pack2(__builtin_bit_cast(float, g[q] << 16) * inv, __builtin_bit_cast(float, g[q] & 0xFFFF0000u) * inv);
     return o;
 }
+
+// ... and eight of those where the bits that the last convolution's forward pass leaves in place of its activations are set (bit c
+// of m: channel c of the eight is positive; ConvCall::bits).  16 instructions; scaled and rounded at every position it was 45,
+// more than half of what the weight gradient's wavefronts did beside their products.
+__device__ __forceinline__ pool_u32x4 pool_mask(uint32_t m, pool_u32x4 scaled) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        scaled[q] &= ((uint32_t)__builtin_amdgcn_sbfe((int)m, 2 * q, 1) & 0xFFFFu) | ((uint32_t)__builtin_amdgcn_sbfe((int)m, 2 * q + 1, 1) & 0xFFFF0000u);
+    return scaled;
+}
+__device__ __forceinline__ pool_u32x4 pool_grad_bits(uint32_t m, pool_u32x4 g, float inv) { return pool_mask(m, pool_scale(g, inv)); }
 
 }  // namespace kavg

@@ -28,6 +28,7 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int IMG_W = 32;                    // image width the tiling is built for
@@ -77,7 +78,7 @@ __global__ void __launch_bounds__(64 * 3 * (C_OUT / 32)) conv_wgrad_halo_kernel(
     constexpr int OB = SH::OB, NB = SH::NB, NT = SH::NT, ZP = SH::ZP, AP = SH::AP;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     uint16_t* const lds = (uint16_t*)smem;       // buffer b: dZ rows at lds + b*BUF, halo at + Z_ELEMS
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     // A wavefront owns the taps with dx = tl - 1 and, of the OB x NB blocks (output channels x input channels), either
     // one output block and all input blocks or -- when there are two input blocks and an even number of output
     // blocks -- two output blocks and one input block: the same six accumulator blocks, five fragment reads per
@@ -100,11 +101,11 @@ __global__ void __launch_bounds__(64 * 3 * (C_OUT / 32)) conv_wgrad_halo_kernel(
         *(u32x4*)(lds + b * SH::BUF + SH::Z_ELEMS + (row * HALO_W + side * (HALO_W - 1)) * AP + ch8 * 8) = zero;
     }
 
-    // the dpool rows of this workgroup's images: behind the two slice buffers
+    // the dpool rows of this workgroup's images, scaled: behind the two slice buffers
     uint16_t* const gl = lds + 2 * SH::BUF;
     if constexpr (POOL) {
         const uint16_t* dpool = a.dpool + (size_t)learner * a.dpool_lstride + (size_t)range * a.images * C_OUT;
-        for (int e = tid; e < a.images * (C_OUT / 8); e += NT) *(u32x4*)(gl + e * 8) = *(const u32x4*)(dpool + (size_t)e * 8);
+        for (int e = tid; e < a.images * (C_OUT / 8); e += NT) *(u32x4*)(gl + e * 8) = pool_scale(*(const u32x4*)(dpool + (size_t)e * 8), a.inv);
     }
     u32x4 zr[POOL ? 1 : SH::ZN], ar[SH::AN];
     uint8_t br[POOL ? SH::ZN : 1];
@@ -140,7 +141,7 @@ __global__ void __launch_bounds__(64 * 3 * (C_OUT / 32)) conv_wgrad_halo_kernel(
             if (e < SH::Z_PIECES) {
                 u32x4 v;
                 if constexpr (!POOL) v = zr[i];
-                if constexpr (POOL) v = pool_grad_bits(br[i], *(const u32x4*)(gl + b * C_OUT + (e % (C_OUT / 8)) * 8), a.inv);
+                if constexpr (POOL) v = pool_mask(br[i], *(const u32x4*)(gl + b * C_OUT + (e % (C_OUT / 8)) * 8));
                 *(u32x4*)(Z + (e / (C_OUT / 8)) * ZP + (e % (C_OUT / 8)) * 8) = v;
             }
         }
@@ -165,11 +166,15 @@ __global__ void __launch_bounds__(64 * 3 * (C_OUT / 32)) conv_wgrad_halo_kernel(
             for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[ty][oi][ni][e] = 0.f;
-    // column sums of dZ: the workgroup has 6 threads per output channel (NT = 6 C_OUT); thread (g, ch) adds the
-    // positions g, g + 6, ... of every slice, and the six partial sums are joined in fixed order at the end
-    static_assert(NT == 6 * C_OUT, "six threads per output channel");
-    const int bch = tid % C_OUT, bg = tid / C_OUT;
-    float bias_sum = 0.f;
+    // Column sums of dZ, taken by the wavefronts of the three dx in turn: a slab's operand (lane l: channel l%32, positions
+    // 8 (l/32) ..) read as one of the 16x16x32 instruction is rows c (lanes 0-15, 32-47) and 16 + c (the others) of the sum, so
+    // column n of the other operand holds ones where (lane / 16) % 2 = n.  (Four accumulators and half a matrix instruction; added up
+    // out of LDS, 11 reads and 33 instructions of every wavefront per slice.)
+    const int b_oi = PAIR ? nb0 : 0;                     // the output block whose bias this wavefront sums (of its OI)
+    f32x4 bacc = {0.f, 0.f, 0.f, 0.f};
+    bf16x8 ones;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ones[e] = (__bf16)((lane & 15) == ((lane >> 4) & 1) ? 1.0f : 0.0f);
 
     fetch(0);
     if constexpr (POOL) __syncthreads();         // the dpool rows are in LDS
@@ -186,6 +191,7 @@ __global__ void __launch_bounds__(64 * 3 * (C_OUT / 32)) conv_wgrad_halo_kernel(
             bf16x8 zf[OI];
 #pragma unroll
             for (int oi = 0; oi < OI; ++oi) zf[oi] = frag_tr(Z, ZP, kq * 16, (ob0 + oi) * 32, lane);
+            if ((s + kq) % 3 == tl) bacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b_oi ? zf[OI - 1] : zf[0], ones, bacc, 0, 0, 0);
             const int r = kq >> 1, w0 = (kq & 1) * 16;
 #pragma unroll
             for (int ty = 0; ty < 3; ++ty) {
@@ -200,9 +206,6 @@ __global__ void __launch_bounds__(64 * 3 * (C_OUT / 32)) conv_wgrad_halo_kernel(
                 }
             }
         }
-#pragma unroll
-        for (int k = 0; k < SLP; k += 6)
-            if (k + bg < SLP) bias_sum += __builtin_bit_cast(float, (uint32_t)Z[(k + bg) * ZP + bch] << 16);
         if (s + 1 < slices) stash(buf ^ 1, s + 1);   // the other buffer: last read before the previous barrier
         __syncthreads();
     }
@@ -220,15 +223,14 @@ __global__ void __launch_bounds__(64 * 3 * (C_OUT / 32)) conv_wgrad_halo_kernel(
                     const int o = (ob0 + oi) * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
                     out[(size_t)o * 9 * C_IN + (ty * 3 + tl) * C_IN + (nb0 + ni) * 32 + (lane & 31)] = acc[ty][oi][ni][e];
                 }
-    float* red = (float*)smem;                   // (the tiles are dead: the loop ended with a barrier)
-    red[bg * C_OUT + bch] = bias_sum;
-    __syncthreads();
-    if (tid < C_OUT) {
-        float b = 0.f;
+    // accumulator e of bacc: row 4 (lane/16) + e, column lane%16
+    float* red = (float*)smem;                   // [tl][output channel] (the tiles are dead: the loop ended with a barrier)
+    if ((lane & 15) < 2) {
 #pragma unroll
-        for (int g = 0; g < 6; ++g) b += red[g * C_OUT + tid];
-        a.partial_bias[(size_t)lp * C_OUT + tid] = b;
+        for (int e = 0; e < 4; ++e) red[tl * C_OUT + (ob0 + b_oi) * 32 + (lane & 15) * 16 + (lane >> 4) * 4 + e] = bacc[e];
     }
+    __syncthreads();
+    if (tid < C_OUT) a.partial_bias[(size_t)lp * C_OUT + tid] = red[tid] + red[C_OUT + tid] + red[2 * C_OUT + tid];
 }
 
 template <int C_IN, int C_OUT, bool POOL>

@@ -1,7 +1,7 @@
 // Division by a runtime constant as a multiply and a shift, for the index arithmetic of the implicit
 // convolution loaders (position -> (image, row, column), contraction index -> (tap, channel)).
 //
-// For a divisor 2 <= d < 2^14:  s = 31 + ceil(log2 d),  m = floor(2^s / d) + 1 < 2^32  (d = 1: m = 2^31, s = 31).
+// For a divisor 2 <= d <= 2^30:  s = 31 + ceil(log2 d),  m = floor(2^s / d) + 1 < 2^32  (d = 1: m = 2^31, s = 31).
 // Then for every n < 2^30:  floor(n / d) = (n * m) >> s, because n * m / 2^s = n/d + n * (m d - 2^s) / (d 2^s), where
 // 0 < m d - 2^s <= d, so the excess is below n / 2^s < 1/d: too small to reach the next integer.
 #pragma once

@@ -150,9 +150,14 @@ Layout make_layout(int P, int K, int B, int L, const int* dims, int dtype, const
             const int S1 = (t == 1 && lo.conv_implicit) ? conv_first_splits(P, B, cv.H, cv.W, cv.ch[0], cv.ch[1]) : 0;
             int Sh = t == 1 ? S1 : lo.conv_implicit ? conv_wgrad_halo_splits(P, B, cv.H, cv.W, cv.ch[t - 1], cv.ch[t]) : 0;
             // Which kernels run convolution t: those for images 32 pixels wide where they cover the layer, those for any width
-            // elsewhere.  (The workload's layers on the latter, us per launch against the former: forward 33 / 69 / 174 against
-            // 26 / 71 / 183, data gradient 85 / 226 against 75 / 199, weight gradient 32 / 89 / 260 against 33 / 54 / 168: with the
-            // forward pass of layers 2 and 3 on the latter a round would take 1.4 % less.)
+            // elsewhere, and for forward pass and data gradient of 64 or more channels out where these have three rounds of workgroups
+            // or more.  (The workload's layers on the latter, us per launch against the former: forward 29 / 61 / 161 against
+            // 27 / 72 / 183, data gradient 83 / 158 against 80 / 182, weight gradient 32 / 89 / 260 against 35 / 57 / 148.  Fewer workgroups:
+            // 16 learners of 32 images, 64 -> 64 -> 64 channels (1089) 918 against 898 per round, 8 of 16 (273) 255 against 240.)
+            auto direct = [&](int c_in, int c_out, bool backward) {
+                const int c_n = backward ? c_in : c_out;
+                return conv_direct_ok(cv.H, cv.W, c_in, c_out, backward) && (c_n < 64 || conv_flat_workgroups(P, B, cv.H, cv.W, c_n) < 3 * 512);
+            };
             FlatPlan pf = {}, pb = {};
             int Sf = 0;
             if (lo.conv_implicit) {
@@ -162,19 +167,19 @@ Layout make_layout(int P, int K, int B, int L, const int* dims, int dtype, const
                 // is odd; where that leaves them a third fewer compute units than the others' ranges, which end anywhere, those
                 // run.  (15 learners of 6 images, 64 -> 64 channels: 76 against 24 us; 16 learners of 64, 64 -> 128: 168 / 260.)
                 if (Sh > 0 && std::min(256, P * Sh) * 3 >= std::min(256, P * Sf) * 2) Sf = 0;
-                if (t == 1 ? Sf > 0 && Sh == 0 : !conv_direct_ok(cv.H, cv.W, cin, cout, false)) (void)conv_flat_plan(B, cv.H, cv.W, cin, cout, &pf);
-                if (t > 1 && !conv_direct_ok(cv.H, cv.W, cin, cout, true)) (void)conv_flat_plan(B, cv.H, cv.W, cout, cin, &pb);
+                if (t == 1 ? Sf > 0 && Sh == 0 : !direct(cin, cout, false)) (void)conv_flat_plan(P, B, cv.H, cv.W, cin, cout, false, &pf);
+                if (t > 1 && !direct(cin, cout, true)) (void)conv_flat_plan(P, B, cv.H, cv.W, cout, cin, true, &pb);
                 if (t == 1 && !pf.slabs && Sh == 0) Sf = 0;
             }
             // The last convolution: bits and partial sums where its forward pass runs on images of any width and kernels that
             // form their dZ cover both of its gradients.
-            if (t == M && lo.conv_implicit && conv_pool_slots(cv.H, cv.W)) {
+            if (t == M && lo.conv_implicit) {
                 const int cin = cv.ch[t - 1], cout = cv.ch[t];
                 FlatPlan p = {};
                 const int S = t == 1 ? conv_flat_wgrad_splits(P, B, cv.H, cv.W, cin, cout, true) : 0;
                 const bool gradients = t == 1 ? S > 0 : (pb.slabs || conv_direct_ok(cv.H, cv.W, cin, cout, true)) &&
                                                         (Sf > 0 || (Sh > 0 && B / Sh <= conv_wgrad_halo_pool_images()));
-                lo.pool_bits = gradients && conv_flat_plan(B, cv.H, cv.W, cin, cout, &p);
+                lo.pool_bits = gradients && conv_flat_plan(P, B, cv.H, cv.W, cin, cout, false, &p) && conv_pool_slots(cv.H, cv.W, p);
                 if (lo.pool_bits) {
                     pf = p;
                     if (t == 1) { Sf = S; Sh = 0; }
@@ -1080,7 +1085,7 @@ int issue_steps_conv(kavg_ctx* c) {
         for (int t = 1; t <= M; ++t) {                              // convolutions, forward
             Bracket br(c, KAVG_CLASS_FORWARD);
             if (pack[t - 1].fwd) {
-                KAVG_HIP(c, conv_flat_forward(t == 1 ? first_call() : implicit_call(t), lo.flat_f[t - 1], pack[t - 1].fwd, table, c->X,
+                KAVG_HIP(c, conv_flat_forward(t == 1 ? first_call() : implicit_call(t), lo.flat_f[t - 1], pack[t - 1].fwd, c->X,
                                               t == 1 ? idx_k : nullptr, idx_ls, st));
                 continue;
             }
@@ -1168,7 +1173,7 @@ int issue_steps_conv(kavg_ctx* c) {
                 {
                     Bracket br(c, KAVG_CLASS_BACKWARD);
                     if (pack[t - 1].bwd) {
-                        KAVG_HIP(c, conv_flat_backward_data(v, lo.flat_b[t - 1], pack[t - 1].bwd, table,
+                        KAVG_HIP(c, conv_flat_backward_data(v, lo.flat_b[t - 1], pack[t - 1].bwd,
                                                             (pool_fused && t == M) ? dpool_M : nullptr, st));
                     } else if (conv_direct_ok(H, W, v.c_in, v.c_out, true)) {
                         KAVG_HIP(c, conv_direct_backward_data(v, (pool_fused && t == M) ? dpool_M : nullptr, st));

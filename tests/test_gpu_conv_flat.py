@@ -62,6 +62,33 @@ def test_last_convolution(P, B, H, W, channels, dims):
     test_one_step(P, B, H, W, channels, dims)
 
 
+MANY = [
+    # More than 256 workgroups: whole ones (the cases above have half as many positions each); two learners are checked.
+    (257, 3, 5, 6, (8, 16, 40), (40, 10)),           # images across and beside the ends of tiles
+    (257, 70, 2, 1, (8, 8, 128), (128, 3)),          # 22 images of six positions to a wavefront
+    (130, 5, 9, 13, (8, 72, 64), (64, 10)),          # three slabs at a time; 64 and 128 channels out
+    (129, 3, 7, 41, (8, 64, 24), (24, 10)),          # four slabs, the widest images (in 512 positions) that take them
+    (257, 1, 3, 80, (8, 48, 128, 40), (40, 10)),
+    (512, 2, 32, 32, (8, 64, 64, 128), (128, 17)),   # 32 pixels wide, forward pass and data gradient on the kernels for any width
+]
+
+
+@pytest.mark.parametrize("P,B,H,W,channels,dims", MANY, ids=["%dx%d-%s" % (c[2], c[3], "-".join(map(str, c[4]))) for c in MANY])
+def test_whole_workgroups(P, B, H, W, channels, dims):
+    """Tolerance as in test_one_step."""
+    g, o, spec = _setup(P, 1, B, H, W, channels, dims, 76, lr=0.5)
+    start = g.params().astype(np.float64)
+    g.local_steps()
+    o.local_steps(learners=[0, P - 1])
+    for j in (0, P - 1):
+        got, want = g.replica(j) - start, np.asarray(o.replica(j)) - start
+        for name, sl in conv_slices(spec):
+            e = np.max(np.abs(got[sl] - want[sl])) / max(np.max(np.abs(want[sl])), 1e-30)
+            print("  learner %d %-8s %.3g" % (j, name, e))
+            assert e < 2.0 ** -8, "%s of learner %d: %.3g" % (name, j, e)
+    g.close()
+
+
 @pytest.mark.parametrize("size,bad", [(3, 0), (3, 7), (12, 2)], ids=["first-of-eight", "last-of-eight", "two-tiles"])
 def test_an_infinite_activation_stays_in_its_image(size, bad):
     """One image whose first output channel overflows bf16.  Every hidden unit takes that channel with a negative weight, so
