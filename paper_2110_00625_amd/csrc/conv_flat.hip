@@ -69,7 +69,7 @@ struct FlatArgs {
     int end, image;                                      // positions up to the last pixel of the last image; positions of an image
     uint32_t div_row_m; int div_row_s;                   // division by the positions of an image row, W + 1
     uint32_t div_img_m; int div_img_s;                   // division by the rows of an image, H + 1
-    int tiles, total, padded; uint32_t div_tiles_m; int div_tiles_s;      // tiles per learner; workgroups
+    int PB, tiles, total, padded; uint32_t div_tiles_m; int div_tiles_s;      // tiles per learner; workgroups
     const uint16_t* dpool; size_t dpool_lstride; float inv; int images, places;      // BWD_POOL: gradients from the bits and these; images per learner, of a tile
     uint32_t* bits; int bits_pitch; size_t bits_lstride;             // words per pixel; LAST: written, BWD_POOL: read
     float* sums; int slots;                                          // LAST: places of images per 128 positions
@@ -524,11 +524,17 @@ __global__ void __launch_bounds__(NT) pack_weights_kernel(PackArgs a) {
 int tile_images(int n_px, int H, int W) { return (n_px - 1) / ((H + 1) * (W + 1)) + 2; }
 
 // the tile, where its pixels lie, the bias or (dpool_channels) the gradients of the means
-size_t lds_bytes(const FlatPlan& p, int H, int W, int dpool_channels, int source) {
-    const int n_px = p.PWAVES * p.PB * 32 + 2 * (W + 1) + 2;
-    return (size_t)tile_area(n_px, p.CK, p.NB, p.PB) + (size_t)((n_px + 3) & ~3) * source +
+size_t lds_bytes(const FlatPlan& p, int PB, int H, int W, int dpool_channels, int source) {
+    const int n_px = p.PWAVES * PB * 32 + 2 * (W + 1) + 2;
+    return (size_t)tile_area(n_px, p.CK, p.NB, PB) + (size_t)((n_px + 3) & ~3) * source +
            (dpool_channels ? (size_t)tile_images(n_px, H, W) * dpool_channels * 2 : 128 * 4);
 }
+
+// Blocks of 32 positions per wavefront: four, and half as many (with weights requested further ahead) where workgroups of four would
+// not even be one for each of the 256 compute units.  us per round of two steps, half / whole: 2 learners of 32 images of 11x24,
+// 8-32-128 (40 workgroups) 162 / 178, 4 of 60 of 14x14, 8-64-64-64 (106) 274 / 309, 10 of 6 of 45x35, 8-16-16 (200) 156 / 156; but
+// 8 of 32 of 28x28, 8-32-64 (424) 233 / 224.
+int blocks_per_wave(int P, int B, int H, int W, const FlatPlan& plan) { return conv_flat_workgroups(P, B, H, W, plan.PWAVES == 2 ? 128 : 64) <= 256 ? 2 : 4; }
 
 FlatArgs make_args(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag) {
     FlatArgs a = {};
@@ -537,7 +543,8 @@ FlatArgs make_args(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag
     a.end = ((c.B - 1) * (c.H + 1) + c.H - 1) * (c.W + 1) + c.W;
     fastdiv_make((uint32_t)(c.W + 1), &a.div_row_m, &a.div_row_s);
     fastdiv_make((uint32_t)(c.H + 1), &a.div_img_m, &a.div_img_s);
-    const int TP = plan.PWAVES * plan.PB * 32;
+    a.PB = blocks_per_wave(c.P, c.B, c.H, c.W, plan);
+    const int TP = plan.PWAVES * a.PB * 32;
     a.tiles = (a.end + TP - 1) / TP;
     a.total = a.tiles * c.P;
     a.padded = (a.total + 7) / 8 * 8;
@@ -550,7 +557,7 @@ template <int CK, int NB, int PWAVES, int PB, int KIND, bool LAST>
 hipError_t launch(const FlatArgs& a, size_t smem, hipStream_t st) {
     if (smem > 64 * 1024) {
         static hipError_t raised = hipFuncSetAttribute((const void*)conv_flat_kernel<CK, NB, PWAVES, PB, KIND, LAST>,
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (raised != hipSuccess) return raised;
     }
     hipLaunchKernelGGL((conv_flat_kernel<CK, NB, PWAVES, PB, KIND, LAST>), dim3(a.padded), dim3(NT), smem, st, a);
@@ -560,7 +567,7 @@ hipError_t launch(const FlatArgs& a, size_t smem, hipStream_t st) {
 template <int PB, int KIND, bool LAST>
 hipError_t run_pb(const FlatArgs& a, const FlatPlan& p, hipStream_t st) {
     const int source = KIND == FWD_GATHER || KIND == BWD_POOL ? 8 : 4;
-    const size_t smem = lds_bytes(p, a.H, a.W, KIND == BWD_POOL ? a.c_k : 0, source);
+    const size_t smem = lds_bytes(p, PB, a.H, a.W, KIND == BWD_POOL ? a.c_k : 0, source);
     if (p.PWAVES == 2) {
         if (p.CK == 64) return launch<64, 2, 2, PB, KIND, LAST>(a, smem, st);
         if (p.CK == 48) return launch<48, 2, 2, PB, KIND, LAST>(a, smem, st);
@@ -581,7 +588,7 @@ hipError_t run_pb(const FlatArgs& a, const FlatPlan& p, hipStream_t st) {
 
 template <int KIND, bool LAST = false>
 hipError_t run(const FlatArgs& a, const FlatPlan& p, hipStream_t st) {
-    return p.PB == 2 ? run_pb<2, KIND, LAST>(a, p, st) : run_pb<4, KIND, LAST>(a, p, st);
+    return a.PB == 2 ? run_pb<2, KIND, LAST>(a, p, st) : run_pb<4, KIND, LAST>(a, p, st);
 }
 
 }  // namespace
@@ -599,13 +606,15 @@ int conv_flat_workgroups(int P, int B, int H, int W, int c_n) {
     return (int)std::min((end + tile - 1) / tile * P, (long)INT32_MAX);
 }
 
-bool conv_flat_plan(int P, int B, int H, int W, int c_k, int c_n, bool backward, FlatPlan* plan) {
+namespace {
+
+// dpool_channels: those of a data gradient below the mean over the positions, whose gradients lie in LDS as well
+bool plan_of(int B, int H, int W, int c_k, int c_n, int dpool_channels, FlatPlan* plan) {
     FlatPlan p = {};
     if (c_n > 128 || (size_t)B * (H + 1) * (W + 1) >= ((size_t)1 << 30)) return false;
     p.NB = c_n <= 32 ? 1 : 2;
     p.PWAVES = c_n <= 64 ? 4 : 2;
     p.blocks = p.NB * (4 / p.PWAVES);
-    p.PB = 4;
     // Slabs per group: the largest number whose tile leaves room for two workgroups per compute unit, among those that
     // pad the contraction least.  (More channels per group: fewer reloads, each of which the workgroup waits for.)
     const int slabs = (c_k + 15) / 16;
@@ -614,16 +623,21 @@ bool conv_flat_plan(int P, int B, int H, int W, int c_k, int c_n, bool backward,
         FlatPlan q = p;
         q.CK = SL * 16;
         q.slabs = (slabs + SL - 1) / SL * SL;
-        if (lds_bytes(q, H, W, backward ? c_k : 0, 8) > 80 * 1024 || (best && q.slabs > best)) continue;
+        if (lds_bytes(q, 4, H, W, dpool_channels, 8) > 80 * 1024 || (best && q.slabs > best)) continue;
         p.CK = q.CK; p.slabs = best = q.slabs;
     }
     if (!best) return false;
-    // Half the positions per workgroup, and weights requested further ahead, where whole ones would not even be one for each of the
-    // 256 compute units: us per round of two steps, half / whole: 2 learners of 32 images of 11x24, 8-32-128 (40 workgroups) 162 / 178,
-    // 4 of 60 of 14x14, 8-64-64-64 (106) 274 / 309, 10 of 6 of 45x35, 8-16-16 (200) 156 / 156; but 8 of 32 of 28x28, 8-32-64 (424) 233 / 224.
-    if (conv_flat_workgroups(P, B, H, W, c_n) <= 256) p.PB = 2;
     *plan = p;
     return true;
+}
+
+}  // namespace
+
+bool conv_flat_plan(int B, int H, int W, int c_k, int c_n, FlatPlan* plan) { return plan_of(B, H, W, c_k, c_n, 0, plan); }
+
+// (Where the mean's gradients leave no room for a second workgroup, the plan without them: then there is one.)
+bool conv_flat_plan_last(int B, int H, int W, int c_k, int c_n, FlatPlan* plan) {
+    return plan_of(B, H, W, c_k, c_n, c_k, plan) || plan_of(B, H, W, c_k, c_n, 0, plan);
 }
 
 hipError_t launch_pack_weights(const PackLayer* layers, int n, size_t w_lstride, int P, hipStream_t st) {
@@ -651,24 +665,24 @@ hipError_t launch_pack_weights(const PackLayer* layers, int n, size_t w_lstride,
     return flush();
 }
 
-int conv_pool_slots(int H, int W, const FlatPlan& plan) {
+int conv_pool_slots(int P, int B, int H, int W, const FlatPlan& plan) {
     const int image = (H + 1) * (W + 1);
-    return image < 5 ? 0 : plan.PB * 32 / image + 2;          // (at most the 32 rows of a matrix instruction)
+    return image < 5 ? 0 : blocks_per_wave(P, B, H, W, plan) * 32 / image + 2;          // (at most the 32 rows of a matrix instruction)
 }
 
 size_t conv_pool_elems(int P, int B, int H, int W, const FlatPlan& plan) {
-    const int end = ((B - 1) * (H + 1) + H - 1) * (W + 1) + W, TP = plan.PWAVES * plan.PB * 32;
-    return (size_t)P * ((end + TP - 1) / TP) * plan.PWAVES * conv_pool_slots(H, W, plan) * plan.blocks * 32;
+    const int end = ((B - 1) * (H + 1) + H - 1) * (W + 1) + W, TP = plan.PWAVES * blocks_per_wave(P, B, H, W, plan) * 32;
+    return (size_t)P * ((end + TP - 1) / TP) * plan.PWAVES * conv_pool_slots(P, B, H, W, plan) * plan.blocks * 32;
 }
 
 hipError_t launch_pool_finish(const float* sums, const FlatPlan& plan, void* pooled, int P, int B, int H, int W, int c, hipStream_t st) {
-    const int end = ((B - 1) * (H + 1) + H - 1) * (W + 1) + W, TP = plan.PWAVES * plan.PB * 32, outputs = B * c;      // (at most 2^16 images of 128 channels)
+    const int end = ((B - 1) * (H + 1) + H - 1) * (W + 1) + W, PB = blocks_per_wave(P, B, H, W, plan), TP = plan.PWAVES * PB * 32, outputs = B * c;      // (at most 2^16 images of 128 channels)
     hipLaunchKernelGGL(pool_finish_kernel, dim3((outputs + NT - 1) / NT, P), dim3(NT), 0, st, sums, (uint16_t*)pooled, (H + 1) * (W + 1),
-                       (H - 1) * (W + 1) + W - 1, conv_pool_slots(H, W, plan), plan.PB * 32, (end + TP - 1) / TP * plan.PWAVES, plan.blocks * 32, c, 1.0f / (float)(H * W), outputs);
+                       (H - 1) * (W + 1) + W - 1, conv_pool_slots(P, B, H, W, plan), PB * 32, (end + TP - 1) / TP * plan.PWAVES, plan.blocks * 32, c, 1.0f / (float)(H * W), outputs);
     return hipGetLastError();
 }
 
-hipError_t conv_flat_forward(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag, const void* X,
+hipError_t conv_flat_forward(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag, const int32_t*, const void* X,
                              const int32_t* gather, long gstride, hipStream_t st) {
     if (!c.bits && !c.out) return hipErrorInvalidValue;
     FlatArgs a = make_args(c, plan, frag);
@@ -680,14 +694,14 @@ hipError_t conv_flat_forward(const ConvCall& c, const FlatPlan& plan, const uint
     a.sign = 1;
     if (c.bits) {
         a.bits = c.bits; a.bits_pitch = conv_bits_pitch(c.c_out); a.bits_lstride = rows * a.bits_pitch;
-        a.sums = c.pool_sums; a.slots = conv_pool_slots(c.H, c.W, plan);
+        a.sums = c.pool_sums; a.slots = conv_pool_slots(c.P, c.B, c.H, c.W, plan);
         if (!a.sums || !a.slots) return hipErrorInvalidValue;
         return gather ? run<FWD_GATHER, true>(a, plan, st) : run<FWD, true>(a, plan, st);
     }
     return gather ? run<FWD_GATHER>(a, plan, st) : run<FWD>(a, plan, st);
 }
 
-hipError_t conv_flat_backward_data(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag, const void* dpool,
+hipError_t conv_flat_backward_data(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag, const int32_t*, const void* dpool,
                                    hipStream_t st) {
     if (dpool ? !c.bits : !c.dz) return hipErrorInvalidValue;
     FlatArgs a = make_args(c, plan, frag);
@@ -695,7 +709,7 @@ hipError_t conv_flat_backward_data(const ConvCall& c, const FlatPlan& plan, cons
     a.in = (const uint16_t*)c.dz; a.in_lstride = rows * c.c_out; a.c_k = c.c_out;
     a.bits = c.bits; a.bits_pitch = conv_bits_pitch(c.c_out); a.bits_lstride = rows * a.bits_pitch;
     a.dpool = (const uint16_t*)dpool; a.dpool_lstride = (size_t)c.B * c.c_out; a.inv = 1.0f / (float)(c.H * c.W);
-    a.images = c.B; a.places = tile_images(plan.PWAVES * plan.PB * 32 + 2 * (c.W + 1) + 2, c.H, c.W);
+    a.images = c.B; a.places = tile_images(plan.PWAVES * a.PB * 32 + 2 * (c.W + 1) + 2, c.H, c.W);
     a.act = (const uint16_t*)c.in;
     a.out = (uint16_t*)c.dz_in; a.out_lstride = rows * c.c_in; a.c_n = c.c_in;
     a.sign = -1;

@@ -167,8 +167,8 @@ Layout make_layout(int P, int K, int B, int L, const int* dims, int dtype, const
                 // is odd; where that leaves them a third fewer compute units than the others' ranges, which end anywhere, those
                 // run.  (15 learners of 6 images, 64 -> 64 channels: 76 against 24 us; 16 learners of 64, 64 -> 128: 168 / 260.)
                 if (Sh > 0 && std::min(256, P * Sh) * 3 >= std::min(256, P * Sf) * 2) Sf = 0;
-                if (t == 1 ? Sf > 0 && Sh == 0 : !direct(cin, cout, false)) (void)conv_flat_plan(P, B, cv.H, cv.W, cin, cout, false, &pf);
-                if (t > 1 && !direct(cin, cout, true)) (void)conv_flat_plan(P, B, cv.H, cv.W, cout, cin, true, &pb);
+                if (t == 1 ? Sf > 0 && Sh == 0 : !direct(cin, cout, false)) (void)conv_flat_plan(B, cv.H, cv.W, cin, cout, &pf);
+                if (t > 1 && !direct(cin, cout, true)) (void)(t == M ? conv_flat_plan_last : conv_flat_plan)(B, cv.H, cv.W, cout, cin, &pb);
                 if (t == 1 && !pf.slabs && Sh == 0) Sf = 0;
             }
             // The last convolution: bits and partial sums where its forward pass runs on images of any width and kernels that
@@ -179,7 +179,7 @@ Layout make_layout(int P, int K, int B, int L, const int* dims, int dtype, const
                 const int S = t == 1 ? conv_flat_wgrad_splits(P, B, cv.H, cv.W, cin, cout, true) : 0;
                 const bool gradients = t == 1 ? S > 0 : (pb.slabs || conv_direct_ok(cv.H, cv.W, cin, cout, true)) &&
                                                         (Sf > 0 || (Sh > 0 && B / Sh <= conv_wgrad_halo_pool_images()));
-                lo.pool_bits = gradients && conv_flat_plan(P, B, cv.H, cv.W, cin, cout, false, &p) && conv_pool_slots(cv.H, cv.W, p);
+                lo.pool_bits = gradients && conv_flat_plan(B, cv.H, cv.W, cin, cout, &p) && conv_pool_slots(P, B, cv.H, cv.W, p);
                 if (lo.pool_bits) {
                     pf = p;
                     if (t == 1) { Sf = S; Sh = 0; }
@@ -1085,7 +1085,7 @@ int issue_steps_conv(kavg_ctx* c) {
         for (int t = 1; t <= M; ++t) {                              // convolutions, forward
             Bracket br(c, KAVG_CLASS_FORWARD);
             if (pack[t - 1].fwd) {
-                KAVG_HIP(c, conv_flat_forward(t == 1 ? first_call() : implicit_call(t), lo.flat_f[t - 1], pack[t - 1].fwd, c->X,
+                KAVG_HIP(c, conv_flat_forward(t == 1 ? first_call() : implicit_call(t), lo.flat_f[t - 1], pack[t - 1].fwd, table, c->X,
                                               t == 1 ? idx_k : nullptr, idx_ls, st));
                 continue;
             }
@@ -1173,7 +1173,7 @@ int issue_steps_conv(kavg_ctx* c) {
                 {
                     Bracket br(c, KAVG_CLASS_BACKWARD);
                     if (pack[t - 1].bwd) {
-                        KAVG_HIP(c, conv_flat_backward_data(v, lo.flat_b[t - 1], pack[t - 1].bwd,
+                        KAVG_HIP(c, conv_flat_backward_data(v, lo.flat_b[t - 1], pack[t - 1].bwd, table,
                                                             (pool_fused && t == M) ? dpool_M : nullptr, st));
                     } else if (conv_direct_ok(H, W, v.c_in, v.c_out, true)) {
                         KAVG_HIP(c, conv_direct_backward_data(v, (pool_fused && t == M) ? dpool_M : nullptr, st));
