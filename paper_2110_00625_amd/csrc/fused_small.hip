@@ -6,7 +6,7 @@
 // learner's first-layer weights are cut into S column chunks of CW input features (CW a multiple of
 // 64, at most 192); workgroup (j, s) keeps chunk s of learner j's W_1 in LDS for the whole call,
 // together with private copies of b_1, W_2 and b_2.  (Where the device has the compute units for it and the
-// layer has more than 32 units, two workgroups share a chunk, each with half of the hidden units: "its chunk"
+// layer has more than 32 units, two or four workgroups share a chunk, each with half or a quarter of the hidden units: "its chunk"
 // is then those units' rows of the chunk; everything else is unchanged.)  Per step
 //   1. the workgroup multiplies its CW columns of the gathered rows X[idx] with its chunk of W_1
 //      (fp32 matrix instructions) and writes the B x 64 partial pre-activations to device memory;
@@ -49,21 +49,24 @@ namespace {
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int NT = 512;         // threads per workgroup (8 wavefronts)
-constexpr int CWMAX = 192;      // input features per workgroup, at most
+constexpr int CWMAX = 192;      // input features per workgroup, at most (WIDE: twice as many)
 constexpr int HID = 64;         // hidden units (upper bound)
 constexpr int CLS = 16;         // classes (upper bound)
-constexpr int ROWS = 64;        // minibatch rows (upper bound)
+constexpr int MAXROWS = 64;     // minibatch rows (upper bound)
 // Row pitches of the LDS tiles, in words.  A matrix instruction reads a tile either as (16 rows) x (4 consecutive
 // words) or as (4 rows) x (16 consecutive words); pitches of 12 or 4 modulo the 64 banks spread the first pattern
 // over all banks (the hot one: the operands of the two big products) and the second over most.
-constexpr int PW = CWMAX + 12;  // tiles CW wide
+__host__ __device__ constexpr int pw_of(bool wide) { return (wide ? 2 * CWMAX : CWMAX) + 12; }      // tiles CW wide
 constexpr int PH = HID + 4;     // tiles 64 wide
 constexpr int PD = CLS + 4;     // dZ_2
-constexpr int TILE = ROWS * HID;
+constexpr int TILE = MAXROWS * HID;
 constexpr int KBMAX = 1024;     // K*B, at most
 
+// WIDE: a quarter of the units, minibatches of at most half as many rows
+template <bool WIDE>
 struct Smem {
-    float W1[HID * PW];         // chunk of W_1: [unit][feature]
+    static constexpr int PW = pw_of(WIDE), ROWS = MAXROWS / (WIDE ? 2 : 1), UNITS = WIDE ? HID / 4 : HID;
+    float W1[UNITS * PW];       // chunk of W_1: [unit][feature]
     float X[ROWS * PW];         // gathered rows, this chunk's columns: [row][feature]
     float A1[ROWS * PH];        // hidden activations [row][unit]
     float D1[ROWS * PH];        // dZ_1 [row][unit]
@@ -73,15 +76,52 @@ struct Smem {
     int y[ROWS];
     int idx[KBMAX];             // the learner's minibatch indices [K][B]
     int gave_up;                // a wait ran out of polls
+    float sums[WIDE ? 4 * ROWS * UNITS : 1];     // pre-activations of the four quarters of the chunk's columns
 };
 
+// acc + acc1 += sum over `columns` (a multiple of 32) of x[row][c] w[unit][c], in two chains so that the matrix pipeline does not wait for its
+// own result.  (The compiler does not unroll a loop of unknown length around matrix instructions: the operands of the next 32 columns
+// are requested by hand before those at hand are used.)
+__device__ __forceinline__ void contract(const float* xp, const float* wp, int columns, f32x4& acc, f32x4& acc1) {
+    float x[2][8], w[2][8];
+    auto request = [&](int set, int c) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) { x[set][i] = xp[c + 4 * i]; w[set][i] = wp[c + 4 * i]; }
+    };
+    auto use = [&](int set) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 8; i += 2) {
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[set][i], w[set][i], acc, 0, 0, 0);
+            acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(x[set][i + 1], w[set][i + 1], acc1, 0, 0, 0);
+        }
+    };
+    request(0, 0);
+    for (int c = 0; c < columns; c += 64) {
+        request(1, min(c + 32, columns - 32));
+        __builtin_amdgcn_sched_barrier(0);
+        use(0);
+        if (c + 32 < columns) {
+            request(0, min(c + 64, columns - 32));
+            __builtin_amdgcn_sched_barrier(0);
+            use(1);
+        }
+    }
+}
+
+// WIDE: chunks of up to 384 columns, each shared by four workgroups of 16 units, for minibatches of at most 32 rows.  A
+// workgroup then gathers the partials of half as many chunks (131 instead of 262 KB per step for 32 rows of 3072, all requested at once): the
+// exchange, not the arithmetic, is the longest part of a step.  us per round of four steps: 3072-64-10, 4 learners of 32 rows 72.2 -> 65.0,
+// 1024-64-10, 8 learners 62.0 -> 55.1, 784-64-10, 4 of 24 rows 56.2 -> 50.7.
+template <bool WIDE>
 __global__ void __launch_bounds__(NT)
 fused_small_kernel(FusedSmallCall a, int S, int CW, int UH) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    Smem& sm = *(Smem*)smem_raw;
+    typedef Smem<WIDE> Lds;
+    Lds& sm = *(Lds*)smem_raw;
+    constexpr int PW = Lds::PW, ROWS = Lds::ROWS;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // workgroup (j, s, h): learner j, column chunk s, and -- with UH = 2 -- half h of the hidden units (the chunk's
-    // two products are then shared by two compute units; everything else is as if UH were 1)
+    // workgroup (j, s, h): learner j, column chunk s, and -- with UH = 2 or 4 -- half or quarter h of the hidden units (the chunk's
+    // two products are then shared by several compute units; everything else is as if UH were 1)
     const int j = blockIdx.x / (S * UH), s = (blockIdx.x / UH) % S, h = blockIdx.x % UH;
     const int UN = HID / UH, ub = h * UN;                       // hidden units ub .. ub+UN-1 are this workgroup's
     const bool first = s == 0 && h == 0;                        // the learner's workgroup that writes what all of them hold
@@ -122,9 +162,9 @@ fused_small_kernel(FusedSmallCall a, int S, int CW, int UH) {
 
     // The thread's 16-byte pieces of a step's X tile: piece i covers row (tid / CW4 + i * (NT / CW4)) ... laid
     // out so that consecutive threads read consecutive 16 bytes of a row.
-    const int rows_per_pass = NT / CW4;                         // CW4 in {16, 32, 48}: 32, 16, 10 rows per pass
+    const int rows_per_pass = NT / CW4;                         // CW4 in {16, 32, 48}: 32, 16, 10 rows per pass; WIDE, up to 96: at least 5
     const int xr = tid / CW4, xc = (tid % CW4) * 4;
-    constexpr int XMAX = 7;                                     // passes: ceil(64 / 10)
+    constexpr int XMAX = 7;                                     // passes: ceil(64 / 10), ceil(32 / 5)
     const int xpasses = (a.B + rows_per_pass - 1) / rows_per_pass;
     // the next step's pieces (and label) are requested one step ahead
     int ynext = 0;
@@ -200,16 +240,30 @@ fused_small_kernel(FusedSmallCall a, int S, int CW, int UH) {
         //     and receives Zp[m0 + 4*(l/16) + v][u0 + l%16] in accumulator v)
         const uint32_t tag = a.tag0 + (uint32_t)k + 1u;
         uint64_t* part = a.partial + (((size_t)(k & 1) * a.P + j) * S + s) * TILE;
+        if constexpr (WIDE) {                                   // one block of units, at most two of rows: eight wavefronts take a quarter of the columns of a block each
+            const int m0 = (wave & 1) * 16, c0w = (wave >> 1) * (CW / 4);
+            if (m0 < a.B) {
+                f32x4 acc = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
+                const float* xp = sm.X + (m0 + (lane & 15)) * PW + c0w + (lane >> 4);
+                const float* wp = sm.W1 + (lane & 15) * PW + c0w + (lane >> 4);
+                contract(xp, wp, CW / 4, acc, acc1);
+                acc += acc1;
+#pragma unroll
+                for (int v = 0; v < 4; ++v) sm.sums[((wave >> 1) * ROWS + m0 + 4 * (lane >> 4) + v) * Lds::UNITS + (lane & 15)] = acc[v];
+            }
+            __syncthreads();
+            const int m = tid / Lds::UNITS, u = tid % Lds::UNITS;
+            static_assert(NT == ROWS * Lds::UNITS, "a thread per partial");
+            const float* q = sm.sums + m * Lds::UNITS + u;
+            constexpr int Q = ROWS * Lds::UNITS;
+            if (m < a.B) st_tagged(part + m * HID + ub + u, (q[0] + q[Q]) + (q[2 * Q] + q[3 * Q]), tag);
+        } else
         for (int blk = wave; blk < rblocks * (UN / 16); blk += NT / 64) {
             const int m0 = (blk / (UN / 16)) * 16, u0 = (blk % (UN / 16)) * 16;        // u0: row of sm.W1, unit ub + u0
             f32x4 acc = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};   // two chains: the matrix pipeline never waits for its own result
             const float* xp = sm.X + (m0 + (lane & 15)) * PW + (lane >> 4);
             const float* wp = sm.W1 + (u0 + (lane & 15)) * PW + (lane >> 4);
-#pragma unroll 4
-            for (int c = 0; c < CW; c += 8) {
-                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xp[c], wp[c], acc, 0, 0, 0);
-                acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(xp[c + 4], wp[c + 4], acc1, 0, 0, 0);
-            }
+            contract(xp, wp, CW, acc, acc1);
             acc += acc1;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
@@ -331,7 +385,7 @@ fused_small_kernel(FusedSmallCall a, int S, int CW, int UH) {
         //    owns one 16-unit block and every G-th 16-column block (G = wavefronts per unit block): one dZ_1 operand
         //    feeds all its blocks.
         {
-            const int nub = UN / 16, G = (NT / 64) / nub;       // 4 unit blocks x 2 column groups, or 2 x 4
+            const int nub = UN / 16, G = (NT / 64) / nub;       // 4 unit blocks x 2 column groups, or 2 x 4, or 1 x 8
             const int u0 = (wave % nub) * 16, cb0 = (wave / nub) * 16;
             const float* dp = sm.D1 + (lane >> 4) * PH + ub + u0 + (lane & 15);
             const float* xp = sm.X + (lane >> 4) * PW + cb0 + (lane & 15);
@@ -341,11 +395,18 @@ fused_small_kernel(FusedSmallCall a, int S, int CW, int UH) {
                 f32x4 acc[NB];
 #pragma unroll
                 for (int i = 0; i < NB; ++i) acc[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
-#pragma unroll 2
-                for (int m = 0; m < Bk; m += 4) {
-                    const float d = dp[m * PH];
+                for (int m = 0; m < Bk; m += 16) {              // (zeros beyond B)
+                    float d[4], x[4][NB];
 #pragma unroll
-                    for (int i = 0; i < NB; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(d, xp[m * PW + cstep * i], acc[i], 0, 0, 0);
+                    for (int t = 0; t < 4; ++t) {
+                        d[t] = dp[(m + 4 * t) * PH];
+#pragma unroll
+                        for (int i = 0; i < NB; ++i) x[t][i] = xp[(m + 4 * t) * PW + cstep * i];
+                    }
+#pragma unroll
+                    for (int t = 0; t < 4; ++t)
+#pragma unroll
+                        for (int i = 0; i < NB; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(d[t], x[t][i], acc[i], 0, 0, 0);
                 }
 #pragma unroll
                 for (int i = 0; i < NB; ++i)
@@ -391,35 +452,52 @@ int fused_small_chunk_width(int d0) {
 int fused_small_chunks(int d0) { const int cw = fused_small_chunk_width(d0); return (d0 + cw - 1) / cw; }
 
 bool fused_small_shape_ok(int P, int K, int B, int d0, int d1, int C, int compute_units) {
-    if (d1 < 1 || d1 > HID || C < 1 || C > CLS || B < 1 || B > ROWS || d0 < 4 || d0 % 4 != 0) return false;
+    if (d1 < 1 || d1 > HID || C < 1 || C > CLS || B < 1 || B > MAXROWS || d0 < 4 || d0 % 4 != 0) return false;
     if ((long)K * B > KBMAX) return false;
     return (long)P * fused_small_chunks(d0) <= compute_units;
 }
 
-// Workgroups per column chunk: two (each with half of the hidden units) when the layer is wider than 32 units and
-// the device has the compute units for it.
-int fused_small_unit_split(int P, int d0, int d1, int compute_units) {
-    return d1 > HID / 2 && (long)2 * P * fused_small_chunks(d0) <= compute_units ? 2 : 1;
+namespace {
+
+// How a learner's workgroups share W_1: S chunks of CW columns, each in the hands of UH workgroups with 64 / UH units.
+struct Split { int S, CW, UH; bool wide; };
+
+// Two workgroups per chunk when the layer is wider than 32 units and the device has the compute units for it; with more than eight
+// chunks and at most 32 rows, half as many chunks with four workgroups each.
+Split split_of(int P, int B, int d0, int d1, int compute_units) {
+    const int CW = fused_small_chunk_width(d0), S = fused_small_chunks(d0), half = (S + 1) / 2;
+    if (d1 > HID / 2 && S > 8 && B <= MAXROWS / 2 && (long)4 * P * half <= compute_units) {
+        for (int cw = 128; cw <= 2 * CWMAX; cw += 128)         // (16 columns for each of eight wavefronts)
+            if ((d0 + cw - 1) / cw <= half) return {(d0 + cw - 1) / cw, cw, 4, true};
+    }
+    return {S, CW, d1 > HID / 2 && (long)2 * P * S <= compute_units ? 2 : 1, false};
 }
+
+template <bool WIDE>
+hipError_t launch_split(const FusedSmallCall& c, const Split& p, hipStream_t st) {
+    static hipError_t raised = hipFuncSetAttribute((const void*)fused_small_kernel<WIDE>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                   (int)sizeof(Smem<WIDE>));
+    if (raised != hipSuccess) return raised;
+    hipLaunchKernelGGL(fused_small_kernel<WIDE>, dim3(c.P * p.S * p.UH), dim3(NT), sizeof(Smem<WIDE>), st, c, p.S, p.CW, p.UH);
+    return hipGetLastError();
+}
+
+}  // namespace
 
 // two buffers of P x chunks tiles of (value, tag) words, then two of P x chunks x wavefronts hint words
 size_t fused_small_partial_words(int P, int d0) { return (size_t)2 * P * fused_small_chunks(d0) * TILE; }
-size_t fused_small_scratch_bytes(int P, int d0) {          // (hint words for a unit split of two)
-    return fused_small_partial_words(P, d0) * 8 + (size_t)2 * P * fused_small_chunks(d0) * 2 * (NT / 64) * 4;
+size_t fused_small_scratch_bytes(int P, int d0) {          // (hint words for a unit split of two, or of four and half as many chunks)
+    return fused_small_partial_words(P, d0) * 8 + (size_t)2 * P * ((fused_small_chunks(d0) + 1) / 2 * 2) * 2 * (NT / 64) * 4;
 }
 
-int fused_small_workgroups(int P, int d0, int d1, int compute_units) {
-    return P * fused_small_chunks(d0) * fused_small_unit_split(P, d0, d1, compute_units);
+int fused_small_workgroups(int P, int B, int d0, int d1, int compute_units) {
+    const Split p = split_of(P, B, d0, d1, compute_units);
+    return P * p.S * p.UH;
 }
 
 hipError_t launch_fused_small(const FusedSmallCall& c, hipStream_t st) {
-    const int S = fused_small_chunks(c.d0), CW = fused_small_chunk_width(c.d0);
-    const int UH = fused_small_unit_split(c.P, c.d0, c.d1, c.compute_units);
-    static hipError_t raised = hipFuncSetAttribute((const void*)fused_small_kernel,
-                                                   hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(Smem));
-    if (raised != hipSuccess) return raised;
-    hipLaunchKernelGGL(fused_small_kernel, dim3(c.P * S * UH), dim3(NT), sizeof(Smem), st, c, S, CW, UH);
-    return hipGetLastError();
+    const Split p = split_of(c.P, c.B, c.d0, c.d1, c.compute_units);
+    return p.wide ? launch_split<true>(c, p, st) : launch_split<false>(c, p, st);
 }
 
 }  // namespace kavg

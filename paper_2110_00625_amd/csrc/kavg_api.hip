@@ -645,7 +645,7 @@ int init_common(kavg_ctx** out, int P, int K, float lr, float mu, int n_layers, 
         if (c->units_ok)
             c->workgroups = fused_units_workgroups(P, dims[1], fused_units_plan(P, K, B, dims[0], dims[1], dims[2], c->compute_units), c->compute_units);
         else if (c->fused_ok)
-            c->workgroups = fused_small_workgroups(P, dims[0], dims[1], c->compute_units);
+            c->workgroups = fused_small_workgroups(P, B, dims[0], dims[1], c->compute_units);
         if (e == hipSuccess) e = hipMemsetAsync(c->ws + lo.off_fused, 0, lo.fused_bytes, c->stream);
     }
     if (e == hipSuccess && lo.off_flat_table) e = launch_flat_table((int32_t*)(c->ws + lo.off_flat_table), B, cv.H, cv.W, c->stream);

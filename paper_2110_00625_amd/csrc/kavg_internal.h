@@ -214,7 +214,7 @@ int fused_small_chunks(int d0);
 bool fused_small_shape_ok(int P, int K, int B, int d0, int d1, int C, int compute_units);
 size_t fused_small_scratch_bytes(int P, int d0);
 size_t fused_small_partial_words(int P, int d0);
-int fused_small_workgroups(int P, int d0, int d1, int compute_units);        // of one launch
+int fused_small_workgroups(int P, int B, int d0, int d1, int compute_units);        // of one launch
 hipError_t launch_fused_small(const FusedSmallCall& c, hipStream_t st);
 // the same for wide hidden layers on short inputs (fused_units.hip; no hints): hidden units per workgroup, 0 = not covered
 int fused_units_plan(int P, int K, int B, int d0, int d1, int C, int compute_units);

@@ -44,6 +44,23 @@ def test_split_by_inputs(P, K, B, dims):
     _run_and_compare(g, o, dims, 2, TOL_FP32, "by inputs %s, caller's indices" % (dims,))
 
 
+# four workgroups of 16 units to a chunk of up to 384 columns, where its chunks, rows and units end
+QUARTERS = [
+    (4, 3, 32, (3072, 64, 10)),        # eight chunks of 384 columns
+    (3, 3, 31, (3076, 33, 16)),        # nine chunks, the last one 4 columns wide; 33 units; odd batch
+    (2, 4, 1, (580, 64, 2)),           # one row; ten chunks of 64 columns become five of 128, the last one 68 wide
+    (5, 2, 17, (1028, 49, 9)),         # one row in the second block of rows; chunks of 256
+    (1, 2, 16, (4092, 64, 10)),        # one block of rows
+]
+
+
+@pytest.mark.parametrize("P,K,B,dims", QUARTERS, ids=["B%d-%s" % (c[2], c[3]) for c in QUARTERS])
+def test_quarters_of_the_units(P, K, B, dims):
+    g, o = _pair(P, K, 0.05, 0.9, dims, B, False, 97)
+    assert g.one_launch == 1
+    _run_and_compare(g, o, dims, 3, TOL_FP32, "quarters %s" % (dims,))
+
+
 LINES = [
     # P, B, dims, kernel: on either side of the lines of the rule where both kernels cover a shape
     (48, 16, (256, 64, 10), 2), (49, 16, (256, 64, 10), 1), (200, 9, (64, 64, 10), 2), (128, 9, (64, 64, 10), 1),
