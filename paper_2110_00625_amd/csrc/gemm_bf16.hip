@@ -61,8 +61,9 @@ enum { MODE_FWD = 0, MODE_BWD = 1, MODE_UPD = 2 };
 // memory pipeline while its MFMAs could run); whole slices only.  LATE (update, long contractions): as PLAIN, but
 // the master is requested under the last slice, which leaves registers for a third workgroup per compute unit but for eight
 // (166 - 168 used, 36 bytes of scratch per lane), and the tiles of eight tile rows follow each other column by column.
-enum { PIPE_PLAIN = 0, PIPE_LDS2 = 1, PIPE_DMA = 2, PIPE_RING = 3, PIPE_LATE = 4 };
-constexpr int RING_LOADERS = 2, RING_BYTES = 144 * 1024;
+// DEEP: as DMA, four LDS buffers, three slices in flight (one workgroup per compute unit).
+enum { PIPE_PLAIN = 0, PIPE_LDS2 = 1, PIPE_DMA = 2, PIPE_RING = 3, PIPE_LATE = 4, PIPE_DEEP = 5 };
+constexpr int RING_LOADERS = 2, RING_BYTES = 144 * 1024, DEEP_BUFS = 4;
 
 struct Operand {
     const uint16_t* base;    // learner 0
@@ -444,12 +445,12 @@ struct Shape {
     static constexpr int MR = TR / (32 * WR), MC = TC / (32 * WC);
     static constexpr int WTC = MC * 32;                 // columns of a wavefront's tile
     static constexpr int SPITCH = WTC + 4;              // update epilogue: fp32 staging row, padded
-    static constexpr bool DIRECT = PIPE == PIPE_DMA || PIPE == PIPE_RING;       // global -> LDS loads, unpadded swizzled tiles
+    static constexpr bool DIRECT = PIPE == PIPE_DMA || PIPE == PIPE_RING || PIPE == PIPE_DEEP;       // global -> LDS loads, unpadded swizzled tiles
     static constexpr int THREADS = 64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING_LOADERS : 0));
     static constexpr int R_ELEMS = DIRECT ? TR * BK : RTRANS ? BK * tpitch(TR) : TR * dpitch(BK);
     static constexpr int C_ELEMS = DIRECT ? TC * BK : CTRANS ? BK * tpitch(TC) : TC * dpitch(BK);
     static constexpr int RING_BUFS = RING_BYTES / ((R_ELEMS + C_ELEMS) * 2);
-    static constexpr int OPER_BYTES = (PIPE == PIPE_PLAIN || PIPE == PIPE_LATE ? 1 : PIPE == PIPE_RING ? RING_BUFS : 2) * (R_ELEMS + C_ELEMS) * 2;
+    static constexpr int OPER_BYTES = (PIPE == PIPE_PLAIN || PIPE == PIPE_LATE ? 1 : PIPE == PIPE_RING ? RING_BUFS : PIPE == PIPE_DEEP ? DEEP_BUFS : 2) * (R_ELEMS + C_ELEMS) * 2;
     static constexpr int STAGE_BYTES = MODE == MODE_UPD ? 4 * 32 * SPITCH * 4 : 0;
     static constexpr int KRED_BYTES = WK > 1 ? WR * WC * MR * MC * 16 * 64 * 4 : 0;   // one k group's partial tiles
     static constexpr int SMEM1 = OPER_BYTES > STAGE_BYTES ? OPER_BYTES : STAGE_BYTES;
@@ -465,17 +466,17 @@ struct Shape {
 // MERGED (forward, backward-data): all learners multiply by the same weights, so their rows are those of one product: each tile of
 // weights is read once per 256 or 128 rows instead of once per learner (learner strides of R, bias, mask and output by row).
 // CONV_R / CONV_C: that operand is the implicit patch matrix of a convolution (Operand::cv_c).
-template <int MODE, int TR, int TC, int WR, int WC, int WK, int BK, bool RTRANS, bool CTRANS, int PIPE, bool SHADOW_CACHED = false,
+template <int MODE, int TR, int TC, int WR, int WC, int WK, int BK, bool RTRANS, bool CTRANS, int PIPE, int STREAM = STREAM_BOTH,
           bool GATHER_C = false, bool CONV_R = false, bool CONV_C = false, bool MERGED = false>
 __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING_LOADERS : 0)), PIPE == PIPE_LATE ? 3 : 1) gemm_bf16_kernel(Args a) {
-    static_assert(!CONV_R || (!RTRANS && PIPE != PIPE_DMA), "implicit R operand: k-contiguous, staged through registers");
+    static_assert(!CONV_R || (!RTRANS && PIPE != PIPE_DMA && PIPE != PIPE_DEEP), "implicit R operand: k-contiguous, staged through registers");
     static_assert(!CONV_C || (CTRANS && !GATHER_C && MODE == MODE_UPD), "implicit C operand: the update's transposed operand");
     constexpr int NW = WR * WC * WK, NT = 64 * NW;
     constexpr int MR = TR / (32 * WR), MC = TC / (32 * WC);
     static_assert(MR >= 1 && MC >= 1, "tile too small for the wave grid");
     static_assert((BK / 16) % WK == 0, "slice must split evenly over the k groups");
     static_assert(MODE != MODE_UPD || (WK == 1 && NW == 4 && (PIPE == PIPE_PLAIN || PIPE == PIPE_LATE)), "the update epilogue assumes 4 wavefronts, no k split, one LDS buffer");
-    constexpr bool DIRECT = PIPE == PIPE_DMA || PIPE == PIPE_RING;
+    constexpr bool DIRECT = PIPE == PIPE_DMA || PIPE == PIPE_RING || PIPE == PIPE_DEEP;
     static_assert(PIPE != PIPE_RING || (WK == 1 && MODE != MODE_UPD), "ring pipeline: forward / backward-data without a k split");
     static_assert(NT % (TR / 8) == 0 && NT % (TC / 8) == 0, "loader column mapping");
     typedef Shape<MODE, TR, TC, WR, WC, WK, BK, RTRANS, CTRANS, PIPE> SH;
@@ -706,6 +707,38 @@ __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING
             buf = buf == NB - 1 ? 0 : buf + 1;
         }
         __syncthreads();                                // tiles are dead: the epilogue reuses their LDS
+    } else if constexpr (PIPE == PIPE_DEEP) {
+        static_assert(!RTRANS && !CTRANS && MODE != MODE_UPD, "direct LDS loads: k-contiguous operands only");
+        DmaLoader<TR, BK, NT> rdma; DmaLoader<TC, BK, NT> cdma;
+        rdma.template init<MERGED>(a.R, Rbase, Rg, r0, tid, a.rows);
+        cdma.init(a.C, Cbase, Cg, c0, tid);
+        constexpr int D = DEEP_BUFS - 1, LN = (TR + TC) * BK / 8 / NT;       // slices in flight; loads per wavefront and slice
+        static_assert(D == 3 && 2 * LN <= 63, "the slices in flight must fit the wavefront's load counter");
+        const int slices = (a.nK + BK - 1) / BK;
+        auto request = [&](int s) {
+            rdma.load(a.R, s * BK, Rs + (s % DEEP_BUFS) * BUF_ELEMS, tid);
+            cdma.load(a.C, s * BK, Cs + (s % DEEP_BUFS) * BUF_ELEMS, tid, a.c_stream);
+        };
+#pragma unroll
+        for (int d = 0; d < D; ++d) if (d < slices) request(d);
+        for (int s = 0; s < slices; ++s) {
+            // slice s has landed when at most the younger ones are on their way
+            const int younger = min(D - 1, slices - 1 - s);
+            if (younger == 2) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * LN) : "memory");
+            else if (younger == 1) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LN) : "memory");
+            else asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            const int buf = s % DEEP_BUFS, k0 = s * BK;
+            if (k0 + BK > a.R.n_cont || k0 + BK > a.C.n_cont) {      // ragged end of the contraction
+                rdma.fix_tail(a.R, k0, Rs + buf * BUF_ELEMS, tid);
+                cdma.fix_tail(a.C, k0, Cs + buf * BUF_ELEMS, tid);
+            }
+            // everyone's part is there, and everyone's reads of slice s - 1 are done: its buffer takes slice s + 3.  (A barrier
+            // without the fence that would wait for the slices in flight.)
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            if (s + D < slices) request(s + D);
+            multiply(buf);
+        }
+        __syncthreads();                                // tiles are dead: the k-group reduction reuses their LDS
     } else if constexpr (PIPE == PIPE_DMA) {
         static_assert(!RTRANS && !CTRANS && MODE != MODE_UPD, "direct LDS loads: k-contiguous operands only");
         DmaLoader<TR, BK, NT> rdma; DmaLoader<TC, BK, NT> cdma;
@@ -767,9 +800,8 @@ __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING
             const int r = min(r0 + (wr * MR + i) * 32 + it * ROWS_PER_IT + lane / L8_PER_ROW, a.nR - 1);
             // hi was left in the memory-side cache by the previous writer when it fits there
             // (otherwise it is streamed like lo, so as not to push anything else out)
-            hi = SHADOW_CACHED ? *(const u32x4*)(hbase + (size_t)r * a.nC + c)
-                               : __builtin_nontemporal_load((const u32x4*)(hbase + (size_t)r * a.nC + c));
-            lo = __builtin_nontemporal_load((const u32x4*)(lbase + (size_t)r * a.nC + c));
+            hi = plane_get<STREAM == STREAM_BOTH>((const u32x4*)(hbase + (size_t)r * a.nC + c));
+            lo = plane_get<STREAM != STREAM_NONE>((const u32x4*)(lbase + (size_t)r * a.nC + c));
         };
         if (MODE == MODE_UPD) {
             __builtin_amdgcn_sched_barrier(0);          // keep the operand loads the oldest
@@ -1011,12 +1043,12 @@ __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING
                     float step[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
                     if (a.u) {                                  // heavy ball inside the learner
                         f32x4* up = (f32x4*)(a.u + (size_t)learner * a.w_lstride + (size_t)r * a.nC + c);
-                        const f32x4 u0 = __builtin_nontemporal_load(up), u1 = __builtin_nontemporal_load(up + 1);
+                        const f32x4 u0 = plane_get<STREAM != STREAM_NONE>(up), u1 = plane_get<STREAM != STREAM_NONE>(up + 1);
                         const float uo[8] = {u0.x, u0.y, u0.z, u0.w, u1.x, u1.y, u1.z, u1.w};
 #pragma unroll
                         for (int e = 0; e < 8; ++e) step[e] = a.beta * uo[e] + step[e];
-                        __builtin_nontemporal_store((f32x4){step[0], step[1], step[2], step[3]}, up);
-                        __builtin_nontemporal_store((f32x4){step[4], step[5], step[6], step[7]}, up + 1);
+                        plane_put<STREAM != STREAM_NONE>(up, (f32x4){step[0], step[1], step[2], step[3]});
+                        plane_put<STREAM != STREAM_NONE>(up + 1, (f32x4){step[4], step[5], step[6], step[7]});
                     }
                     u32x4 oh, ol;
 #pragma unroll
@@ -1032,9 +1064,8 @@ __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING
                     // fit there, an ordinary store leaves it in the memory-side cache; when they do not, it
                     // would only displace other lines.  The lo plane (and the velocity) is streamed once
                     // per step and always bypasses the cache.
-                    if (SHADOW_CACHED) *(u32x4*)(hbase + (size_t)r * a.nC + c) = oh;
-                    else __builtin_nontemporal_store(oh, (u32x4*)(hbase + (size_t)r * a.nC + c));
-                    __builtin_nontemporal_store(ol, (u32x4*)(lbase + (size_t)r * a.nC + c));
+                    plane_put<STREAM == STREAM_BOTH>((u32x4*)(hbase + (size_t)r * a.nC + c), oh);
+                    plane_put<STREAM != STREAM_NONE>((u32x4*)(lbase + (size_t)r * a.nC + c), ol);
                 }
             }
         }
@@ -1052,7 +1083,7 @@ __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING
     }
 }
 
-template <int MODE, int TR, int TC, int WR, int WC, int WK, int BK, bool RT, bool CT, int PIPE, bool SC = false, bool GC = false,
+template <int MODE, int TR, int TC, int WR, int WC, int WK, int BK, bool RT, bool CT, int PIPE, int SC = STREAM_BOTH, bool GC = false,
           bool CVR = false, bool CVC = false, bool MG = false>
 hipError_t launch(Args a, int P, hipStream_t st) {
     a.tiles_c = (a.nC + TC - 1) / TC;
@@ -1080,7 +1111,7 @@ int round8(int x) { return (x + 7) / 8 * 8; }
 enum { T128x128 = 0, T128x64 = 1, T64x128 = 2, T64x64_K2 = 3, T256x128 = 4 };
 
 // Measured on MI355X over the workload shapes (batch 64..256, widths 1024..4096, 8..32 learners):
-// with >= 512 tiles of 128x128 the launch fills the chip with the tile that reads LDS least per
+// with >= 512 (forward: 257) tiles of 128x128 the launch fills the chip with the tile that reads LDS least per
 // flop; smaller problems are LDS- and barrier-bound per workgroup, and the 64x64 tile with two k
 // groups (most wavefronts per compute unit, half as many barriers per k) wins.
 int pick_tile(int mode, int nR, int nC, int nK, int P) {
@@ -1090,7 +1121,10 @@ int pick_tile(int mode, int nR, int nC, int nK, int P) {
     if (mode == MODE_FWD) {
         if (nR % 256 == 0 && nK % 64 == 0 && nK >= 128 && (long)(nR / 256) * ((nC + 127) / 128) * P >= 192) return T256x128;
         if (nR <= 64) return (long)((nC + 127) / 128) * P >= 512 ? T64x128 : T64x64_K2;
-        return tiles128 >= 512 ? T128x128 : T64x64_K2;
+        // (64x64 tiles of 65 to 128 rows read every weight twice, streamed ones out of memory.  us per round of four steps, 64x64 / 128x128:
+        // 416 tiles, 32 learners of 107 rows of 568-2872-1616-218 3532 / 3421; 288, 12 of 90 of 1000-3000-10 495 / 473; 256 and 224 742 /
+        // 743 and 549 / 546; 192 870 / 873; 128 756 / 836.)
+        return tiles128 > 256 ? T128x128 : T64x64_K2;
     }
     // backward-data, measured at the 4096-wide layers: 128x128 95 us against 119 us for 128x64 (batch 256),
     // 64x128 222 us against 249 us for 64x64 (batch 64)
@@ -1116,7 +1150,14 @@ hipError_t launch_tiled(const Args& a, int P, int tile, hipStream_t st) {
             // forward: slices of 128 loaded straight into LDS (measured 26 against 30 us for layer 1 of the
             // CIFAR-MLP workload); backward-data (weights read through the transpose path): slices of 64,
             // double-buffered LDS filled from registers
-            if constexpr (MODE == MODE_FWD) return launch<MODE, 64, 64, 2, 2, 2, 128, RT, CT, PIPE_DMA>(a, P, st);
+            if constexpr (MODE == MODE_FWD) {
+                // One workgroup per compute unit or fewer: nothing hides the slices but more of them in flight.  (us per round of
+                // four steps, two / four buffers: 3080-1032-520-24, 5 learners of 70 rows, 170 workgroups 364 / 339; 4096-2048-512-100,
+                // 4 of 64 513 / 474; 4000-600-10, 2 of 16 166 / 153; but with 512 workgroups, two of which share a compute unit's LDS,
+                // 2048-2048-2048-10, 8 of 100 756 / 813.)
+                if ((long)((a.nR + 63) / 64) * ((a.nC + 63) / 64) * P <= 256 && a.nK > 256) return launch<MODE, 64, 64, 2, 2, 2, 128, RT, CT, PIPE_DEEP>(a, P, st);
+                return launch<MODE, 64, 64, 2, 2, 2, 128, RT, CT, PIPE_DMA>(a, P, st);
+            }
             else return launch<MODE, 64, 64, 2, 2, 2, 64, RT, CT, PIPE_LDS2>(a, P, st);
     }
 }
@@ -1136,6 +1177,39 @@ bool merge_rows(const LayerCall& c, Args& a, int tr, int tc) {
     a.R.n_rows = a.nR = (int)rows;
     return true;
 }
+template <int SC>
+hipError_t launch_update(const Args& a, const LayerCall& c, int rows, int P, hipStream_t st) {
+    // Tile shapes from measured sweeps (whole rounds, same box): wavefront tiles of 32x64 in both regimes
+    // (128-byte row segments per plane), as 128x64 where the bf16 planes stay in the memory-side
+    // cache (CIFAR-MLP) and as 64x128 where they stream (the 4096-wide workloads with batches up to 128).
+    const long tiles128 = (long)((a.nR + 127) / 128) * ((a.nC + 127) / 128) * P;
+    if (rows > 256 && !c.partial && (!c.shadow_cached || tiles128 >= 512)) {
+        // Here the contraction is the longer part, its operands come from memory, and one slice of look-ahead in two workgroups per
+        // compute unit does not cover that: a third workgroup instead of an early master.  (Refresh of 32 learners, 1024 rows, us:
+        // 4096 -> 4096 2139 / 1785 = 615 TFLOP/s, 3072 -> 4096 1631 / 1319.  Rounds, without / with it: 3072-4096-10, 32 learners,
+        // 320 rows 4020 / 4000; 4000-2000-100, 8 learners, 300 rows 1100 / 1094; with 256 rows, every step of the 4096-wide model,
+        // 22 200 / 22 380.)  Where the planes are cached the other choice is a tile half as large, which wins below two
+        // workgroups per compute unit: 3072-1024-1024-10, 16 learners, 512 rows, 1024 and more tiles 1243 / 1220; 567 tiles, 7
+        // learners, 1000 rows 1217 / 1213; 384, 6 learners, 768 rows 653 / 660; 126 and 315, 7 learners, 1248 rows 803 / 812.
+        if (c.gather) return launch<MODE_UPD, 128, 128, 2, 2, 1, 64, true, true, PIPE_LATE, SC, true>(a, P, st);
+        return launch<MODE_UPD, 128, 128, 2, 2, 1, 64, true, true, PIPE_LATE, SC, false>(a, P, st);
+    }
+    if constexpr (SC == STREAM_LO) {
+        if (c.gather) return launch<MODE_UPD, 128, 64, 4, 1, 1, 64, true, true, PIPE_PLAIN, SC, true>(a, P, st);
+        return launch<MODE_UPD, 128, 64, 4, 1, 1, 64, true, true, PIPE_PLAIN, SC, false>(a, P, st);
+    } else {
+        if (rows > 128) {
+            // Long contractions: per output tile the two operands (read out of the L2 cache, B rows each) weigh as
+            // much as the master tile itself, and a compute unit can only pull so many bytes per clock; a
+            // 128x128 tile reads a third less of them per weight (large: 15.0 -> 14.5 ms per round).
+            if (c.gather) return launch<MODE_UPD, 128, 128, 2, 2, 1, 64, true, true, PIPE_PLAIN, SC, true>(a, P, st);
+            return launch<MODE_UPD, 128, 128, 2, 2, 1, 64, true, true, PIPE_PLAIN, SC, false>(a, P, st);
+        }
+        if (c.gather) return launch<MODE_UPD, 64, 128, 2, 2, 1, 64, true, true, PIPE_PLAIN, SC, true>(a, P, st);
+        return launch<MODE_UPD, 64, 128, 2, 2, 1, 64, true, true, PIPE_PLAIN, SC, false>(a, P, st);
+    }
+}
+
 }  // namespace
 
 hipError_t bf16_forward(const LayerCall& c, hipStream_t st) {
@@ -1145,7 +1219,7 @@ hipError_t bf16_forward(const LayerCall& c, hipStream_t st) {
     a.nR = c.B; a.nC = c.d_out; a.nK = c.d_in;
     a.bias_hi = c.bhi; a.bias_lo = c.blo; a.bias_lstride = c.ws_stride;
     a.out = c.out; a.out_lstride = c.out_stride; a.ld_out = c.ld_out; a.relu = c.relu;
-    a.c_stream = !c.shadow_cached && !c.shared_w;
+    a.c_stream = !c.shadow_cached && !c.shared_w && whole_lines(c);
     if (a.nK % 64 == 0 && a.nK >= 128 && merge_rows(c, a, 256, 128))
         return launch<MODE_FWD, 256, 128, 2, 2, 1, 64, false, false, PIPE_RING, false, false, false, false, true>(a, 1, st);
     return launch_tiled<MODE_FWD, false, false>(a, c.P, pick_tile(MODE_FWD, a.nR, a.nC, a.nK, c.P), st);
@@ -1186,38 +1260,9 @@ hipError_t bf16_update(const LayerCall& c, hipStream_t st) {
     a.ws = c.ws; a.wlo = c.wlo; a.ws_lstride = c.ws_stride; a.bhi = c.bhi; a.blo = c.blo; a.w_lstride = c.w_stride;
     a.lr = c.lr; a.u = c.u; a.ub = c.ub; a.beta = c.beta;
     a.next_gather = c.gather ? c.next_gather : nullptr;
-    // Tile shapes from measured sweeps (whole rounds, same box): wavefront tiles of 32x64 in both regimes
-    // (128-byte row segments per plane), as 128x64 where the bf16 planes stay in the memory-side
-    // cache (CIFAR-MLP) and as 64x128 where they stream (the 4096-wide workloads with batches up to 128).
-    const long tiles128 = (long)((a.nR + 127) / 128) * ((a.nC + 127) / 128) * P;
-    if (rows > 256 && !c.partial && (!c.shadow_cached || tiles128 >= 512)) {
-        // Here the contraction is the longer part, its operands come from memory, and one slice of look-ahead in two workgroups per
-        // compute unit does not cover that: a third workgroup instead of an early master.  (Refresh of 32 learners, 1024 rows, us:
-        // 4096 -> 4096 2139 / 1785 = 615 TFLOP/s, 3072 -> 4096 1631 / 1319.  Rounds, without / with it: 3072-4096-10, 32 learners,
-        // 320 rows 4020 / 4000; 4000-2000-100, 8 learners, 300 rows 1100 / 1094; with 256 rows, every step of the 4096-wide model,
-        // 22 200 / 22 380.)  Where the planes are cached the other choice is a tile half as large, which wins below two
-        // workgroups per compute unit: 3072-1024-1024-10, 16 learners, 512 rows, 1024 and more tiles 1243 / 1220; 567 tiles, 7
-        // learners, 1000 rows 1217 / 1213; 384, 6 learners, 768 rows 653 / 660; 126 and 315, 7 learners, 1248 rows 803 / 812.
-        if (c.shadow_cached) {
-            if (c.gather) return launch<MODE_UPD, 128, 128, 2, 2, 1, 64, true, true, PIPE_LATE, true, true>(a, P, st);
-            return launch<MODE_UPD, 128, 128, 2, 2, 1, 64, true, true, PIPE_LATE, true, false>(a, P, st);
-        }
-        if (c.gather) return launch<MODE_UPD, 128, 128, 2, 2, 1, 64, true, true, PIPE_LATE, false, true>(a, P, st);
-        return launch<MODE_UPD, 128, 128, 2, 2, 1, 64, true, true, PIPE_LATE, false, false>(a, P, st);
-    }
-    if (c.shadow_cached) {
-        if (c.gather) return launch<MODE_UPD, 128, 64, 4, 1, 1, 64, true, true, PIPE_PLAIN, true, true>(a, P, st);
-        return launch<MODE_UPD, 128, 64, 4, 1, 1, 64, true, true, PIPE_PLAIN, true, false>(a, P, st);
-    }
-    if (rows > 128) {
-        // Long contractions: per output tile the two operands (read out of the L2 cache, B rows each) weigh as
-        // much as the master tile itself, and a compute unit can only pull so many bytes per clock; a
-        // 128x128 tile reads a third less of them per weight (large: 15.0 -> 14.5 ms per round).
-        if (c.gather) return launch<MODE_UPD, 128, 128, 2, 2, 1, 64, true, true, PIPE_PLAIN, false, true>(a, P, st);
-        return launch<MODE_UPD, 128, 128, 2, 2, 1, 64, true, true, PIPE_PLAIN, false, false>(a, P, st);
-    }
-    if (c.gather) return launch<MODE_UPD, 64, 128, 2, 2, 1, 64, true, true, PIPE_PLAIN, false, true>(a, P, st);
-    return launch<MODE_UPD, 64, 128, 2, 2, 1, 64, true, true, PIPE_PLAIN, false, false>(a, P, st);
+    const int stream = stream_policy(c);
+    if (stream == STREAM_NONE) return launch_update<STREAM_NONE>(a, c, rows, P, st);
+    return stream == STREAM_LO ? launch_update<STREAM_LO>(a, c, rows, P, st) : launch_update<STREAM_BOTH>(a, c, rows, P, st);
 }
 
 // ---- 3x3 convolutions on the implicit patch matrix (no im2col): see ConvCall in kavg_internal.h ----
@@ -1271,7 +1316,7 @@ hipError_t bf16_conv_update_partial(const ConvCall& c, hipStream_t st) {
     a.nR = c.c_out; a.nC = 9 * c.c_in; a.nK = range;
     a.ws = c.ws; a.wlo = c.wlo; a.ws_lstride = c.ws_stride; a.bhi = (uint16_t*)c.bhi; a.blo = (uint16_t*)c.blo; a.w_lstride = c.ws_stride;
     a.partial = c.partial; a.partial_bias = c.partial_bias;
-    return launch<MODE_UPD, 128, 64, 4, 1, 1, 64, true, true, PIPE_PLAIN, true, false, false, true>(a, c.P * c.splits, st);
+    return launch<MODE_UPD, 128, 64, 4, 1, 1, 64, true, true, PIPE_PLAIN, STREAM_LO, false, false, true>(a, c.P * c.splits, st);
 }
 
 hipError_t bf16_gram(const GramCall& c, hipStream_t st) {

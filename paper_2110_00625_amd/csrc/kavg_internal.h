@@ -88,6 +88,23 @@ struct LayerCall {
     float* partial; float* partial_bias; int splits;
 };
 
+// Rows of the weights' planes are whole 128-byte lines.  Streaming (non-temporal) accesses pay only there: where rows are ragged two
+// workgroups share a line, and each of them fetches it from memory, or writes its part of it there, by itself.  (Rounds of two steps, us,
+// streaming / ordinary accesses throughout: 3432-1728-10, 32 learners of 64 rows 1595 / 1203; 1544-2504-1320-10, 30 of 40
+// 1826 / 1437; 4088-4008-1000, 8 of 256 1488 / 1320; 4000-4000-10 (half lines), 16 of 100 1582 / 1588; but 4096-4096-10, 16 of 128
+// 1459 / 1638.)
+inline bool whole_lines(const LayerCall& c) {
+    return c.d_in % 64 == 0 && c.ws_stride % 64 == 0 && ((uintptr_t)c.ws | (uintptr_t)c.wlo) % 128 == 0;
+}
+// How an update reads and writes the planes: streaming both, streaming the lo planes alone (the hi planes stay in the memory-side cache),
+// with ordinary accesses (planes that stream, in ragged rows).
+enum { STREAM_BOTH = 0, STREAM_LO = 1, STREAM_NONE = 2 };
+// (Hi planes that stay cached are worth more than the shared lines of the lo planes: 3080-1032-1032-10, 16 learners of 128 rows, four steps, streaming
+// / ordinary lo planes 941 / 1027 us, 1000-1000-1000-10, 30 of 100 768 / 824.)
+inline int stream_policy(const LayerCall& c) { return c.shadow_cached ? STREAM_LO : whole_lines(c) ? STREAM_BOTH : STREAM_NONE; }
+template <bool STREAM, class T> __device__ __forceinline__ T plane_get(const T* p) { return STREAM ? __builtin_nontemporal_load(p) : *p; }
+template <bool STREAM, class T> __device__ __forceinline__ void plane_put(T* p, T v) { if (STREAM) __builtin_nontemporal_store(v, p); else *p = v; }
+
 // ---- deferred weight updates (Algorithm 1: every local step adds a rank-B term -lr dZ^T A to the
 // learner's weights; between two refreshes of the stored replica the products use the stored
 // weights plus those terms, W_k x = W_0 x - lr sum_i dZ_i^T (A_i x)) ----

@@ -86,7 +86,7 @@ __device__ __forceinline__ bf16x8 frag_tr(const uint16_t* tile, int pitch, int k
 
 // STREAM: the hi planes of all learners do not stay in the memory-side cache (the lo planes never do).  CHAINS: the data
 // gradient's sums, one chain over the units, or two (even and odd chunks) that are added up at the end.
-template <int BT, bool STREAM, int CHAINS>
+template <int BT, int STREAM, int CHAINS>
 __global__ void __launch_bounds__(NT) strip_kernel(StripArgs a) {
     typedef StripShape<BT> SH;
     constexpr int ZN = SH::ZN, KS = BT / 16;                 // slabs of 16 samples
@@ -94,7 +94,7 @@ __global__ void __launch_bounds__(NT) strip_kernel(StripArgs a) {
     // with 1024 -> 1024, 32 learners of 128) or has no registers left beside the accumulators.  64: two where a second
     // workgroup per compute unit counts for more (planes that stream: 0.3 % of a round), else three (58 against 59 us); with
     // two chains there are hardly more strips than compute units, and four are 1 - 2 % of a round faster than two.
-    constexpr int SETS = BT > 64 ? 2 : CHAINS == 2 ? 4 : STREAM ? 2 : 3;
+    constexpr int SETS = BT > 64 ? 2 : CHAINS == 2 ? 4 : STREAM == STREAM_LO ? 3 : 2;
     static_assert(CHAINS == 1 || SETS % 2 == 0, "a chunk's set has its parity");
     // blocks of a wavefront's data gradient: input units x samples
     constexpr int CBW = BT == 64 ? 1 : 2, SBW = BT / 32 / CBW;
@@ -124,8 +124,8 @@ __global__ void __launch_bounds__(NT) strip_kernel(StripArgs a) {
     // No load is predicated: places outside are read from clamped ones and dropped later.
     auto load = [&](int set, int r0) __attribute__((always_inline)) {
         const size_t p = (size_t)min(r0 + wrow, a.d_out - 1) * a.d_in + min(c0 + wcol, a.d_in - 8);
-        hr[set] = STREAM ? __builtin_nontemporal_load((const u32x4*)(hi + p)) : *(const u32x4*)(hi + p);
-        lr_[set] = __builtin_nontemporal_load((const u32x4*)(lo + p));
+        hr[set] = plane_get<STREAM == STREAM_BOTH>((const u32x4*)(hi + p));
+        lr_[set] = plane_get<STREAM != STREAM_NONE>((const u32x4*)(lo + p));
 #pragma unroll
         for (int i = 0; i < ZN; ++i) {
             const int e = tid + NT * i, s = e / (RC / 8), r = r0 + (e % (RC / 8)) * 8;
@@ -187,8 +187,8 @@ __global__ void __launch_bounds__(NT) strip_kernel(StripArgs a) {
         }
         if (r0 + wrow < a.d_out && c0 + wcol < a.d_in) {
             const size_t p = (size_t)(r0 + wrow) * a.d_in + c0 + wcol;
-            if (STREAM) __builtin_nontemporal_store(oh, (u32x4*)(hi + p)); else *(u32x4*)(hi + p) = oh;
-            __builtin_nontemporal_store(ol, (u32x4*)(lo + p));
+            plane_put<STREAM == STREAM_BOTH>((u32x4*)(hi + p), oh);
+            plane_put<STREAM != STREAM_NONE>((u32x4*)(lo + p), ol);
         }
         if (tid < RC && r0 + tid < a.d_out && owns_bias(r0)) {
             const float b = __builtin_bit_cast(float, split_join(br[set][0], br[set][1])) - a.lr * GB[tid];
@@ -285,7 +285,7 @@ __global__ void __launch_bounds__(NT) strip_kernel(StripArgs a) {
         }
 }
 
-template <int BT, bool STREAM, int CHAINS>
+template <int BT, int STREAM, int CHAINS>
 hipError_t launch(const StripArgs& a, hipStream_t st) {
     constexpr int SMEM = StripShape<BT>::SMEM;
     static_assert(SMEM <= 160 * 1024, "more LDS than a compute unit has");
@@ -298,8 +298,9 @@ hipError_t launch(const StripArgs& a, hipStream_t st) {
     return hipGetLastError();
 }
 template <int BT, int CHAINS>
-hipError_t launch_stream(const StripArgs& a, bool stream, hipStream_t st) {
-    return stream ? launch<BT, true, CHAINS>(a, st) : launch<BT, false, CHAINS>(a, st);
+hipError_t launch_stream(const StripArgs& a, int stream, hipStream_t st) {
+    if (stream == STREAM_NONE) return launch<BT, STREAM_NONE, CHAINS>(a, st);
+    return stream == STREAM_LO ? launch<BT, STREAM_LO, CHAINS>(a, st) : launch<BT, STREAM_BOTH, CHAINS>(a, st);
 }
 
 }  // namespace
@@ -327,7 +328,7 @@ hipError_t bf16_strip(const LayerCall& c, hipStream_t st) {
     a.padded = (a.total + 7) / 8 * 8;
     // where the separate data gradient would split its contraction (small launches, up to 128 samples), so does this one
     const bool two = bf16_backward_splits(c.P, c.B, c.d_in, c.d_out);
-    const bool stream = !c.shadow_cached;
+    const int stream = stream_policy(c);
     if (c.B <= 64) return two ? launch_stream<64, 2>(a, stream, st) : launch_stream<64, 1>(a, stream, st);
     if (c.B <= 128) return two ? launch_stream<128, 2>(a, stream, st) : launch_stream<128, 1>(a, stream, st);
     if (two) return hipErrorInvalidValue;                    // (never: 192 strips of more than 128 samples are 384 tiles)

@@ -72,11 +72,8 @@ __device__ __forceinline__ bf16x8 frag_tr(const uint16_t* tile, int pitch, int k
     return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-template <bool STREAM, class T> __device__ __forceinline__ T get(const T* p) { return STREAM ? __builtin_nontemporal_load(p) : *p; }
-template <bool STREAM, class T> __device__ __forceinline__ void put(T* p, T v) { if (STREAM) __builtin_nontemporal_store(v, p); else *p = v; }
-
-// STREAM: the lo planes (and velocities) of all learners do not stay in the memory-side cache
-template <bool MOMENTUM, bool STREAM>
+// STREAM: the lo planes (and velocities) of all learners do not stay in the memory-side cache; STREAM_HI: nor do the hi planes
+template <bool MOMENTUM, bool STREAM, bool STREAM_HI>
 __global__ void __launch_bounds__(NT, 2) update_group_kernel(Args a) {
     __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM];
     uint16_t* const Z = (uint16_t*)smem;                     // [BK][ZP] dZ
@@ -165,9 +162,9 @@ __global__ void __launch_bounds__(NT, 2) update_group_kernel(Args a) {
     for (int i = 0; i < WN; ++i) {
         const int e = tid + NT * i;
         const size_t p = lat + (size_t)min(r0 + e / (TC / 8), q.d_out - 1) * q.d_in + min(c0 + e % (TC / 8) * 8, q.d_in - 8);
-        hr[i] = *(const u32x4*)(q.hi + p);
-        lr_[i] = get<STREAM>((const u32x4*)(q.lo + p));
-        if constexpr (MOMENTUM) { ur[i][0] = get<STREAM>((const f32x4*)(q.u + p)); ur[i][1] = get<STREAM>((const f32x4*)(q.u + p + 4)); }
+        hr[i] = plane_get<STREAM_HI>((const u32x4*)(q.hi + p));
+        lr_[i] = plane_get<STREAM>((const u32x4*)(q.lo + p));
+        if constexpr (MOMENTUM) { ur[i][0] = plane_get<STREAM>((const f32x4*)(q.u + p)); ur[i][1] = plane_get<STREAM>((const f32x4*)(q.u + p + 4)); }
     }
 
     const int rb = wave >> 1, cb = (wave & 1) * 2;           // 32 output units, two blocks of 32 input units
@@ -227,9 +224,9 @@ __global__ void __launch_bounds__(NT, 2) update_group_kernel(Args a) {
         }
         if (r < q.d_out && c < q.d_in) {
             const size_t p = lat + (size_t)r * q.d_in + c;
-            *(u32x4*)(q.hi + p) = oh;
-            put<STREAM>((u32x4*)(q.lo + p), ol);
-            if constexpr (MOMENTUM) { put<STREAM>((f32x4*)(q.u + p), g0); put<STREAM>((f32x4*)(q.u + p + 4), g1); }
+            plane_put<STREAM_HI>((u32x4*)(q.hi + p), oh);
+            plane_put<STREAM>((u32x4*)(q.lo + p), ol);
+            if constexpr (MOMENTUM) { plane_put<STREAM>((f32x4*)(q.u + p), g0); plane_put<STREAM>((f32x4*)(q.u + p + 4), g1); }
         }
     }
     if (bias && lane < 32 && r0 + rb * 32 + lane < q.d_out) {
@@ -254,7 +251,11 @@ __global__ void __launch_bounds__(NT, 2) update_group_kernel(Args a) {
 }  // namespace
 
 bool bf16_update_group_ok(const LayerCall& c) {
-    return c.shadow_cached && !c.rows && !c.partial && !c.skip_bias && c.d_in >= 8 && c.ld_dz >= 8;
+    // Planes that do not stay in the cache: with a velocity only, which is the larger part of the traffic and which the one-layer
+    // kernel reads after the contraction; with long contractions that kernel's larger tiles outweigh it where rows are whole lines.  (us
+    // per round of four steps, one-layer / this: 2048-2048-2048-100, 16 learners of 128 rows 2670 / 2554; 3080-1032-520-24, 32 of 70, both with
+    // ordinary accesses to ragged rows, 2700 / 2463; 1504-1504-1504-10, 24 of 200 2718 / 2620; but 3072-4096-10, 8 of 250 1963 / 2021.)
+    return (c.shadow_cached || (c.u && (c.B <= 128 || !whole_lines(c)))) && !c.rows && !c.partial && !c.skip_bias && c.d_in >= 8 && c.ld_dz >= 8;
 }
 
 hipError_t bf16_update_group(const LayerCall* calls, int n, const LossMeans* losses, hipStream_t st) {
@@ -287,11 +288,15 @@ hipError_t bf16_update_group(const LayerCall* calls, int n, const LossMeans* los
         // (the memory-side cache holds 256 MB: read-modify-write at 6.9 TB/s inside it, and outside it 5.4 with ordinary and
         // 6.2 TB/s with streaming accesses)
         const bool momentum = calls[at].u != nullptr;
-        const bool stream = (size_t)calls[at].P * a.lstride * (momentum ? 8 : 4) > ((size_t)224 << 20);
-        if (momentum && stream) hipLaunchKernelGGL((update_group_kernel<true, true>), dim3(wgs), dim3(NT), 0, st, a);
-        else if (momentum) hipLaunchKernelGGL((update_group_kernel<true, false>), dim3(wgs), dim3(NT), 0, st, a);
-        else if (stream) hipLaunchKernelGGL((update_group_kernel<false, true>), dim3(wgs), dim3(NT), 0, st, a);
-        else hipLaunchKernelGGL((update_group_kernel<false, false>), dim3(wgs), dim3(NT), 0, st, a);
+        const LayerCall* most = calls + at;                  // the layer with most weights
+        for (int i = 1; i < a.n_layers; ++i)
+            if ((size_t)calls[at + i].d_in * calls[at + i].d_out > (size_t)most->d_in * most->d_out) most = calls + at + i;
+        const bool stream = (size_t)calls[at].P * a.lstride * (momentum ? 8 : 4) > ((size_t)224 << 20) && (calls[at].shadow_cached || whole_lines(*most));
+        if (stream && !calls[at].shadow_cached) hipLaunchKernelGGL((update_group_kernel<true, true, true>), dim3(wgs), dim3(NT), 0, st, a);
+        else if (momentum && stream) hipLaunchKernelGGL((update_group_kernel<true, true, false>), dim3(wgs), dim3(NT), 0, st, a);
+        else if (momentum) hipLaunchKernelGGL((update_group_kernel<true, false, false>), dim3(wgs), dim3(NT), 0, st, a);
+        else if (stream) hipLaunchKernelGGL((update_group_kernel<false, true, false>), dim3(wgs), dim3(NT), 0, st, a);
+        else hipLaunchKernelGGL((update_group_kernel<false, false, false>), dim3(wgs), dim3(NT), 0, st, a);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
