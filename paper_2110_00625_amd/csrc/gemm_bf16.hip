@@ -61,9 +61,9 @@ enum { MODE_FWD = 0, MODE_BWD = 1, MODE_UPD = 2 };
 // memory pipeline while its MFMAs could run); whole slices only.  LATE (update, long contractions): as PLAIN, but
 // the master is requested under the last slice, which leaves registers for a third workgroup per compute unit but for eight
 // (166 - 168 used, 36 bytes of scratch per lane), and the tiles of eight tile rows follow each other column by column.
-// DEEP: as DMA, four LDS buffers, three slices in flight (one workgroup per compute unit).
+// DEEP: as DMA, as many LDS buffers as one workgroup per compute unit leaves room for (up to four), all but one of them in flight.
 enum { PIPE_PLAIN = 0, PIPE_LDS2 = 1, PIPE_DMA = 2, PIPE_RING = 3, PIPE_LATE = 4, PIPE_DEEP = 5 };
-constexpr int RING_LOADERS = 2, RING_BYTES = 144 * 1024, DEEP_BUFS = 4;
+constexpr int RING_LOADERS = 2, RING_BYTES = 144 * 1024;
 
 struct Operand {
     const uint16_t* base;    // learner 0
@@ -450,6 +450,7 @@ struct Shape {
     static constexpr int R_ELEMS = DIRECT ? TR * BK : RTRANS ? BK * tpitch(TR) : TR * dpitch(BK);
     static constexpr int C_ELEMS = DIRECT ? TC * BK : CTRANS ? BK * tpitch(TC) : TC * dpitch(BK);
     static constexpr int RING_BUFS = RING_BYTES / ((R_ELEMS + C_ELEMS) * 2);
+    static constexpr int DEEP_BUFS = RING_BUFS < 4 ? RING_BUFS : 4;
     static constexpr int OPER_BYTES = (PIPE == PIPE_PLAIN || PIPE == PIPE_LATE ? 1 : PIPE == PIPE_RING ? RING_BUFS : PIPE == PIPE_DEEP ? DEEP_BUFS : 2) * (R_ELEMS + C_ELEMS) * 2;
     static constexpr int STAGE_BYTES = MODE == MODE_UPD ? 4 * 32 * SPITCH * 4 : 0;
     static constexpr int KRED_BYTES = WK > 1 ? WR * WC * MR * MC * 16 * 64 * 4 : 0;   // one k group's partial tiles
@@ -712,8 +713,8 @@ __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING
         DmaLoader<TR, BK, NT> rdma; DmaLoader<TC, BK, NT> cdma;
         rdma.template init<MERGED>(a.R, Rbase, Rg, r0, tid, a.rows);
         cdma.init(a.C, Cbase, Cg, c0, tid);
-        constexpr int D = DEEP_BUFS - 1, LN = (TR + TC) * BK / 8 / NT;       // slices in flight; loads per wavefront and slice
-        static_assert(D == 3 && 2 * LN <= 63, "the slices in flight must fit the wavefront's load counter");
+        constexpr int DEEP_BUFS = SH::DEEP_BUFS, D = DEEP_BUFS - 1, LN = (TR + TC) * BK / 8 / NT;       // slices in flight; loads per wavefront and slice
+        static_assert((D == 2 || D == 3) && 2 * LN <= 63, "the slices in flight must fit the wavefront's load counter");
         const int slices = (a.nK + BK - 1) / BK;
         auto request = [&](int s) {
             rdma.load(a.R, s * BK, Rs + (s % DEEP_BUFS) * BUF_ELEMS, tid);
@@ -732,7 +733,7 @@ __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING
                 rdma.fix_tail(a.R, k0, Rs + buf * BUF_ELEMS, tid);
                 cdma.fix_tail(a.C, k0, Cs + buf * BUF_ELEMS, tid);
             }
-            // everyone's part is there, and everyone's reads of slice s - 1 are done: its buffer takes slice s + 3.  (A barrier
+            // everyone's part is there, and everyone's reads of slice s - 1 are done: its buffer takes slice s + D.  (A barrier
             // without the fence that would wait for the slices in flight.)
             asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
             if (s + D < slices) request(s + D);
@@ -1108,7 +1109,7 @@ hipError_t launch(Args a, int P, hipStream_t st) {
 int round8(int x) { return (x + 7) / 8 * 8; }
 
 // Launch shapes: rows x columns of the output tile (_K2: eight wavefronts, two k groups, slices of 128).
-enum { T128x128 = 0, T128x64 = 1, T64x128 = 2, T64x64_K2 = 3, T256x128 = 4 };
+enum { T128x128 = 0, T128x64 = 1, T64x128 = 2, T256x128 = 3, T64x64_K2 = 4, T128x64_K2 = 5 };
 
 // Measured on MI355X over the workload shapes (batch 64..256, widths 1024..4096, 8..32 learners):
 // with >= 512 (forward: 257) tiles of 128x128 the launch fills the chip with the tile that reads LDS least per
@@ -1124,7 +1125,12 @@ int pick_tile(int mode, int nR, int nC, int nK, int P) {
         // (64x64 tiles of 65 to 128 rows read every weight twice, streamed ones out of memory.  us per round of four steps, 64x64 / 128x128:
         // 416 tiles, 32 learners of 107 rows of 568-2872-1616-218 3532 / 3421; 288, 12 of 90 of 1000-3000-10 495 / 473; 256 and 224 742 /
         // 743 and 549 / 546; 192 870 / 873; 128 756 / 836.)
-        return tiles128 > 256 ? T128x128 : T64x64_K2;
+        if (tiles128 > 256) return T128x128;
+        // One workgroup of 128x64 per compute unit, in the same two k groups, with two slices in flight: a quarter less to bring in than by
+        // two of 64x64 with one.  (us per round, 64x64 / 128x64: 256 tiles, 3072-1024-1024-10, 16 learners of 128 rows 1380 / 1357,
+        // 4096-4096-100, 4 of 256 1086 / 1041; 192, 12 of 128 604 / 596; but 320 976 / 978; 85 338 / 381; 228 of a contraction of 704 184 / 203.)
+        const long tiles = (long)((nR + 127) / 128) * ((nC + 63) / 64) * P;
+        return tiles >= 160 && tiles <= 256 && nK >= 1024 ? T128x64_K2 : T64x64_K2;
     }
     // backward-data, measured at the 4096-wide layers: 128x128 95 us against 119 us for 128x64 (batch 256),
     // 64x128 222 us against 249 us for 64x64 (batch 64)
@@ -1145,6 +1151,9 @@ hipError_t launch_tiled(const Args& a, int P, int tile, hipStream_t st) {
             if constexpr (MODE == MODE_FWD) return launch<MODE, 256, 128, 2, 2, 1, 64, RT, CT, PIPE_RING>(a, P, st);
             else return hipErrorInvalidValue;
         case T128x64:  return launch<MODE, 128, 64, 2, 2, 1, 64, RT, CT, PIPE_PLAIN>(a, P, st);
+        case T128x64_K2:
+            if constexpr (MODE == MODE_FWD) return launch<MODE, 128, 64, 2, 2, 2, 128, RT, CT, PIPE_DEEP>(a, P, st);
+            else return hipErrorInvalidValue;
         case T64x128:  return launch<MODE, 64, 128, 2, 2, 1, 64, RT, CT, PIPE_PLAIN>(a, P, st);
         default:
             // forward: slices of 128 loaded straight into LDS (measured 26 against 30 us for layer 1 of the
@@ -1225,7 +1234,7 @@ hipError_t bf16_forward(const LayerCall& c, hipStream_t st) {
     return launch_tiled<MODE_FWD, false, false>(a, c.P, pick_tile(MODE_FWD, a.nR, a.nC, a.nK, c.P), st);
 }
 
-bool bf16_forward_splits(int P, int B, int d_in, int d_out) { return pick_tile(MODE_FWD, B, d_out, d_in, P) == T64x64_K2; }
+bool bf16_forward_splits(int P, int B, int d_in, int d_out) { return pick_tile(MODE_FWD, B, d_out, d_in, P) >= T64x64_K2; }
 bool bf16_backward_splits(int P, int B, int d_in, int d_out) { return pick_tile(MODE_BWD, B, d_in, d_out, P) == T64x64_K2; }
 
 hipError_t bf16_backward_data(const LayerCall& c, hipStream_t st) {
