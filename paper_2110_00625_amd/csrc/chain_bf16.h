@@ -1,6 +1,7 @@
 // The last layers of a small MLP, forward pass, loss and data gradients in one launch (chain_bf16.hip).
 #pragma once
 #include "kavg_internal.h"
+#include "conv_pool.h"
 
 namespace kavg {
 
@@ -11,7 +12,9 @@ constexpr int CHAIN_LAYERS = 6;              // layers a launch takes at most
 int chain_layers(int P, int B, int L, const int* dims, bool into_input);
 
 // calls[0..n-1]: those layers in ascending order.  Writes their activations (calls[].out), all dZ (calls[].dz) and, where
-// calls[0].dz_prev is set, the gradient of the input rows; the loss of every sample into rowloss.
-hipError_t bf16_chain(const LayerCall* calls, int n, const int32_t* y, const int32_t* idx, long idx_lstride, float* rowloss, hipStream_t st);
+// calls[0].dz_prev is set, the gradient of the input rows; the loss of every sample into rowloss.  pool != null: the input rows are
+// means that are formed here, and written to calls[0].in.
+hipError_t bf16_chain(const LayerCall* calls, int n, const int32_t* y, const int32_t* idx, long idx_lstride, float* rowloss, const PoolSums* pool,
+                      hipStream_t st);
 
 }  // namespace kavg

@@ -64,6 +64,7 @@ struct Args {
     size_t lstride;                          // between learners, in the weights
     const uint16_t* in; int ld_in; size_t in_lstride;                // rows of the first layer, or (gather_in) of the data set
     int gather_in;
+    PoolSums pool; uint16_t* pooled;         // pooled != null: the rows are means over positions, formed here and written there ([P][B][d_in])
     const int32_t* idx; long idx_lstride;    // samples of this step
     const int32_t* y;
     float* rowloss;                          // [P][B]
@@ -218,8 +219,17 @@ __global__ void __launch_bounds__(NT, 2) chain_kernel(Args a) {
         const Layer l = a.layer[0];
         uint16_t* const x = (uint16_t*)(smem + l.in_at);
         const uint16_t* p = a.gather_in ? a.in + (size_t)sample * a.ld_in : a.in + (size_t)learner * a.in_lstride + (size_t)(row0 + my) * a.ld_in;
+        if (a.pooled) {
+#pragma unroll 1
+            for (int c = lane; c < l.d_in; c += 64) {
+                const uint16_t h = pool_mean(a.pool, learner, row0 + my, c);
+                x[wave * pitch(l.d_in) + c] = h;
+                if (wave < rows) a.pooled[(lrow + wave) * l.d_in + c] = h;
+            }
+        } else {
 #pragma unroll 4
-        for (int c = lane * 8; c < l.d_in; c += 512) *(u32x4*)(x + wave * pitch(l.d_in) + c) = *(const u32x4*)(p + c);
+            for (int c = lane * 8; c < l.d_in; c += 512) *(u32x4*)(x + wave * pitch(l.d_in) + c) = *(const u32x4*)(p + c);
+        }
         ahead(no, l);
         pad(x, l.d_in);
         for (int i = 0; i < a.L; ++i) {
@@ -464,7 +474,8 @@ int chain_layers(int P, int B, int L, const int* dims, bool into_input) {
     return best;
 }
 
-hipError_t bf16_chain(const LayerCall* calls, int n, const int32_t* y, const int32_t* idx, long idx_lstride, float* rowloss, hipStream_t st) {
+hipError_t bf16_chain(const LayerCall* calls, int n, const int32_t* y, const int32_t* idx, long idx_lstride, float* rowloss, const PoolSums* pool,
+                      hipStream_t st) {
     if (n < 1 || n > CHAIN_LAYERS) return hipErrorInvalidValue;
     Args a = {};
     int dims[CHAIN_LAYERS + 1];
@@ -481,6 +492,7 @@ hipError_t bf16_chain(const LayerCall* calls, int n, const int32_t* y, const int
     a.lstride = calls[0].ws_stride;
     a.in = (const uint16_t*)calls[0].in; a.ld_in = calls[0].ld_in; a.in_lstride = calls[0].in_stride;
     a.gather_in = calls[0].gather != nullptr;
+    if (pool) { a.pool = *pool; a.pooled = (uint16_t*)calls[0].in; }
     a.idx = idx; a.idx_lstride = idx_lstride; a.y = y; a.rowloss = rowloss;
     a.dz0 = (uint16_t*)calls[0].dz_prev;
     const size_t smem = lds_plan(n, dims, &a);

@@ -20,7 +20,7 @@
 //
 // The weight gradient of a convolution has few outputs (c_out x 9 c_in) and a very long contraction;
 // it is split over S ranges of positions that run as separate workgroups (the update kernel writes
-// fp32 partial tiles instead of stepping the master), and conv_step_kernel adds the S partials in
+// fp32 partial tiles instead of stepping the master), and conv_step.h adds the S partials in
 // ascending order and takes the SGD step of Algorithm 1 on the master's two planes (split.h).
 // Between the last convolution and the MLP sits the mean over the H*W positions.
 //
@@ -32,6 +32,7 @@
 #include "split.h"
 #include "fastdiv.h"
 #include "conv_pool.h"
+#include "conv_step.h"
 
 namespace kavg {
 
@@ -148,54 +149,9 @@ pool_backward_kernel(const uint16_t* __restrict__ dpool, const uint16_t* __restr
     *(u32x4*)(dz + e * 8) = pool_grad_piece(m, g, inv);
 }
 
-// W[j][e] -= lr * sum_s partial[(j*S+s)][e]  and  b[j][r] -= lr * sum_s pbias[(j*S+s)][r]  on the master's planes, for several
-// convolutions: adds up the S partial gradients of an element (eight requested together, added in ascending order).  One
-// launch for all layers whose partial sums lie side by side in the workspace: with one launch each and one partial sum
-// requested at a time it took 14 us per layer on 28x28 images with channels 8-32-64, now 10.5 us for both.
-// The stepped bf16 values are also left in operand order for the next step's products (conv_flat.hip), two bytes at a time: a
-// launch of its own for that was 4 - 5 us of a step (28x28 with channels 8-32-64, a round of four steps: 487 us with it, 479 without).
-constexpr int STEP_GROUP = 8;
-struct StepArgs { ConvStep layer[STEP_GROUP]; uint32_t div_m[STEP_GROUP]; int div_s[STEP_GROUP]; int n; size_t lstride; float lr; };
-
-// element (output x, contraction k, tap) of a layer's weights in operand order (launch_pack_weights)
-__device__ __forceinline__ void put_frag(const FragPlace& f, int j, int x, int k, int tap, uint16_t v) {
-    const int slab = k >> 4, grp = slab / f.SL, it = grp * 9 * f.SL + tap * f.SL + slab - grp * f.SL;
-    f.frag[(size_t)j * f.lstride + ((size_t)(it * f.blocks + (x >> 5)) * 64 + (x & 31) + ((k >> 3) & 1) * 32) * 8 + (k & 7)] = v;
-}
-
-__global__ void __launch_bounds__(256) conv_step_kernel(StepArgs a) {
-    int b = blockIdx.x, i0 = 0;
-    while (i0 + 1 < a.n && b >= (a.layer[i0].n_w + a.layer[i0].n_b + 255) / 256) { b -= (a.layer[i0].n_w + a.layer[i0].n_b + 255) / 256; ++i0; }
-    const ConvStep& q = a.layer[i0];
-    const int e = b * 256 + threadIdx.x;
-    const int j = blockIdx.y;
-    if (e >= q.n_w + q.n_b) return;
-    const bool is_w = e < q.n_w;
-    const int i = is_w ? e : e - q.n_w;
-    const float* p = is_w ? q.partial + (size_t)j * q.S * q.n_w + i : q.pbias + (size_t)j * q.S * q.n_b + i;
-    const size_t step = is_w ? (size_t)q.n_w : (size_t)q.n_b;
-    float s = 0.f;
-    int r = 0;
-    for (; r + 8 <= q.S; r += 8) {
-        float t[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) t[u] = p[(size_t)(r + u) * step];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) s += t[u];
-    }
-    for (; r < q.S; ++r) s += p[(size_t)r * step];
-    uint16_t* hi = (is_w ? q.whi : q.bhi) + (size_t)j * a.lstride + i;
-    uint16_t* lo = (is_w ? q.wlo : q.blo) + (size_t)j * a.lstride + i;
-    const float v = __builtin_bit_cast(float, split_join(*hi, *lo)) - a.lr * s;
-    const uint16_t h = (uint16_t)split_hi(__builtin_bit_cast(uint32_t, v));
-    *hi = h;
-    *lo = (uint16_t)split_lo(__builtin_bit_cast(uint32_t, v));
-    if (is_w && (q.fwd.frag || q.bwd.frag)) {
-        const int ot = (int)fastdiv((uint32_t)i, a.div_m[i0], a.div_s[i0]), c = i - ot * q.c_in, o = ot / 9, tap = ot - 9 * o;
-        if (q.fwd.frag) put_frag(q.fwd, j, o, c, tap, h);
-        if (q.bwd.frag) put_frag(q.bwd, j, c, o, tap, h);
-    }
-}
+// One launch for all layers whose partial sums lie side by side in the workspace: with one launch each and one partial sum requested at
+// a time it took 14 us per layer on 28x28 images with channels 8-32-64.
+__global__ void __launch_bounds__(256) conv_step_kernel(ConvSteps a) { conv_step(a, blockIdx.x, blockIdx.y, threadIdx.x); }
 
 // one lane per 16-byte piece of the rotated weights
 __global__ void __launch_bounds__(256)
@@ -257,16 +213,8 @@ hipError_t launch_rotate_weights(const uint16_t* whi, size_t w_lstride, uint16_t
 
 hipError_t launch_conv_steps(const ConvStep* layers, int n, size_t lstride, int P, float lr, hipStream_t st) {
     for (int at = 0; at < n; at += STEP_GROUP) {
-        StepArgs a = {};
-        a.n = n - at < STEP_GROUP ? n - at : STEP_GROUP;
-        a.lstride = lstride; a.lr = lr;
-        unsigned wgs = 0;
-        for (int i = 0; i < a.n; ++i) {
-            a.layer[i] = layers[at + i];
-            fastdiv_make((uint32_t)a.layer[i].c_in, &a.div_m[i], &a.div_s[i]);
-            wgs += blocks((size_t)a.layer[i].n_w + a.layer[i].n_b);
-        }
-        hipLaunchKernelGGL(conv_step_kernel, dim3(wgs, P), dim3(256), 0, st, a);
+        const ConvSteps a = conv_steps(layers + at, n - at, lstride, lr);
+        hipLaunchKernelGGL(conv_step_kernel, dim3(a.wgs, P), dim3(256), 0, st, a);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -1,6 +1,7 @@
 // 3x3 convolution, forward and data gradient, for images of any width (conv_flat.hip).
 #pragma once
 #include "kavg_internal.h"
+#include "conv_pool.h"
 
 namespace kavg {
 
@@ -34,7 +35,8 @@ hipError_t launch_pack_weights(const PackLayer* layers, int n, size_t w_lstride,
 // elements in all; 0: images too small.  pooled[P][B][c] = bf16(mean) out of them.
 int conv_pool_slots(int P, int B, int H, int W, const FlatPlan& plan);
 size_t conv_pool_elems(int P, int B, int H, int W, const FlatPlan& plan);
-hipError_t launch_pool_finish(const float* sums, const FlatPlan& plan, void* pooled, int P, int B, int H, int W, int c, hipStream_t st);
+PoolSums conv_pool_sums(const float* sums, const FlatPlan& plan, int P, int B, int H, int W);
+hipError_t launch_pool_finish(const PoolSums& q, void* pooled, int P, int B, int c, hipStream_t st);
 
 // (These two compute their positions; the table is the weight gradient's.)
 // c.out = relu(conv(c.in, W) + b), or c.bits and c.pool_sums; gather != null: the images are rows gather[learner * gstride + n] of the data set X

@@ -35,7 +35,7 @@
 //
 // The last convolution, below the mean over the positions, writes no activations: what is read of them afterwards is their
 // ReLU mask, one bit each, and their sums.  The sums of an image are a product with ones out of the epilogue's patch, 128
-// positions at a time, joined in ascending order (pool_finish_kernel).  16 learners of 64 images of 32x32, channels
+// positions at a time, joined in ascending order (pool_mean).  16 learners of 64 images of 32x32, channels
 // 8-32-64-128: 268 MB of activations were written once and read three times; without them the mean takes 5 us instead of 47 and
 // the data gradient 184 instead of 203, a round 6.92 -> 6.28 ms; one convolution on 60x32 images 141 -> 97 us, 28x28 536 -> 514.
 #include "kavg_internal.h"
@@ -331,7 +331,7 @@ __global__ void __launch_bounds__(NT, 2) conv_flat_kernel(FlatArgs a) {
             for (int q = 0; q < 4; ++q) bias[j][q] = *(const float4*)(BIAS + (cw * NB + j) * 32 + q * 8 + half * 4);
     }
     // LAST: an infinity would reach every sum of the product with ones (0 times infinity is NaN), so the largest finite bf16 number
-    // stands for it.  A sum that holds such a number is at least as large, and infinite again in pool_finish_kernel.
+    // stands for it.  A sum that holds such a number is at least as large, and infinite again in pool_mean.
     auto relu = [&](float v) __attribute__((always_inline)) {
         if constexpr (LAST) return __builtin_amdgcn_fmed3f(v, 0.f, BF16_MAX); else return fmaxf(v, 0.f);
     };
@@ -462,23 +462,11 @@ __global__ void __launch_bounds__(NT, 2) conv_flat_kernel(FlatArgs a) {
     }
 }
 
-// pooled[learner][image][channel] = bf16(mean): one lane per output adds the image's partial sums in ascending order.  (One row of
-// the grid per learner: all learners' outputs together may be more than 2^31.)
-__global__ void __launch_bounds__(NT) pool_finish_kernel(const float* sums, uint16_t* pooled, int image, int last, int slots, int group, int groups, int pitch, int c, float inv,
-                                                         int outputs) {
+// pooled[learner][image][channel] = bf16(mean), one lane per output.  (One row of the grid per learner: all learners' outputs together may be
+// more than 2^31.)  Where one launch takes all layers of the MLP it forms its rows itself (chain_bf16.hip).
+__global__ void __launch_bounds__(NT) pool_finish_kernel(PoolSums q, uint16_t* pooled, int c, int outputs) {
     const int e = blockIdx.x * NT + threadIdx.x, learner = blockIdx.y;
-    if (e >= outputs) return;
-    const int ch = e % c, n = e / c;
-    const int g1 = (n * image + last) / group;
-    const float* p = sums + (size_t)learner * groups * slots * pitch + ch;
-    float s = 0.f;
-#pragma unroll 4
-    for (int g = n * image / group; g <= g1; ++g) {
-        const float x = p[((size_t)g * slots + n - g * group / image) * pitch];
-        s += x < BF16_MAX ? x : INFINITY;                     // (see relu in conv_flat_kernel)
-    }
-    const __bf16 h = (__bf16)(s * inv);                       // round to nearest even
-    pooled[(size_t)learner * outputs + e] = __builtin_bit_cast(uint16_t, h);
+    if (e < outputs) pooled[(size_t)learner * outputs + e] = pool_mean(q, learner, e / c, e % c);
 }
 
 __global__ void __launch_bounds__(NT) flat_table_kernel(int32_t* table, int len, int end, int H, int W) {
@@ -675,10 +663,15 @@ size_t conv_pool_elems(int P, int B, int H, int W, const FlatPlan& plan) {
     return (size_t)P * ((end + TP - 1) / TP) * plan.PWAVES * conv_pool_slots(P, B, H, W, plan) * plan.blocks * 32;
 }
 
-hipError_t launch_pool_finish(const float* sums, const FlatPlan& plan, void* pooled, int P, int B, int H, int W, int c, hipStream_t st) {
-    const int end = ((B - 1) * (H + 1) + H - 1) * (W + 1) + W, PB = blocks_per_wave(P, B, H, W, plan), TP = plan.PWAVES * PB * 32, outputs = B * c;      // (at most 2^16 images of 128 channels)
-    hipLaunchKernelGGL(pool_finish_kernel, dim3((outputs + NT - 1) / NT, P), dim3(NT), 0, st, sums, (uint16_t*)pooled, (H + 1) * (W + 1),
-                       (H - 1) * (W + 1) + W - 1, conv_pool_slots(P, B, H, W, plan), PB * 32, (end + TP - 1) / TP * plan.PWAVES, plan.blocks * 32, c, 1.0f / (float)(H * W), outputs);
+PoolSums conv_pool_sums(const float* sums, const FlatPlan& plan, int P, int B, int H, int W) {
+    const int end = ((B - 1) * (H + 1) + H - 1) * (W + 1) + W, PB = blocks_per_wave(P, B, H, W, plan), TP = plan.PWAVES * PB * 32;
+    return {sums, (H + 1) * (W + 1), (H - 1) * (W + 1) + W - 1, conv_pool_slots(P, B, H, W, plan), PB * 32, (end + TP - 1) / TP * plan.PWAVES, plan.blocks * 32,
+            1.0f / (float)(H * W)};
+}
+
+hipError_t launch_pool_finish(const PoolSums& q, void* pooled, int P, int B, int c, hipStream_t st) {
+    const int outputs = B * c;                                // (at most 2^16 images of 128 channels)
+    hipLaunchKernelGGL(pool_finish_kernel, dim3((outputs + NT - 1) / NT, P), dim3(NT), 0, st, q, (uint16_t*)pooled, c, outputs);
     return hipGetLastError();
 }
 

@@ -4,6 +4,7 @@
 // while loading, instead of reading them from a buffer.
 #pragma once
 #include <stdint.h>
+#include <stddef.h>
 
 namespace kavg {
 
@@ -44,5 +45,30 @@ __device__ __forceinline__ pool_u32x4 pool_mask(uint32_t m, pool_u32x4 scaled) {
     return scaled;
 }
 __device__ __forceinline__ pool_u32x4 pool_grad_bits(uint32_t m, pool_u32x4 g, float inv) { return pool_mask(m, pool_scale(g, inv)); }
+
+
+// The mean over the positions from the partial sums that the last convolution's forward pass leaves (conv_flat.hip): places of images, of
+// `pitch` channels each, per `group` positions.
+struct PoolSums { const float* sums; int image, last, slots, group, groups, pitch; float inv; };
+
+// ... of channel ch of image n, bf16: the partial sums in ascending order.  (A sum that holds the largest finite number stands for an
+// infinity, see conv_flat.hip.)
+__device__ __forceinline__ uint16_t pool_mean(const PoolSums& q, int learner, int n, int ch) {
+    const int g1 = (n * q.image + q.last) / q.group;
+    const float* p = q.sums + (size_t)learner * q.groups * q.slots * q.pitch + ch;
+    float s = 0.f;
+    for (int g0 = n * q.image / q.group; g0 <= g1; g0 += 4) {
+        float x[4];                                           // (requested together; places beyond the last are read from there, and not used)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int g = min(g0 + i, g1);
+            x[i] = p[((size_t)g * q.slots + n - g * q.group / q.image) * q.pitch];
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) if (g0 + i <= g1) s += x[i] < 0x1.FEp127f ? x[i] : __builtin_inff();
+    }
+    const __bf16 h = (__bf16)(s * q.inv);                     // round to nearest even
+    return __builtin_bit_cast(uint16_t, h);
+}
 
 }  // namespace kavg

@@ -848,7 +848,7 @@ int issue_update_group(kavg_ctx* c, const std::vector<LayerCall>& group, bool he
     const bool bf = c->dtype == KAVG_BF16;
     const LossMeans losses = {c->rowloss(), c->losses(), c->K * c->P, c->B};
     auto update = [&](const LayerCall* q, int n, const LossMeans* l) {
-        return bf ? bf16_update_group(q, n, l, c->stream) : f32_update(q, n, l, c->stream);
+        return bf ? bf16_update_group(q, n, l, nullptr, 0, c->stream) : f32_update(q, n, l, c->stream);
     };
     const unsigned apart = (1u << KAVG_CLASS_UPDATE) | (1u << KAVG_CLASS_HEAD) | (1u << KAVG_CLASS_LOSS);
     if (group.empty() || (c->prof_mask & apart)) {
@@ -873,11 +873,11 @@ int chained_layers(const kavg_ctx* c) {
     if (c->dtype != KAVG_BF16 || (c->prof_mask & apart)) return 0;
     return chain_layers(c->P, c->B, c->L, c->dims.data(), !c->cv.ch.empty());
 }
-int issue_chain(kavg_ctx* c, int from, int k) {
+int issue_chain(kavg_ctx* c, int from, int k, const PoolSums* pool) {
     LayerCall calls[CHAIN_LAYERS];
     for (int l = from + 1; l <= c->L; ++l) calls[l - from - 1] = layer_call(c, l, k);
     KAVG_HIP(c, bf16_chain(calls, c->L - from, c->y, c->idx() + (size_t)k * c->B, (long)c->K * c->B, c->rowloss() + (size_t)k * c->P * c->B,
-                           c->stream));
+                           pool, c->stream));
     return KAVG_OK;
 }
 
@@ -905,7 +905,7 @@ int issue_steps(kavg_ctx* c) {
             KAVG_HIP(c, bf ? bf16_forward(q, st) : f32_forward(q, st));
         }
         if (chained) {
-            const int rc = issue_chain(c, below, k);
+            const int rc = issue_chain(c, below, k, nullptr);
             if (rc != KAVG_OK) return rc;
         } else if (head) {
             const LayerCall q = layer_call(c, L, k), q_below = finish ? layer_call(c, L - 1, k) : q;
@@ -1105,11 +1105,15 @@ int issue_steps_conv(kavg_ctx* c) {
                                           c->ws + lo.off_patch[t - 1], P, B, H, W, cv.ch[t - 1], st));
             KAVG_HIP(c, bf16_forward(conv_call(t), st));
         }
+        // The mean over the positions: by the launch of the MLP where that takes all its layers.
+        const bool pooled_there = lo.pool_bits && below == 0 && chained > 0;
+        PoolSums pool_sums = {};
+        if (lo.pool_bits) pool_sums = conv_pool_sums((const float*)(c->ws + lo.off_sums), lo.flat_f[M - 1], P, B, H, W);
         {
             Bracket br(c, KAVG_CLASS_FORWARD);
-            if (lo.pool_bits)
-                KAVG_HIP(c, launch_pool_finish((const float*)(c->ws + lo.off_sums), lo.flat_f[M - 1], c->ws + lo.off_pool, P, B, H, W, cv.ch[M], st));
-            else
+            if (lo.pool_bits && !pooled_there)
+                KAVG_HIP(c, launch_pool_finish(pool_sums, c->ws + lo.off_pool, P, B, cv.ch[M], st));
+            else if (!lo.pool_bits)
                 KAVG_HIP(c, launch_pool_forward(c->ws + lo.off_cact[M - 1], c->ws + lo.off_pool, P, B, H * W, cv.ch[M], st));
         }
         for (int l = 1; l <= (head && !chained ? L - 1 : below); ++l) {             // MLP, forward
@@ -1117,7 +1121,7 @@ int issue_steps_conv(kavg_ctx* c) {
             KAVG_HIP(c, bf16_forward(layer_call(c, l, k), st));
         }
         if (chained) {
-            const int rc = issue_chain(c, below, k);
+            const int rc = issue_chain(c, below, k, pooled_there ? &pool_sums : nullptr);
             if (rc != KAVG_OK) return rc;
         } else if (head) {
             Bracket br(c, KAVG_CLASS_HEAD);
@@ -1143,10 +1147,6 @@ int issue_steps_conv(kavg_ctx* c) {
                 Bracket br(c, KAVG_CLASS_UPDATE);
                 KAVG_HIP(c, bf16_update(q, st));
             }
-        }
-        {
-            const int rc = issue_update_group(c, group, head, k == c->K - 1);
-            if (rc != KAVG_OK) return rc;
         }
         // The gradient of the mean over the positions: formed by the gradients of the last convolution from its bits, or written out.
         const bool pool_fused = lo.pool_bits;
@@ -1225,8 +1225,18 @@ int issue_steps_conv(kavg_ctx* c) {
             KAVG_HIP(c, bf16_update(q, st));
             steps.push_back({q.ws, q.wlo, q.bhi, q.blo, q.partial, q.partial_bias, q.splits, q.d_out * q.d_in, q.d_out, cv.ch[t - 1], frag_place(t, false, k), frag_place(t, true, k)});
         }
-        const int rc = take_steps();
-        if (rc != KAVG_OK) return rc;
+        // The steps of the last convolutions and the updates of the MLP, which depend on nothing in between, in one launch (a launch less: 5 us of
+        // a step), unless updates are profiled.
+        const unsigned apart_updates = (1u << KAVG_CLASS_UPDATE) | (1u << KAVG_CLASS_HEAD) | (1u << KAVG_CLASS_LOSS);
+        if (!group.empty() && steps.size() <= 8 && !(c->prof_mask & apart_updates)) {
+            const LossMeans losses = {c->rowloss(), c->losses(), c->K * c->P, c->B};
+            KAVG_HIP(c, bf16_update_group(group.data(), (int)group.size(), k == c->K - 1 ? &losses : nullptr, steps.data(), (int)steps.size(), st));
+        } else {
+            const int rc = issue_update_group(c, group, head, k == c->K - 1);
+            if (rc != KAVG_OK) return rc;
+            const int rc2 = take_steps();
+            if (rc2 != KAVG_OK) return rc2;
+        }
     }
     return KAVG_OK;
 }

@@ -136,6 +136,15 @@ hipError_t bf16_apply(const ApplyCall& c, hipStream_t st);
 hipError_t launch_bias_step(uint16_t* bhi, uint16_t* blo, size_t b_stride, const void* dz, int ld_dz,
                             size_t dz_stride, int P, int rows, int d, float lr, hipStream_t st);
 
+// master -= lr * (sum of the S fp32 partial gradients) for n layers, weights [n_w] and bias [n_b] of each, planes of split.h
+// fwd, bwd: where not null, the stepped weights go to those places as well, in the operand order of conv_flat.hip (the zeros around
+// them stay)
+struct FragPlace { uint16_t* frag; size_t lstride; int SL, blocks; };
+struct ConvStep {
+    uint16_t* whi; uint16_t* wlo; uint16_t* bhi; uint16_t* blo; const float* partial; const float* pbias; int S, n_w, n_b, c_in;
+    FragPlace fwd, bwd;
+};
+
 // fp32 path
 // splits of the forward contraction of a layer and the contraction range of each; shapes only
 int f32_forward_plan(int P, int B, int d_in, int d_out, int* chunk_out);
@@ -157,7 +166,8 @@ hipError_t bf16_strip(const LayerCall& c, hipStream_t st);
 // the updates of n layers in one launch (update_bf16.hip), with the mean losses as f32_update; which calls it takes (the
 // same batch and options for all)
 bool bf16_update_group_ok(const LayerCall& c);
-hipError_t bf16_update_group(const LayerCall* layers, int n, const LossMeans* losses, hipStream_t st);
+// (convs: steps of up to eight convolutions, taken by the same launch, see conv_step.h)
+hipError_t bf16_update_group(const LayerCall* layers, int n, const LossMeans* losses, const ConvStep* convs, int n_convs, hipStream_t st);
 
 // ---- classifier head for small class counts (last layer: forward + loss + data gradient, then update) ----
 bool head_supported(int C);
@@ -176,14 +186,7 @@ hipError_t launch_col2im_mask(const float* draw, const void* act, void* dprev, i
                               hipStream_t st);
 hipError_t launch_pool_forward(const void* act, void* pooled, int P, int B, int HW, int c, hipStream_t st);
 hipError_t launch_pool_backward(const void* dpool, const void* act, void* dz, int P, int B, int HW, int c, hipStream_t st);
-// master -= lr * (sum of the S fp32 partial gradients) for n layers, weights [n_w] and bias [n_b] of each, planes of split.h
-// fwd, bwd: where not null, the stepped weights go to those places as well, in the operand order of conv_flat.hip (the zeros around
-// them stay)
-struct FragPlace { uint16_t* frag; size_t lstride; int SL, blocks; };
-struct ConvStep {
-    uint16_t* whi; uint16_t* wlo; uint16_t* bhi; uint16_t* blo; const float* partial; const float* pbias; int S, n_w, n_b, c_in;
-    FragPlace fwd, bwd;
-};
+// (ConvStep: above)
 hipError_t launch_conv_steps(const ConvStep* layers, int n, size_t lstride, int P, float lr, hipStream_t st);
 
 // ---- 3x3 convolution (stride 1, zero padding 1) on channels-last images [P][B][H][W][c], the patch matrix formed

@@ -20,6 +20,7 @@
 // kernel is as fast (4096 wide, 32 learners: 630 against 595 + 23) and stays.
 #include "kavg_internal.h"
 #include "column_sum.h"
+#include "conv_step.h"
 #include "head_update.h"
 #include "loss_mean.h"
 #include "split.h"
@@ -59,7 +60,8 @@ struct Args {
     int head_every;                          // > 0: layer 0 is the head, its workgroups (latency, hardly any traffic) are spread over the launch
     size_t lstride;                          // between learners, in planes and velocities
     float lr, beta;
-    LossMeans losses;                        // n > 0: computed by the workgroups behind those of the layers, four each
+    ConvSteps conv; int conv_wgs;            // conv_wgs > 0: steps of convolutions, by the workgroups behind those of the layers
+    LossMeans losses;                        // n > 0: computed by the workgroups behind those, four each
 };
 
 // fragment of a [k][x] tile by transpose reads: lane l receives x0 + l%32 at k = k0 + 8 (l/32) .. +7
@@ -91,7 +93,13 @@ __global__ void __launch_bounds__(NT, 2) update_group_kernel(Args a) {
     while (!head && li + 1 < a.n_layers && g >= a.layer[li].padded) g -= a.layer[li++].padded;
     const Layer& q = a.layer[li];
     if (g >= q.padded) {
-        const int r = (g - q.padded) * 4 + wave;
+        g -= q.padded;
+        if (g < a.conv_wgs) {
+            const int learner = g / a.conv.wgs;
+            conv_step(a.conv, g - learner * a.conv.wgs, learner, tid);
+            return;
+        }
+        const int r = (g - a.conv_wgs) * 4 + wave;
         if (r < a.losses.n) loss_mean_wave(a.losses, r, lane);
         return;
     }
@@ -258,7 +266,8 @@ bool bf16_update_group_ok(const LayerCall& c) {
     return (c.shadow_cached || (c.u && (c.B <= 128 || !whole_lines(c)))) && !c.rows && !c.partial && !c.skip_bias && c.d_in >= 8 && c.ld_dz >= 8;
 }
 
-hipError_t bf16_update_group(const LayerCall* calls, int n, const LossMeans* losses, hipStream_t st) {
+hipError_t bf16_update_group(const LayerCall* calls, int n, const LossMeans* losses, const ConvStep* convs, int n_convs, hipStream_t st) {
+    if (n_convs > STEP_GROUP) return hipErrorInvalidValue;
     for (int at = 0; at < n; at += GROUP) {
         Args a = {};
         a.n_layers = n - at < GROUP ? n - at : GROUP;
@@ -281,6 +290,11 @@ hipError_t bf16_update_group(const LayerCall* calls, int n, const LossMeans* los
         // Long launches spread the head's workgroups, which fetch little and wait much (3072-1024-1024-10, 16 learners: a round 1.5 %
         // faster than with the head in front); in short ones the head would be the tail.
         if (a.n_layers > 1 && a.layer[0].head && wgs >= 9 * a.layer[0].padded) a.head_every = wgs / a.layer[0].padded;
+        if (n_convs > 0 && at + a.n_layers == n) {
+            a.conv = conv_steps(convs, n_convs, calls[at].ws_stride, calls[at].lr);
+            a.conv_wgs = a.conv.wgs * calls[at].P;
+            wgs += a.conv_wgs;
+        }
         if (losses && at + a.n_layers == n) {
             a.losses = *losses;
             wgs += (losses->n + 3) / 4;
