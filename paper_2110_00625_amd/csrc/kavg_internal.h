@@ -42,6 +42,9 @@ hipError_t launch_softmax_ce(const float* logits, int ldz, int C, const int32_t*
                              void* dz, long dz_learner_stride, int dz_bf16, float* rowloss, hipStream_t st);
 // losses[r] = mean_m rowloss[r][m], r = k*P + j, n of them (loss_mean.h)
 struct LossMeans { const float* rowloss; float* losses; int n, B; };
+// words of device memory to pinned host memory
+hipError_t launch_report(const void* from, void* to_pinned, int words, hipStream_t st);
+constexpr size_t REPORT_BYTES = 32 * 1024;
 hipError_t launch_loss_mean(const LossMeans& a, hipStream_t st);
 
 // ---- per-learner dense layers ----

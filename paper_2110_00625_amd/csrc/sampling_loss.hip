@@ -171,7 +171,16 @@ hipError_t launch_softmax_ce(const float* logits, int ldz, int C, const int32_t*
     return hipGetLastError();
 }
 
+__global__ void __launch_bounds__(1024) report_kernel(const uint32_t* from, uint32_t* to, int words) {
+    for (int i = threadIdx.x; i < words; i += 1024) to[i] = from[i];
+}
+
 __global__ void __launch_bounds__(64) loss_mean_kernel(LossMeans a) { loss_mean_wave(a, blockIdx.x, threadIdx.x); }
+
+hipError_t launch_report(const void* from, void* to_pinned, int words, hipStream_t st) {
+    hipLaunchKernelGGL(report_kernel, dim3(1), dim3(1024), 0, st, (const uint32_t*)from, (uint32_t*)to_pinned, words);
+    return hipGetLastError();
+}
 
 hipError_t launch_loss_mean(const LossMeans& a, hipStream_t st) {
     hipLaunchKernelGGL(loss_mean_kernel, dim3(a.n), dim3(64), 0, st, a);

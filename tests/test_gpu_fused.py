@@ -168,3 +168,18 @@ def test_fused_path_is_taken_only_where_it_fits():
     assert not g.fused
     g.set_learner_momentum(0.0)
     assert g.fused
+
+
+@pytest.mark.parametrize("P", [2720, 2740])
+def test_losses_that_fit_the_pinned_buffer_and_more(P):
+    """Three steps of P learners are 32 640 and 32 880 bytes of losses, the buffer holds 32 768; the first learners' do not depend on
+    how many others there are."""
+    dims, K, B = (8, 4, 2), 3, 2
+    many, _ = _pair(P, K, 0.05, 0.9, dims, B, False, 98)
+    few, _ = _pair(5, K, 0.05, 0.9, dims, B, False, 98)
+    for _ in range(2):
+        for g in (many, few):
+            g.local_steps()
+        got, want = many.losses(), few.losses()
+        assert got.shape == (K, P) and np.all(np.isfinite(got)) and np.all(got > 0)
+        assert np.max(np.abs(got[:, :5] - want)) < 1e-5          # (fp32, sums of eight terms in another order)
