@@ -145,7 +145,7 @@ __global__ void __launch_bounds__(NT, 4) conv_direct_kernel(DirectArgs a) {
         u32x4 v[SH::INN], gp;
         uint8_t bt[POOL ? SH::INN : 1];
         static_assert(NT % (CK / 8) == 0, "a thread's pieces are the same channels of their pixels");
-        if constexpr (POOL) gp = *(const u32x4*)(a.dpool + (size_t)learner * a.dpool_lstride + (size_t)b * a.c_k + g * CK + (tid % (CK / 8)) * 8);
+        if constexpr (POOL) gp = pool_scale(*(const u32x4*)(a.dpool + (size_t)learner * a.dpool_lstride + (size_t)b * a.c_k + g * CK + (tid % (CK / 8)) * 8), a.inv);
 #pragma unroll
         for (int i = 0; i < SH::INN; ++i) {
             const int e = min(tid + NT * i, SH::IN_PIECES - 1);
@@ -164,7 +164,7 @@ __global__ void __launch_bounds__(NT, 4) conv_direct_kernel(DirectArgs a) {
         }
         if constexpr (POOL) {
 #pragma unroll
-            for (int i = 0; i < SH::INN; ++i) v[i] = pool_grad_bits(bt[i], gp, a.inv);
+            for (int i = 0; i < SH::INN; ++i) v[i] = pool_mask(bt[i], gp);
         }
 #pragma unroll
         for (int i = 0; i < SH::INN; ++i) {
@@ -228,20 +228,24 @@ __global__ void __launch_bounds__(NT, 4) conv_direct_kernel(DirectArgs a) {
     uint16_t* out = a.out + (size_t)learner * a.out_lstride + pos_row * CN;
     const uint16_t* act = BWD ? a.act + (size_t)learner * a.out_lstride + pos_row * CN : nullptr;
     uint16_t* patch = (uint16_t*)smem + wave * 32 * OPITCH;                  // (the tile is dead)
+    // Data gradient: the mask is applied to row segments on their way out, from 16-byte reads of the same shape, requested before the
+    // patch is written (as in conv_flat.hip). 32 -> 64 channels, 16 learners of 128 images of 32x32: 80 us with 8-byte reads of the
+    // fragments' shape, 77 so.
+    u32x4 mask[BWD ? NB : 1][2];
+    if constexpr (BWD) {
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+            for (int pass = 0; pass < 2; ++pass)
+                mask[j][pass] = *(const u32x4*)(act + (size_t)((pass * 64 + lane) >> 2) * CN + j * 32 + (lane & 3) * 8);
+    }
 #pragma unroll
     for (int j = 0; j < NB; ++j) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int n = j * 32 + q * 8 + (lane >> 5) * 4;
             float v0 = acc[j][4 * q + 0], v1 = acc[j][4 * q + 1], v2 = acc[j][4 * q + 2], v3 = acc[j][4 * q + 3];
-            if constexpr (BWD) {
-                const u32x2 m = *(const u32x2*)(act + (size_t)(lane & 31) * CN + n);
-                // stored activations are ReLU outputs (never negative): positive <=> non-zero magnitude
-                v0 = (m.x & 0x7FFFu) ? v0 : 0.f;
-                v1 = (m.x & 0x7FFF0000u) ? v1 : 0.f;
-                v2 = (m.y & 0x7FFFu) ? v2 : 0.f;
-                v3 = (m.y & 0x7FFF0000u) ? v3 : 0.f;
-            } else {
+            if constexpr (!BWD) {
                 const u32x2 h2 = *(const u32x2*)(a.bhi + (size_t)learner * a.b_lstride + n);
                 const u32x2 l2 = *(const u32x2*)(a.blo + (size_t)learner * a.b_lstride + n);
                 uint32_t b0, b1, b2, b3;
@@ -258,7 +262,11 @@ __global__ void __launch_bounds__(NT, 4) conv_direct_kernel(DirectArgs a) {
 #pragma unroll
         for (int pass = 0; pass < 2; ++pass) {
             const int id = pass * 64 + lane, px = id >> 2, ch = id & 3;
-            const u32x4 v = *(const u32x4*)(patch + px * OPITCH + ch * 8);
+            u32x4 v = *(const u32x4*)(patch + px * OPITCH + ch * 8);
+            if constexpr (BWD) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) v[q] &= where_nonzero2(mask[j][pass][q]);
+            }
             *(u32x4*)(out + (size_t)px * CN + j * 32 + ch * 8) = v;
         }
     }

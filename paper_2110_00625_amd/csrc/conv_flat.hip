@@ -86,12 +86,6 @@ constexpr float BF16_MAX = 0x1.FEp127f;
 // Two bf16 numbers that are +-0 or positive and finite: bits 15 and 31, those that are positive.  (No half of the sum carries.)
 __device__ __forceinline__ uint32_t positive2(uint32_t two) { return (two + 0x7FFF7FFFu) & ~two & 0x80008000u; }
 
-// ones in the halves of `two` that are not +-0
-__device__ __forceinline__ uint32_t where_nonzero2(uint32_t two) {
-    typedef short i16x2 __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(i16x2, (two & 0x7FFF7FFFu) + 0x7FFF7FFFu) >> (i16x2){15, 15});
-}
-
 // fragment of a [position][channel] patch by transpose reads: lane l receives channel x0 + l%32 at positions 8 (l/32) .. +7
 __device__ __forceinline__ bf16x8 frag_tr(const uint16_t* patch, int pitch, int x0, int lane) {
     typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));

@@ -15,6 +15,12 @@ __device__ __forceinline__ uint32_t pool_pack2(float lo, float hi) {
     return (uint32_t)__builtin_bit_cast(uint16_t, a) | ((uint32_t)__builtin_bit_cast(uint16_t, b) << 16);
 }
 
+// ones in the halves of `two` that are not +-0 (stored activations are ReLU outputs, never negative: positive <=> non-zero magnitude)
+__device__ __forceinline__ uint32_t where_nonzero2(uint32_t two) {
+    typedef short i16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(i16x2, (two & 0x7FFF7FFFu) + 0x7FFF7FFFu) >> (i16x2){15, 15});
+}
+
 // m: eight activations (ReLU outputs, bf16 pairs); g: the eight channels' dpool; inv = 1 / (H W)
 __device__ __forceinline__ pool_u32x4 pool_grad_piece(pool_u32x4 m, pool_u32x4 g, float inv) {
     pool_u32x4 o;
