@@ -207,11 +207,14 @@ __global__ void __launch_bounds__(64 * 3 * (C_OUT / 32)) conv_first_wgrad_kernel
     f32x16 acc;
 #pragma unroll
     for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-    // column sums of dZ: four accumulators of a 16x16x32 instruction, taken by the three wavefronts of an output block in turn (conv_wgrad.hip)
+    // column sums of dZ: a slab's operand times ones, taken by the three wavefronts of an output block in turn (conv_wgrad.hip)
     f32x4 bacc = {0.f, 0.f, 0.f, 0.f};
-    bf16x8 ones;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) ones[e] = (__bf16)((lane & 15) == ((lane >> 4) & 1) ? 1.0f : 0.0f);
+    const bf16x4 ones = {(__bf16)1.0f, (__bf16)1.0f, (__bf16)1.0f, (__bf16)1.0f};
+    auto add_bias = [&](bf16x8 z) __attribute__((always_inline)) {
+        typedef short i16x4 __attribute__((ext_vector_type(4)));
+        bacc = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(i16x4, __builtin_shufflevector(z, z, 0, 1, 2, 3)), __builtin_bit_cast(i16x4, ones), bacc, 0, 0, 0);
+        bacc = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(i16x4, __builtin_shufflevector(z, z, 4, 5, 6, 7)), __builtin_bit_cast(i16x4, ones), bacc, 0, 0, 0);
+    };
 
     // slice s: buffer and set s % 2.  (Slices beyond the last are requested, in place of a branch around the requests, and not used.)
     constexpr std::integral_constant<int, 0> set0;
@@ -231,7 +234,7 @@ __global__ void __launch_bounds__(64 * 3 * (C_OUT / 32)) conv_first_wgrad_kernel
             const bf16x4 alo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr)ap);
             const bf16x4 ahi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((lds_ptr)(ap + 4 * CH));
             const bf16x8 zf = __builtin_shufflevector(zlo, zhi, 0, 1, 2, 3, 4, 5, 6, 7);
-            if ((s + kq) % 3 == nbk) bacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(zf, ones, bacc, 0, 0, 0);
+            if ((s + kq) % 3 == nbk) add_bias(zf);
             acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(zf, __builtin_shufflevector(alo, ahi, 0, 1, 2, 3, 4, 5, 6, 7), acc, 0, 0, 0);
         }
         if (s + 1 < slices) stash(next, buf ^ 1);
@@ -255,14 +258,16 @@ __global__ void __launch_bounds__(64 * 3 * (C_OUT / 32)) conv_first_wgrad_kernel
 #pragma unroll
         for (int e = 0; e < 16; ++e) out[(size_t)(ob * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)) * KW + col] = acc[e];
     }
-    // accumulator e of bacc: row 4 (lane/16) + e, column lane%16
-    float* red = (float*)smem;                   // [nbk][output channel] (the tiles are dead: the loop ended with a barrier)
-    if ((lane & 15) < 2) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) red[nbk * C_OUT + ob * 32 + (lane & 15) * 16 + (lane >> 4) * 4 + e] = bacc[e];
-    }
+    // accumulator e of bacc, in each lane of four: the sum of the values of the e-th of them
+    float* red = (float*)smem;                   // [nbk][half of the positions][output channel] (the tiles are dead: the loop ended with a barrier)
+    if ((lane & 3) == 0) *(f32x4*)(red + (nbk * 2 + (lane >> 5)) * C_OUT + ob * 32 + (lane & 31)) = bacc;
     __syncthreads();
-    if (tid < C_OUT) a.partial_bias[(size_t)lp * C_OUT + tid] = red[tid] + red[C_OUT + tid] + red[2 * C_OUT + tid];
+    if (tid < C_OUT) {
+        float b = 0.f;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) b += red[i * C_OUT + tid];
+        a.partial_bias[(size_t)lp * C_OUT + tid] = b;
+    }
 }
 
 template <int CN>

@@ -166,15 +166,20 @@ __global__ void __launch_bounds__(64 * 3 * (C_OUT / 32)) conv_wgrad_halo_kernel(
             for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
                 for (int e = 0; e < 16; ++e) acc[ty][oi][ni][e] = 0.f;
-    // Column sums of dZ, taken by the wavefronts of the three dx in turn: a slab's operand (lane l: channel l%32, positions
-    // 8 (l/32) ..) read as one of the 16x16x32 instruction is rows c (lanes 0-15, 32-47) and 16 + c (the others) of the sum, so
-    // column n of the other operand holds ones where (lane / 16) % 2 = n.  (Four accumulators and half a matrix instruction; added up
-    // out of LDS, 11 reads and 33 instructions of every wavefront per slice.)
+    // Column sums of dZ, taken by the wavefronts of the three dx in turn: a slab's operand (lane l: channel l%32, positions 8 (l/32) ..) times
+    // ones, four positions at a time in the 4x4x4 instruction, whose 16 blocks take a lane's values as a row of their own.  (A larger
+    // instruction with as few accumulators has two channels in a row, and an infinite gradient of one would void the other's sum.
+    // Added up out of LDS the sums were 11 reads and 33 instructions of every wavefront per slice.  us per launch, with two channels in a
+    // row / so: 64 -> 128 channels, 16 learners of 64 images of 32x32 149.9 / 151.5, 64 -> 64 113.4 / 111.3, 32 -> 64 57.2 / 57.7, the
+    // first layer, 8 -> 64, 38.6 / 39.5; with 16 accumulators, a channel per row, that one 40.0.)
     const int b_oi = PAIR ? nb0 : 0;                     // the output block whose bias this wavefront sums (of its OI)
     f32x4 bacc = {0.f, 0.f, 0.f, 0.f};
-    bf16x8 ones;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) ones[e] = (__bf16)((lane & 15) == ((lane >> 4) & 1) ? 1.0f : 0.0f);
+    const bf16x4 ones = {(__bf16)1.0f, (__bf16)1.0f, (__bf16)1.0f, (__bf16)1.0f};
+    auto add_bias = [&](bf16x8 z) __attribute__((always_inline)) {
+        typedef short i16x4 __attribute__((ext_vector_type(4)));
+        bacc = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(i16x4, __builtin_shufflevector(z, z, 0, 1, 2, 3)), __builtin_bit_cast(i16x4, ones), bacc, 0, 0, 0);
+        bacc = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(i16x4, __builtin_shufflevector(z, z, 4, 5, 6, 7)), __builtin_bit_cast(i16x4, ones), bacc, 0, 0, 0);
+    };
 
     fetch(0);
     if constexpr (POOL) __syncthreads();         // the dpool rows are in LDS
@@ -191,7 +196,7 @@ __global__ void __launch_bounds__(64 * 3 * (C_OUT / 32)) conv_wgrad_halo_kernel(
             bf16x8 zf[OI];
 #pragma unroll
             for (int oi = 0; oi < OI; ++oi) zf[oi] = frag_tr(Z, ZP, kq * 16, (ob0 + oi) * 32, lane);
-            if ((s + kq) % 3 == tl) bacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b_oi ? zf[OI - 1] : zf[0], ones, bacc, 0, 0, 0);
+            if ((s + kq) % 3 == tl) add_bias(b_oi ? zf[OI - 1] : zf[0]);
             const int r = kq >> 1, w0 = (kq & 1) * 16;
 #pragma unroll
             for (int ty = 0; ty < 3; ++ty) {
@@ -223,14 +228,16 @@ __global__ void __launch_bounds__(64 * 3 * (C_OUT / 32)) conv_wgrad_halo_kernel(
                     const int o = (ob0 + oi) * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
                     out[(size_t)o * 9 * C_IN + (ty * 3 + tl) * C_IN + (nb0 + ni) * 32 + (lane & 31)] = acc[ty][oi][ni][e];
                 }
-    // accumulator e of bacc: row 4 (lane/16) + e, column lane%16
-    float* red = (float*)smem;                   // [tl][output channel] (the tiles are dead: the loop ended with a barrier)
-    if ((lane & 15) < 2) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) red[tl * C_OUT + (ob0 + b_oi) * 32 + (lane & 15) * 16 + (lane >> 4) * 4 + e] = bacc[e];
-    }
+    // accumulator e of bacc, in each lane of four: the sum of the values of the e-th of them
+    float* red = (float*)smem;                   // [tl][half of the positions][output channel] (the tiles are dead: the loop ended with a barrier)
+    if ((lane & 3) == 0) *(f32x4*)(red + (tl * 2 + (lane >> 5)) * C_OUT + (ob0 + b_oi) * 32 + (lane & 31)) = bacc;
     __syncthreads();
-    if (tid < C_OUT) a.partial_bias[(size_t)lp * C_OUT + tid] = red[tid] + red[C_OUT + tid] + red[2 * C_OUT + tid];
+    if (tid < C_OUT) {
+        float b = 0.f;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) b += red[i * C_OUT + tid];
+        a.partial_bias[(size_t)lp * C_OUT + tid] = b;
+    }
 }
 
 template <int C_IN, int C_OUT, bool POOL>
