@@ -1112,7 +1112,7 @@ int round8(int x) { return (x + 7) / 8 * 8; }
 enum { T128x128 = 0, T128x64 = 1, T64x128 = 2, T256x128 = 3, T64x64_K2 = 4, T128x64_K2 = 5 };
 
 // Measured on MI355X over the workload shapes (batch 64..256, widths 1024..4096, 8..32 learners):
-// with >= 512 (forward: 257) tiles of 128x128 the launch fills the chip with the tile that reads LDS least per
+// with >= 512 (forward: from 257 on) tiles of 128x128 the launch fills the chip with the tile that reads LDS least per
 // flop; smaller problems are LDS- and barrier-bound per workgroup, and the 64x64 tile with two k
 // groups (most wavefronts per compute unit, half as many barriers per k) wins.
 int pick_tile(int mode, int nR, int nC, int nK, int P) {
@@ -1122,15 +1122,26 @@ int pick_tile(int mode, int nR, int nC, int nK, int P) {
     if (mode == MODE_FWD) {
         if (nR % 256 == 0 && nK % 64 == 0 && nK >= 128 && (long)(nR / 256) * ((nC + 127) / 128) * P >= 192) return T256x128;
         if (nR <= 64) return (long)((nC + 127) / 128) * P >= 512 ? T64x128 : T64x64_K2;
-        // (64x64 tiles of 65 to 128 rows read every weight twice, streamed ones out of memory.  us per round of four steps, 64x64 / 128x128:
-        // 416 tiles, 32 learners of 107 rows of 568-2872-1616-218 3532 / 3421; 288, 12 of 90 of 1000-3000-10 495 / 473; 256 and 224 742 /
-        // 743 and 549 / 546; 192 870 / 873; 128 756 / 836.)
-        if (tiles128 > 256) return T128x128;
+        // 64x64 tiles read every weight at least twice, streamed ones out of memory; 128x128 ones may be half padding (129 - 192 rows: 256
+        // against 192).  The line lies where the small ones no longer fit the chip twice over, two workgroups to a compute unit.  (us per round
+        // of four steps, 64x64 / 128x128.  Up to 128 rows, four small tiles to a large one: 416 large ones, 32 learners of 107 rows of
+        // 568-2872-1616-218 3532 / 3421; 288, 12 of 90 of 1000-3000-10 495 / 473; 256 and 224 742 / 743 and 549 / 546; 192 870 / 873; 128
+        // 756 / 836.  More rows, small tiles: 1152, 12 of 160 of 1024-2048-2048-10 1111 / 1046; 1120, 7 of 260 936 / 873; 1056, 22 of 140 of
+        // 3072-1024-10 860 / 824, 11 of 150 of 1024-2048-10 387 / 367; but 960, 20 of 150 of 3072-1024-1024-10 1113 / 1140; 1008, 21 of 140 of
+        // 1024-1024-10 340 / 345; 816, 17 of 130 of 2048-1024-10 462 / 480.)
+        const long tiles64 = (long)((nR + 63) / 64) * ((nC + 63) / 64) * P;
+        if (tiles128 >= 512 || (tiles128 > 256 && tiles64 > 1024)) return T128x128;
         // One workgroup of 128x64 per compute unit, in the same two k groups, with two slices in flight: a quarter less to bring in than by
         // two of 64x64 with one.  (us per round, 64x64 / 128x64: 256 tiles, 3072-1024-1024-10, 16 learners of 128 rows 1380 / 1357,
         // 4096-4096-100, 4 of 256 1086 / 1041; 192, 12 of 128 604 / 596; but 320 976 / 978; 85 338 / 381; 228 of a contraction of 704 184 / 203.)
+        // Where 64 of the rows are padding there is a third more to multiply, which only a long contraction on few workgroups makes up
+        // for.  (4096-2048-10, 3 of 160, 192 tiles 378 / 371, 4096-2816-10, 2 of 130, 176 tiles 382 / 372, 3072-2048-10, 3 of 130 307 / 303; but 4 of 150, 256 tiles 443 / 450;
+        // 2048-2048-10, 4 of 192 270 / 276; 2048-1024-1024-10, 8 of 192 397 / 408; 1024-1024-10, 6 of 130 143 / 147; and where the 64x64
+        // tiles are one per compute unit, 4096-1024-10, 5 of 192 292 / 317.)
         const long tiles = (long)((nR + 127) / 128) * ((nC + 63) / 64) * P;
-        return tiles >= 160 && tiles <= 256 && nK >= 1024 ? T128x64_K2 : T64x64_K2;
+        const bool padding = (nR + 63) / 64 % 2 != 0;
+        if (tiles >= 160 && tiles <= 256 && nK >= 1024 && (!padding || (nK >= 3072 && tiles <= 192 && tiles64 > 256))) return T128x64_K2;
+        return T64x64_K2;
     }
     // backward-data, measured at the 4096-wide layers: 128x128 95 us against 119 us for 128x64 (batch 256),
     // 64x128 222 us against 249 us for 64x64 (batch 64)
