@@ -1,4 +1,5 @@
-// The SGD updates of several layers in one launch (KAVG_BF16), for models whose weights stay in the memory-side cache:
+// The SGD updates of several layers in one launch (KAVG_BF16), for models whose weights stay in the memory-side cache, and with
+// learner momentum for those whose weights do not:
 //
 //     W_l <- W_l - lr * dZ_l^T A_{l-1};    b_l <- b_l - lr * colsum(dZ_l)       (with learner momentum: u <- beta u + gradient, W <- W - lr u)
 //
@@ -16,8 +17,8 @@
 // Measured, all updates of a step, us (one launch per layer, the velocity read after the contraction -> this kernel):
 // 3072-1024-1024-10, 16 learners of 128 samples 79 + 31 + 9 -> 104 (5.3 TB/s); 3080-1032-520-24 with momentum, 5 learners of
 // 70: 84 + 27 -> 58 (5.2 TB/s); models of a few hundred units: 4 - 6 per layer -> 5 - 8 in all.  What bounds
-// it: the traffic of the planes on large models, latency on small ones.  Where the hi planes stream as well the one-layer
-// kernel is as fast (4096 wide, 32 learners: 630 against 595 + 23) and stays.
+// it: the traffic of the planes on large models, latency on small ones.  Where the hi planes stream as well and there is no velocity, the
+// one-layer kernel is as fast (4096 wide, 32 learners: 630 against 595 + 23) and stays.
 #include "kavg_internal.h"
 #include "column_sum.h"
 #include "conv_step.h"
@@ -58,6 +59,7 @@ struct Args {
     Layer layer[GROUP];
     int n_layers, B;
     int head_every;                          // > 0: layer 0 is the head, its workgroups (latency, hardly any traffic) are spread over the launch
+    int by_rows;                             // the tiles of a row follow each other, not those of a column
     size_t lstride;                          // between learners, in planes and velocities
     float lr, beta;
     ConvSteps conv; int conv_wgs;            // conv_wgs > 0: steps of convolutions, by the workgroups behind those of the layers
@@ -103,11 +105,12 @@ __global__ void __launch_bounds__(NT, 2) update_group_kernel(Args a) {
         if (r < a.losses.n) loss_mean_wave(a.losses, r, lane);
         return;
     }
-    // workgroup g runs on XCD g mod 8: each XCD gets one contiguous range of (learner, column tile, row tile)
+    // workgroup g runs on XCD g mod 8: each XCD gets one contiguous range of (learner, column tile, row tile), or row before column
     int at = (g & 7) * (q.padded >> 3) + (g >> 3);
     if (at >= q.total) return;
-    const int rt = at % q.tiles_r; at /= q.tiles_r;
-    const int ct = at % q.tiles_c, learner = at / q.tiles_c;
+    const int inner = a.by_rows ? q.tiles_c : q.tiles_r, outer = a.by_rows ? q.tiles_r : q.tiles_c;
+    const int ti = at % inner; at /= inner;
+    const int to = at % outer, learner = at / outer, rt = a.by_rows ? to : ti, ct = a.by_rows ? ti : to;
     if (q.head) {
         HeadStep h = {};
         h.act = q.in; h.ld_act = q.ld_in; h.act_lstride = q.in_lstride; h.gather = q.gather; h.gather_lstride = q.gather_lstride;
@@ -260,10 +263,12 @@ __global__ void __launch_bounds__(NT, 2) update_group_kernel(Args a) {
 
 bool bf16_update_group_ok(const LayerCall& c) {
     // Planes that do not stay in the cache: with a velocity only, which is the larger part of the traffic and which the one-layer
-    // kernel reads after the contraction; with long contractions that kernel's larger tiles outweigh it where rows are whole lines.  (us
-    // per round of four steps, one-layer / this: 2048-2048-2048-100, 16 learners of 128 rows 2670 / 2554; 3080-1032-520-24, 32 of 70, both with
-    // ordinary accesses to ragged rows, 2700 / 2463; 1504-1504-1504-10, 24 of 200 2718 / 2620; but 3072-4096-10, 8 of 250 1963 / 2021.)
-    return (c.shadow_cached || (c.u && (c.B <= 128 || !whole_lines(c)))) && !c.rows && !c.partial && !c.skip_bias && c.d_in >= 8 && c.ld_dz >= 8;
+    // kernel reads after the contraction; with long contractions that kernel's larger tiles outweigh it.  (us per round of two steps,
+    // one-layer / this.  Rows of whole lines: 2048-2048-10, 24 learners of 16 and 250 rows 922 / 899 and 1118 / 1071, 4096-4096-10, 8 of 64
+    // and 400 1202 / 1151 and 1750 / 1629, 4096-4096-1000, 9 of 400 2528 / 2496.  Ragged rows, both with ordinary accesses:
+    // 1000-3000-1000-10, 20 of 64 and 400 1359 / 1253 and 2087 / 2007, 1544-2504-1320-10, 30 of 400 3626 / 3493; but 4088-4008-1000, 10 of
+    // 400, 450 and 1024 3159 / 3162, 3233 / 3272 and 4442 / 4988, 1000-3000-1000-10, 20 of 768 2619 / 2710.)
+    return (c.shadow_cached || (c.u && c.B <= 400)) && !c.rows && !c.partial && !c.skip_bias && c.d_in >= 8 && c.ld_dz >= 8;
 }
 
 hipError_t bf16_update_group(const LayerCall* calls, int n, const LossMeans* losses, const ConvStep* convs, int n_convs, hipStream_t st) {
@@ -306,6 +311,11 @@ hipError_t bf16_update_group(const LayerCall* calls, int n, const LossMeans* los
         for (int i = 1; i < a.n_layers; ++i)
             if ((size_t)calls[at + i].d_in * calls[at + i].d_out > (size_t)most->d_in * most->d_out) most = calls + at + i;
         const bool stream = (size_t)calls[at].P * a.lstride * (momentum ? 8 : 4) > ((size_t)224 << 20) && (calls[at].shadow_cached || whole_lines(*most));
+        // Out of memory whole rows of tiles: a column of tiles is a stripe of the planes whose lines lie a row apart, on few of the memory's
+        // channels where rows are powers of two long, and with as many learners as XCDs, or a multiple, every XCD is at the same stripe.
+        // (us per round of two steps, column by column / so: 4096-4096-10, 8 learners of 16 rows 1271 / 1152, 16 of 64 2497 / 2262; 9 of 64
+        // of 4096-4096-1000 1708 / 1682; 1000-3000-1000-10, 20 of 64 1341 / 1253.)
+        a.by_rows = !calls[at].shadow_cached;
         if (stream && !calls[at].shadow_cached) hipLaunchKernelGGL((update_group_kernel<true, true, true>), dim3(wgs), dim3(NT), 0, st, a);
         else if (momentum && stream) hipLaunchKernelGGL((update_group_kernel<true, true, false>), dim3(wgs), dim3(NT), 0, st, a);
         else if (momentum) hipLaunchKernelGGL((update_group_kernel<true, false, false>), dim3(wgs), dim3(NT), 0, st, a);

@@ -20,8 +20,12 @@ CASES = [
     (264, WHOLE, 0.0),
     (33, WHOLE, 0.9),                 # with velocities: all layers in one launch
     (33, RAGGED, 0.9),
-    (136, RAGGED, 0.9),               # ... ragged rows also where batches are long
-    (136, WHOLE, 0.9),                # a launch per layer
+    (136, RAGGED, 0.9),
+    (136, WHOLE, 0.9),
+    (400, RAGGED, 0.9),               # ... up to 400 rows
+    (400, WHOLE, 0.9),
+    (401, RAGGED, 0.9),               # a launch per layer
+    (401, WHOLE, 0.9),
 ]
 
 
