@@ -4,7 +4,7 @@
 // Such a model (d_0 x 64 + 64 x C weights per learner) takes a few microseconds of arithmetic per
 // step; run as a chain of generic kernels it is bound by ~6 dependent launches per step.  Here the
 // learner's first-layer weights are cut into S column chunks of CW input features (CW a multiple of
-// 64, at most 192); workgroup (j, s) keeps chunk s of learner j's W_1 in LDS for the whole call,
+// 64, at most 192, or 384 where four workgroups share a chunk); workgroup (j, s) keeps chunk s of learner j's W_1 in LDS for the whole call,
 // together with private copies of b_1, W_2 and b_2.  (Where the device has the compute units for it and the
 // layer has more than 32 units, two or four workgroups share a chunk, each with half or a quarter of the hidden units: "its chunk"
 // is then those units' rows of the chunk; everything else is unchanged.)  Per step
@@ -112,7 +112,11 @@ __device__ __forceinline__ void contract(const float* xp, const float* wp, int c
 // workgroup then gathers the partials of half as many chunks (131 instead of 262 KB per step for 32 rows of 3072, all requested at once): the
 // exchange, not the arithmetic, is the longest part of a step.  us per round of four steps: 3072-64-10, 4 learners of 32 rows 72.2 -> 65.0,
 // 1024-64-10, 8 learners 62.0 -> 55.1, 784-64-10, 4 of 24 rows 56.2 -> 50.7.
-template <bool WIDE>
+// BATCH (WIDE, and more than 32 rows): the operands of 16 rows of the update of W_1 are requested before those at hand are used.  Shorter
+// minibatches do better with four rows at a time, and chunks of at most 192 columns with the compiler's loop around their products.
+// (us per round of four steps, both by hand / neither: 784-64-10, 12 learners of 8 rows 56.0 / 54.4, 16 of 32 65.1 / 63.4, 256-64-10, 60 of 32
+// 56.0 / 53.6; but more rows 3072-64-10, 4 of 64 97.3 / 101.2, the rows alone by hand 96.1.)
+template <bool WIDE, bool BATCH>
 __global__ void __launch_bounds__(NT)
 fused_small_kernel(FusedSmallCall a, int S, int CW, int UH) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -263,7 +267,11 @@ fused_small_kernel(FusedSmallCall a, int S, int CW, int UH) {
             f32x4 acc = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};   // two chains: the matrix pipeline never waits for its own result
             const float* xp = sm.X + (m0 + (lane & 15)) * PW + (lane >> 4);
             const float* wp = sm.W1 + (u0 + (lane & 15)) * PW + (lane >> 4);
-            contract(xp, wp, CW, acc, acc1);
+#pragma unroll 4
+            for (int c = 0; c < CW; c += 8) {
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xp[c], wp[c], acc, 0, 0, 0);
+                acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(xp[c + 4], wp[c + 4], acc1, 0, 0, 0);
+            }
             acc += acc1;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
@@ -395,18 +403,27 @@ fused_small_kernel(FusedSmallCall a, int S, int CW, int UH) {
                 f32x4 acc[NB];
 #pragma unroll
                 for (int i = 0; i < NB; ++i) acc[i] = (f32x4){0.f, 0.f, 0.f, 0.f};
-                for (int m = 0; m < Bk; m += 16) {              // (zeros beyond B)
-                    float d[4], x[4][NB];
+                if constexpr (!BATCH) {
+#pragma unroll 2
+                    for (int m = 0; m < Bk; m += 4) {
+                        const float d = dp[m * PH];
 #pragma unroll
-                    for (int t = 0; t < 4; ++t) {
-                        d[t] = dp[(m + 4 * t) * PH];
-#pragma unroll
-                        for (int i = 0; i < NB; ++i) x[t][i] = xp[(m + 4 * t) * PW + cstep * i];
+                        for (int i = 0; i < NB; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(d, xp[m * PW + cstep * i], acc[i], 0, 0, 0);
                     }
+                } else {
+                    for (int m = 0; m < Bk; m += 16) {              // (zeros beyond B)
+                        float d[4], x[4][NB];
 #pragma unroll
-                    for (int t = 0; t < 4; ++t)
+                        for (int t = 0; t < 4; ++t) {
+                            d[t] = dp[(m + 4 * t) * PH];
 #pragma unroll
-                        for (int i = 0; i < NB; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(d[t], x[t][i], acc[i], 0, 0, 0);
+                            for (int i = 0; i < NB; ++i) x[t][i] = xp[(m + 4 * t) * PW + cstep * i];
+                        }
+#pragma unroll
+                        for (int t = 0; t < 4; ++t)
+#pragma unroll
+                            for (int i = 0; i < NB; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(d[t], x[t][i], acc[i], 0, 0, 0);
+                    }
                 }
 #pragma unroll
                 for (int i = 0; i < NB; ++i)
@@ -473,12 +490,12 @@ Split split_of(int P, int B, int d0, int d1, int compute_units) {
     return {S, CW, d1 > HID / 2 && (long)2 * P * S <= compute_units ? 2 : 1, false};
 }
 
-template <bool WIDE>
+template <bool WIDE, bool BATCH>
 hipError_t launch_split(const FusedSmallCall& c, const Split& p, hipStream_t st) {
-    static hipError_t raised = hipFuncSetAttribute((const void*)fused_small_kernel<WIDE>, hipFuncAttributeMaxDynamicSharedMemorySize,
+    static hipError_t raised = hipFuncSetAttribute((const void*)fused_small_kernel<WIDE, BATCH>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                                    (int)sizeof(Smem<WIDE>));
     if (raised != hipSuccess) return raised;
-    hipLaunchKernelGGL(fused_small_kernel<WIDE>, dim3(c.P * p.S * p.UH), dim3(NT), sizeof(Smem<WIDE>), st, c, p.S, p.CW, p.UH);
+    hipLaunchKernelGGL((fused_small_kernel<WIDE, BATCH>), dim3(c.P * p.S * p.UH), dim3(NT), sizeof(Smem<WIDE>), st, c, p.S, p.CW, p.UH);
     return hipGetLastError();
 }
 
@@ -497,7 +514,8 @@ int fused_small_workgroups(int P, int B, int d0, int d1, int compute_units) {
 
 hipError_t launch_fused_small(const FusedSmallCall& c, hipStream_t st) {
     const Split p = split_of(c.P, c.B, c.d0, c.d1, c.compute_units);
-    return p.wide ? launch_split<true>(c, p, st) : launch_split<false>(c, p, st);
+    if (p.wide) return launch_split<true, true>(c, p, st);
+    return c.B > 32 ? launch_split<false, true>(c, p, st) : launch_split<false, false>(c, p, st);
 }
 
 }  // namespace kavg
