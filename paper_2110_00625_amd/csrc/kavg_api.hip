@@ -1304,6 +1304,7 @@ int issue_steps_deferred(kavg_ctx* c) {
         else { q.out = c->logits(); q.ld_out = lo.ldz; q.out_stride = (size_t)B * lo.ldz; q.relu = 0; }
         q.dz = dzH(l, slot); q.ld_dz = ld_of(l); q.dz_stride = (size_t)m * B * q.ld_dz;
         q.lr = c->lr;
+        q.deferred = 1;
         // until the first refresh of a round every stored replica still holds the global model: all
         // learners then read learner 0's copy, which the caches serve, instead of P copies from memory
         q.shared_w = (c->replicas_equal && k < m) ? 1 : 0;

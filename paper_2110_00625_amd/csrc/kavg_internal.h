@@ -84,6 +84,7 @@ struct LayerCall {
     int shared_w;          // forward / backward-data: every learner's stored weights equal learner 0's (round start): read those
     int bwd_raw;           // backward-data: write the unmasked fp32 product to dz_prev instead of the masked bf16 one
     int rows;              // update: rows of dz / in to contract over (0: B) -- the steps since the last refresh
+    int deferred;          // the stored weights serve several steps
     int skip_bias;         // update: leave the bias alone (it is stepped after every local step)
     // update with fp32 partial outputs instead of a step on the master (long contractions split over
     // `splits` ranges of rows that run as separate workgroups): partial [P*splits][d_out][d_in],
@@ -91,20 +92,24 @@ struct LayerCall {
     float* partial; float* partial_bias; int splits;
 };
 
-// Rows of the weights' planes are whole 128-byte lines.  Streaming (non-temporal) accesses pay only there: where rows are ragged two
-// workgroups share a line, and each of them fetches it from memory, or writes its part of it there, by itself.  (Rounds of two steps, us,
-// streaming / ordinary accesses throughout: 3432-1728-10, 32 learners of 64 rows 1595 / 1203; 1544-2504-1320-10, 30 of 40
-// 1826 / 1437; 4088-4008-1000, 8 of 256 1488 / 1320; 4000-4000-10 (half lines), 16 of 100 1582 / 1588; but 4096-4096-10, 16 of 128
-// 1459 / 1638.)
-inline bool whole_lines(const LayerCall& c) {
-    return c.d_in % 64 == 0 && c.ws_stride % 64 == 0 && ((uintptr_t)c.ws | (uintptr_t)c.wlo) % 128 == 0;
+// Rows of the weights' planes are whole 128-byte lines, or (halves) whole halves of them.  Streaming (non-temporal) accesses pay only
+// there: where rows are ragged two workgroups share a line, and each of them fetches it from memory, or writes its part of it there, by
+// itself.  (Rounds of two steps, us, streaming / ordinary accesses throughout: 3432-1728-10, 32 learners of 64 rows 1595 / 1203;
+// 1544-2504-1320-10, 30 of 40 1826 / 1437; 4088-4008-1000, 8 of 256 1488 / 1320; but 4096-4096-10, 16 of 128 1459 / 1638.)
+inline bool whole_lines(const LayerCall& c, bool halves) {
+    const int n = halves ? 32 : 64;
+    return c.d_in % n == 0 && c.ws_stride % n == 0 && ((uintptr_t)c.ws | (uintptr_t)c.wlo) % (2 * n) == 0;
 }
 // How an update reads and writes the planes: streaming both, streaming the lo planes alone (the hi planes stay in the memory-side cache),
 // with ordinary accesses (planes that stream, in ragged rows).
 enum { STREAM_BOTH = 0, STREAM_LO = 1, STREAM_NONE = 2 };
 // (Hi planes that stay cached are worth more than the shared lines of the lo planes: 3080-1032-1032-10, 16 learners of 128 rows, four steps, streaming
 // / ordinary lo planes 941 / 1027 us, 1000-1000-1000-10, 30 of 100 768 / 824.)
-inline int stream_policy(const LayerCall& c) { return c.shadow_cached ? STREAM_LO : whole_lines(c) ? STREAM_BOTH : STREAM_NONE; }
+// halves: rows of whole half lines stream too.  That is the better way where the stored weights serve several steps and in the tiles of
+// 128x128 of long contractions.  (us per round, ordinary / streaming: eight steps, weights refreshed every four or eight, 16 learners of
+// 4000-3000-10, 16, 32 and 64 rows 1448 / 1412, 1576 / 1522 and 1784 / 1759, 12 of 100 of 4000-4000-100 2882 / 2839; four steps, 18 of 136
+// and 320 of 4000-3000-10 2870 / 2781 and 3643 / 3579; but, in tiles of 64x128, 18 of 8 and 64 2146 / 2192 and 2296 / 2350.)
+inline int stream_policy(const LayerCall& c, bool halves) { return c.shadow_cached ? STREAM_LO : whole_lines(c, halves) ? STREAM_BOTH : STREAM_NONE; }
 template <bool STREAM, class T> __device__ __forceinline__ T plane_get(const T* p) { return STREAM ? __builtin_nontemporal_load(p) : *p; }
 template <bool STREAM, class T> __device__ __forceinline__ void plane_put(T* p, T v) { if (STREAM) __builtin_nontemporal_store(v, p); else *p = v; }
 

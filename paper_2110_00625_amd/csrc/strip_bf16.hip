@@ -328,7 +328,7 @@ hipError_t bf16_strip(const LayerCall& c, hipStream_t st) {
     a.padded = (a.total + 7) / 8 * 8;
     // where the separate data gradient would split its contraction (small launches, up to 128 samples), so does this one
     const bool two = bf16_backward_splits(c.P, c.B, c.d_in, c.d_out);
-    const int stream = stream_policy(c);
+    const int stream = stream_policy(c, false);
     if (c.B <= 64) return two ? launch_stream<64, 2>(a, stream, st) : launch_stream<64, 1>(a, stream, st);
     if (c.B <= 128) return two ? launch_stream<128, 2>(a, stream, st) : launch_stream<128, 1>(a, stream, st);
     if (two) return hipErrorInvalidValue;                    // (never: 192 strips of more than 128 samples are 384 tiles)

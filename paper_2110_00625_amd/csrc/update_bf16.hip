@@ -310,7 +310,7 @@ hipError_t bf16_update_group(const LayerCall* calls, int n, const LossMeans* los
         const LayerCall* most = calls + at;                  // the layer with most weights
         for (int i = 1; i < a.n_layers; ++i)
             if ((size_t)calls[at + i].d_in * calls[at + i].d_out > (size_t)most->d_in * most->d_out) most = calls + at + i;
-        const bool stream = (size_t)calls[at].P * a.lstride * (momentum ? 8 : 4) > ((size_t)224 << 20) && (calls[at].shadow_cached || whole_lines(*most));
+        const bool stream = (size_t)calls[at].P * a.lstride * (momentum ? 8 : 4) > ((size_t)224 << 20) && (calls[at].shadow_cached || whole_lines(*most, false));
         // Out of memory whole rows of tiles: a column of tiles is a stripe of the planes whose lines lie a row apart, on few of the memory's
         // channels where rows are powers of two long, and with as many learners as XCDs, or a multiple, every XCD is at the same stripe.
         // (us per round of two steps, column by column / so: 4096-4096-10, 8 learners of 16 rows 1271 / 1152, 16 of 64 2497 / 2262; 9 of 64

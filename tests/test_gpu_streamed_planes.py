@@ -10,7 +10,8 @@ from tests.util import bf16_plane_bits, layer_slices
 
 pytestmark = pytest.mark.gpu
 
-WHOLE, RAGGED = (576, 1984, 320, 24), (584, 1976, 328, 24)       # 1.78 M weights, 228 MB of bf16 planes over 64 learners
+# (HALVES: every other row begins in the middle of a line)
+WHOLE, RAGGED, HALVES = (576, 1984, 320, 24), (584, 1976, 328, 24), (608, 2016, 352, 24)       # 1.78 M weights and more, 228 MB of bf16 planes over 64 learners
 CASES = [
     # B, dims, learner momentum
     (33, RAGGED, 0.0),                # strips of up to 64 samples; the first layer in tiles of 64x128
@@ -18,6 +19,9 @@ CASES = [
     (136, RAGGED, 0.0),               # tiles of 128x128
     (264, RAGGED, 0.0),               # ... with the late master
     (264, WHOLE, 0.0),
+    (33, HALVES, 0.0),                # ordinary accesses to strips and tiles of 64x128,
+    (136, HALVES, 0.0),               # streaming ones in tiles of 128x128
+    (264, HALVES, 0.0),
     (33, WHOLE, 0.9),                 # with velocities: all layers in one launch
     (33, RAGGED, 0.9),
     (136, RAGGED, 0.9),
