@@ -72,7 +72,7 @@ struct FlatArgs {
     int PB, tiles, total, padded; uint32_t div_tiles_m; int div_tiles_s;      // tiles per learner; workgroups
     const uint16_t* dpool; size_t dpool_lstride; float inv; int images, places;      // BWD_POOL: gradients from the bits and these; images per learner, of a tile
     uint32_t* bits; int bits_pitch; size_t bits_lstride;             // words per pixel; LAST: written, BWD_POOL: read
-    float* sums; int slots;                                          // LAST: places of images per 128 positions
+    float* sums; int slots;                                          // LAST: places of images per wavefront
 };
 
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
@@ -113,9 +113,9 @@ __host__ __device__ constexpr bool permuted(int CK) { return CK == 64; }
 __host__ __device__ constexpr int pixel_pitch(int CK) { return permuted(CK) ? CK : CK + 8; }
 // bytes of the output patches of the four wavefronts (two each, in turn), and of the pixels of a tile, which those lie over;
 // behind the patches a byte for each position of each wavefront (LAST)
-__host__ __device__ constexpr int patch_area(int NB, int PB) { return 2 * 4 * 32 * (NB * 32 + 8) * 2; }
+__host__ __device__ constexpr int patch_area(int NB) { return 2 * 4 * 32 * (NB * 32 + 8) * 2; }
 __host__ __device__ constexpr int tile_area(int n_px, int CK, int NB, int PB) {
-    return n_px * pixel_pitch(CK) * 2 > patch_area(NB, PB) + 4 * PB * 32 ? n_px * pixel_pitch(CK) * 2 : patch_area(NB, PB) + 4 * PB * 32;
+    return n_px * pixel_pitch(CK) * 2 > patch_area(NB) + 4 * PB * 32 ? n_px * pixel_pitch(CK) * 2 : patch_area(NB) + 4 * PB * 32;
 }
 
 // PB: blocks of 32 positions per wavefront.  LAST (forward): the layer below the mean over the positions; bits and partial sums instead of activations
@@ -394,7 +394,7 @@ __global__ void __launch_bounds__(NT, 2) conv_flat_kernel(FlatArgs a) {
         }
     } else {
         f32x16 sums[NB];                                      // [place of an image][channel] of the wavefront's positions
-        uint8_t* const SLOT = (uint8_t*)smem + patch_area(NB, PB) + wave * (PB * 32);      // place of a position's image among those of its wavefront; 255: margin
+        uint8_t* const SLOT = (uint8_t*)smem + patch_area(NB) + wave * (PB * 32);      // place of a position's image among those of its wavefront; 255: margin
         const int group = q0 / (PB * 32) + pw, first = (q0 + pw * PB * 32) / a.image, last = (q0 + pw * PB * 32 + PB * 32 - 1) / a.image - first;
 #pragma unroll
         for (int h = 0; h < PB / 2; ++h) {
@@ -669,8 +669,8 @@ hipError_t launch_pool_finish(const PoolSums& q, void* pooled, int P, int B, int
     return hipGetLastError();
 }
 
-hipError_t conv_flat_forward(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag, const int32_t*, const void* X,
-                             const int32_t* gather, long gstride, hipStream_t st) {
+hipError_t conv_flat_forward(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag, const void* X, const int32_t* gather,
+                             long gstride, hipStream_t st) {
     if (!c.bits && !c.out) return hipErrorInvalidValue;
     FlatArgs a = make_args(c, plan, frag);
     const size_t rows = (size_t)c.B * c.H * c.W;
@@ -688,8 +688,7 @@ hipError_t conv_flat_forward(const ConvCall& c, const FlatPlan& plan, const uint
     return gather ? run<FWD_GATHER>(a, plan, st) : run<FWD>(a, plan, st);
 }
 
-hipError_t conv_flat_backward_data(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag, const int32_t*, const void* dpool,
-                                   hipStream_t st) {
+hipError_t conv_flat_backward_data(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag, const void* dpool, hipStream_t st) {
     if (dpool ? !c.bits : !c.dz) return hipErrorInvalidValue;
     FlatArgs a = make_args(c, plan, frag);
     const size_t rows = (size_t)c.B * c.H * c.W;

@@ -1241,7 +1241,7 @@ hipError_t bf16_forward(const LayerCall& c, hipStream_t st) {
     a.out = c.out; a.out_lstride = c.out_stride; a.ld_out = c.ld_out; a.relu = c.relu;
     a.c_stream = !c.shadow_cached && !c.shared_w && whole_lines(c, c.deferred);
     if (a.nK % 64 == 0 && a.nK >= 128 && merge_rows(c, a, 256, 128))
-        return launch<MODE_FWD, 256, 128, 2, 2, 1, 64, false, false, PIPE_RING, false, false, false, false, true>(a, 1, st);
+        return launch<MODE_FWD, 256, 128, 2, 2, 1, 64, false, false, PIPE_RING, STREAM_BOTH, false, false, false, true>(a, 1, st);
     return launch_tiled<MODE_FWD, false, false>(a, c.P, pick_tile(MODE_FWD, a.nR, a.nC, a.nK, c.P), st);
 }
 
@@ -1257,7 +1257,7 @@ hipError_t bf16_backward_data(const LayerCall& c, hipStream_t st) {
     a.out = c.dz_prev; a.out_lstride = c.dz_prev_stride; a.ld_out = c.ld_in;
     if (c.bwd_raw) { a.epi = EPI_RAW; a.act_prev = nullptr; }
     if (merge_rows(c, a, 128, 128))
-        return launch<MODE_BWD, 128, 128, 2, 2, 1, 64, false, true, PIPE_PLAIN, false, false, false, false, true>(a, 1, st);
+        return launch<MODE_BWD, 128, 128, 2, 2, 1, 64, false, true, PIPE_PLAIN, STREAM_BOTH, false, false, false, true>(a, 1, st);
     return launch_tiled<MODE_BWD, false, true>(a, c.P, pick_tile(MODE_BWD, a.nR, a.nC, a.nK, c.P), st);
 }
 
@@ -1303,8 +1303,8 @@ hipError_t bf16_conv_forward(const ConvCall& c, hipStream_t st) {
     a.nR = rows; a.nC = c.c_out; a.nK = 9 * c.c_in;
     a.bias_hi = c.bhi; a.bias_lo = c.blo; a.bias_lstride = c.ws_stride;
     a.out = c.out; a.out_lstride = (size_t)rows * c.c_out; a.ld_out = c.c_out; a.relu = 1;
-    if (c.c_out <= 64) return launch<MODE_FWD, 128, 64, 2, 2, 1, 64, false, false, PIPE_PLAIN, false, false, true, false>(a, c.P, st);
-    return launch<MODE_FWD, 128, 128, 2, 2, 1, 64, false, false, PIPE_PLAIN, false, false, true, false>(a, c.P, st);
+    if (c.c_out <= 64) return launch<MODE_FWD, 128, 64, 2, 2, 1, 64, false, false, PIPE_PLAIN, STREAM_BOTH, false, true, false>(a, c.P, st);
+    return launch<MODE_FWD, 128, 128, 2, 2, 1, 64, false, false, PIPE_PLAIN, STREAM_BOTH, false, true, false>(a, c.P, st);
 }
 
 // dZ_in[n,h,w,ci] = [act_in > 0] * sum_{tap,o} dZ[n, h-(kh-1), w-(kw-1), o] * Wrot[(tap,o)][ci]
@@ -1318,8 +1318,8 @@ hipError_t bf16_conv_backward_data(const ConvCall& c, hipStream_t st) {
     a.nR = rows; a.nC = c.c_in; a.nK = 9 * c.c_out;
     a.act_prev = (const uint16_t*)c.in; a.act_lstride = (size_t)rows * c.c_in; a.ld_act = c.c_in;
     a.out = c.dz_in; a.out_lstride = (size_t)rows * c.c_in; a.ld_out = c.c_in;
-    if (c.c_in <= 64) return launch<MODE_BWD, 128, 64, 2, 2, 1, 64, false, true, PIPE_PLAIN, false, false, true, false>(a, c.P, st);
-    return launch<MODE_BWD, 128, 128, 2, 2, 1, 64, false, true, PIPE_PLAIN, false, false, true, false>(a, c.P, st);
+    if (c.c_in <= 64) return launch<MODE_BWD, 128, 64, 2, 2, 1, 64, false, true, PIPE_PLAIN, STREAM_BOTH, false, true, false>(a, c.P, st);
+    return launch<MODE_BWD, 128, 128, 2, 2, 1, 64, false, true, PIPE_PLAIN, STREAM_BOTH, false, true, false>(a, c.P, st);
 }
 
 // fp32 partial weight gradients of `splits` ranges of positions per learner (conv_step_kernel adds them)

@@ -229,8 +229,8 @@ Layout make_layout(int P, int K, int B, int L, const int* dims, int dtype, const
         }
         lo.off_draw = draw ? take(draw) : 0;
         lo.off_wrot = wrot ? take(wrot) : 0;
-        bool flat = false;
-        for (int t = 1; t <= M; ++t) flat = flat || lo.flat_f[t - 1].slabs || lo.flat_b[t - 1].slabs || lo.splits_flat[t - 1];
+        bool flat = false;                                      // (the forward pass and the data gradient compute their positions)
+        for (int t = 1; t <= M; ++t) flat = flat || lo.splits_flat[t - 1];
         lo.off_flat_table = flat ? take((size_t)conv_flat_table_len(B, cv.H, cv.W) * 4) : 0;
         lo.off_pool = take((size_t)P * B * cv.ch[M] * 2);
         lo.off_dpool = take((size_t)P * B * cv.ch[M] * 2);
@@ -1115,7 +1115,7 @@ int issue_steps_conv(kavg_ctx* c) {
         for (int t = 1; t <= M; ++t) {                              // convolutions, forward
             Bracket br(c, KAVG_CLASS_FORWARD);
             if (pack[t - 1].fwd) {
-                KAVG_HIP(c, conv_flat_forward(t == 1 ? first_call() : implicit_call(t), lo.flat_f[t - 1], pack[t - 1].fwd, table, c->X,
+                KAVG_HIP(c, conv_flat_forward(t == 1 ? first_call() : implicit_call(t), lo.flat_f[t - 1], pack[t - 1].fwd, c->X,
                                               t == 1 ? idx_k : nullptr, idx_ls, st));
                 continue;
             }
@@ -1203,7 +1203,7 @@ int issue_steps_conv(kavg_ctx* c) {
                 {
                     Bracket br(c, KAVG_CLASS_BACKWARD);
                     if (pack[t - 1].bwd) {
-                        KAVG_HIP(c, conv_flat_backward_data(v, lo.flat_b[t - 1], pack[t - 1].bwd, table,
+                        KAVG_HIP(c, conv_flat_backward_data(v, lo.flat_b[t - 1], pack[t - 1].bwd,
                                                             (pool_fused && t == M) ? dpool_M : nullptr, st));
                     } else if (conv_direct_ok(H, W, v.c_in, v.c_out, true)) {
                         KAVG_HIP(c, conv_direct_backward_data(v, (pool_fused && t == M) ? dpool_M : nullptr, st));
