@@ -599,10 +599,10 @@ std::vector<char*> g_reports;                    // not in use
 constexpr size_t REPORTS_KEPT = 16;
 
 char* take_report() {
-    {
+    try {
         std::lock_guard<std::mutex> lock(g_report_mutex);
         if (!g_reports.empty()) { char* p = g_reports.back(); g_reports.pop_back(); return p; }
-    }
+    } catch (...) {}                             // (the mutex: kavg_init may not throw)
     void* p = nullptr;
     if (hipHostMalloc(&p, REPORT_BYTES, hipHostMallocPortable) == hipSuccess) return (char*)p;
     (void)hipGetLastError();                     // (kavg_losses does without)
@@ -615,7 +615,7 @@ void give_report(char* p) {                      // (nothing on the device write
         std::lock_guard<std::mutex> lock(g_report_mutex);
         if (g_reports.size() < REPORTS_KEPT) { g_reports.push_back(p); return; }
     } catch (...) {}
-    (void)hipHostFree(p);
+    if (hipHostFree(p) != hipSuccess) (void)hipGetLastError();      // (not to be reported by the next launch)
 }
 
 int init_common(kavg_ctx** out, int P, int K, float lr, float mu, int n_layers, const int* dims, int B,
