@@ -62,6 +62,19 @@ def test_last_convolution(P, B, H, W, channels, dims):
     test_one_step(P, B, H, W, channels, dims)
 
 
+LARGE = [
+    # the mean over the positions out of many partial sums, one per 64 positions: sixteen and eight at a time
+    (2, 2, 60, 40, (8, 16), (16, 10)),               # 40 of them
+    (1, 2, 31, 33, (8, 8, 24), (24, 10)),            # 17, images at the ends of wavefronts
+    (1, 3, 17, 31, (8, 8, 24), (24, 32, 10)),        # nine, the mean in the launch of the MLP
+]
+
+
+@pytest.mark.parametrize("P,B,H,W,channels,dims", LARGE, ids=["%dx%d-%s" % (c[2], c[3], "-".join(map(str, c[4]))) for c in LARGE])
+def test_mean_of_large_images(P, B, H, W, channels, dims):
+    test_one_step(P, B, H, W, channels, dims)
+
+
 MANY = [
     # More than 256 workgroups: whole ones (the cases above have half as many positions each); two learners are checked.
     (257, 3, 5, 6, (8, 16, 40), (40, 10)),           # images across and beside the ends of tiles
