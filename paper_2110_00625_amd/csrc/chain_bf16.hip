@@ -64,7 +64,7 @@ struct Args {
     size_t lstride;                          // between learners, in the weights
     const uint16_t* in; int ld_in; size_t in_lstride;                // rows of the first layer, or (gather_in) of the data set
     int gather_in;
-    PoolSums pool; uint16_t* pooled;         // pooled != null: the rows are means over positions, formed here and written there ([P][B][d_in])
+    PoolSums pool; uint16_t* pooled;         // POOL: the rows are means over positions, formed here and written there ([P][B][d_in])
     const int32_t* idx; long idx_lstride;    // samples of this step
     const int32_t* y;
     float* rowloss;                          // [P][B]
@@ -97,7 +97,9 @@ __device__ __forceinline__ void unpack(const u32x4& p, float (&v)[8]) {
 }
 
 // HEAD: a last layer of few classes, which takes its sums in the order of head.hip
-template <bool HEAD>
+// POOL: the rows of the first layer are means over positions that are formed here.  (An instance of its own: as a branch it cost rounds
+// without it 1 %, 4 learners of 94 rows of 264-128-10, six steps 114.9 -> 116.4 us, 10 of 21 of 152-120-696-10, eleven 363.9 -> 366.3.)
+template <bool HEAD, bool POOL>
 __global__ void __launch_bounds__(NT, 2) chain_kernel(Args a) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -219,7 +221,7 @@ __global__ void __launch_bounds__(NT, 2) chain_kernel(Args a) {
         const Layer l = a.layer[0];
         uint16_t* const x = (uint16_t*)(smem + l.in_at);
         const uint16_t* p = a.gather_in ? a.in + (size_t)sample * a.ld_in : a.in + (size_t)learner * a.in_lstride + (size_t)(row0 + my) * a.ld_in;
-        if (a.pooled) {
+        if constexpr (POOL) {
 #pragma unroll 1
             for (int c = lane; c < l.d_in; c += 64) {
                 const uint16_t h = pool_mean(a.pool, learner, row0 + my, c);
@@ -440,6 +442,14 @@ size_t lds_plan(int L, const int* dims, Args* q) {
     return at;
 }
 
+template <bool HEAD, bool POOL>
+hipError_t launch(const Args& a, dim3 grid, size_t smem, hipStream_t st) {
+    static const hipError_t raised = hipFuncSetAttribute((const void*)chain_kernel<HEAD, POOL>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (raised != hipSuccess) return raised;
+    hipLaunchKernelGGL((chain_kernel<HEAD, POOL>), grid, dim3(NT), smem, st, a);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 // Times in tenths of a microsecond, from the shapes alone.  One launch: 40 whatever it does, its loss, and a product 9, 4 per
@@ -498,14 +508,8 @@ hipError_t bf16_chain(const LayerCall* calls, int n, const int32_t* y, const int
     const size_t smem = lds_plan(n, dims, &a);
     if (smem > 160 * 1024) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(calls[0].P * a.blocks));
-    static const hipError_t raised[2] = {
-        hipFuncSetAttribute((const void*)chain_kernel<false>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024),
-        hipFuncSetAttribute((const void*)chain_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024)};
-    const bool head = head_supported(dims[n]);
-    if (raised[head] != hipSuccess) return raised[head];
-    if (head) hipLaunchKernelGGL(chain_kernel<true>, grid, dim3(NT), smem, st, a);
-    else hipLaunchKernelGGL(chain_kernel<false>, grid, dim3(NT), smem, st, a);
-    return hipGetLastError();
+    return head_supported(dims[n]) ? pool ? launch<true, true>(a, grid, smem, st) : launch<true, false>(a, grid, smem, st)
+                                   : pool ? launch<false, true>(a, grid, smem, st) : launch<false, false>(a, grid, smem, st);
 }
 
 }  // namespace kavg
