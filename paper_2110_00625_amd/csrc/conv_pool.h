@@ -5,6 +5,7 @@
 #pragma once
 #include <stdint.h>
 #include <stddef.h>
+#include <type_traits>
 
 namespace kavg {
 
@@ -57,32 +58,33 @@ __device__ __forceinline__ pool_u32x4 pool_grad_bits(uint32_t m, pool_u32x4 g, f
 // `pitch` channels each, per `group` positions.
 struct PoolSums { const float* sums; int image, last, slots, group, groups, pitch; float inv; };
 
-// ... of channel ch of image n, bf16: the partial sums in ascending order, sixteen or eight on their way.  (A sum that holds the largest
-// finite number stands for an infinity, see conv_flat.hip.)  Latency bounds it where images are large: four at a time it was
-// 64 waits for an image of 127x128 (256 partial sums, of 64 positions each).  (us per round of four steps, four / sixteen and eight: 127x128, channels 8-128, one
-// learner of one image 265 / 166, 100x100, 8-8, 2 of 1 204 / 138, 64x64, 8-16-128, 8 of 16 864 / 845; 28x28, 8-32-64, 8 of 32 407 / 408.)
+// ... of channel ch of image n, bf16: the partial sums in ascending order, the first four and then sixteen or eight on their way.  (A
+// sum that holds the largest finite number stands for an infinity, see conv_flat.hip.)  Latency bounds it: four at a time it was 64 waits for
+// an image of 127x128, of 256 partial sums.  (us per round of four steps, four at a time / so: 127x128, channels 8-128, one learner of one
+// image 265 / 172, 100x100, 8-8, 2 of 1 202 / 141, 64x64, 8-16-128, 8 of 16 872 / 861; 28x28, 8-32-64, 8 of 32 410 / 412; with eight instead of the
+// first four, images of few partial sums wait longer: 14x6, 8-128, 8 of 16, five steps 187 / 192.)
 __device__ __forceinline__ uint16_t pool_mean(const PoolSums& q, int learner, int n, int ch) {
     const int g0 = n * q.image / q.group, g1 = (n * q.image + q.last) / q.group;
     const float* p = q.sums + ((size_t)learner * q.groups + g0) * q.slots * q.pitch + ch;
     const size_t step = (size_t)q.slots * q.pitch;
-    auto finite = [](float x) __attribute__((always_inline)) { return x < 0x1.FEp127f ? x : __builtin_inff(); };
-    float s = finite(p[(size_t)(n - g0 * q.group / q.image) * q.pitch]);
-    // (the positions of the following groups begin in this image: their first place)
-    int g = 1;
-    for (; g + 15 <= g1 - g0; g += 16) {
-        float x[16];
+    // (the positions of the groups behind the first begin in this image: their first place.  Places beyond the last are read from there,
+    // and not used)
+    const size_t first = (size_t)(n - g0 * q.group / q.image) * q.pitch;
+    const int m = g1 - g0;
+    float s = 0.f;
+    int g = 0;
+    auto batch = [&](auto count) __attribute__((always_inline)) {
+        constexpr int N = decltype(count)::value;
+        float x[N];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) x[i] = p[(g + i) * step];
+        for (int i = 0; i < N; ++i) x[i] = p[g + i == 0 ? first : min(g + i, m) * step];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) s += finite(x[i]);
-    }
-    for (; g <= g1 - g0; g += 8) {
-        float x[8];                                           // (places beyond the last are read from there, and not used)
-#pragma unroll
-        for (int i = 0; i < 8; ++i) x[i] = p[min(g + i, g1 - g0) * step];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) if (g + i <= g1 - g0) s += finite(x[i]);
-    }
+        for (int i = 0; i < N; ++i) if (g + i <= m) s += x[i] < 0x1.FEp127f ? x[i] : __builtin_inff();
+        g += N;
+    };
+    batch(std::integral_constant<int, 4>());
+    while (m - g >= 8) batch(std::integral_constant<int, 16>());
+    while (g <= m) batch(std::integral_constant<int, 8>());
     const __bf16 h = (__bf16)(s * q.inv);                     // round to nearest even
     return __builtin_bit_cast(uint16_t, h);
 }
