@@ -62,6 +62,28 @@ def test_last_convolution(P, B, H, W, channels, dims):
     test_one_step(P, B, H, W, channels, dims)
 
 
+@pytest.mark.parametrize("n_conv", [8, 9])
+def test_steps_of_many_convolutions(n_conv):
+    """The SGD steps of up to eight convolutions run in the launch of the MLP's updates, those of more in launches of their own, and
+    with the updates profiled layer by layer eight do as well.  One step of each of two contexts: the same bits.  Tolerance as in
+    test_one_step."""
+    channels, dims = (8,) + (16,) * n_conv, (16, 8, 10)
+    g, o, spec = _setup(2, 1, 6, 5, 7, channels, dims, 79, lr=0.5)
+    apart, _, _ = _setup(2, 1, 6, 5, 7, channels, dims, 79, lr=0.5)
+    start = g.params().astype(np.float64)
+    apart.profile(["update"])
+    for c in (g, apart, o):
+        c.local_steps()
+    apart.profile([])
+    for j in range(2):
+        got, want = g.replica(j) - start, np.asarray(o.replica(j)) - start
+        assert np.array_equal(g.replica(j), apart.replica(j))
+        for name, sl in conv_slices(spec):
+            assert np.any(want[sl] != 0.0)
+            e = np.linalg.norm(got[sl] - want[sl]) / np.linalg.norm(want[sl])
+            assert e < 2.0 ** -8, "%s of learner %d: %.3g" % (name, j, e)
+
+
 LARGE = [
     # the mean over the positions out of many partial sums, one per 64 positions: sixteen and eight at a time
     (2, 2, 60, 40, (8, 16), (16, 10)),               # 40 of them

@@ -1,5 +1,8 @@
 """Small fp32 models: all K local steps of Algorithm 1 in one launch (kavg_fused) against the oracle
 and against the launch-per-layer path of the same library."""
+import os
+import re
+
 import numpy as np
 import pytest
 
@@ -170,16 +173,23 @@ def test_fused_path_is_taken_only_where_it_fits():
     assert g.fused
 
 
-@pytest.mark.parametrize("P", [2720, 2740])
-def test_losses_that_fit_the_pinned_buffer_and_more(P):
-    """Three steps of P learners are 32 640 and 32 880 bytes of losses, the buffer holds 32 768; the first learners' do not depend on
-    how many others there are."""
+def _constant(file, name):
+    """A size that the library's sources state, `name = <product>;`."""
+    text = open(os.path.join(os.path.dirname(kavg.__file__), "csrc", file)).read()
+    return int(np.prod([int(f) for f in re.search(r"\b%s = ([0-9 *]+);" % name, text).group(1).split("*")]))
+
+
+def test_losses_that_fit_the_pinned_buffer_and_more():
+    """As many learners as leave three steps of losses, and the flags in front of them, room in the buffer, and one more: those are read
+    the other way.  A learner's losses do not depend on how many others there are."""
     dims, K, B = (8, 4, 2), 3, 2
-    many, _ = _pair(P, K, 0.05, 0.9, dims, B, False, 98)
-    few, _ = _pair(5, K, 0.05, 0.9, dims, B, False, 98)
+    P = (_constant("kavg_internal.h", "REPORT_BYTES") - _constant("kavg_api.hip", "ALIGN")) // (4 * K)
+    g = [_pair(p, K, 0.05, 0.9, dims, B, False, 98)[0] for p in (P, P + 1, 5)]
     for _ in range(2):
-        for g in (many, few):
-            g.local_steps()
-        got, want = many.losses(), few.losses()
-        assert got.shape == (K, P) and np.all(np.isfinite(got)) and np.all(got > 0)
-        assert np.max(np.abs(got[:, :5] - want)) < 1e-5          # (fp32, sums of eight terms in another order)
+        for c in g:
+            c.local_steps()
+        fit, more, few = (c.losses() for c in g)
+        for got, want in ((fit, more[:, :P]), (fit[:, :5], few)):
+            assert np.all(np.isfinite(got)) and np.all(got > 0)
+            assert np.max(np.abs(got - want)) < 1e-5             # (fp32, sums of eight terms in another order)
+        assert np.isfinite(more[-1, P]) and more[-1, P] > 0
