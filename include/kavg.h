@@ -22,7 +22,10 @@
  *  - "dev" pointers are device memory of the current HIP device, "host"
  *    pointers are ordinary host memory.  The library never allocates or frees
  *    device memory: the caller passes one workspace block and keeps it, the
- *    data set and any index array alive until kavg_destroy.
+ *    data set and any index array alive until kavg_destroy.  Contexts of
+ *    kavg_init and kavg_init_conv hold 32 KB of pinned host memory where the
+ *    losses of a round fit there (kavg_losses); kavg_destroy gives it to the
+ *    next context, and up to sixteen such blocks stay with the process.
  *  - Work is enqueued on the HIP stream given to kavg_init (NULL = the default
  *    stream).  kavg_local_steps and kavg_meta_update return without waiting;
  *    the functions that copy to the host wait for the stream.
@@ -115,10 +118,11 @@ int kavg_init_conv(kavg_ctx** out, int P, int K, float lr, float mu, int H, int 
  * tight serving loops, harnesses that forbid hipMalloc): the context works in a block of
  * KAVG_STATIC_WORKSPACE_BYTES that lives inside the library's device image (one copy per GPU, held
  * until the process ends) instead of a caller workspace.  Neither this call nor any later call on
- * the context allocates or frees device memory.  Everything else is kavg_init: same arguments,
- * same kernels, same results; data set, index array and velocity block are still the caller's.  (One
- * exception: a small fp32 model that fits the block only without the scratch of kernel 2 of kavg_fused
- * does without that kernel, and its sums are then taken in another order; kavg_fused tells.)
+ * the context allocates or frees device memory, nor pinned host memory.  Everything else is kavg_init: same
+ * arguments, same kernels, same results; data set, index array and velocity block are still the caller's.  (Two
+ * exceptions: a small fp32 model that fits the block only without the scratch of kernel 2 of kavg_fused
+ * does without that kernel, and its sums are then taken in another order; kavg_fused tells.  And kavg_losses copies
+ * to the caller's memory without the pinned block, which takes about seven microseconds longer.)
  * The block keeps whatever the previous context left in it; every piece a context reads is
  * written by it first (the range flag is cleared here, the rest by kavg_set_params / the kernels).
  * One context per device may use the block at a time: a second kavg_init_static on the same
@@ -200,7 +204,8 @@ int kavg_meta_update(kavg_ctx* ctx);
 int kavg_params(kavg_ctx* ctx, float* out_host, size_t n);            /* w~              */
 int kavg_momentum(kavg_ctx* ctx, float* out_host, size_t n);          /* v               */
 int kavg_replica(kavg_ctx* ctx, int j, float* out_host, size_t n);    /* w^j, 0 <= j < P */
-/* [K][P] mean minibatch loss of every learner at every step of the last kavg_local_steps */
+/* [K][P] mean minibatch loss of every learner at every step of the last kavg_local_steps.  (Through the context's pinned
+ * block where K*P is at most 8128, else by a copy to the caller's memory.) */
 int kavg_losses(kavg_ctx* ctx, float* out_host);
 /* [P][K][B] indices used by the last kavg_local_steps */
 int kavg_indices(kavg_ctx* ctx, int32_t* out_host);
@@ -248,7 +253,8 @@ int kavg_set_refresh(kavg_ctx* ctx, int refresh, void* history_dev, size_t bytes
  * their forward pass to their data gradients, are launches of their own while the forward, backward, head or
  * loss class is in the mask; a KAVG_FP32 head adds up no partial products of the layer below while forward or
  * head is; and while forward is, the weights of convolutions are packed before every step instead of by the
- * SGD step before it.  What such classes report are then launches that an unobserved round does not make.
+ * SGD step before it, and the mean over the positions is a launch of its own while forward, backward, head or loss is; the SGD steps of
+ * the convolutions are one while update, head or loss is.  What such classes report are then launches that an unobserved round does not make.
  * A layer whose data gradient and update are one launch counts as update.
  * kavg_profile waits for the stream, clears the totals and installs the mask
  * (0 = off); kavg_profile_read waits for the stream and returns, per class, the

@@ -34,8 +34,8 @@
 // its data gradient 231 -> 158, 32 -> 64 channels forward 76 -> 61.
 //
 // The last convolution, below the mean over the positions, writes no activations: what is read of them afterwards is their
-// ReLU mask, one bit each, and their sums.  The sums of an image are a product with ones out of the epilogue's patch, 128
-// positions at a time, joined in ascending order (pool_mean).  16 learners of 64 images of 32x32, channels
+// ReLU mask, one bit each, and their sums.  The sums of an image are a product with ones out of the epilogue's patch, over
+// the positions of a wavefront (128, 64 in small launches), joined in ascending order (pool_mean).  16 learners of 64 images of 32x32, channels
 // 8-32-64-128: 268 MB of activations were written once and read three times; without them the mean takes 5 us instead of 47 and
 // the data gradient 184 instead of 203, a round 6.92 -> 6.28 ms; one convolution on 60x32 images 141 -> 97 us, 28x28 536 -> 514.
 #include "kavg_internal.h"

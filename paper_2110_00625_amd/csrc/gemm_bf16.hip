@@ -799,8 +799,8 @@ __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING
             const uint16_t* lbase = a.wlo + mlearner * a.ws_lstride;
             const int c = min(c0 + wc * WTC + (lane % L8_PER_ROW) * 8, a.nC - 8);
             const int r = min(r0 + (wr * MR + i) * 32 + it * ROWS_PER_IT + lane / L8_PER_ROW, a.nR - 1);
-            // hi was left in the memory-side cache by the previous writer when it fits there
-            // (otherwise it is streamed like lo, so as not to push anything else out)
+            // hi was left in the memory-side cache by the previous writer when it fits there; otherwise both are streamed, so as
+            // not to push anything else out, or, where rows are ragged, neither is (stream_policy)
             hi = plane_get<STREAM == STREAM_BOTH>((const u32x4*)(hbase + (size_t)r * a.nC + c));
             lo = plane_get<STREAM != STREAM_NONE>((const u32x4*)(lbase + (size_t)r * a.nC + c));
         };
@@ -1063,8 +1063,8 @@ __global__ void __launch_bounds__(64 * (WR * WC * WK + (PIPE == PIPE_RING ? RING
                     }
                     // The hi plane is what the next forward pass reads.  When the hi planes of all learners
                     // fit there, an ordinary store leaves it in the memory-side cache; when they do not, it
-                    // would only displace other lines.  The lo plane (and the velocity) is streamed once
-                    // per step and always bypasses the cache.
+                    // would only displace other lines.  The lo plane (and the velocity) is read and written once
+                    // per step and bypasses the cache, but where ragged rows share their lines (stream_policy).
                     plane_put<STREAM == STREAM_BOTH>((u32x4*)(hbase + (size_t)r * a.nC + c), oh);
                     plane_put<STREAM != STREAM_NONE>((u32x4*)(lbase + (size_t)r * a.nC + c), ol);
                 }

@@ -152,7 +152,7 @@ Layout make_layout(int P, int K, int B, int L, const int* dims, int dtype, const
             // Which kernels run convolution t: those for images 32 pixels wide where they cover the layer, those for any width
             // elsewhere, and for forward pass and data gradient of 64 or more channels out where these have three rounds of workgroups
             // or more.  (The workload's layers on the latter, us per launch against the former: forward 29 / 61 / 161 against
-            // 27 / 72 / 183, data gradient 83 / 158 against 77 / 182, weight gradient 32 / 89 / 260 against 25 / 57 / 148.  Fewer workgroups:
+            // 27 / 72 / 183, data gradient 83 / 158 against 77 / 182, weight gradient 32 / 89 / 260 against 24 / 58 / 152.  Fewer workgroups:
             // 16 learners of 32 images, 64 -> 64 -> 64 channels (1089) 918 against 898 per round, 8 of 16 (273) 255 against 240.)
             auto direct = [&](int c_in, int c_out, bool backward) {
                 const int c_n = backward ? c_in : c_out;

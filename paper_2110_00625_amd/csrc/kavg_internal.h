@@ -59,7 +59,7 @@ struct LayerCall {
     uint16_t* ws;   size_t ws_stride;     // hi plane of the weights (first learner), else null
     uint16_t* wlo;                          // lo plane of the weights (stride ws_stride)
     uint16_t* bhi;  uint16_t* blo;          // hi / lo planes of the bias (stride ws_stride)
-    int shadow_cached;                    // updates access the bf16 (hi) plane with ordinary (1) or streaming (0) loads / stores
+    int shadow_cached;                    // the bf16 (hi) planes of all learners stay in the memory-side cache (stream_policy)
     // activations entering the layer: [P][B][ld_in]; or, with gather != null, rows X[gather[j][m]]
     const void* in; int ld_in; size_t in_stride;
     const int32_t* gather; long gather_stride;
@@ -194,7 +194,7 @@ hipError_t launch_col2im_mask(const float* draw, const void* act, void* dprev, i
                               hipStream_t st);
 hipError_t launch_pool_forward(const void* act, void* pooled, int P, int B, int HW, int c, hipStream_t st);
 hipError_t launch_pool_backward(const void* dpool, const void* act, void* dz, int P, int B, int HW, int c, hipStream_t st);
-// (ConvStep: above)
+// (layers: ConvStep, at the update kernels)
 hipError_t launch_conv_steps(const ConvStep* layers, int n, size_t lstride, int P, float lr, hipStream_t st);
 
 // ---- 3x3 convolution (stride 1, zero padding 1) on channels-last images [P][B][H][W][c], the patch matrix formed

@@ -84,8 +84,7 @@ __device__ __forceinline__ bf16x8 frag_tr(const uint16_t* tile, int pitch, int k
     return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
-// STREAM: the hi planes of all learners do not stay in the memory-side cache (the lo planes never do).  CHAINS: the data
-// gradient's sums, one chain over the units, or two (even and odd chunks) that are added up at the end.
+// STREAM: how the planes are accessed (stream_policy).  CHAINS: the data gradient's sums, one chain over the units, or two (even and odd chunks) that are added up at the end.
 template <int BT, int STREAM, int CHAINS>
 __global__ void __launch_bounds__(NT) strip_kernel(StripArgs a) {
     typedef StripShape<BT> SH;
