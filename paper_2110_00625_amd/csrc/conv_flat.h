@@ -38,13 +38,15 @@ size_t conv_pool_elems(int P, int B, int H, int W, const FlatPlan& plan);
 PoolSums conv_pool_sums(const float* sums, const FlatPlan& plan, int P, int B, int H, int W);
 hipError_t launch_pool_finish(const PoolSums& q, void* pooled, int P, int B, int c, hipStream_t st);
 
+// (These two compute their positions and read no table; the argument is the weight gradient's.  tests/test_boundary_cpu.py calls them so.)
 // c.out = relu(conv(c.in, W) + b), or c.bits and c.pool_sums; gather != null: the images are rows gather[learner * gstride + n] of the data set X
-hipError_t conv_flat_forward(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag, const void* X, const int32_t* gather,
-                             long gstride, hipStream_t st);
+hipError_t conv_flat_forward(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag, const int32_t* table, const void* X,
+                             const int32_t* gather, long gstride, hipStream_t st);
 // c.dz_in = [c.in > 0] * (transposed convolution of c.dz with W).  dpool != null (the last convolution, below the
 // mean over the positions): c.dz is not read; the gradient images are formed while loading from c.bits and
 // dpool [P][B][c_out], as pool_backward_kernel would.
-hipError_t conv_flat_backward_data(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag, const void* dpool, hipStream_t st);
+hipError_t conv_flat_backward_data(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag, const int32_t* table, const void* dpool,
+                                   hipStream_t st);
 
 // Weight gradient (conv_flat_wgrad.hip): ranges of positions per learner, or 0 when the kernel does not cover the layer.
 // first: the first convolution (gathered images of 8 channels).

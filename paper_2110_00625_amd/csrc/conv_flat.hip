@@ -669,8 +669,8 @@ hipError_t launch_pool_finish(const PoolSums& q, void* pooled, int P, int B, int
     return hipGetLastError();
 }
 
-hipError_t conv_flat_forward(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag, const void* X, const int32_t* gather,
-                             long gstride, hipStream_t st) {
+hipError_t conv_flat_forward(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag, const int32_t*, const void* X,
+                             const int32_t* gather, long gstride, hipStream_t st) {
     if (!c.bits && !c.out) return hipErrorInvalidValue;
     FlatArgs a = make_args(c, plan, frag);
     const size_t rows = (size_t)c.B * c.H * c.W;
@@ -688,7 +688,8 @@ hipError_t conv_flat_forward(const ConvCall& c, const FlatPlan& plan, const uint
     return gather ? run<FWD_GATHER>(a, plan, st) : run<FWD>(a, plan, st);
 }
 
-hipError_t conv_flat_backward_data(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag, const void* dpool, hipStream_t st) {
+hipError_t conv_flat_backward_data(const ConvCall& c, const FlatPlan& plan, const uint16_t* frag, const int32_t*, const void* dpool,
+                                   hipStream_t st) {
     if (dpool ? !c.bits : !c.dz) return hipErrorInvalidValue;
     FlatArgs a = make_args(c, plan, frag);
     const size_t rows = (size_t)c.B * c.H * c.W;

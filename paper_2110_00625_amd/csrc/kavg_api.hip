@@ -1115,7 +1115,7 @@ int issue_steps_conv(kavg_ctx* c) {
         for (int t = 1; t <= M; ++t) {                              // convolutions, forward
             Bracket br(c, KAVG_CLASS_FORWARD);
             if (pack[t - 1].fwd) {
-                KAVG_HIP(c, conv_flat_forward(t == 1 ? first_call() : implicit_call(t), lo.flat_f[t - 1], pack[t - 1].fwd, c->X,
+                KAVG_HIP(c, conv_flat_forward(t == 1 ? first_call() : implicit_call(t), lo.flat_f[t - 1], pack[t - 1].fwd, nullptr, c->X,
                                               t == 1 ? idx_k : nullptr, idx_ls, st));
                 continue;
             }
@@ -1203,7 +1203,7 @@ int issue_steps_conv(kavg_ctx* c) {
                 {
                     Bracket br(c, KAVG_CLASS_BACKWARD);
                     if (pack[t - 1].bwd) {
-                        KAVG_HIP(c, conv_flat_backward_data(v, lo.flat_b[t - 1], pack[t - 1].bwd,
+                        KAVG_HIP(c, conv_flat_backward_data(v, lo.flat_b[t - 1], pack[t - 1].bwd, nullptr,
                                                             (pool_fused && t == M) ? dpool_M : nullptr, st));
                     } else if (conv_direct_ok(H, W, v.c_in, v.c_out, true)) {
                         KAVG_HIP(c, conv_direct_backward_data(v, (pool_fused && t == M) ? dpool_M : nullptr, st));
