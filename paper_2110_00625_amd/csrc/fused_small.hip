@@ -112,10 +112,12 @@ __device__ __forceinline__ void contract(const float* xp, const float* wp, int c
 // workgroup then gathers the partials of half as many chunks (131 instead of 262 KB per step for 32 rows of 3072, all requested at once): the
 // exchange, not the arithmetic, is the longest part of a step.  us per round of four steps: 3072-64-10, 4 learners of 32 rows 72.2 -> 65.0,
 // 1024-64-10, 8 learners 62.0 -> 55.1, 784-64-10, 4 of 24 rows 56.2 -> 50.7.
-// BATCH (WIDE, and more than 32 rows): the operands of 16 rows of the update of W_1 are requested before those at hand are used.  Shorter
-// minibatches do better with four rows at a time, and chunks of at most 192 columns with the compiler's loop around their products.
-// (us per round of four steps, both by hand / neither: 784-64-10, 12 learners of 8 rows 56.0 / 54.4, 16 of 32 65.1 / 63.4, 256-64-10, 60 of 32
-// 56.0 / 53.6; but more rows 3072-64-10, 4 of 64 97.3 / 101.2, the rows alone by hand 96.1.)
+// BATCH (WIDE, and chunks of more than 64 columns): the operands of 16 rows of the update of W_1 are requested before those at hand are
+// used.  With 64 columns a wavefront has one or two blocks of them to a row, and four rows at a time are faster.  (us per round of four steps,
+// eight and more where stated, four rows / 16: 128 columns, 1836-54-4, 10 learners of 32 rows, eight 129.8 / 123.5, 1500-32-10, 16 of 20,
+// eight 125.7 / 120.5, 192, 3072-64-10, 4 of 64 101.2 / 96.5; 64, 256-64-10, 60 of 32 53.7 / 55.1, 64-52-16, 51 of 39, fourteen 154.8 / 158.5,
+// 784-64-10, 16 of 64 89.6 / 88.9.)  The products' loop by hand in chunks of up to 192 columns: 784-64-10, 16 of 32 64.0 / 64.7,
+// 512-32-10, 30 of 24 55.7 / 57.5.
 template <bool WIDE, bool BATCH>
 __global__ void __launch_bounds__(NT)
 fused_small_kernel(FusedSmallCall a, int S, int CW, int UH) {
@@ -411,19 +413,23 @@ fused_small_kernel(FusedSmallCall a, int S, int CW, int UH) {
                         for (int i = 0; i < NB; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(d, xp[m * PW + cstep * i], acc[i], 0, 0, 0);
                     }
                 } else {
-                    for (int m = 0; m < Bk; m += 16) {              // (zeros beyond B)
-                        float d[4], x[4][NB];
+                    auto rows = [&](auto count, int m) __attribute__((always_inline)) {
+                        constexpr int N = decltype(count)::value / 4;
+                        float d[N], x[N][NB];
 #pragma unroll
-                        for (int t = 0; t < 4; ++t) {
+                        for (int t = 0; t < N; ++t) {
                             d[t] = dp[(m + 4 * t) * PH];
 #pragma unroll
                             for (int i = 0; i < NB; ++i) x[t][i] = xp[(m + 4 * t) * PW + cstep * i];
                         }
 #pragma unroll
-                        for (int t = 0; t < 4; ++t)
+                        for (int t = 0; t < N; ++t)
 #pragma unroll
                             for (int i = 0; i < NB; ++i) acc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(d[t], x[t][i], acc[i], 0, 0, 0);
-                    }
+                    };
+                    int m = 0;
+                    for (; m + 16 <= Bk; m += 16) rows(std::integral_constant<int, 16>(), m);
+                    if (m < Bk) rows(std::integral_constant<int, 8>(), m);
                 }
 #pragma unroll
                 for (int i = 0; i < NB; ++i)
@@ -515,7 +521,7 @@ int fused_small_workgroups(int P, int B, int d0, int d1, int compute_units) {
 hipError_t launch_fused_small(const FusedSmallCall& c, hipStream_t st) {
     const Split p = split_of(c.P, c.B, c.d0, c.d1, c.compute_units);
     if (p.wide) return launch_split<true, true>(c, p, st);
-    return c.B > 32 ? launch_split<false, true>(c, p, st) : launch_split<false, false>(c, p, st);
+    return p.CW > 64 ? launch_split<false, true>(c, p, st) : launch_split<false, false>(c, p, st);
 }
 
 }  // namespace kavg
