@@ -1239,7 +1239,7 @@ hipError_t bf16_forward(const LayerCall& c, hipStream_t st) {
     a.nR = c.B; a.nC = c.d_out; a.nK = c.d_in;
     a.bias_hi = c.bhi; a.bias_lo = c.blo; a.bias_lstride = c.ws_stride;
     a.out = c.out; a.out_lstride = c.out_stride; a.ld_out = c.ld_out; a.relu = c.relu;
-    a.c_stream = !c.shadow_cached && !c.shared_w && whole_lines(c, c.deferred);
+    a.c_stream = !c.shadow_cached && !c.shared_w && whole_lines(c, c.halves && c.deferred);
     if (a.nK % 64 == 0 && a.nK >= 128 && merge_rows(c, a, 256, 128))
         return launch<MODE_FWD, 256, 128, 2, 2, 1, 64, false, false, PIPE_RING, STREAM_BOTH, false, false, false, true>(a, 1, st);
     return launch_tiled<MODE_FWD, false, false>(a, c.P, pick_tile(MODE_FWD, a.nR, a.nC, a.nK, c.P), st);
@@ -1280,7 +1280,7 @@ hipError_t bf16_update(const LayerCall& c, hipStream_t st) {
     a.ws = c.ws; a.wlo = c.wlo; a.ws_lstride = c.ws_stride; a.bhi = c.bhi; a.blo = c.blo; a.w_lstride = c.w_stride;
     a.lr = c.lr; a.u = c.u; a.ub = c.ub; a.beta = c.beta;
     a.next_gather = c.gather ? c.next_gather : nullptr;
-    const int stream = stream_policy(c, c.deferred || rows > 128);
+    const int stream = stream_policy(c, c.halves && (c.deferred || rows > 128));
     if (stream == STREAM_NONE) return launch_update<STREAM_NONE>(a, c, rows, P, st);
     return stream == STREAM_LO ? launch_update<STREAM_LO>(a, c, rows, P, st) : launch_update<STREAM_BOTH>(a, c, rows, P, st);
 }

@@ -416,6 +416,13 @@ int shadows_stay_cached(int P, size_t elems_per_learner) {
     return (size_t)P * elems_per_learner * 2 <= ((size_t)192 << 20) ? 1 : 0;
 }
 
+// The rows of all layers of a plain MLP but a last one of few classes are whole half lines.
+int rows_are_halves(const kavg_ctx* c) {
+    const int wide = head_supported(c->dims[c->L]) ? c->L - 1 : c->L;
+    for (int l = 1; l <= wide; ++l) if (c->dims[l - 1] % 32 != 0 || c->dims[l - 1] % 64 == 0) return 0;
+    return c->cv.ch.empty() && wide > 0;
+}
+
 LayerCall layer_call(const kavg_ctx* c, int l /*1..L*/, int k) {
     const Layout& lo = c->lo;
     const size_t esz = c->dtype == KAVG_BF16 ? 2 : 4;
@@ -432,6 +439,7 @@ LayerCall layer_call(const kavg_ctx* c, int l /*1..L*/, int k) {
         q.b = c->reps() + lo.b_off[l - 1];
     }
     q.shadow_cached = shadows_stay_cached(c->P, lo.stride);
+    q.halves = rows_are_halves(c);
     if (l == 1 && !c->cv.ch.empty()) {       // behind a convolution stack: the mean over the positions
         q.in = c->ws + lo.off_pool; q.ld_in = c->dims[0]; q.in_stride = (size_t)c->B * q.ld_in;
         q.dz_prev = c->ws + lo.off_dpool; q.dz_prev_stride = q.in_stride;
@@ -1304,7 +1312,7 @@ int issue_steps_deferred(kavg_ctx* c) {
         else { q.out = c->logits(); q.ld_out = lo.ldz; q.out_stride = (size_t)B * lo.ldz; q.relu = 0; }
         q.dz = dzH(l, slot); q.ld_dz = ld_of(l); q.dz_stride = (size_t)m * B * q.ld_dz;
         q.lr = c->lr;
-        q.deferred = 1;
+        q.deferred = 1; q.halves = rows_are_halves(c);
         // until the first refresh of a round every stored replica still holds the global model: all
         // learners then read learner 0's copy, which the caches serve, instead of P copies from memory
         q.shared_w = (c->replicas_equal && k < m) ? 1 : 0;

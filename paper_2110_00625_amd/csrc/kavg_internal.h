@@ -85,6 +85,7 @@ struct LayerCall {
     int bwd_raw;           // backward-data: write the unmasked fp32 product to dz_prev instead of the masked bf16 one
     int rows;              // update: rows of dz / in to contract over (0: B) -- the steps since the last refresh
     int deferred;          // the stored weights serve several steps
+    int halves;            // the rows of all wide layers of the model are whole half lines (stream_policy)
     int skip_bias;         // update: leave the bias alone (it is stepped after every local step)
     // update with fp32 partial outputs instead of a step on the master (long contractions split over
     // `splits` ranges of rows that run as separate workgroups): partial [P*splits][d_out][d_in],
@@ -106,9 +107,12 @@ enum { STREAM_BOTH = 0, STREAM_LO = 1, STREAM_NONE = 2 };
 // (Hi planes that stay cached are worth more than the shared lines of the lo planes: 3080-1032-1032-10, 16 learners of 128 rows, four steps, streaming
 // / ordinary lo planes 941 / 1027 us, 1000-1000-1000-10, 30 of 100 768 / 824.)
 // halves: rows of whole half lines stream too.  That is the better way where the stored weights serve several steps and in the tiles of
-// 128x128 of long contractions.  (us per round, ordinary / streaming: eight steps, weights refreshed every four or eight, 16 learners of
-// 4000-3000-10, 16, 32 and 64 rows 1448 / 1412, 1576 / 1522 and 1784 / 1759, 12 of 100 of 4000-4000-100 2882 / 2839; four steps, 18 of 136
-// and 320 of 4000-3000-10 2870 / 2781 and 3643 / 3579; but, in tiles of 64x128, 18 of 8 and 64 2146 / 2192 and 2296 / 2350.)
+// 128x128 of long contractions, if the whole model is of such rows (LayerCall::halves): beside others that stream, planes accessed the
+// ordinary way have the cache to themselves.  (us per round, ordinary / streaming: eight steps, weights refreshed every three, four or
+// eight, 16 learners of 4000-3000-10, 64, 40 and 16 rows 2498 / 2385, 2055 / 1966 and 1444 / 1410, 16 of 40 of 2080-4000-100, every four 1855 / 1760;
+// four steps, 16 of 136 and 320 of 4000-3000-10 2586 / 2513 and 3219 / 3181, 70 of 320 of 1312-1312-10 2429 / 2399; but, in tiles of
+// 64x128, 18 of 8 and 64 of 4000-3000-10 2146 / 2192 and 2296 / 2350, and with other rows in the model 40 of 32 of 2152-1056-2688-10, every three
+// steps 3077 / 3170, 18 of 136 of 1312-1056-2176-3840-60 4066 / 4156.)
 inline int stream_policy(const LayerCall& c, bool halves) { return c.shadow_cached ? STREAM_LO : whole_lines(c, halves) ? STREAM_BOTH : STREAM_NONE; }
 template <bool STREAM, class T> __device__ __forceinline__ T plane_get(const T* p) { return STREAM ? __builtin_nontemporal_load(p) : *p; }
 template <bool STREAM, class T> __device__ __forceinline__ void plane_put(T* p, T v) { if (STREAM) __builtin_nontemporal_store(v, p); else *p = v; }
