@@ -1135,9 +1135,9 @@ int pick_tile(int mode, int nR, int nC, int nK, int P) {
         // two of 64x64 with one.  (us per round, 64x64 / 128x64: 256 tiles, 3072-1024-1024-10, 16 learners of 128 rows 1380 / 1357,
         // 4096-4096-100, 4 of 256 1086 / 1041; 192, 12 of 128 604 / 596; but 320 976 / 978; 85 338 / 381; 228 of a contraction of 704 184 / 203.)
         // Where 64 of the rows are padding there is a third more to multiply, which only a long contraction on few workgroups makes up
-        // for.  (4096-2048-10, 3 of 160, 192 tiles 378 / 371, 4096-2816-10, 2 of 130, 176 tiles 382 / 372, 3072-2048-10, 3 of 130 307 / 303; but 4 of 150, 256 tiles 443 / 450;
-        // 2048-2048-10, 4 of 192 270 / 276; 2048-1024-1024-10, 8 of 192 397 / 408; 1024-1024-10, 6 of 130 143 / 147; and where the 64x64
-        // tiles are one per compute unit, 4096-1024-10, 5 of 192 292 / 317.)
+        // for.  (4096-2048-10, 3 of 160, 192 tiles 378 / 371, 4096-2816-10, 2 of 130, 176 tiles 382 / 372, 3072-2048-10, 3 of 130 307 / 303; but
+        // 4 of 150 of 4096-2048-10, 256 tiles 443 / 450, 2048-2048-10, 4 of 192 270 / 276; 2048-1024-1024-10, 8 of 192 397 / 408;
+        // 1024-1024-10, 6 of 130 143 / 147; and where the 64x64 tiles are one per compute unit, 4096-1024-10, 5 of 192 292 / 317.)
         const long tiles = (long)((nR + 127) / 128) * ((nC + 63) / 64) * P;
         const bool padding = (nR + 63) / 64 % 2 != 0;
         if (tiles >= 160 && tiles <= 256 && nK >= 1024 && (!padding || (nK >= 3072 && tiles <= 192 && tiles64 > 256))) return T128x64_K2;
